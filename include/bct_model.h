@@ -60,8 +60,8 @@ bct_status bctm_pack_weight(const void* w, void* packed, uint32_t N, uint32_t K,
  * K a multiple of 32, N a multiple of 16; fp32 accumulation (MFMA), one rounding to bf16 at the end.
  * out may alias residual; x must not alias out.  Two kernels: up to 127 rows (a decode batch) the weights
  * are streamed once per 32 rows against activations read from cache; from 128 rows on (a prompt chunk), when
- * N is a multiple of 128 (bctm_swiglu: 64), a tiled matrix-core kernel with 128 x 128 or 256 x 256 workgroups
- * runs instead - fastest with a tiled x.  Both give the sum in fp32 with their own, fixed, summation order. */
+ * N is a multiple of 128 (bctm_swiglu: 64), a tiled matrix-core kernel runs instead, with workgroup tiles from
+ * 64 x 64 to 256 x 256 chosen to fill the chip - fastest with a tiled x.  Both give the sum in fp32 with their own, fixed, summation order. */
 bct_status bctm_linear(const void* x, const void* w_packed, const void* residual, void* out, uint32_t rows,
                        uint32_t K, uint32_t N, uint32_t flags, void* hip_stream);
 
@@ -82,8 +82,8 @@ bct_status bctm_swiglu(const void* x, const void* w_gate_packed, const void* w_u
  * shape: host logic only, no GPU call.  *kernel receives one of the values below. */
 #define BCTM_KERNEL_STREAMING 0u /* weights streamed once per 32 rows (one 16-feature tile per workgroup) */
 #define BCTM_KERNEL_STREAMING_WIDE 1u /* the same with two feature tiles per workgroup (wide output heads) */
-#define BCTM_KERNEL_TILE128 2u   /* matrix-core kernel, 128 rows x 128 features per workgroup */
-#define BCTM_KERNEL_TILE256 3u   /* matrix-core kernel, 256 rows x 256 features per workgroup */
+#define BCTM_KERNEL_TILE128 2u   /* matrix-core kernel for some hundred rows, or for features only its 128-wide tiles divide */
+#define BCTM_KERNEL_TILE256 3u   /* matrix-core kernel for many rows: 256 x 256 per workgroup where that fills the chip */
 #define BCTM_KERNEL_STREAMING_TRIPLE 4u /* streaming with three feature tiles per workgroup */
 bct_status bctm_linear_plan(uint32_t rows, uint32_t K, uint32_t N, uint32_t swiglu, uint32_t* kernel);
 

@@ -1,0 +1,360 @@
+// The projections of the decoder stack for MANY token rows (a prompt chunk: batch x T rows; gfx950), where the
+// product is a dense contraction bound by the matrix cores and no longer by streaming the weights.
+//
+// Both operands are already stored in MFMA operand order (packed weights, tiled activations), so a K step of 32
+// inputs is a set of 1 KB tiles that go from memory to LDS unchanged (global_load_lds: 16 bytes per lane, no
+// trip through registers) and are read back by the wavefronts as v_mfma_f32_16x16x32_bf16 operands with linear
+// 16-byte LDS reads (no bank conflicts).  Row-major activations take the same path with one row of 64 bytes
+// per 16 lanes.
+//
+// What bounds it: the matrix cores, once loads and LDS reads are out of their way.  Three things do that:
+//   - four LDS stages, so that a tile is requested three K steps before it is used.  A wavefront waits only for
+//     its own requests of the next stage (vmcnt leaves the two later stages in flight); the barrier that
+//     follows makes the stage the workgroup's.  Each stage is a __shared__ array of its own: the compiler
+//     then knows that reading one stage does not depend on requests into another and adds no wait.
+//   - two wavefronts per SIMD that take turns ("ping"): while one issues the K step's products, the other
+//     reads its operands of the next one from LDS and requests tiles; two barriers per K step keep them
+//     half a step apart, and s_setprio lets the products go first.
+//   - workgroup ids mapped so that the workgroups resident on one XCD cover 4 row tiles x consecutive
+//     feature tiles: each operand panel enters that XCD's L2 once per four uses.
+// With one stage ahead held in registers, one barrier per K step and no turns, the same 256 x 256 tile took
+// 1353 us at 16384 rows x 11008 -> 4096 (1.09 PFLOP/s); this form takes 955 us (1.55 PFLOP/s); four stages
+// without turns 1131 us; bands of 8 instead of 4 row tiles 1033 us.
+//
+// Where 256 x 256 tiles are too few for 256 compute units, smaller tiles follow; and where even 128 x 128 tiles
+// leave every compute unit at most one workgroup of four wavefronts, two groups of wavefronts share a
+// tile, each with half of the inputs, and are the two that take turns on a SIMD (see rows_shape for the choice
+// and the measurements).
+#include "bct_device.h"
+#include "bct_linear.h"
+
+namespace bct {
+
+namespace {
+
+__device__ __forceinline__ void load_to_lds(const void* g, void* lds) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                   (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+// A barrier that waits for nothing else: requests into LDS stay in flight across it.
+__device__ __forceinline__ void bare_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+}
+// s_waitcnt operands: at most n vector-memory operations outstanding / no LDS operation outstanding
+constexpr int wait_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
+constexpr int kWaitLds = 15 | (7 << 4) | (0 << 8) | (3 << 14);
+
+template <int I>
+struct Int {
+  static constexpr int v = I;
+};
+
+// KS groups of WR x WC wavefronts; a wavefront owns 16 * MI token rows x 16 * NJ B-tile columns (SwiGLU: gate and
+// up tiles alternate, so half as many output features); group g sums the K steps [KT * g / KS, ...).
+template <bool SWIGLU, bool XT, int MI, int NJ, int WR, int WC, int KS>
+__global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
+    const uint16_t* __restrict__ x, const u32x4* __restrict__ w, const u32x4* __restrict__ w2, const uint16_t* residual,
+    LinearOut dst, uint32_t rows, uint32_t K, uint32_t NT, uint32_t out_tiled) {
+  constexpr int NW = WR * WC;                      // wavefronts of a group
+  constexpr int TA = MI * WR, TB = NJ * WC, TT = TA + TB;  // 1 KB tiles of a K step: activations, weights
+  constexpr int ND = TT / NW;                      // of them per wavefront
+  static_assert(TT % NW == 0, "tiles must divide among the wavefronts");
+  constexpr int S = 4;                             // LDS stages
+  constexpr bool PING = NW * KS == 8;              // two wavefronts per SIMD that take turns
+  constexpr uint32_t HB = 4;                       // row tiles of a band
+  constexpr uint32_t BM = 16 * MI * WR;            // token rows of a workgroup
+  constexpr uint32_t CW = 16 * NJ;                 // B columns of a wavefront
+  constexpr uint32_t BNF = CW * WC / (SWIGLU ? 2 : 1);  // output features of a workgroup
+  __shared__ __attribute__((aligned(16))) u32x4 st0[KS * TT * 64];
+  __shared__ __attribute__((aligned(16))) u32x4 st1[KS * TT * 64];
+  __shared__ __attribute__((aligned(16))) u32x4 st2[KS * TT * 64];
+  __shared__ __attribute__((aligned(16))) u32x4 st3[KS * TT * 64];
+
+  const uint32_t RT = (rows + BM - 1) / BM, total = RT * NT, per = (total + 7) / 8;
+  const uint32_t vid = (blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (vid >= total) return;   // the grid is 8 * per workgroups: every id below total comes up once
+  const uint32_t nfull = RT / HB;
+  uint32_t rt, nt;
+  if (vid < nfull * HB * NT) {
+    const uint32_t band = vid / (HB * NT), rem = vid % (HB * NT);
+    nt = rem / HB;
+    rt = band * HB + rem % HB;
+  } else {
+    const uint32_t rem = vid - nfull * HB * NT, cnt = RT - nfull * HB;
+    nt = rem / cnt;
+    rt = nfull * HB + rem % cnt;
+  }
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64, jl = lane % 16, kg = lane / 16;
+  const int grp = KS > 1 ? wv / NW : 0, wave = wv % NW, wr = wave / WC, wc = wave % WC;
+  const uint32_t r0 = rt * BM, KT = K / 32;
+  const uint32_t kfirst = grp ? (KT + 1) / 2 : 0u;                       // this group's K steps
+  const uint32_t kcount = KS > 1 ? (grp ? KT / 2 : (KT + 1) / 2) : KT;
+  const uint32_t kboth = KS > 1 ? KT / 2 : KT, kmost = KS > 1 ? (KT + 1) / 2 : KT;  // steps all groups / some group have
+
+  // this lane's 16 bytes of the tiles wave, wave + NW, ... of a K step
+  const char* src[ND];
+  uint32_t step[ND];
+#pragma unroll
+  for (int j = 0; j < ND; ++j) {
+    const uint32_t tile = wave + NW * j;
+    if (tile < (uint32_t)TA) {
+      if (XT) {
+        const uint32_t g = min(r0 / 32 + tile / 2, (rows + 31) / 32 - 1);   // row groups past the end: a valid one
+        src[j] = (const char*)(x + (((size_t)g * KT * 2 + tile % 2) * 64 + lane) * 8);
+        step[j] = 2048;
+      } else {
+        const uint32_t r = min(r0 + tile * 16 + jl, rows - 1);
+        src[j] = (const char*)(x + (size_t)r * K + kg * 8);
+        step[j] = 64;
+      }
+    } else {
+      const uint32_t bt = tile - TA;
+      if (SWIGLU) src[j] = (const char*)(((bt % 2) ? w2 : w) + (size_t)(nt * (TB / 2) + bt / 2) * KT * 64 + lane);
+      else src[j] = (const char*)(w + (size_t)(nt * TB + bt) * KT * 64 + lane);
+      step[j] = 1024;
+    }
+  }
+
+  f32x4 acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  auto stage = [&](auto c) -> u32x4* {
+    if constexpr (decltype(c)::v % S == 0) return st0;
+    else if constexpr (decltype(c)::v % S == 1) return st1;
+    else if constexpr (decltype(c)::v % S == 2) return st2;
+    else return st3;
+  };
+  // one index into the stage each: the compiler loses track of which array an access belongs to when the
+  // address is a long chain
+  const int put0 = (grp * TT + wave) * 64, geta = (grp * TT + MI * wr) * 64 + lane, getb = (grp * TT + TA + NJ * wc) * 64 + lane;
+  auto request = [&](auto c, uint32_t kt) {
+    u32x4* s = stage(c);
+    const uint32_t k = min(kfirst + kt, KT - 1);   // past the end: the last step again, never multiplied
+#pragma unroll
+    for (int j = 0; j < ND; ++j) load_to_lds(src[j] + (size_t)k * step[j], s + put0 + NW * 64 * j);
+  };
+  // K step kt from stage c; requests step kt + S - 1 into the stage whose reads all wavefronts have finished
+  // (they waited for them before the barrier that ended their step kt - 1)
+  auto k_step = [&](auto c, uint32_t kt, auto last) {
+    u32x4* s = stage(c);
+    bf16x8 a[MI], b[NJ];
+#pragma unroll
+    for (int i = 0; i < NJ; ++i) b[i] = __builtin_bit_cast(bf16x8, s[getb + 64 * i]);
+#pragma unroll
+    for (int i = 0; i < MI; ++i) a[i] = __builtin_bit_cast(bf16x8, s[geta + 64 * i]);
+    request(Int<decltype(c)::v + S - 1>{}, kt + S - 1);
+    if constexpr (PING) {
+      __builtin_amdgcn_s_waitcnt(kWaitLds);
+      __builtin_amdgcn_s_waitcnt(wait_vm((S - 2) * ND));
+      bare_barrier();
+    }
+    auto products = [&] {
+      if constexpr (PING) __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+      if constexpr (PING) __builtin_amdgcn_s_setprio(0);
+    };
+    if constexpr (decltype(last)::v == 0) products();
+    else if (kt < kcount) products();   // the second group of an odd number of steps has one fewer
+    if constexpr (!PING) {
+      // the operands have been read: a wavefront's products wait for them and come before the barrier
+      __builtin_amdgcn_s_waitcnt(kWaitLds);
+      __builtin_amdgcn_s_waitcnt(wait_vm((S - 2) * ND));
+    }
+    bare_barrier();
+  };
+
+  request(Int<0>{}, 0);
+  request(Int<1>{}, 1);
+  request(Int<2>{}, 2);
+  __builtin_amdgcn_s_waitcnt(wait_vm((S - 2) * ND));
+  bare_barrier();
+  const bool second = PING && wv >= 4;   // the wavefront of a SIMD that is half a step behind
+  if (second) bare_barrier();
+  uint32_t kt = 0;
+  for (; kt + S <= kboth; kt += S) {
+    k_step(Int<0>{}, kt, Int<0>{});
+    k_step(Int<1>{}, kt + 1, Int<0>{});
+    k_step(Int<2>{}, kt + 2, Int<0>{});
+    k_step(Int<3>{}, kt + 3, Int<0>{});
+  }
+  if (kt < kmost) k_step(Int<0>{}, kt, Int<1>{});
+  if (kt + 1 < kmost) k_step(Int<1>{}, kt + 1, Int<1>{});
+  if (kt + 2 < kmost) k_step(Int<2>{}, kt + 2, Int<1>{});
+  if (KS > 1 && kt + 3 < kmost) k_step(Int<3>{}, kt + 3, Int<1>{});
+  if (PING && !second) bare_barrier();   // every wavefront passes the same number of barriers
+  __builtin_amdgcn_s_waitcnt(wait_vm(0));   // the stages are free once the last requests have arrived
+  __syncthreads();
+
+  // the row tiles this wavefront writes out: with two groups, the first half is summed and written by group 0,
+  // the second by group 1
+  constexpr int MO = MI / KS;
+  f32x4 res[MO][NJ];
+  if constexpr (KS > 1) {
+    f32x4* ex = (f32x4*)(wave % 2 ? st1 : st0) + (wave / 2) * (2 * MO * NJ * 64);   // [for group][tile][lane]
+#pragma unroll
+    for (int i = 0; i < MO; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const f32x4 lo = acc[i][j], hi = acc[MO + i][j];
+        f32x4 other;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          other[v] = grp ? lo[v] : hi[v];
+          res[i][j][v] = grp ? hi[v] : lo[v];
+        }
+        ex[((1 - grp) * MO * NJ + i * NJ + j) * 64 + lane] = other;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < MO; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const f32x4 o = ex[(grp * MO * NJ + i * NJ + j) * 64 + lane];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) res[i][j][v] += o[v];   // group 0's sum + group 1's, either way round
+      }
+    __syncthreads();
+  } else {
+#pragma unroll
+    for (int i = 0; i < MO; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) res[i][j] = acc[i][j];
+  }
+
+  // Output, one row tile of every wavefront at a time, through an LDS strip of the wavefront's own (so no
+  // barriers).  Accumulator element v of a lane: token row 4 * kg + v of the row tile, column jl of B tile j.  Staging
+  // columns: plain, B tile j at 16 * j; SwiGLU, B tile j = 2 * f + matrix at CW / 2 * matrix + 16 * f.
+  constexpr int ES = CW + 4;                       // floats per staged row
+  constexpr int CPR = (SWIGLU ? CW / 2 : CW) / 8;  // 16-byte output chunks per row
+  constexpr int RPP = 64 / CPR < 16 ? 64 / CPR : 16;   // rows per pass
+  static_assert((NW * KS + 1) / 2 * 16 * ES * 4 <= KS * TT * 1024, "the strips of four wavefronts fit a stage");
+  float(*e)[ES] = (float(*)[ES])((wv % 2 ? (char*)st1 : (char*)st0) + (wv / 2) * (16 * ES * 4));
+#pragma unroll
+  for (int i = 0; i < MO; ++i) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int col = SWIGLU ? (int)(CW / 2) * (j % 2) + 16 * (j / 2) + jl : 16 * j + jl;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) e[4 * kg + v][col] = res[i][j][v];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int cc = lane % CPR;
+#pragma unroll
+    for (int ps = 0; ps < 16 / RPP; ++ps) {
+      const int rr = ps * RPP + lane / CPR;
+      const uint32_t row = r0 + wr * (16 * MI) + (grp * MO + i) * 16 + rr;
+      if (rr < 16 && row < rows) {
+        float y[8];
+        *(f32x4*)&y[0] = *(const f32x4*)&e[rr][8 * cc];
+        *(f32x4*)&y[4] = *(const f32x4*)&e[rr][8 * cc + 4];
+        const uint32_t n = nt * BNF + wc * (BNF / WC) + 8 * cc;
+        const int which = n >= dst.start[2] ? 2 : n >= dst.start[1] ? 1 : 0;
+        const uint32_t width = dst.start[which + 1] - dst.start[which], col = n - dst.start[which];
+        const size_t oo = (size_t)row * width + col;
+        if (SWIGLU) {
+          float u[8];
+          *(f32x4*)&u[0] = *(const f32x4*)&e[rr][CW / 2 + 8 * cc];
+          *(f32x4*)&u[4] = *(const f32x4*)&e[rr][CW / 2 + 8 * cc + 4];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) y[k] = y[k] / (1.0f + __expf(-y[k])) * u[k];
+        } else if (residual) {
+          float rv[8];
+          unpack16<BF16>(*(const u32x4*)(residual + oo), rv);
+#pragma unroll
+          for (int k = 0; k < 8; ++k) y[k] += rv[k];
+        }
+        const u32x4 o = pack16_round<BF16>(y);
+        if (out_tiled) ((u32x4*)dst.ptr[which])[tiled_chunk(row, col, width)] = o;
+        else *(u32x4*)(dst.ptr[which] + oo) = o;
+      }
+    }
+  }
+}
+
+// The tile of a shape.  The time of a launch is the number of rounds its workgroups take on 256 compute units
+// times the K steps times what a step of a resident workgroup takes; measured us per K step at 640 and 16384
+// rows, K = 11008 / 4096:
+//   256 x 256             one workgroup per compute unit  0.46 (few) - 0.69 (chip full)
+//   128 x 256             one                             0.34 - 0.44
+//   128 x 128             two of four wavefronts          0.26 alone on its compute unit, 0.46 for a pair
+//   128 x 128, K in two   one                             0.19 - 0.25
+//   64 x 64, K in two     two                             0.11 alone, 0.19 for a pair
+// so 256 x 256 wins where the chip is full (4 rounds of it against 16 of 128 x 128), the others where its
+// workgroups are few: 640 rows x 11008 -> 4096 takes 157, 117, 88, 67, 94 us in this order.
+enum RowsShape { kTile256, kTile128x256, kTile128, kTile128K2, kTile64K2 };
+
+RowsShape rows_shape(uint32_t rows, uint32_t bcols) {
+  auto tiles = [&](uint32_t bm, uint32_t bn) { return (uint64_t)((rows + bm - 1) / bm) * (bcols / bn); };
+  // hundredths of a us per K step: one workgroup per compute unit at a time; two, a last one may have it alone
+  auto one = [](uint64_t t, uint64_t cost) { return (t + 255) / 256 * cost; };
+  auto two = [](uint64_t t, uint64_t alone, uint64_t pair) {
+    const uint64_t rem = t % 512;
+    return t / 512 * pair + (rem > 256 ? pair : rem ? alone : 0);
+  };
+  RowsShape best = kTile128;
+  uint64_t cost = two(tiles(128, 128), 26, 46);
+  auto take = [&](RowsShape s, uint64_t c) {
+    if (c < cost) {
+      cost = c;
+      best = s;
+    }
+  };
+  take(kTile128K2, one(tiles(128, 128), 25));
+  take(kTile64K2, two(tiles(64, 64), 11, 19));
+  if (bcols % 256 == 0) {
+    take(kTile128x256, one(tiles(128, 256), 44));
+    take(kTile256, one(tiles(256, 256), 69));
+  }
+  return best;
+}
+
+template <bool SWIGLU, bool XT, int MI, int NJ, int WR, int WC, int KS>
+void launch_shape(const void* x, const void* w, const void* w2, const void* residual, const LinearOut& dst, uint32_t rows,
+                  uint32_t K, uint32_t bcols, bool out_tiled, hipStream_t s) {
+  const uint32_t NT = bcols / (16 * NJ * WC), RT = (rows + 16 * MI * WR - 1) / (16 * MI * WR);
+  hipLaunchKernelGGL((linear_rows_kernel<SWIGLU, XT, MI, NJ, WR, WC, KS>), dim3(8 * ((RT * NT + 7) / 8)),
+                     dim3(64 * WR * WC * KS), 0, s, (const uint16_t*)x, (const u32x4*)w, (const u32x4*)w2,
+                     (const uint16_t*)residual, dst, rows, K, NT, out_tiled ? 1u : 0u);
+}
+
+template <bool SWIGLU, bool XT>
+void launch_rows(const void* x, const void* w, const void* w2, const void* residual, const LinearOut& dst, uint32_t rows,
+                 uint32_t K, uint32_t N, bool out_tiled, hipStream_t s) {
+  const uint32_t bcols = SWIGLU ? 2 * N : N;
+  switch (rows_shape(rows, bcols)) {
+    case kTile256: return launch_shape<SWIGLU, XT, 8, 4, 2, 4, 1>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
+    case kTile128x256: return launch_shape<SWIGLU, XT, 4, 4, 2, 4, 1>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
+    case kTile128: return launch_shape<SWIGLU, XT, 4, 4, 2, 2, 1>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
+    case kTile128K2: return launch_shape<SWIGLU, XT, 4, 4, 2, 2, 2>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
+    case kTile64K2: return launch_shape<SWIGLU, XT, 2, 2, 2, 2, 2>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
+  }
+}
+
+}  // namespace
+
+hipError_t launch_linear_rows(const void* x, const void* w, const void* w2, const void* residual, const LinearOut& dst,
+                              uint32_t rows, uint32_t K, uint32_t N, bool x_tiled, bool out_tiled, hipStream_t s) {
+  if (w2) {
+    if (x_tiled) launch_rows<true, true>(x, w, w2, residual, dst, rows, K, N, out_tiled, s);
+    else launch_rows<true, false>(x, w, w2, residual, dst, rows, K, N, out_tiled, s);
+  } else {
+    if (x_tiled) launch_rows<false, true>(x, w, w2, residual, dst, rows, K, N, out_tiled, s);
+    else launch_rows<false, false>(x, w, w2, residual, dst, rows, K, N, out_tiled, s);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace bct

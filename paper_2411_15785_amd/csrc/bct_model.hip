@@ -17,6 +17,7 @@
 #include <stdio.h>
 
 #include "bct_device.h"
+#include "bct_linear.h"
 
 namespace bct {
 
@@ -43,13 +44,6 @@ __global__ __launch_bounds__(256) void pack_weight_kernel(const uint16_t* __rest
   packed[c] = *(const u32x4*)(w + (size_t)n * K + k);
 }
 
-// Tiled activations: rows in groups of 32, inputs in groups of 32; group (r / 32, k / 32) is 2 KB, two A
-// operands of v_mfma_f32_16x16x32_bf16 (rows 0-15 and 16-31 of the group), each 64 lanes x 16 bytes with
-// lane 16 * ((k % 32) / 8) + r % 16 holding the inputs k % 8 = 0..7.  Returns the 16-byte chunk index.
-__device__ __forceinline__ size_t tiled_chunk(uint32_t r, uint32_t k, uint32_t K) {
-  return ((((size_t)(r / 32) * (K / 32) + k / 32) * 2 + (r % 32) / 16) * 64) + 16 * ((k % 32) / 8) + r % 16;
-}
-
 __global__ __launch_bounds__(256) void pack_rows_kernel(const uint16_t* __restrict__ x, u32x4* __restrict__ packed,
                                                         uint32_t rows, uint32_t K) {
   const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;  // 16-byte chunk of the row-major array
@@ -57,12 +51,6 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const uint16_t* __restri
   const uint32_t r = (uint32_t)(c / (K / 8)), k = (uint32_t)(c % (K / 8)) * 8;
   packed[tiled_chunk(r, k, K)] = *(const u32x4*)(x + (size_t)r * K + k);
 }
-
-// Up to three row-major outputs side by side along N: output i takes the features [start[i], start[i + 1]).
-struct LinearOut {
-  uint16_t* ptr[3];
-  uint32_t start[4];
-};
 
 // FT: feature tiles (of 16) per workgroup.  Every wavefront streams FT (x 2 for SwiGLU) weight tiles against
 // each activation fragment it loads: the activations come from L2, where all workgroups ask for the same
@@ -181,176 +169,6 @@ __global__ __launch_bounds__(64 * WAVES) void linear_kernel(const uint16_t* __re
   }
 }
 
-// The same projections for MANY token rows (a prefill chunk: batch x T rows), where the product is a
-// dense contraction bound by the matrix cores and no longer by streaming the weights.  A workgroup of
-// 2 x WC wavefronts owns 32 * MI token rows x 64 * WC output features (SwiGLU: 32 * WC features of both
-// matrices), each wavefront 16 * MI x 64 of it as MI x 4 accumulators of v_mfma_f32_16x16x32_bf16; built as
-// 128 x 128 (MI 4, WC 2) and 256 x 256 (MI 8, WC 4).  Both operands are already stored in MFMA operand
-// order (packed weights, tiled activations), so a K step of 32 inputs is a set of one-KB tiles that the
-// workgroup copies to LDS unchanged (linear 16-byte accesses on both sides) and every wavefront reads back
-// its MI row tiles and four feature tiles; the loads of the next K step are in flight in registers while the
-// current one is multiplied (two LDS stages, one barrier per K step).
-// Workgroups are numbered so that those resident on one XCD at a time (every eighth workgroup id) cover
-// 8 row tiles x consecutive feature tiles: each operand panel is fetched into that XCD's L2 once for
-// eight uses.  Output: the accumulators go through LDS (fp32) and leave as 16-byte row-contiguous chunks,
-// with the residual added / the SwiGLU applied in fp32 before the one rounding to bf16.
-template <bool SWIGLU, bool XT, int MI, int WC>
-__global__ __launch_bounds__(128 * WC, 2) void linear_rows_kernel(const uint16_t* __restrict__ x,
-                                                                  const u32x4* __restrict__ w,
-                                                                  const u32x4* __restrict__ w2,
-                                                                  const uint16_t* residual, LinearOut dst,
-                                                                  uint32_t rows, uint32_t K, uint32_t NT,
-                                                                  uint32_t out_tiled) {
-  // 2 x WC wavefronts; a wavefront owns MI row tiles x 4 feature tiles (of 16 each)
-  constexpr int NW = 2 * WC;                       // wavefronts
-  constexpr int TA = 2 * MI, TB = 4 * WC;          // 1 KB tiles of a K step: activations, weights
-  constexpr int NA = TA / NW, NB = TB / NW;        // of them per thread
-  static_assert(TA % NW == 0 && TB % NW == 0, "tiles must divide among the wavefronts");
-  constexpr uint32_t HB = 8;                       // row tiles of a band
-  constexpr uint32_t BM = 32 * MI;                 // token rows of a workgroup
-  constexpr uint32_t BNF = (SWIGLU ? 32 : 64) * WC;  // output features of a workgroup
-  constexpr int ES = 68;                           // floats per row of the output staging (64 + pad)
-  constexpr int ER = NW > 4 ? 16 : 32;             // rows of a wavefront staged at a time
-  constexpr int kStage = (TA + TB) * 1024, kOut = NW * ER * ES * 4;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * kStage > kOut ? 2 * kStage : kOut];
-  u32x4(*sA)[TA][64] = (u32x4(*)[TA][64])smem;             // [stage][tile][lane]
-  u32x4(*sB)[TB][64] = (u32x4(*)[TB][64])(smem + 2 * TA * 1024);
-  float(*sE)[ER][ES] = (float(*)[ER][ES])smem;             // [wavefront][row][column], after the K loop
-
-  const uint32_t RT = (rows + BM - 1) / BM, total = RT * NT, per = (total + 7) / 8;
-  const uint32_t vid = (blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (vid >= total) return;
-  const uint32_t nfull = RT / HB;
-  uint32_t rt, nt;
-  if (vid < nfull * HB * NT) {
-    const uint32_t band = vid / (HB * NT), rem = vid % (HB * NT);
-    nt = rem / HB;
-    rt = band * HB + rem % HB;
-  } else {
-    const uint32_t rem = vid - nfull * HB * NT, cnt = RT - nfull * HB;
-    nt = rem / cnt;
-    rt = nfull * HB + rem % cnt;
-  }
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, jl = lane % 16, kg = lane / 16;
-  const int wr = wave / WC, wc = wave % WC;
-  const uint32_t r0 = rt * BM, KT = K / 32;
-
-  // this thread's chunks of a K step: tiles wave, wave + NW, ... of either operand
-  const uint16_t* pa[NA];
-  const u32x4* pb[NB];
-#pragma unroll
-  for (int j = 0; j < NA; ++j) {
-    const uint32_t tile = wave + NW * j;
-    if (XT) {
-      const uint32_t g = min(r0 / 32 + tile / 2, (rows + 31) / 32 - 1);   // row groups past the end: a valid one
-      pa[j] = x + (((size_t)g * KT * 2 + tile % 2) * 64 + lane) * 8;
-    } else {
-      const uint32_t r = min(r0 + tile * 16 + jl, rows - 1);
-      pa[j] = x + (size_t)r * K + kg * 8;
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const uint32_t tile = wave + NW * j;
-    if (SWIGLU) pb[j] = ((tile % 2) ? w2 : w) + (size_t)(nt * (TB / 2) + tile / 2) * KT * 64 + lane;
-    else pb[j] = w + (size_t)(nt * TB + tile) * KT * 64 + lane;
-  }
-  constexpr size_t astep = XT ? 128 * 8 : 32;
-
-  f32x4 acc[MI][4];
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  u32x4 ga[NA], gb[NB];
-#pragma unroll
-  for (int j = 0; j < NA; ++j) ga[j] = *(const u32x4*)pa[j];
-#pragma unroll
-  for (int j = 0; j < NB; ++j) gb[j] = *pb[j];
-#pragma unroll
-  for (int j = 0; j < NA; ++j) sA[0][wave + NW * j][lane] = ga[j];
-#pragma unroll
-  for (int j = 0; j < NB; ++j) sB[0][wave + NW * j][lane] = gb[j];
-  __syncthreads();
-  for (uint32_t kt = 0; kt < KT; ++kt) {
-    const int st = kt & 1;
-    const bool more = kt + 1 < KT;
-    if (more) {
-#pragma unroll
-      for (int j = 0; j < NA; ++j) ga[j] = *(const u32x4*)(pa[j] + (size_t)(kt + 1) * astep);
-#pragma unroll
-      for (int j = 0; j < NB; ++j) gb[j] = pb[j][(size_t)(kt + 1) * 64];
-    }
-    bf16x8 a[MI], b[4];
-#pragma unroll
-    for (int i = 0; i < MI; ++i) a[i] = __builtin_bit_cast(bf16x8, sA[st][MI * wr + i][lane]);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) b[i] = __builtin_bit_cast(bf16x8, sB[st][4 * wc + i][lane]);
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-    if (more) {
-#pragma unroll
-      for (int j = 0; j < NA; ++j) sA[st ^ 1][wave + NW * j][lane] = ga[j];
-#pragma unroll
-      for (int j = 0; j < NB; ++j) sB[st ^ 1][wave + NW * j][lane] = gb[j];
-    }
-    __syncthreads();
-  }
-
-  // Output, ER rows of every wavefront at a time.  Accumulator element v of a lane: token row 4 * kg + v of
-  // row tile i, column jl of B tile j.  Staging columns: plain, B tile j at 16 * j; SwiGLU, B tile
-  // j = 2 * f + matrix at 32 * matrix + 16 * f (gate columns 0..31, up columns 32..63).
-  constexpr int TPP = ER / 16;                     // row tiles per pass
-#pragma unroll
-  for (int hf = 0; hf < MI / TPP; ++hf) {
-    if (hf) __syncthreads();
-#pragma unroll
-    for (int ii = 0; ii < TPP; ++ii)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int col = SWIGLU ? 32 * (j % 2) + 16 * (j / 2) + jl : 16 * j + jl;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) sE[wave][16 * ii + 4 * kg + v][col] = acc[TPP * hf + ii][j][v];
-      }
-    __syncthreads();
-    const int cc = lane % 8;
-    if (!SWIGLU || cc < 4) {
-#pragma unroll
-      for (int ps = 0; ps < ER / 8; ++ps) {
-        const int rr = ps * 8 + lane / 8;
-        const uint32_t row = r0 + wr * (16 * MI) + hf * ER + rr;
-        if (row < rows) {
-          float y[8];
-          *(f32x4*)&y[0] = *(const f32x4*)&sE[wave][rr][8 * cc];
-          *(f32x4*)&y[4] = *(const f32x4*)&sE[wave][rr][8 * cc + 4];
-          const uint32_t n = nt * BNF + (SWIGLU ? wc * 32 : wc * 64) + 8 * cc;
-          const int which = n >= dst.start[2] ? 2 : n >= dst.start[1] ? 1 : 0;
-          const uint32_t width = dst.start[which + 1] - dst.start[which], col = n - dst.start[which];
-          const size_t oo = (size_t)row * width + col;
-          if (SWIGLU) {
-            float u[8];
-            *(f32x4*)&u[0] = *(const f32x4*)&sE[wave][rr][32 + 8 * cc];
-            *(f32x4*)&u[4] = *(const f32x4*)&sE[wave][rr][32 + 8 * cc + 4];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) y[e] = y[e] / (1.0f + __expf(-y[e])) * u[e];
-          } else if (residual) {
-            float rv[8];
-            unpack16<BF16>(*(const u32x4*)(residual + oo), rv);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) y[e] += rv[e];
-          }
-          const u32x4 o = pack16_round<BF16>(y);
-          if (out_tiled) ((u32x4*)dst.ptr[which])[tiled_chunk(row, col, width)] = o;
-          else *(u32x4*)(dst.ptr[which] + oo) = o;
-        }
-      }
-    }
-  }
-}
-
 // One workgroup per row; a thread keeps its (up to eight) 16-byte chunks of the row in registers between
 // the sum of squares and the scaling, so the row is read once.
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const uint16_t* x, const uint16_t* gain, uint16_t* out,
@@ -460,8 +278,7 @@ bct_status mfail(bct_status s, const char* msg) {
   snprintf(g_merr, sizeof(g_merr), "%s", msg);
   return s;
 }
-bct_status launched(const char* what) {
-  const hipError_t e = hipGetLastError();
+bct_status launched(const char* what, hipError_t e = hipGetLastError()) {
   if (e == hipSuccess) return BCT_OK;
   snprintf(g_merr, sizeof(g_merr), "%s launch failed: %s", what, hipGetErrorString(e));
   return BCT_ERR_HIP;
@@ -494,9 +311,9 @@ static void launch_linear_w(const void* x, const void* w, const void* residual, 
                        K, 0u);
 }
 
-// The kernel of a projection shape.  Many rows (from 128 on): the matrix-core kernel, for feature counts its
-// 128-feature (SwiGLU: 64) workgroup tiles cover exactly; 256 x 256 workgroups halve the LDS and L1 traffic
-// per flop (measured +5..10 % at 16384 rows) but pad the rows to 256 and need a feature count they divide.
+// The kernel of a projection shape.  Many rows (from 128 on): the matrix-core kernel (bct_linear_rows.hip), for
+// feature counts its 128-feature (SwiGLU: 64) tiles cover exactly; from 1024 rows on with tiles of up to
+// 256 x 256 where the feature count allows.
 // Few rows: the streaming kernel; measured at 32 rows (weights in TB/s): K = 4096, N = 4096 / 12288: 16
 // wavefronts, one feature tile 3.6 / 4.0 against 2.8 / 3.8 for two tiles (too few workgroups); N = 32000:
 // two tiles 5.0 against 4.3.
@@ -508,33 +325,6 @@ static uint32_t linear_kernel_of(uint32_t rows, uint32_t N, bool swiglu) {
   // features (W_q | W_wq | W_wv at 4096 each) are exactly 256 workgroups, 19.5 us against 24.3
   if (!swiglu && N % 48 == 0 && N / 48 >= 256) return BCTM_KERNEL_STREAMING_TRIPLE;
   return BCTM_KERNEL_STREAMING;
-}
-
-template <bool SWIGLU, int MI, int WC>
-static void launch_rows_shape(const void* x, const void* w, const void* w2, const void* residual,
-                              const LinearOut& dst, uint32_t rows, uint32_t K, uint32_t N, uint32_t flags,
-                              void* hip_stream) {
-  const uint32_t NT = N / ((SWIGLU ? 32u : 64u) * WC), RT = (rows + 32 * MI - 1) / (32 * MI);
-  const dim3 grid(8 * ((RT * NT + 7) / 8)), block(128 * WC);
-  const uint32_t ot = flags & BCTM_OUT_TILED ? 1u : 0u;
-  if (flags & BCTM_X_TILED)
-    hipLaunchKernelGGL((linear_rows_kernel<SWIGLU, true, MI, WC>), grid, block, 0, (hipStream_t)hip_stream,
-                       (const uint16_t*)x, (const u32x4*)w, (const u32x4*)w2, (const uint16_t*)residual, dst, rows, K,
-                       NT, ot);
-  else
-    hipLaunchKernelGGL((linear_rows_kernel<SWIGLU, false, MI, WC>), grid, block, 0, (hipStream_t)hip_stream,
-                       (const uint16_t*)x, (const u32x4*)w, (const u32x4*)w2, (const uint16_t*)residual, dst, rows, K,
-                       NT, ot);
-}
-
-template <bool SWIGLU>
-static void launch_rows(uint32_t kernel, const void* x, const void* w, const void* w2, const void* residual,
-                        const LinearOut& dst, uint32_t rows, uint32_t K, uint32_t N, uint32_t flags,
-                        void* hip_stream) {
-  if (kernel == BCTM_KERNEL_TILE256)
-    launch_rows_shape<SWIGLU, 8, 4>(x, w, w2, residual, dst, rows, K, N, flags, hip_stream);
-  else
-    launch_rows_shape<SWIGLU, 4, 2>(x, w, w2, residual, dst, rows, K, N, flags, hip_stream);
 }
 
 template <int WV, int UN, int FT>
@@ -606,8 +396,9 @@ static bct_status launch_linear(const void* x, const void* w, const void* residu
                                 uint32_t rows, uint32_t K, uint32_t N, uint32_t flags, void* hip_stream) {
   const uint32_t kernel = linear_kernel_of(rows, N, false);
   if (kernel == BCTM_KERNEL_TILE128 || kernel == BCTM_KERNEL_TILE256)
-    launch_rows<false>(kernel, x, w, nullptr, residual, dst, rows, K, N, flags, hip_stream);
-  else if (kernel == BCTM_KERNEL_STREAMING_WIDE) launch_linear_w<8, 4, 2>(x, w, residual, dst, rows, K, N, flags, hip_stream);
+    return launched("linear", launch_linear_rows(x, w, nullptr, residual, dst, rows, K, N, flags & BCTM_X_TILED, false,
+                                                 (hipStream_t)hip_stream));
+  if (kernel == BCTM_KERNEL_STREAMING_WIDE) launch_linear_w<8, 4, 2>(x, w, residual, dst, rows, K, N, flags, hip_stream);
   else if (kernel == BCTM_KERNEL_STREAMING_TRIPLE) launch_linear_w<8, 4, 3>(x, w, residual, dst, rows, K, N, flags, hip_stream);
   else launch_linear_w<16, 8, 1>(x, w, residual, dst, rows, K, N, flags, hip_stream);
   return launched("linear");
@@ -653,8 +444,10 @@ bct_status bctm_swiglu(const void* x, const void* w_gate, const void* w_up, void
   if (!al16(w_up)) return mfail(BCT_ERR_MISALIGNED, "pointers must be 16-byte aligned");
   const LinearOut dst = {{(uint16_t*)out, nullptr, nullptr}, {0u, N, N, N}};
   const uint32_t kernel = linear_kernel_of(rows, N, true);
-  if (kernel == BCTM_KERNEL_TILE128 || kernel == BCTM_KERNEL_TILE256) launch_rows<true>(kernel, x, w_gate, w_up, nullptr, dst, rows, K, N, flags, hip_stream);
-  else launch_swiglu_w<4, 8, 1>(x, w_gate, w_up, dst, rows, K, N, flags, hip_stream);   // 36 us at 4096 -> 11008 (8 wavefronts: 38)
+  if (kernel == BCTM_KERNEL_TILE128 || kernel == BCTM_KERNEL_TILE256)
+    return launched("swiglu", launch_linear_rows(x, w_gate, w_up, nullptr, dst, rows, K, N, flags & BCTM_X_TILED,
+                                                 flags & BCTM_OUT_TILED, (hipStream_t)hip_stream));
+  launch_swiglu_w<4, 8, 1>(x, w_gate, w_up, dst, rows, K, N, flags, hip_stream);   // 36 us at 4096 -> 11008 (8 wavefronts: 38)
   return launched("swiglu");
 }
 

@@ -80,6 +80,19 @@ def test_linear_many_rows(M, rows, K, N, with_res, tiled):
     check_close(host(out), R.linear(x, w, res), 2.0 ** -20 * mass, f"linear {rows}x{K}x{N}")
 
 
+# one shape for each workgroup tile of the many-rows kernel (64 x 64 and 128 x 128 with K in two parts, 128 x 128,
+# 128 x 256, 256 x 256), with K steps of 1 up to more than the four stages, odd and even, and ragged last row tiles
+@pytest.mark.parametrize("rows,K,N", [(129, 32, 128), (191, 160, 384), (128, 4096, 128), (520, 32, 4096), (521, 96, 4096),
+                                      (640, 288, 4096), (1030, 32, 4224), (1030, 224, 4224), (900, 32, 4608),
+                                      (1000, 192, 4608), (4000, 32, 4096), (3841, 160, 4096)])
+@pytest.mark.parametrize("tiled", [False, True])
+def test_linear_every_workgroup_tile(M, rows, K, N, tiled):
+    x, w, res = draw(1, (rows, K)), draw(2, (N, K), K ** -0.5), draw(3, (rows, N))
+    out = M.bctm_linear(M.bctm_pack_rows(dev(x)) if tiled else dev(x), M.bctm_pack_weight(dev(w)), dev(res))
+    mass = np.abs(R.bf16_to_f64(x)) @ np.abs(R.bf16_to_f64(w)).T
+    check_close(host(out), R.linear(x, w, res), 2.0 ** -20 * mass, f"linear {rows}x{K}x{N}")
+
+
 def test_linear_many_rows_selects_the_right_operands(M):
     # one-hot weight rows pick input features, distinct per output feature and row: exact
     rows, K, N = 200, 256, 256
@@ -125,6 +138,11 @@ def test_swiglu_many_rows(M, rows, K, N):
     if N % 32 == 0:
         t = M.bctm_swiglu(M.bctm_pack_rows(dev(x)), pg, pu, tiled=True)
         assert np.array_equal(untile(t, rows, N), host(out))
+
+
+@pytest.mark.parametrize("rows,K,N", [(640, 96, 2048), (1030, 160, 2112), (900, 32, 2304), (3841, 160, 2048)])
+def test_swiglu_every_workgroup_tile(M, rows, K, N):
+    test_swiglu_many_rows(M, rows, K, N)
 
 
 def tiled_offsets(rows, K):
