@@ -72,7 +72,8 @@ def dominant_kernel(plan, w):
     if plan["one_launch"]:
         return f"decode_fused_kernel<{dt},{w.d},{gt}>"
     if w.dtype == "bf16" and w.d == 128 and w.G > 2:
-        return f"mv_pass_gqa_kernel<true,{plan['mv_workgroup']},{norm},{plan['mv_loads_per_lane']}>"
+        rescore = "true" if w.B * w.Hkv * plan["mv_splits"] > 16384 else "false"   # keys shared by the batch
+        return f"mv_pass_gqa_kernel<true,{plan['mv_workgroup']},{norm},{plan['mv_loads_per_lane']},{rescore}>"
     return f"mv_pass_kernel<{dt},{w.d},{gt},true,true,{plan['mv_workgroup']},{plan['mv_loads_per_lane']},{norm}>"
 
 

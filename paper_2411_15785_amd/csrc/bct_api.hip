@@ -180,6 +180,7 @@ bct_status run_decode(bct_cache* c, char* ws, const void* q, const void* k_new, 
   p.has_write = k_new ? 1u : 0u;
   p.has_read = q ? 1u : 0u;
   p.R = p.has_write + (p.has_read ? p.G : 0u);
+  if (!p.has_read) p.rescore = 0u;
   p.q_bstride = q_bstride;
   p.kv_bstride = kv_bstride;
   p.gate = gate;

@@ -194,6 +194,82 @@ __global__ __launch_bounds__(64) void scores_mfma_bf16_kernel(const DecodeParams
   }
 }
 
+// The (max, sum) pairs alone, for an MV pass that scores its own slots again (p.rescore): one wavefront owns
+// 16*NT slots and walks the query rows 16 at a time with v_mfma_f32_16x16x32_bf16, the products of that pass
+// (score16).  Element v of a lane: slot 4 * (l / 16) + v of a group of 16, query row l % 16, so a row's (max,
+// sum) over the tile is an in-lane reduction plus two exchanges.  Bound by the latency of a wavefront's walk over
+// the query rows; with nothing to store, splitting the rows over two wavefronts per SIMD pays (a tile's keys
+// are then read twice, from L2): B = 64, Hkv = 8, G = 4, M = 8192, whole step: 1024 wavefronts 425 us, 2048 418,
+// 4096 418, 8192 424.
+template <int D, int NT>
+__global__ __launch_bounds__(64) void stats_mfma_bf16_kernel(const DecodeParams p) {
+  constexpr int KS = D / 32;
+  const uint32_t tile = blockIdx.x, h = blockIdx.y;
+  const int lane = threadIdx.x, col = lane % 16, kg = lane / 16;
+  const uint16_t* mk = (const uint16_t*)p.mk + (size_t)h * p.M * D;
+  const uint32_t slot0 = tile * (16 * NT);
+  const uint32_t rtot = p.B * p.R;
+
+  // Order of the requests: the first block of query rows, then the keys; the rows of the next block of 16 are
+  // requested before the products of the current one.
+  auto load_rows = [&](uint32_t rb, u32x4 (&xf)[KS]) {
+    const uint32_t rho = rb * 16 + col;
+    if (rho < rtot) {
+      const uint32_t b = rho / p.R, r = rho % p.R;
+      const uint16_t* x = (p.has_write && r == 0)
+                              ? (const uint16_t*)p.wq + (size_t)b * p.kv_bstride + (size_t)h * D
+                              : (const uint16_t*)p.q + (size_t)b * p.q_bstride +
+                                    (size_t)(h * p.G + (r - p.has_write)) * D;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) xf[ks] = *(const u32x4*)(x + ks * 32 + kg * 8);
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) xf[ks] = (u32x4){0u, 0u, 0u, 0u};
+    }
+  };
+  u32x4 xn[KS];
+  if (blockIdx.z * 16 < rtot) load_rows(blockIdx.z, xn);
+
+  u32x4 kf[NT][KS];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      kf[t][ks] = *(const u32x4*)(mk + (size_t)(slot0 + t * 16 + col) * D + ks * 32 + kg * 8);
+
+  for (uint32_t rb = blockIdx.z; rb * 16 < rtot; rb += gridDim.z) {
+    const uint32_t rho = rb * 16 + col;   // this lane's query row
+    const bool valid = rho < rtot;
+    const uint32_t b = valid ? rho / p.R : 0u, r = valid ? rho % p.R : 0u;
+    u32x4 xf[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) xf[ks] = xn[ks];
+    if ((rb + gridDim.z) * 16 < rtot) load_rows(rb + gridDim.z, xn);
+    const float scale = (p.has_write && r == 0) ? p.wscale_l2e : p.rscale_l2e;
+    const size_t urow = (size_t)(b * p.Hkv + h) * p.R + r;
+    f32x4 c[NT];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      c[t] = score16<D>(kf[t], xf);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        c[t][v] *= scale;
+        mx = fmaxf(mx, c[t][v]);
+      }
+    }
+    // (max, sum of exp2(score - max)) of the row over the tile
+    mx = xor_max<16, 32>(mx);
+    float sm = 0.f;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sm += fast_exp2(c[t][v] - mx);
+    sm = xor_sum<16, 32>(sm);
+    if (valid && kg == 0) p.stats[urow * p.n_tiles + tile] = make_float2(mx, sm);
+  }
+}
+
 // Softmax normalisers: one wavefront per (memory, row) merges the per-tile
 // (max, sum) pairs into the row's (max, 1 / sum of exp2(score - max)).  A step
 // size, if given, multiplies the write row's 1 / sum: the MV pass then applies
@@ -313,11 +389,19 @@ void plan_decode(DecodeParams& p, int dtype) {
   }
   p.n_tiles = p.M / p.stat_tile;
   plan_mv_pass(p, dtype);
+  if (!use_mfma_scores(p, dtype)) p.rescore = 0u;
   p.fused = (p.M <= kFusedMaxM && (uint64_t)p.B * p.Hkv <= kFusedMaxUnits) ? 1u : 0u;
 }
 
 template <int D, int NT>
 static hipError_t launch_scores_mfma(const DecodeParams& p, hipStream_t s) {
+  if (p.rescore) {
+    const uint32_t stiles = p.M / (32 * NT), blocks = (p.B * p.R + 15) / 16;
+    uint32_t zs = (uint32_t)((2048 + (uint64_t)stiles * p.Hkv - 1) / ((uint64_t)stiles * p.Hkv));
+    if (zs > blocks) zs = blocks;
+    hipLaunchKernelGGL((stats_mfma_bf16_kernel<D, 2 * NT>), dim3(stiles, p.Hkv, zs), dim3(64), 0, s, p);
+    return hipGetLastError();
+  }
   const uint32_t tiles = p.M / (32 * NT);
   const uint32_t rbs = (p.B * p.R + 31) / 32;
   uint32_t z = 1;

@@ -139,6 +139,26 @@ __device__ __forceinline__ float xor_max(float v) {
   return v;
 }
 
+// The value that lane L of this lane's row of 16 holds (a data-parallel-primitive move, no LDS crossbar).
+template <int L>
+__device__ __forceinline__ float row_lane(float v) {
+  return dpp_partner<0x150 + L>(v);   // row_newbcast
+}
+
+// Scores of 16 key rows against up to 16 query rows on v_mfma_f32_16x16x32_bf16, D the head dimension.  key: this
+// lane's key row (row l % 16 of the 16), query: this lane's query row (column l % 16), both already advanced
+// to the lane's 8 inputs at 8 * (l / 16).  Element v of the result: key row 4 * (l / 16) + v, query row l % 16.
+// The statistics pass and the MV pass both call this, so a score has the same bits in both.
+template <int D>
+__device__ __forceinline__ f32x4 score16(const u32x4* key, const u32x4* query) {
+  f32x4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int ks = 0; ks < D / 32; ++ks)
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, key[ks]), __builtin_bit_cast(bf16x8, query[ks]),
+                                                c, 0, 0, 0);
+  return c;
+}
+
 // One wavefront merges the per-tile (max, sum of exp2(score - max)) pairs of a row, up to 128 of them (lane l
 // takes tiles l and l + 64), into the row's (max, sum).  The operations and their order are those of
 // normalise_kernel, so both give the same bits.

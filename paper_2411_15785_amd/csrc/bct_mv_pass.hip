@@ -236,6 +236,14 @@ void plan_mv_pass(DecodeParams& p, int dtype) {
   // to the launch.
   const uint64_t wgs = (uint64_t)p.B * p.Hkv * p.S;
   p.fuse_norm = (p.n_tiles <= kMaxMergedTiles && (!gqa || wgs <= 16384)) ? 1u : 0u;
+  // Such a grid also scores its slots again instead of reading scores: what 1 + G fp32 scores per slot cost on their
+  // way through memory then exceeds the keys' extra trip from L2.  Whole step, us, scores through memory ->
+  // scored again (several caches in turn, so that scratch does not stay in the last-level cache): B = 64, Hkv = 8,
+  // G = 4, M = 8192 (65536 workgroups) 442 -> 418; B = 32 223 -> 212; G = 8: B = 64, M = 3072 206 -> 192, B = 36,
+  // M = 4096 (18432 workgroups) 160 -> 145; 16384 workgroups (B = 16, Hkv = 16, G = 4) 117 -> 118, 8192 80 -> 83.
+  // With one query head per KV head (2 scores per slot) it loses at every size: 345 -> 378 us for the pass at
+  // B = 32, H = 32, M = 4096.
+  p.rescore = gqa && wgs > 16384 ? 1u : 0u;
 }
 
 template <typename DT, int D, int GT, int BS, int U, bool NORM>

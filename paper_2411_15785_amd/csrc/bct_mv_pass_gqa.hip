@@ -17,6 +17,13 @@
 //     into hi + lo bf16 parts (two MFMAs) so that the weights keep fp32 grade;
 //   accumulator e of lane (sub, sl): out[g = 4 sl + v][column 8 sub + e].
 // The MFMA also sums over the four lane groups, so no lane exchange is needed.
+//
+// RESCORE (keys shared by the batch): the scores are not read from memory but computed again from the
+// workgroup's 16 KB of keys (from L2: every sequence's workgroups read the same table): two v_mfma_f32_16x16x32_bf16 per 32 inputs,
+// key row 4 a + c of group n = slot 8 a + 4 n + c, column g = query head g, column 15 = the write row.  Lane
+// (sub, sl) then holds, in the two groups, exactly the scores of head g = sub for its 8 slots, the A
+// operand above; the write weights reach the 16 lanes of a slot row by a row broadcast from column 15.
+// For large grids only (plan_mv_pass has the measurements); those take their normalisers from the launch.
 #include "bct_device.h"
 #include "bct_internal.h"
 
@@ -26,12 +33,13 @@ namespace {
 
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
-template <bool WRITE, int BS, bool NORM, int U>
+template <bool WRITE, int BS, bool NORM, int U, bool RESCORE>
 __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
   constexpr int D = 128, NB = U / 8, NW = BS / 64, SPB = NW * 4 * U;   // a wavefront covers 4 U slots
   constexpr uint32_t W = WRITE ? 1u : 0u;
   __shared__ float s_red[NW * kMaxG * D];
 
+  static_assert(!RESCORE || U == 8, "a lane's slots are two MFMA groups of four");
   const uint32_t split = blockIdx.x, unit = block_unit();
   if (unit >= p.B * p.Hkv) return;
   const uint32_t b = unit / p.Hkv, h = unit % p.Hkv;
@@ -44,6 +52,27 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
   const bool active = slot0 < M;
   uint16_t* mv = (uint16_t*)p.mv + ((size_t)unit * M + slot0) * D + sub * 8;
 
+  // RESCORE: the keys and this lane's query row (column sub), requested before MV
+  u32x4 kf[RESCORE ? 2 : 1][4], xq[4];
+  const bool wcol = WRITE && sub == 15;
+  if (RESCORE) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) xq[ks] = (u32x4){0u, 0u, 0u, 0u};
+    if ((uint32_t)sub < G || wcol) {
+      const uint16_t* x = wcol ? (const uint16_t*)p.wq + (size_t)b * p.kv_bstride + (size_t)h * D
+                               : (const uint16_t*)p.q + (size_t)b * p.q_bstride + (size_t)(h * G + sub) * D;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) xq[ks] = *(const u32x4*)(x + ks * 32 + sl * 8);
+    }
+    if (active) {
+      const uint16_t* mk = (const uint16_t*)p.mk + ((size_t)h * M + split * SPB + wave * (4 * U)) * D + sl * 8;
+#pragma unroll
+      for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+          kf[RESCORE ? n : 0][ks] = *(const u32x4*)(mk + (size_t)(8 * (sub / 4) + 4 * n + sub % 4) * D + ks * 32);
+    }
+  }
   u32x4 raw[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) raw[u] = (u32x4){0u, 0u, 0u, 0u};
@@ -78,16 +107,42 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
     if ((uint32_t)sub < G) nr = p.norm[(size_t)unit * R + W + sub];
   }
 
-  const float* sc = p.scores + (size_t)unit * R * M + slot0;  // row r at sc + r * M
-  float rw[U];
+  // rw: the lane's weights as an A operand (zero in lanes without a query head); ww: the write weights of its slots
+  float rw[U], ww[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) rw[u] = 0.f;
-  if (active && (uint32_t)sub < G) {
+  for (int u = 0; u < U; ++u) rw[u] = ww[u] = 0.f;
+  if (RESCORE) {
+    if (active) {
+      const float scale = wcol ? p.wscale_l2e : p.rscale_l2e;
+      const float2 n2 = wcol ? nw : nr;
 #pragma unroll
-    for (int k = 0; k < U / 4; ++k) {
-      const f32x4v a = *(const f32x4v*)(sc + (size_t)(W + sub) * M + 4 * k);
+      for (int n = 0; n < 2; ++n) {
+        const f32x4 c = score16<D>(kf[RESCORE ? n : 0], xq);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) rw[4 * k + i] = fast_exp2(a[i] - nr.x) * nr.y;
+        for (int v = 0; v < 4; ++v) {
+          const float e = fast_exp2(c[v] * scale - n2.x) * n2.y;
+          if (WRITE) ww[4 * n + v] = row_lane<15>(e);
+          rw[4 * n + v] = (uint32_t)sub < G ? e : 0.f;
+        }
+      }
+    }
+  } else {
+    const float* sc = p.scores + (size_t)unit * R * M + slot0;  // row r at sc + r * M
+    if (active && (uint32_t)sub < G) {
+#pragma unroll
+      for (int k = 0; k < U / 4; ++k) {
+        const f32x4v a = *(const f32x4v*)(sc + (size_t)(W + sub) * M + 4 * k);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rw[4 * k + i] = fast_exp2(a[i] - nr.x) * nr.y;
+      }
+    }
+    if (WRITE && active) {
+#pragma unroll
+      for (int k = 0; k < U / 4; ++k) {
+        const f32x4v a = *(const f32x4v*)(sc + 4 * k);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ww[4 * k + i] = fast_exp2(a[i] - nw.x) * nw.y;
+      }
     }
   }
   // hi + lo bf16 parts of the lane's weights, 8 slots per block: the A operands
@@ -103,13 +158,6 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
     }
 
   if (WRITE && active) {
-    float ww[U];
-#pragma unroll
-    for (int k = 0; k < U / 4; ++k) {
-      const f32x4v a = *(const f32x4v*)(sc + 4 * k);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) ww[4 * k + i] = fast_exp2(a[i] - nw.x) * nw.y;
-    }
     float wvf[8];
     const uint16_t* wv = (const uint16_t*)p.wv + (size_t)b * p.kv_bstride + (size_t)h * D;
     unpack16<BF16>(*(const u32x4*)(wv + sub * 8), wvf);
@@ -174,11 +222,13 @@ template <int BS, int U>
 static void launch_gqa_bs(const DecodeParams& p, hipStream_t s) {
   const dim3 grid = unit_grid(p.S, (uint64_t)p.B * p.Hkv), block(BS);
   if (p.has_write) {
-    if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, true, U>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U>), grid, block, 0, s, p);
+    if (p.rescore) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U, true>), grid, block, 0, s, p);
+    else if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, true, U, false>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U, false>), grid, block, 0, s, p);
   } else {
-    if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, true, U>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, false, U>), grid, block, 0, s, p);
+    if (p.rescore) hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, false, U, true>), grid, block, 0, s, p);
+    else if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, true, U, false>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, false, U, false>), grid, block, 0, s, p);
   }
 }
 
@@ -187,6 +237,7 @@ static void launch_gqa_bs(const DecodeParams& p, hipStream_t s) {
 hipError_t launch_stream_gqa(const DecodeParams& p, hipStream_t s) {
   if (p.d != 128 || p.G <= 2 || p.G > kMaxG || !p.has_read) return hipErrorInvalidConfiguration;
   if (p.mv_bs != 128 || p.mv_u != 8) return hipErrorInvalidConfiguration;
+  if (p.rescore && p.fuse_norm) return hipErrorInvalidConfiguration;
   launch_gqa_bs<128, 8>(p, s);
   return hipGetLastError();
 }

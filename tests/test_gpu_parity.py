@@ -165,6 +165,13 @@ def test_one_step_from_common_state(P, R, name, B, Hq, Hkv, d, M, dtype, mode, f
         assert st == t + 1
 
 
+# Several query heads per KV head over more than 16384 workgroups of 64 slots: the MV pass scores its slots again.
+@pytest.mark.parametrize("B,G,M,mode", [(2100, 3, 64, "rw"), (2100, 3, 64, "read_only"), (2100, 4, 64, "write_only"),
+                                        (420, 8, 320, "rw")])
+def test_one_step_of_a_large_grid_with_several_query_heads(P, R, B, G, M, mode):
+    test_one_step_from_common_state(P, R, f"large_grid_g{G}_m{M}", B, 8 * G, 8, 128, M, "bf16", mode, 0)
+
+
 @pytest.mark.parametrize("dtype,G", [("bf16", 1), ("f32", 2)])
 def test_more_memories_than_one_grid_dimension_holds(P, R, dtype, G):
     """66000 memories (batch 1100 x 60 KV heads): launches indexed by memory spill from grid.y into grid.z.
