@@ -465,7 +465,7 @@ bct_status bct_prefill_gated(bct_cache* c, const void* q, const void* k_new, con
   pp.wv = (const uint16_t*)v_new;
   pp.out = (uint16_t*)out;
   pp.gate = gate;
-  pp.norm_w = (float2*)(c->ws + c->off_pf_norm_w);
+  pp.norm_w = (float*)(c->ws + c->off_pf_norm_w);
   pp.norm_r = (float2*)(c->ws + c->off_pf_norm_r);
   pp.snap = (uint16_t*)(c->ws + c->off_pf_snap);
   pp.wvt = (uint16_t*)(c->ws + c->off_pf_wvt);

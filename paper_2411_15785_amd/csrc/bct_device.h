@@ -91,6 +91,36 @@ __device__ __forceinline__ float load_elem(const uint16_t* p, size_t i) {
   return __uint_as_float((uint32_t)p[i] << 16);
 }
 
+// 16 bytes per lane from memory (an address per lane) to LDS at lds + 16 * lane, lds the same in every lane; no trip
+// through registers.  Counts as an outstanding vector-memory operation until the bytes are in LDS.
+__device__ __forceinline__ void load_to_lds(const void* g, void* lds) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                   (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+// The same address, opaque to the compiler: with it as the scalar base of a lane's 32-bit offset a request needs one
+// vector register for its address, where the compiler would keep a 64-bit address per lane and request.
+__device__ __forceinline__ const char* scalar_base(const void* p) {
+  const char* q = (const char*)p;
+  asm("" : "+s"(q));
+  return q;
+}
+// A barrier that waits for nothing else: requests into LDS stay in flight across it.
+__device__ __forceinline__ void bare_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+}
+// s_waitcnt operands: at most n vector-memory operations outstanding / no LDS operation outstanding
+constexpr int wait_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
+constexpr int kWaitLds = 15 | (7 << 4) | (0 << 8) | (3 << 14);
+
+template <int I>
+struct Int {
+  static constexpr int v = I;
+};
+
 // The memory a workgroup of a unit_grid launch works on (see bct_internal.h).
 __device__ __forceinline__ uint32_t block_unit() { return blockIdx.z * 32768u + blockIdx.y; }
 

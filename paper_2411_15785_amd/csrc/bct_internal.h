@@ -63,16 +63,19 @@ struct PrefillParams {
   const uint16_t* wq;  // [B][T][Hkv][d] or null
   const uint16_t* wv;  // [B][T][Hkv][d] or null
   uint16_t* out;       // [B][T][Hq][d] or null
-  float2* norm_w;      // [B*Hkv][T]   (max, 1/sum) of each write row
-  float2* norm_r;      // [B*Hkv][T*G] (max, 1/sum) of each read row
-  uint16_t* snap;      // [ceil(T/128)][B*Hkv][d][M]: MV at the start of each sub-chunk, transposed
-  uint16_t* wvt;       // [B*Hkv][d][Tpad]: WV transposed, zero beyond T
+  float* norm_w;       // [B*Hkv][T]   shift of each write row: max + log2(sum of exp2(score - max))
+  float2* norm_r;      // [B*Hkv][T*G] (the same, unused) of each read row, for a chunk that only reads
+  uint16_t* snap;      // [ceil(T/128)][B*Hkv] MV at the start of each sub-chunk as operand tiles (M x d); a chunk that
+                       // only reads: one copy of MV as [B*Hkv][d][M]
+  uint16_t* wvt;       // [B*Hkv] WV as operand tiles (Tpad x d), zero beyond T
   uint32_t Tpad;       // T rounded up to whole sub-chunks
   uint32_t B, Hq, Hkv, G, M, d, T;
   uint32_t has_write, has_read, mk_per_seq;
   float rscale_l2e, wscale_l2e;
   uint32_t c_begin;    // first sub-chunk of a read launch
   uint32_t stats_read; // the statistics kernel also covers the read rows (chunks that only read)
+  uint32_t stats_split;  // workgroups of the statistics kernel that share a row tile's keys
+  float2* stats_part;    // [B*Hkv][stats_split][rows] their (max, sum) pairs, if more than one
   const float* gate;   // [B][T][Hkv] step sizes (any sign) or null
 };
 constexpr uint32_t kPrefillSubChunk = 128;

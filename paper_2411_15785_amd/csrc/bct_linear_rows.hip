@@ -32,27 +32,6 @@ namespace bct {
 
 namespace {
 
-__device__ __forceinline__ void load_to_lds(const void* g, void* lds) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
-                                   (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
-}
-// A barrier that waits for nothing else: requests into LDS stay in flight across it.
-__device__ __forceinline__ void bare_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("" ::: "memory");
-}
-// s_waitcnt operands: at most n vector-memory operations outstanding / no LDS operation outstanding
-constexpr int wait_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
-constexpr int kWaitLds = 15 | (7 << 4) | (0 << 8) | (3 << 14);
-
-template <int I>
-struct Int {
-  static constexpr int v = I;
-};
-
 // KS groups of WR x WC wavefronts; a wavefront owns 16 * MI token rows x 16 * NJ B-tile columns (SwiGLU: gate and
 // up tiles alternate, so half as many output features); group g sums the K steps [KT * g / KS, ...).
 template <bool SWIGLU, bool XT, int MI, int NJ, int WR, int WC, int KS>

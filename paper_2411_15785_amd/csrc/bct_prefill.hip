@@ -17,15 +17,12 @@
 // sub-chunks, the read rows normalised on the fly); a chunk that only reads: transpose (MV) -> stats
 // (read rows) -> read.
 //
-// All matrix products use v_mfma_f32_32x32x16_bf16 with both operands read from
-// LDS tiles whose rows run along the contraction index (C[i][j] += sum_k
-// A[i][k] B[j][k]); the two operands whose memory layout runs the other way
-// (MV over slots, WV over tokens) are transposed once per chunk into the
-// workspace, and the MV snapshots are written transposed in the first place.  Rows are padded by 16 bytes so that the 32
-// lanes of an operand read fall into different banks.  The accumulator of lane
-// l holds column j = l % 32 and rows i = 8*(v/4) + 4*(l/32) + v%4; each product
-// is oriented so that a lane's four consecutive v run along the NEXT product's
-// contraction index and can be written to LDS as one 8-byte store.
+// All matrix products use v_mfma_f32_32x32x16_bf16, whose operands are rows along the contraction index
+// (C[i][j] += sum_k A[i][k] B[j][k]); the accumulator of lane l holds column j = l % 32 and rows
+// i = 8*(v/4) + 4*(l/32) + v%4.  Operands that are contracted the other way than they lie in memory (MV over slots, WV
+// over tokens) are kept in the workspace as operand tiles (below), in the order in which a lane's accumulator
+// registers become the next product's operand.  Tiles come to LDS by load_to_lds, one or two tiles ahead,
+// and LDS reads are issued a region ahead of the products that use them.
 //
 // Precision: scores in fp32 from exact bf16 products; softmax weights are
 // rounded to bf16 as MFMA operands for the reads; for the state they are split
@@ -40,6 +37,7 @@ namespace {
 
 constexpr int kTC = 128;          // tokens per sub-chunk = rows per tile
 constexpr float kNegBig = -1e30f;  // stands in for -inf in running maxima
+constexpr uint32_t kMaxStatsSplit = 8;  // shares of the keys in a statistics launch
 constexpr float kNoRow = 1e30f;    // shift of a row that does not exist: exp2(score - kNoRow) = 0
 
 __device__ __forceinline__ f32x16 mfma_bf16(const bf16x8 a, const bf16x8 b, const f32x16 c) {
@@ -86,14 +84,6 @@ struct Tile {
       missing |= ok ? 0u : (1u << i);
     }
   }
-  // the same for data read once (past the caches, so that it does not push out what is reused)
-  __device__ __forceinline__ void fetch_block_once(const uint16_t* src, size_t src_ld) {
-    const int ch = threadIdx.x % CPR, r0 = threadIdx.x / CPR;
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-      v[i] = __builtin_nontemporal_load((const u32x4*)(src + (size_t)(r0 + i * RPP) * src_ld + ch * 8));
-    missing = 0;
-  }
   // rows at src + r * src_ld, all present
   __device__ __forceinline__ void fetch_block(const uint16_t* src, size_t src_ld) {
     const int ch = threadIdx.x % CPR, r0 = threadIdx.x / CPR;
@@ -108,18 +98,6 @@ struct Tile {
       *(u32x4*)(dst + (r0 + i * RPP) * ld + ch * 8) = ((missing >> i) & 1u) ? (u32x4){0u, 0u, 0u, 0u} : v[i];
   }
 };
-template <int D, int NROWS, typename F>
-__device__ __forceinline__ void rows_to_lds(uint16_t* dst, int ld, const uint16_t* safe, F rowptr) {
-  Tile<NROWS, D> t;
-  t.fetch_rows(safe, rowptr);
-  t.put(dst, ld);
-}
-template <int NROWS, int NCOLS>
-__device__ __forceinline__ void block_to_lds(uint16_t* dst, int ld, const uint16_t* src, size_t src_ld) {
-  Tile<NROWS, NCOLS> t;
-  t.fetch_block(src, src_ld);
-  t.put(dst, ld);
-}
 __device__ __forceinline__ void store4_bf16(uint16_t* dst, float a, float b, float c, float d) {
   uint2 w;
   w.x = pack_bf16x2(a, b);
@@ -135,13 +113,61 @@ __device__ __forceinline__ void merge_stat(float& m, float& s, float mo, float s
 
 }  // namespace
 
+// ------------------------------------------------------------------ operand tiles and key tiles
+
+// A matrix contracted over its ROWS (slots of MV, tokens of WV), stored as tiles of 16 rows x 32 columns in the order
+// a lane of v_mfma_f32_32x32x16_bf16 holds them, with the rows in the order in which a product's accumulator
+// hands its own rows on: lane l = column l % 32, half h = l / 32, its 8 elements are the rows
+// 4 h + {0, 1, 2, 3} and 8 + 4 h + {0, 1, 2, 3} of the 16.  A lane's accumulator registers 8 j .. 8 j + 7 (rows
+// 8 (v / 4) + 4 h + v % 4), packed to bf16, then ARE an operand of the next product: weights and states go
+// from product to product without leaving the registers or through LDS as whole 16-byte chunks.
+// Chunk index of (row group of 16, column group of 32, lane) in a matrix of D columns.
+template <int D>
+__device__ __forceinline__ size_t operand_chunk(uint32_t g16, uint32_t c32, uint32_t lane) {
+  return ((size_t)g16 * (D / 32) + c32) * 64 + lane;
+}
+__device__ __forceinline__ bf16x8 pack8(const f32x16& a, int j) {
+  return __builtin_bit_cast(bf16x8, (u32x4){pack_bf16x2(a[8 * j + 0], a[8 * j + 1]), pack_bf16x2(a[8 * j + 2], a[8 * j + 3]),
+                                            pack_bf16x2(a[8 * j + 4], a[8 * j + 5]), pack_bf16x2(a[8 * j + 6], a[8 * j + 7])});
+}
+
+// Rows contracted along their own elements (keys, write queries) come to LDS as operand tiles of 32 rows x 16
+// elements: load instruction ks of 32 rows brings, per lane, the 16 bytes that the lane then reads as its operand
+// (row l % 32, elements 16 ks + 8 (l / 32) ..), at 1 KB * ks + 16 l, so that every LDS read is linear and its address
+// a constant away from the lane's.  Byte offset of a lane in the rows, from element 16 ks of the first one; rows are
+// `stride` elements apart:
+__device__ __forceinline__ uint32_t row_operand(uint32_t lane, uint32_t stride) {
+  return ((lane % 32) * stride + (lane / 32) * 8) * 2;
+}
+// ... and a tile that comes and goes in whole rows: the 16-byte chunk c of row r at position c ^ swizzle(r) of the row
+template <int D>
+__device__ __forceinline__ int swizzle(int r) {
+  return D == 128 ? r % 16 : (r / 2) % 8;
+}
+// Instructions are not moved across.
+__device__ __forceinline__ void region() { __builtin_amdgcn_sched_barrier(0); }
+
+template <int D>
+struct RowTile {
+  static constexpr int CPR = D / 8;        // chunks per row
+  static constexpr int RPL = 64 / CPR;     // rows per load instruction
+  // load instruction n of a tile: this lane's row and chunk
+  static __device__ __forceinline__ int row(int n, int lane) { return n * RPL + lane / CPR; }
+  static __device__ __forceinline__ int chunk(int n, int lane) { return (lane % CPR) ^ swizzle<D>(row(n, lane)); }
+};
+
+// max over the two lanes l, l ^ 32 (v_permlane32_swap: no LDS crossbar)
+__device__ __forceinline__ float max_of_halves(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 // ------------------------------------------------------------------ transposes
 
-// MFMA operands must run along the contraction index, and two of them do not
-// in memory: WV [token][column] is contracted over tokens and MV [slot][column]
-// over slots.  This kernel writes the transposed copies once per chunk:
-//   which = 0:  WVt[unit][column][token]  (tokens >= T zero-filled up to Tpad)
-//   which = 1:  snap[0][unit][column][slot] = MV at the start of the chunk
+// MFMA operands must run along the contraction index, and two of them do not in memory: WV [token][column] is
+// contracted over tokens and MV [slot][column] over slots.  Once per chunk:
+//   which = 0:  WVt[unit], WV as operand tiles (see operand_chunk; tokens >= T zero-filled up to Tpad)
+//   which = 1:  snap[0][unit][column][slot] = MV, for a chunk that only reads
 // One workgroup transposes 64 rows through LDS.
 template <int D>
 __global__ __launch_bounds__(256) void prefill_transpose_kernel(const PrefillParams p, int which) {
@@ -152,24 +178,39 @@ __global__ __launch_bounds__(256) void prefill_transpose_kernel(const PrefillPar
   const uint32_t b = unit / p.Hkv, h = unit % p.Hkv;
   const uint32_t r0 = blockIdx.x * 64;
   const uint32_t rows = which == 0 ? p.Tpad : p.M;
-  rows_to_lds<D, 64>(sT, LD, p.mv, [&](int r) -> const uint16_t* {
-    if (which == 0) return r0 + r < p.T ? p.wv + (((size_t)b * p.T + r0 + r) * p.Hkv + h) * D : nullptr;
-    return p.mv + ((size_t)unit * p.M + r0 + r) * D;
-  });
-  __syncthreads();
-  uint16_t* dst = (which == 0 ? p.wvt : p.snap) + (size_t)unit * D * rows + r0;
-  // A negative step size eta_t (section 3.5 reading: MV += eta_t ww^T wv) flips the sign of token t's row of
-  // WV here, which is exact; the statistics kernel folds |eta_t| into the token's shift.  A thread's 8 rows
-  // are the same in every pass of the loop below (256 is a multiple of 8).
-  u32x4 flip = {0u, 0u, 0u, 0u};
-  if (which == 0 && p.gate) {
-    const uint32_t t8 = r0 + (threadIdx.x % 8) * 8;
-    uint32_t sg[8];
+  {
+    Tile<64, D> t;
+    t.fetch_rows(p.mv, [&](int r) -> const uint16_t* {
+      if (which == 0) return r0 + r < p.T ? p.wv + (((size_t)b * p.T + r0 + r) * p.Hkv + h) * D : nullptr;
+      return p.mv + ((size_t)unit * p.M + r0 + r) * D;
+    });
+    if (which == 0 && p.gate) {
+      // A negative step size eta_t (section 3.5 reading: MV += eta_t ww^T wv) flips the sign of token t's row of
+      // WV here, which is exact; the statistics kernel folds |eta_t| into the token's shift.
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      sg[k] = (t8 + k < p.T && p.gate[((size_t)b * p.T + t8 + k) * p.Hkv + h] < 0.f) ? 0x8000u : 0u;
-    flip = (u32x4){sg[0] | (sg[1] << 16), sg[2] | (sg[3] << 16), sg[4] | (sg[5] << 16), sg[6] | (sg[7] << 16)};
+      for (int i = 0; i < Tile<64, D>::N; ++i) {
+        const uint32_t tk = r0 + threadIdx.x / Tile<64, D>::CPR + i * Tile<64, D>::RPP;
+        const uint32_t flip = tk < p.T && p.gate[((size_t)b * p.T + tk) * p.Hkv + h] < 0.f ? 0x80008000u : 0u;
+        t.v[i] ^= (u32x4){flip, flip, flip, flip};
+      }
+    }
+    t.put(sT, LD);
   }
+  __syncthreads();
+  if (which == 0) {
+    uint16_t* dst = p.wvt + ((size_t)unit * rows + r0) * D;
+    // thread -> (column j, the 8 tokens of an operand lane)
+    for (int i = threadIdx.x; i < D * 8; i += 256) {
+      const int lane = i % 64, tile = i / 64, half = lane / 32;
+      const int j = 32 * (tile % (D / 32)) + lane % 32, t8 = 16 * (tile / (D / 32)) + 4 * half;
+      uint32_t e[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) e[k] = sT[(t8 + (k / 4) * 8 + k % 4) * LD + j];
+      *(u32x4*)(dst + (size_t)i * 8) = (u32x4){e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+    }
+    return;
+  }
+  uint16_t* dst = p.snap + (size_t)unit * D * rows + r0;
   // thread -> (column j, 8 consecutive rows)
   for (int i = threadIdx.x; i < D * 8; i += 256) {
     const int j = i / 8, rr = (i % 8) * 8;
@@ -178,7 +219,7 @@ __global__ __launch_bounds__(256) void prefill_transpose_kernel(const PrefillPar
     v.y = (uint32_t)sT[(rr + 2) * LD + j] | ((uint32_t)sT[(rr + 3) * LD + j] << 16);
     v.z = (uint32_t)sT[(rr + 4) * LD + j] | ((uint32_t)sT[(rr + 5) * LD + j] << 16);
     v.w = (uint32_t)sT[(rr + 6) * LD + j] | ((uint32_t)sT[(rr + 7) * LD + j] << 16);
-    *(u32x4*)(dst + (size_t)j * rows + rr) = v ^ flip;
+    *(u32x4*)(dst + (size_t)j * rows + rr) = v;
   }
 }
 
@@ -187,18 +228,33 @@ __global__ __launch_bounds__(256) void prefill_transpose_kernel(const PrefillPar
 // Row statistics of the score matrix: for each write row (token t) and read
 // row (token t, query head g) of a memory, the shift max + log2(sum of
 // exp2(score - max)) over all M slots, so that a weight is exp2(score - shift)
-// with no further multiplication (stored in .x of a float2; rows that do not
-// exist use kNoRow, which makes every weight zero).  One workgroup = 128 rows;
-// it walks the keys 128 slots at a time; each of its eight wavefronts scores
-// 32 slots of the tile against 64 of the rows.
+// with no further multiplication (rows that do not exist use kNoRow, which makes every weight zero).
+// One workgroup = 128 rows; it walks its share of the keys 128 slots at a time; each of its eight wavefronts
+// scores 32 slots of the tile against 64 of the rows.  Bound by the vector work for the exponentials (32 per lane
+// and tile against 16 matrix instructions); the products of a tile are issued in between the exponentials of
+// the one before, and the keys are requested into LDS two tiles ahead.
+// A launch with few rows splits the keys over p.stats_split workgroups and leaves their (max, sum) pairs in
+// p.stats_part for prefill_stats_merge_kernel.
+__device__ __forceinline__ void store_shift(const PrefillParams& p, uint32_t unit, uint32_t b, uint32_t h, uint32_t nw,
+                                            uint32_t nr, uint32_t row, float m, float s) {
+  if (row < nw) {
+    // a step size eta scales the token's write weights: exp2(score - shift) * |eta|
+    // = exp2(score - (shift - log2 |eta|)); eta = 0 gives shift = +inf and weights 0
+    // (|eta| here; the sign of eta rides on the token's row of WV^T, see prefill_transpose_kernel)
+    const float le = p.gate ? __log2f(fabsf(p.gate[((size_t)b * p.T + row) * p.Hkv + h])) : 0.f;
+    p.norm_w[(size_t)unit * p.T + row] = m + __log2f(s) - le;
+  } else if (row - nw < nr) {
+    p.norm_r[(size_t)unit * p.T * p.G + (row - nw)] = make_float2(m + __log2f(s), 0.f);
+  }
+}
+
 template <int D>
-__global__ __launch_bounds__(512, 4) void prefill_stats_kernel(const PrefillParams p) {
-  constexpr int LD = D + 8, KS = D / 16, NT = 512;
-  // the query tile is only read into registers before the loop: the key tiles reuse its memory
-  __shared__ __attribute__((aligned(16))) uint16_t sTile[128 * LD];
+__global__ __launch_bounds__(512, 2) void prefill_stats_kernel(const PrefillParams p) {
+  constexpr int KS = D / 16;
+  constexpr int kTile = 128 * D;           // elements of a key tile
+  constexpr int NL = kTile / 512 / 8;      // its load instructions per wavefront
+  __shared__ __attribute__((aligned(16))) uint16_t sK0[kTile], sK1[kTile], sK2[kTile];
   __shared__ float2 sRed[4][kTC];
-  uint16_t* const sX = sTile;
-  uint16_t* const sK = sTile;
 
   // launch order: all sequences of one KV head, then the next head, so that the workgroups in flight
   // share one head's keys (1 MB at M = 4096) in each XCD's L2 instead of cycling through all heads
@@ -206,81 +262,121 @@ __global__ __launch_bounds__(512, 4) void prefill_stats_kernel(const PrefillPara
   if (uy >= p.B * p.Hkv) return;
   const uint32_t h = uy / p.B, b = uy % p.B, unit = b * p.Hkv + h;
   const uint32_t nw = p.has_write ? p.T : 0u, nr = (p.has_read && p.stats_read) ? p.T * p.G : 0u;
-  const uint32_t row0 = blockIdx.x * kTC;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, col = lane % 32, half = lane / 32;
+  const uint32_t row0 = blockIdx.x / p.stats_split * kTC, part = blockIdx.x % p.stats_split;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64, col = lane % 32, half = lane / 32;
   // wavefront = (32 slots sg of the key tile, 64 rows rh of the row tile)
   const int sg = wave & 3, rh = wave >> 2;
-
-  {
-    Tile<kTC, D, NT> t;
-    t.fetch_rows(p.mk, [&](int r) -> const uint16_t* {
-      uint32_t row = row0 + r;
-      if (row < nw) return p.wq + (((size_t)b * p.T + row) * p.Hkv + h) * D;
-      row -= nw;
-      if (row < nr) return p.q + (((size_t)b * p.T + row / p.G) * p.Hq + h * p.G + row % p.G) * D;
-      return nullptr;
-    });
-    t.put(sX, LD);
-  }
+  // this workgroup's slots: whole tiles but for the last share, whose end may cut a tile in half
+  const uint32_t tiles = (p.M + 127) / 128, tile0 = (uint32_t)((uint64_t)tiles * part / p.stats_split),
+                 tile1 = (uint32_t)((uint64_t)tiles * (part + 1) / p.stats_split), n = tile1 - tile0;
   const uint16_t* mk = p.mk + (size_t)(p.mk_per_seq ? unit : h) * p.M * D;
 
-  float scale[2], m[2], s[2];
-#pragma unroll
-  for (int jt = 0; jt < 2; ++jt) {
-    scale[jt] = (row0 + 64 * rh + 32 * jt + col < nw) ? p.wscale_l2e : p.rscale_l2e;
-    m[jt] = kNegBig;
-    s[jt] = 0.f;
-  }
-  // the query rows do not change over the loop: keep their operand fragments in registers.
+  // the query rows do not change over the loop: their operand fragments stay in registers.
   // A negative scale is moved into the row itself (negating bf16 is exact), so that below the
   // largest raw score is also the largest scaled one and the scaling can ride in the exponent's fma.
-  __syncthreads();
+  float scale[2], m[2], s[2];
   bf16x8 xb[2][KS];
 #pragma unroll
   for (int jt = 0; jt < 2; ++jt) {
+    const uint32_t row = row0 + 64 * rh + 32 * jt + col;
+    scale[jt] = row < nw ? p.wscale_l2e : p.rscale_l2e;
+    m[jt] = kNegBig;
+    s[jt] = 0.f;
     const uint32_t flip = scale[jt] < 0.f ? 0x80008000u : 0u;
     scale[jt] = fabsf(scale[jt]);
+    const uint32_t rr = row - nw;
+    const uint16_t* src = row < nw ? p.wq + (((size_t)b * p.T + row) * p.Hkv + h) * D
+                                   : p.q + (((size_t)b * p.T + rr / p.G) * p.Hq + h * p.G + rr % p.G) * D;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      u32x4 v = __builtin_bit_cast(u32x4, frag(sX, LD, 64 * rh + 32 * jt + col, ks * 16 + half * 8));
-      v ^= (u32x4){flip, flip, flip, flip};
-      xb[jt][ks] = __builtin_bit_cast(bf16x8, v);
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (row < nw + nr) v = *(const u32x4*)(src + ks * 16 + half * 8);
+      xb[jt][ks] = __builtin_bit_cast(bf16x8, v ^ (u32x4){flip, flip, flip, flip});
     }
   }
-  Tile<128, D, NT> tk;
-  auto fetch_keys = [&](uint32_t m0) {
-    tk.fetch_rows(p.mk, [&](int r) -> const uint16_t* { return (m0 + r < p.M) ? mk + (size_t)(m0 + r) * D : nullptr; });
+  auto stage = [&](auto i) -> uint16_t* {
+    if constexpr (decltype(i)::v % 3 == 0) return sK0;
+    else if constexpr (decltype(i)::v % 3 == 1) return sK1;
+    else return sK2;
   };
-  fetch_keys(0);
-  for (uint32_t m0 = 0; m0 < p.M; m0 += 128) {
-    __syncthreads();
-    tk.put(sK, LD);
-    if (m0 + 128 < p.M) fetch_keys(m0 + 128);  // in flight during this tile's products
-    __syncthreads();
-    if (m0 + 32 * sg < p.M) {  // M is a multiple of 64: a wavefront's 32 slots are all in or all out
-      f32x16 acc[2];
+  // slots past the end of the memory (the second half of a last tile; M is a multiple of 64): its last 32 again
+  auto request = [&](auto i, uint32_t t) {
+    const uint32_t m0 = (tile0 + min(t, n - 1)) * 128;
 #pragma unroll
-      for (int jt = 0; jt < 2; ++jt) acc[jt] = zero16();
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 a = frag(sK, LD, 32 * sg + col, ks * 16 + half * 8);
-#pragma unroll
-        for (int jt = 0; jt < 2; ++jt) acc[jt] = mfma_bf16(a, xb[jt][ks], acc[jt]);
-      }
-#pragma unroll
-      for (int jt = 0; jt < 2; ++jt) {
-        float tmax = acc[jt][0];
-#pragma unroll
-        for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, acc[jt][v]);
-        const float mn = fmaxf(m[jt], tmax * scale[jt]);
-        float add = 0.f;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) add += fast_exp2(__builtin_fmaf(acc[jt][v], scale[jt], -mn));
-        s[jt] = s[jt] * fast_exp2(m[jt] - mn) + add;
-        m[jt] = mn;
-      }
+    for (int j = 0; j < NL; ++j) {
+      const int ld = wave * NL + j;
+      const uint32_t slot = min(m0 + 32 * (ld / KS), p.M - 32);
+      load_to_lds(scalar_base(mk + (size_t)slot * D + (ld % KS) * 16) + row_operand(lane, D), stage(i) + ld * 512);
     }
+  };
+  f32x16 acc[2][2];   // [tile parity][row group]
+  // The products of a tile, and between them the exponentials of the tile before (from its maximum on: m is already
+  // what it has to be).  OLD: there is a tile before.
+  auto tile = [&](auto i, auto par, auto old, uint32_t t) {
+    constexpr int P = decltype(par)::v;
+    request(Int<decltype(i)::v + 2>{}, t + 2);
+    const bf16x8* k = (const bf16x8*)(stage(i) + sg * KS * 512) + lane;
+    bf16x8 f[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) f[ks] = k[ks * 64];
+    acc[P][0] = zero16();
+    acc[P][1] = zero16();
+    float add[2] = {0.f, 0.f};
+    region();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+      for (int jt = 0; jt < 2; ++jt) acc[P][jt] = mfma_bf16(f[ks], xb[jt][ks], acc[P][jt]);
+      if constexpr (decltype(old)::v != 0) {
+#pragma unroll
+        for (int v = ks * (16 / KS); v < (ks + 1) * (16 / KS); ++v)
+#pragma unroll
+          for (int jt = 0; jt < 2; ++jt) add[jt] += fast_exp2(__builtin_fmaf(acc[1 - P][jt][v], scale[jt], -m[jt]));
+      }
+      region();
+    }
+#pragma unroll
+    for (int jt = 0; jt < 2; ++jt) {
+      s[jt] += add[jt];
+      float tmax = acc[P][jt][0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, acc[P][jt][v]);
+      const float mn = fmaxf(m[jt], tmax * scale[jt]);   // of slots that come twice as well: the same maximum
+      s[jt] *= fast_exp2(m[jt] - mn);
+      m[jt] = mn;
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitLds);
+    __builtin_amdgcn_s_waitcnt(wait_vm(NL));   // the next tile has arrived, the one after it is in flight
+    bare_barrier();
+  };
+  request(Int<0>{}, 0);
+  request(Int<1>{}, 1);
+  __builtin_amdgcn_s_waitcnt(wait_vm(NL));
+  bare_barrier();
+  tile(Int<0>{}, Int<0>{}, Int<0>{}, 0);
+  uint32_t t = 1;
+  for (; t + 6 <= n; t += 6) {
+    tile(Int<1>{}, Int<1>{}, Int<1>{}, t);
+    tile(Int<2>{}, Int<0>{}, Int<1>{}, t + 1);
+    tile(Int<0>{}, Int<1>{}, Int<1>{}, t + 2);
+    tile(Int<1>{}, Int<0>{}, Int<1>{}, t + 3);
+    tile(Int<2>{}, Int<1>{}, Int<1>{}, t + 4);
+    tile(Int<0>{}, Int<0>{}, Int<1>{}, t + 5);
   }
+  if (t < n) tile(Int<1>{}, Int<1>{}, Int<1>{}, t);
+  if (t + 1 < n) tile(Int<2>{}, Int<0>{}, Int<1>{}, t + 1);
+  if (t + 2 < n) tile(Int<0>{}, Int<1>{}, Int<1>{}, t + 2);
+  if (t + 3 < n) tile(Int<1>{}, Int<0>{}, Int<1>{}, t + 3);
+  if (t + 4 < n) tile(Int<2>{}, Int<1>{}, Int<1>{}, t + 4);
+  // the exponentials of the last tile (parity (n - 1) % 2); a wavefront whose slots of it lie outside has none
+  if ((tile1 - 1) * 128 + 32 * sg < p.M) {
+#pragma unroll
+    for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        s[jt] += fast_exp2(__builtin_fmaf((n & 1) ? acc[0][jt][v] : acc[1][jt][v], scale[jt], -m[jt]));
+  }
+  __builtin_amdgcn_s_waitcnt(wait_vm(0));
 #pragma unroll
   for (int jt = 0; jt < 2; ++jt) {
     merge_stat(m[jt], s[jt], __shfl_xor(m[jt], 32, 64), __shfl_xor(s[jt], 32, 64));
@@ -291,17 +387,28 @@ __global__ __launch_bounds__(512, 4) void prefill_stats_kernel(const PrefillPara
     float mm = sRed[0][threadIdx.x].x, ss = sRed[0][threadIdx.x].y;
 #pragma unroll
     for (int w = 1; w < 4; ++w) merge_stat(mm, ss, sRed[w][threadIdx.x].x, sRed[w][threadIdx.x].y);
-    uint32_t row = row0 + threadIdx.x;
-    if (row < nw) {
-      // a step size eta scales the token's write weights: exp2(score - shift) * |eta|
-      // = exp2(score - (shift - log2 |eta|)); eta = 0 gives shift = +inf and weights 0
-      // (|eta| here; the sign of eta rides on the token's row of WV^T, see prefill_transpose_kernel)
-      const float le = p.gate ? __log2f(fabsf(p.gate[((size_t)b * p.T + row) * p.Hkv + h])) : 0.f;
-      p.norm_w[(size_t)unit * p.T + row] = make_float2(mm + __log2f(ss) - le, 0.f);
-    } else if (row - nw < nr) {
-      p.norm_r[(size_t)unit * p.T * p.G + (row - nw)] = make_float2(mm + __log2f(ss), 0.f);
-    }
+    const uint32_t row = row0 + threadIdx.x;
+    if (p.stats_split == 1) store_shift(p, unit, b, h, nw, nr, row, mm, ss);
+    else if (row < nw + nr) p.stats_part[((size_t)unit * p.stats_split + part) * (nw + nr) + row] = make_float2(mm, ss);
   }
+}
+
+// The shares of a split statistics launch, merged in their order.
+__global__ __launch_bounds__(256) void prefill_stats_merge_kernel(const PrefillParams p) {
+  const uint32_t unit = block_unit();
+  if (unit >= p.B * p.Hkv) return;
+  const uint32_t nw = p.has_write ? p.T : 0u, nr = (p.has_read && p.stats_read) ? p.T * p.G : 0u;
+  const uint32_t row = blockIdx.x * 256 + threadIdx.x;
+  if (row >= nw + nr) return;
+  const float2* part = p.stats_part + (size_t)unit * p.stats_split * (nw + nr) + row;
+  float2 v[kMaxStatsSplit];   // requested together
+#pragma unroll
+  for (uint32_t k = 0; k < kMaxStatsSplit; ++k) v[k] = part[(size_t)min(k, p.stats_split - 1) * (nw + nr)];
+  float m = v[0].x, s = v[0].y;
+#pragma unroll
+  for (uint32_t k = 1; k < kMaxStatsSplit; ++k)
+    if (k < p.stats_split) merge_stat(m, s, v[k].x, v[k].y);
+  store_shift(p, unit, unit / p.Hkv, unit % p.Hkv, nw, nr, row, m, s);
 }
 
 // ------------------------------------------------------------------ read of a chunk that does not write
@@ -417,434 +524,464 @@ __global__ __launch_bounds__(512) void prefill_read_only_kernel(const PrefillPar
 // e_m = exp2(score_m - shift), and the shift follows the row's running maximum lazily - it moves only
 // when a tile's maximum exceeds it by more than kTau (the weights then reach at most 2^kTau, far inside
 // bf16 and fp32 range), which after the first tile is rare, so rescaling what has been accumulated is a
-// seldom-taken, workgroup-uniform branch.  The write rows keep their shifts from the statistics kernel
+// seldom-taken branch of one wavefront.  The write rows keep their shifts from the statistics kernel
 // (the state kernel needs those before it can add anything to MV).
 // Output rows of one tile of 128 read rows of sub-chunk c:
 //     out = RW . MV_c  +  mask(RW . WW_c^T) . WV_c ,  mask: write token s <= the row's token.
-// The workgroup walks the M slots 64 at a time, recomputing the score tiles.  Eight wavefronts.
-// Score step: wavefront = (role, row group of 32): role 0 scores 32 read rows, role 1 32 write tokens,
-// against all 64 slots of the tile, so a row's tile maximum and its sum are in two lanes.  Product step:
-// 32 output rows x d/2 value columns and 32 write tokens x 64 read rows of the within-sub-chunk
-// matrix; that keeps a lane under 256 registers, so two wavefronts share a SIMD.
+// The workgroup walks the M slots 64 at a time.  Of its eight wavefronts four are readers and four writers, one of
+// each on a SIMD.  A writer owns 32 write tokens: it scores them against the tile and leaves their weights in
+// LDS as operand tiles.  A reader owns 32 read rows: every product has its rows as the columns (lane = read
+// row), so its weights pass from the score product to the next ones in registers, a row's shift, sum and rescaling
+// factor are the lane's own, and what is accumulated (32 rows x d columns and 32 rows x 128 tokens) never
+// needs another wavefront.  The writers are one tile ahead; one barrier per tile.  Keys and MV_c come through LDS,
+// requested two tiles ahead without a trip through registers.
+// What bounds it: 64 matrix instructions per SIMD and tile (2048 cycles) beside about as many cycles of vector work
+// for 64 exponentials per lane.
 template <int D>
-__global__ __launch_bounds__(512) void prefill_read_online_kernel(const PrefillParams p) {
-  constexpr int NT = 512;
-  constexpr int LD = D + 8, KS = D / 16;
-  constexpr int LP = 64 + 8;    // row length of tiles contracted over 64 slots
-  constexpr int LA = kTC + 8;   // row length of tiles contracted over 128 tokens
+__global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const PrefillParams p) {
+  constexpr int KS = D / 16, NC = D / 32;
   constexpr float kTau = 8.f;
-  constexpr int kLoop = 64 * LD + D * LP + 2 * kTC * LP;  // sK, sVt, sPr, sPw
-  constexpr int kTail = kTC * LA + D * LA;                // sA, sWVt
-  constexpr int kRows = 2 * kTC * LD;                     // sXr, sXw
-  constexpr int kSet = kLoop > kTail ? (kLoop > kRows ? kLoop : kRows) : (kTail > kRows ? kTail : kRows);
-  // Two sets of the loop's tiles, used in turn, so that a wavefront can be a step ahead of the others
-  // (one barrier per slot tile, see the loop).  The row tiles are only read into registers before the
-  // loop and share the second set's memory; the tiles of the tail share the first set's.
-  __shared__ __attribute__((aligned(16))) uint16_t sBuf[2][kSet];
-  __shared__ float sScale[2][kTC];  // per read row: this tile's rescaling factor; at the end ([0]) 1 / sum
-  __shared__ uint32_t sFlag[3];     // slot tile number % 3 -> some row's shift moved in that tile
-  uint16_t* const sXr = sBuf[1];
-  uint16_t* const sXw = sBuf[1] + kTC * LD;
-  uint16_t* const sA = sBuf[0];
-  uint16_t* const sWVt = sA + kTC * LA;
+  constexpr int kTile = 64 * D;                 // elements of a 64-slot tile
+  constexpr int NL = kTile / 512 / 8;           // its load instructions per wavefront
+  // three stages each; separate arrays, so that the compiler knows what a request into one does not touch
+  __shared__ __attribute__((aligned(16))) uint16_t sK0[kTile], sK1[kTile], sK2[kTile];
+  __shared__ __attribute__((aligned(16))) uint16_t sV0[kTile], sV1[kTile], sV2[kTile];
+  __shared__ __attribute__((aligned(16))) bf16x8 sW[2 * 4 * 4 * 64];   // [tile parity][token group][16 slots][lane]
 
   // launch order: all sequences of one KV head, then the next head (shared keys stay in L2)
   const uint32_t uy = block_unit();
   if (uy >= p.B * p.Hkv) return;
   const uint32_t h = uy / p.B, b = uy % p.B, unit = b * p.Hkv + h;
-  const uint32_t G = p.G, T = p.T;
+  const uint32_t G = p.G, T = p.T, n = p.M / 64;
   const uint32_t c = p.c_begin + blockIdx.x / G, gp = blockIdx.x % G;
   const uint32_t t0 = c * kTC, rho0 = gp * kTC;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, col = lane % 32, half = lane / 32;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64, col = lane % 32, half = lane / 32;
   const size_t units = (size_t)p.B * p.Hkv;
-
-  {
-    Tile<kTC, D, NT> t;
-    t.fetch_rows(p.mk, [&](int r) -> const uint16_t* {
-      const uint32_t rho = rho0 + r, tk = t0 + rho / G;
-      return tk < T ? p.q + (((size_t)b * T + tk) * p.Hq + h * G + rho % G) * D : nullptr;
-    });
-    t.put(sXr, LD);
-  }
-  {
-    Tile<kTC, D, NT> t;
-    t.fetch_rows(p.mk, [&](int r) -> const uint16_t* {
-      return t0 + r < T ? p.wq + (((size_t)b * T + t0 + r) * p.Hkv + h) * D : nullptr;
-    });
-    t.put(sXw, LD);
-  }
-  if (threadIdx.x < 3) sFlag[threadIdx.x] = 0u;
   const uint16_t* mk = p.mk + (size_t)(p.mk_per_seq ? unit : h) * p.M * D;
-  const uint16_t* mvt = p.snap + ((size_t)c * units + unit) * p.M * D;   // MV_c, transposed: [column][slot]
+  const uint16_t* mvc = p.snap + ((size_t)c * units + unit) * p.M * D;   // MV_c as operand tiles
 
-  // score step: role 0 = read rows, role 1 = write tokens; row (token) 32 * rg + col of the tile
-  const int role = wave >> 2, rg = wave & 3;
-  const int srow = 32 * rg + col;
-  float cs = role == 0 ? p.rscale_l2e : p.wscale_l2e;   // scale of this wavefront's rows (log2 domain)
-  // role 0: the lazily followed running maximum of the row (scaled); role 1: the token's fixed shift
-  float shift = kNegBig, zsum = 0.f;
-  if (role == 1) shift = (t0 + srow < T) ? p.norm_w[(size_t)unit * T + t0 + srow].x : kNoRow;
-  // product step: wavefront = (32 output rows, half of the value columns) and, for the
-  // within-sub-chunk matrix, (32 write tokens, 64 read rows)
-  constexpr int NOC = D / 64;
-  const int orow = 32 * (wave & 3), ocol = 32 * NOC * (wave >> 2);
-  const int as0 = 32 * (wave & 3), ar0 = 64 * (wave >> 2);
-  f32x16 oacc[NOC], aacc[2];
+  auto stage_k = [&](auto i) -> uint16_t* {
+    if constexpr (decltype(i)::v % 3 == 0) return sK0;
+    else if constexpr (decltype(i)::v % 3 == 1) return sK1;
+    else return sK2;
+  };
+  auto stage_v = [&](auto i) -> uint16_t* {
+    if constexpr (decltype(i)::v % 3 == 0) return sV0;
+    else if constexpr (decltype(i)::v % 3 == 1) return sV1;
+    else return sV2;
+  };
+  auto request = [&](auto i, uint32_t tile) {
+    const uint32_t t = min(tile, n - 1);   // past the end: the last tile again, never used
+    const uint16_t *k = mk + (size_t)t * kTile, *v = mvc + (size_t)t * kTile;
 #pragma unroll
-  for (int jt = 0; jt < NOC; ++jt) oacc[jt] = zero16();
+    for (int j = 0; j < NL; ++j) {   // 32 slots' operand tiles, then the other 32's
+      const int ld = wave * NL + j;
+      load_to_lds(scalar_base(k + (ld / KS) * 32 * D + (ld % KS) * 16) + row_operand(lane, D), stage_k(i) + ld * 512);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // the keys are needed a tile before the values: see tile_end
 #pragma unroll
-  for (int jt = 0; jt < 2; ++jt) aacc[jt] = zero16();
+    for (int j = 0; j < NL; ++j) {
+      const int ld = wave * NL + j;
+      load_to_lds(scalar_base(v + ld * 512) + (uint32_t)lane * 16u, stage_v(i) + ld * 512);
+    }
+  };
+  // 32 slots of the tile (blk = 0, 1) against this wavefront's 32 rows: lane = row, register v = slot
+  // 8 (v / 4) + 4 half + v % 4 of the 32
+  // LDS operands are requested a region ahead of the products that use them (region(): the scheduler keeps its
+  // order; left to itself it waits out an LDS latency before every second product).
+  auto scores = [&](const uint16_t* k, const bf16x8* x, f32x16* s) {
+    bf16x8 f[2][4];
+    auto load = [&](int bt) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) f[bt & 1][i] = *(const bf16x8*)(k + lane * 8 + ((i & 1) * KS + 2 * bt + i / 2) * 512);
+    };
+    s[0] = zero16();
+    s[1] = zero16();
+    load(0);
+    region();
+#pragma unroll
+    for (int bt = 0; bt < KS / 2; ++bt) {
+      if (bt + 1 < KS / 2) load(bt + 1);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[i & 1] = mfma_bf16(f[bt & 1][i], x[2 * bt + i / 2], s[i & 1]);
+      region();
+    }
+  };
+  // End of tile i: this wavefront's LDS accesses are done; of its requests the values of tile i + 2 may still be on
+  // their way, the keys of i + 2 (for the writers) and the values of i + 1 have arrived
+  auto tile_end = [&] {
+    __builtin_amdgcn_s_waitcnt(kWaitLds);
+    __builtin_amdgcn_s_waitcnt(wait_vm(NL));
+    bare_barrier();
+  };
 
+  const bool reader = wave < 4;
+  const int rg = wave & 3, srow = 32 * rg + col;
+  // A row's own token and the earlier ones of the sub-chunk are all it can read: of the four groups of 32 write
+  // tokens a reader needs the first nsb (none: its rows are all past the chunk's end), the workgroup those
+  // whose writer is asked
+  auto groups = [&](uint32_t first_row, uint32_t last_row) -> int {
+    const uint32_t left = T - t0;   // tokens of the sub-chunk, at least one
+    return (rho0 + first_row) / G >= left ? 0 : (int)(min((rho0 + last_row) / G, left - 1) / 32 + 1);
+  };
+  const int nsb = groups(32 * rg, 32 * rg + 31);
+  const bool asked = rg < groups(0, kTC - 1);
   // this wavefront's rows as operand fragments, kept in registers.  A negative read scale moves into the
   // row (negating bf16 is exact), so that the largest raw score is also the largest scaled one.
-  __syncthreads();
+  float cs = reader ? p.rscale_l2e : p.wscale_l2e;   // scale of this wavefront's rows (log2 domain)
+  const uint32_t rtok = reader ? t0 + (rho0 + srow) / G : t0 + srow;   // the row's token
+  const bool present = rtok < T;
   bf16x8 x[KS];
   {
-    const uint32_t flip = (role == 0 && cs < 0.f) ? 0x80008000u : 0u;
-    if (role == 0) cs = fabsf(cs);
-    const uint16_t* sX = role == 0 ? sXr : sXw;
+    const uint32_t flip = reader && cs < 0.f ? 0x80008000u : 0u;
+    if (reader) cs = fabsf(cs);
+    const uint16_t* src = reader ? p.q + (((size_t)b * T + rtok) * p.Hq + h * G + (rho0 + srow) % G) * D
+                                 : p.wq + (((size_t)b * T + rtok) * p.Hkv + h) * D;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      u32x4 v = __builtin_bit_cast(u32x4, frag(sX, LD, srow, ks * 16 + half * 8));
-      v ^= (u32x4){flip, flip, flip, flip};
-      x[ks] = __builtin_bit_cast(bf16x8, v);
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (present) v = *(const u32x4*)(src + ks * 16 + half * 8);
+      x[ks] = __builtin_bit_cast(bf16x8, v ^ (u32x4){flip, flip, flip, flip});
     }
   }
-  // One barrier per slot tile.  Tile i uses set i % 2 of the buffers:
-  //   before the barrier: the keys of tile i + 1 go to the other set (its keys were last read in the
-  //     score step of tile i - 1, which every wavefront finished before the previous barrier); scores of
-  //     tile i from this set's keys -> this set's weights (last read in the product step of tile i - 2);
-  //   after the barrier: the values of tile i + 1 go to the other set (last read in the product step
-  //     of tile i - 1, which every wavefront left before it arrived at this barrier); products of tile i.
-  // So the wavefronts drift up to a step apart, and one's exponentials overlap another's products.
-  Tile<64, D, NT> tk;
-  Tile<D, 64, NT> tv;
-  auto next_values = [&](uint32_t m) {
-    if (G == 1) tv.fetch_block_once(mvt + m, p.M);   // nobody else reads this copy of MV
-    else tv.fetch_block(mvt + m, p.M);
-  };
-  tk.fetch_block(mk, D);
-  next_values(0);
-  __syncthreads();             // the row fragments are in registers: the second set is free
-  tk.put(sBuf[0], LD);
-  tv.put(sBuf[0] + 64 * LD, LP);
-  if (64 < p.M) {
-    tk.fetch_block(mk + (size_t)64 * D, D);
-    next_values(64);
+  request(Int<0>{}, 0);
+  request(Int<1>{}, 1);
+  tile_end();
+
+  if (!reader) {
+    const float shift = present ? p.norm_w[(size_t)unit * T + rtok] : kNoRow;
+    auto weights = [&](auto i, uint32_t it) {
+      f32x16 s[2];
+      scores(stage_k(i), x, s);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[k][v] = fast_exp2(__builtin_fmaf(s[k][v], cs, -shift));
+#pragma unroll
+        for (int j = 0; j < 2; ++j) sW[(((it & 1) * 4 + rg) * 4 + 2 * k + j) * 64 + lane] = pack8(s[k], j);
+      }
+    };
+    auto tile = [&](auto i, uint32_t it) {
+      request(Int<decltype(i)::v + 2>{}, it + 2);
+      if (asked) weights(Int<decltype(i)::v + 1>{}, it + 1);   // past the end: of whatever tile is there, never used
+      tile_end();
+    };
+    if (asked) weights(Int<0>{}, 0);
+    tile_end();
+    uint32_t it = 0;
+    for (; it + 3 <= n; it += 3) {
+      tile(Int<0>{}, it);
+      tile(Int<1>{}, it + 1);
+      tile(Int<2>{}, it + 2);
+    }
+    if (it < n) tile(Int<0>{}, it);
+    if (it + 1 < n) tile(Int<1>{}, it + 1);
+    __builtin_amdgcn_s_waitcnt(wait_vm(0));
+    return;   // no barrier follows
   }
-  uint32_t it = 0;
-  for (uint32_t m0 = 0; m0 < p.M; m0 += 64, ++it) {
-    uint16_t* const sK = sBuf[it & 1];
-    uint16_t* const sVt = sK + 64 * LD;
-    uint16_t* const sPr = sVt + D * LP;
-    uint16_t* const sPw = sPr + kTC * LP;
-    uint16_t* const sKn = sBuf[(it + 1) & 1];
-    float* const sSc = sScale[it & 1];
-    const uint32_t fl = it % 3;
-    if (m0 + 64 < p.M) {
-      tk.put(sKn, LD);
-      if (m0 + 128 < p.M) tk.fetch_block(mk + (size_t)(m0 + 128) * D, D);
-    }
-    if (threadIdx.x == 0) sFlag[(it + 1) % 3] = 0u;   // last read in the product step of tile i - 2
-    if (it == 0) __syncthreads();                     // the first tile's keys were staged just above
-    {
-      f32x16 s0 = zero16(), s1 = zero16();
+
+  f32x16 oacc[NC], aacc[4];   // [columns][row], [write tokens][row]: lane = this wavefront's row
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        s0 = mfma_bf16(frag(sK, LD, col, ks * 16 + half * 8), x[ks], s0);
-        s1 = mfma_bf16(frag(sK, LD, 32 + col, ks * 16 + half * 8), x[ks], s1);
-      }
-      if (role == 0) {
-        float tm = fmaxf(s0[0], s1[0]);
+  for (int jt = 0; jt < NC; ++jt) oacc[jt] = zero16();
 #pragma unroll
-        for (int v = 1; v < 16; ++v) tm = fmaxf(tm, fmaxf(s0[v], s1[v]));
-        tm = fmaxf(tm, __shfl_xor(tm, 32, 64)) * cs;
-        float f = 1.f;
-        if (tm > shift + kTau) {        // also the first tile (shift = kNegBig: f = 0, nothing accumulated yet)
-          f = fast_exp2(shift - tm);
-          shift = tm;
-          zsum *= f;
-          sFlag[fl] = 1u;
-        }
-        if (half == 0) sSc[srow] = f;
-        float add = 0.f;
+  for (int sb = 0; sb < 4; ++sb) aacc[sb] = zero16();
+  float shift = kNegBig, zsum = 0.f;
+  auto tile = [&](auto i, uint32_t it) {
+    f32x16 s[2];
+    scores(stage_k(i), x, s);
+    float tm = fmaxf(s[0][0], s[1][0]);
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          float e0[4], e1[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            e0[i] = fast_exp2(__builtin_fmaf(s0[4 * q4 + i], cs, -shift));
-            e1[i] = fast_exp2(__builtin_fmaf(s1[4 * q4 + i], cs, -shift));
-            add += e0[i] + e1[i];
-          }
-          store4_bf16(sPr + srow * LP + 8 * q4 + 4 * half, e0[0], e0[1], e0[2], e0[3]);
-          store4_bf16(sPr + srow * LP + 32 + 8 * q4 + 4 * half, e1[0], e1[1], e1[2], e1[3]);
-        }
-        zsum += add;
-      } else {
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          float e0[4], e1[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            e0[i] = fast_exp2(__builtin_fmaf(s0[4 * q4 + i], cs, -shift));
-            e1[i] = fast_exp2(__builtin_fmaf(s1[4 * q4 + i], cs, -shift));
-          }
-          store4_bf16(sPw + srow * LP + 8 * q4 + 4 * half, e0[0], e0[1], e0[2], e0[3]);
-          store4_bf16(sPw + srow * LP + 32 + 8 * q4 + 4 * half, e1[0], e1[1], e1[2], e1[3]);
-        }
-      }
-    }
-    __syncthreads();
-    if (m0 + 64 < p.M) {
-      tv.put(sKn + 64 * LD, LP);
-      if (m0 + 128 < p.M) next_values(m0 + 128);
-    }
-    if (sFlag[fl]) {   // uniform over the workgroup: bring what has been accumulated to the new shifts
+    for (int v = 1; v < 16; ++v) tm = fmaxf(tm, fmaxf(s[0][v], s[1][v]));
+    tm = max_of_halves(tm) * cs;
+    const bool moves = tm > shift + kTau;        // also the first tile (shift = kNegBig, nothing accumulated yet)
+    if (__builtin_amdgcn_ballot_w64(moves)) {    // bring what has been accumulated to the new shifts
+      const float f = moves ? fast_exp2(shift - tm) : 1.f;
+      shift = moves ? tm : shift;
+      zsum *= f;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const float fr = sSc[orow + 8 * (v / 4) + 4 * half + (v % 4)];
 #pragma unroll
-        for (int jt = 0; jt < NOC; ++jt) oacc[jt][v] *= fr;
-      }
+        for (int jt = 0; jt < NC; ++jt) oacc[jt][v] *= f;
 #pragma unroll
-      for (int jt = 0; jt < 2; ++jt) {
-        const float fc = sSc[ar0 + 32 * jt + col];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) aacc[jt][v] *= fc;
+        for (int sb = 0; sb < 4; ++sb) aacc[sb][v] *= f;
       }
     }
+    // regions of: the next operands from LDS, the products of the last, the weights of the next 16 slots
+    const bf16x8* mvt = (const bf16x8*)stage_v(i) + lane;
+    const bf16x8* ww = sW + (it & 1) * 1024 + lane;
+    constexpr int NF = NC > 4 ? NC : 4;
+    bf16x8 f[2][NF], pw[4];     // pw: the row's weights, 16 slots each
+    float add = 0.f;
+    auto weights = [&](int j) {
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int k = ks * 16 + half * 8;
-      const bf16x8 a = frag(sPr, LP, orow + col, k);
+      for (int v = 8 * (j & 1); v < 8 * (j & 1) + 8; ++v) {
+        s[j / 2][v] = fast_exp2(__builtin_fmaf(s[j / 2][v], cs, -shift));
+        add += s[j / 2][v];
+      }
+      pw[j] = pack8(s[j / 2], j & 1);
+    };
 #pragma unroll
-      for (int jt = 0; jt < NOC; ++jt) oacc[jt] = mfma_bf16(a, frag(sVt, LP, ocol + 32 * jt + col, k), oacc[jt]);
-      // rows of this product = write tokens s, columns = read rows
-      const bf16x8 aw = frag(sPw, LP, as0 + col, k);
+    for (int jt = 0; jt < NC; ++jt) f[0][jt] = mvt[jt * 64];
+    weights(0);
+    region();
 #pragma unroll
-      for (int jt = 0; jt < 2; ++jt) aacc[jt] = mfma_bf16(aw, frag(sPr, LP, ar0 + 32 * jt + col, k), aacc[jt]);
+    for (int j = 0; j < 4; ++j) {
+      if (j < 3) {
+#pragma unroll
+        for (int jt = 0; jt < NC; ++jt) f[(j + 1) & 1][jt] = mvt[((j + 1) * NC + jt) * 64];
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[0][k] = ww[k * 64];
+      }
+#pragma unroll
+      for (int jt = 0; jt < NC; ++jt) oacc[jt] = mfma_bf16(f[j & 1][jt], pw[j], oacc[jt]);
+      if (j < 3) weights(j + 1);
+      region();
     }
+    zsum += add;
+#pragma unroll
+    for (int sb = 0; sb < 4; ++sb)
+      if (sb < nsb) {
+        if (sb < 3) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) f[(sb + 1) & 1][k] = ww[((sb + 1) * 4 + k) * 64];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) aacc[sb] = mfma_bf16(f[sb & 1][k], pw[k], aacc[sb]);
+        region();
+      }
+  };
+  auto step = [&](auto i, uint32_t it) {
+    request(Int<decltype(i)::v + 2>{}, it + 2);
+    if (nsb > 0) tile(i, it);
+    tile_end();
+  };
+  tile_end();   // the writers' first tile
+  uint32_t it = 0;
+  for (; it + 3 <= n; it += 3) {
+    step(Int<0>{}, it);
+    step(Int<1>{}, it + 1);
+    step(Int<2>{}, it + 2);
   }
+  if (it < n) step(Int<0>{}, it);
+  if (it + 1 < n) step(Int<1>{}, it + 1);
+  __builtin_amdgcn_s_waitcnt(wait_vm(0));
 
-  __syncthreads();
-  // 1 / (sum of the row's weights): the normaliser of everything accumulated for the row
-  if (role == 0) {
-    const float z = zsum + __shfl_xor(zsum, 32, 64);
-    if (half == 0) sScale[0][srow] = 1.0f / z;
-  }
-  // A[row][s] = (s <= token of the row) ? sum_m e[row][m] ww[s][m] : 0
+  // A'[s] = (s <= token of the row) ? sum_m e[row][m] ww[s][m] : 0, and with it the tokens of the sub-chunk itself
+  const int tl = (int)((rho0 + srow) / G);  // the row's token within the sub-chunk
+  const bf16x8* wvt = (const bf16x8*)(p.wvt + ((size_t)unit * p.Tpad + t0) * D);
 #pragma unroll
-  for (int jt = 0; jt < 2; ++jt) {
-    const int r = ar0 + 32 * jt + col;
-    const int tl = (int)((rho0 + r) / G);  // the row's token within the sub-chunk
+  for (int sb = 0; sb < 4; ++sb) {   // a group that was not multiplied holds zeros
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const int s0 = as0 + 8 * q4 + 4 * half;
-      float e[4];
+    for (int v = 0; v < 16; ++v)
+      if (32 * sb + 8 * (v / 4) + 4 * half + v % 4 > tl) aacc[sb][v] = 0.f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) e[i] = (s0 + i <= tl) ? aacc[jt][4 * q4 + i] : 0.f;
-      store4_bf16(sA + r * LA + s0, e[0], e[1], e[2], e[3]);
+    for (int j = 0; j < 2; ++j) {
+      const bf16x8 a = pack8(aacc[sb], j);
+#pragma unroll
+      for (int jt = 0; jt < NC; ++jt) oacc[jt] = mfma_bf16(wvt[operand_chunk<D>(2 * sb + j, jt, lane)], a, oacc[jt]);
     }
   }
-  {
-    Tile<D, kTC, NT> t;
-    t.fetch_block(p.wvt + (size_t)unit * D * p.Tpad + t0, p.Tpad);
-    t.put(sWVt, LA);
-  }
-  __syncthreads();
+  const float z = zsum + __shfl_xor(zsum, 32, 64), inv = 1.0f / z;   // the normaliser of everything accumulated
+  if (present) {
+    // 8-byte stores: a row's pieces come one after another, and once per M slots
+    uint16_t* o = p.out + (((size_t)b * T + rtok) * p.Hq + h * G + (rho0 + srow) % G) * D + 4 * half;
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) {
-    const int k = ks * 16 + half * 8;
-    const bf16x8 a = frag(sA, LA, orow + col, k);
+    for (int jt = 0; jt < NC; ++jt)
 #pragma unroll
-    for (int jt = 0; jt < NOC; ++jt) oacc[jt] = mfma_bf16(a, frag(sWVt, LA, ocol + 32 * jt + col, k), oacc[jt]);
-  }
-
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const uint32_t r = orow + 8 * (v / 4) + 4 * half + (v % 4);
-    const uint32_t rho = rho0 + r, t = t0 + rho / G;
-    if (t < T) {
-      const float inv = sScale[0][r];
-      uint16_t* o = p.out + (((size_t)b * T + t) * p.Hq + h * G + rho % G) * D;
-#pragma unroll
-      for (int jt = 0; jt < NOC; ++jt) o[ocol + 32 * jt + col] = bf16_bits(oacc[jt][v] * inv);
-    }
+      for (int q4 = 0; q4 < 4; ++q4)
+        store4_bf16(o + 32 * jt + 8 * q4, oacc[jt][4 * q4 + 0] * inv, oacc[jt][4 * q4 + 1] * inv,
+                    oacc[jt][4 * q4 + 2] * inv, oacc[jt][4 * q4 + 3] * inv);
   }
 }
 
 // ------------------------------------------------------------------ state
 
-// MV tile of 128 slots: acc = MV_start; tokens are walked 64 at a time; at the
+// MV tile of 128 slots: acc = MV_start; tokens are walked 32 at a time; at the
 // start of every sub-chunk c (if reads follow) round(acc) is left as MV_c;
 // acc += WW^T . WV; finally MV = round(acc).  The write weights are recomputed
 // per token tile and never leave the registers: a wavefront owns 32 slots and
-// all d value columns.  Its score product has rows = tokens, columns = slots, so
-// lane l ends up with the weights of slot l % 32 for the tokens
-// 8 q + 4 (l / 32) + i (q, i = 0..3) of a 32-token step: per 16 tokens that is
-// 4 + 4 values, which is an A operand (row = slot, 8 contraction entries per
-// lane) of the state product once the B operand (WV^T) takes its tokens in the
-// same order -- two 8-byte LDS reads instead of one 16-byte read.  Only the
-// token tiles (write queries, WV^T, row statistics) go through LDS, two
-// barriers per 64 tokens; between them the four wavefronts run on their own, so
-// one's exponentials overlap another's products.  Each wavefront keeps the key
-// fragments of its slots in registers (loaded straight from memory in operand
-// layout).
+// all d value columns.  Its score product has rows = tokens, columns = slots, so a lane's accumulator registers are
+// the A operand (row = slot) of the state product with WV^T as operand tiles.  MV_c leaves in operand tiles
+// too: a lane's accumulator registers, rounded, are its 16-byte chunks of them, and a wavefront stores whole
+// kilobytes without a detour through LDS.  The token tiles (write queries, WV^T) are requested into LDS a tile
+// ahead; one barrier per tile, between which the wavefronts run on their own.  The key fragments of a
+// wavefront's slots stay in registers.
+// With reads the kernel is partly bound by memory (MV in and out and a copy of MV per sub-chunk: 6.4 GB of the 8.4 a
+// chunk moves at B = 32, H = 32, M = 4096, T = 512), without by its matrix and vector work.  A token tile of 32 keeps
+// a workgroup within 168 registers and 36 KB, so that three of them (three wavefronts per SIMD) hide each
+// other's barriers and stores; two: 2250 us against 1950 at that size, four (registers spilled): 2680.  Row-major
+// token tiles of 64 with padded rows, where a third of the LDS cycles were bank conflicts, took 2170.
 template <int D>
-__global__ __launch_bounds__(256, 2) void prefill_state_kernel(const PrefillParams p) {
-  constexpr int LD = D + 8, KS = D / 16, NT = 256;
-  constexpr int TT = 64;        // tokens per tile
-  constexpr int LP = TT + 8;    // row length of the WV^T tile
-  constexpr int NJ = D / 32;    // 32-column tiles of the state product
-  constexpr int LS = 128 + 8;   // row length of the snapshot staging tile [column][slot]
-  static_assert(TT * LD + D * LP >= 128 * LD, "the MV staging tile reuses the token tiles");
-  __shared__ __attribute__((aligned(16))) uint16_t sTok[TT * LD + D * LP];
-  // the snapshot has LDS of its own: it leaves after the token tile of the step has been staged (see the loop)
-  __shared__ __attribute__((aligned(16))) uint16_t sSnapBuf[D * LS];
-  __shared__ __attribute__((aligned(16))) float sNorm[TT];
-  uint16_t* const sXw = sTok;
-  uint16_t* const sWVt = sTok + TT * LD;
-  uint16_t* const sSnap = sSnapBuf;   // [column][slot] snapshot on its way out
-  uint16_t* const sStage = sTok;   // [slot][column] MV tile on its way in and out
+__global__ __launch_bounds__(256, 3) void prefill_state_kernel(const PrefillParams p) {
+  constexpr int KS = D / 16, NC = D / 32;
+  constexpr int TT = 32;            // tokens per tile
+  constexpr int kTile = TT * D;     // elements of a token tile of either matrix = of a wavefront's 32 slots
+  constexpr int NI = kTile / 512;   // load instructions of a tile
+  constexpr int NL = NI / 4;        // of them per wavefront
+  typedef RowTile<D> RT;
+  // two stages of write queries, WV^T and shifts (a copy per wavefront); before and after the token loop the first
+  // four arrays hold the four wavefronts' slots on their way in and out, as a RowTile each
+  __shared__ __attribute__((aligned(16))) uint16_t sX0[kTile], sX1[kTile], sT0[kTile], sT1[kTile];
+  __shared__ __attribute__((aligned(16))) float sN0[4 * 64], sN1[4 * 64];
 
   const uint32_t unit = block_unit();
   if (unit >= p.B * p.Hkv) return;
   const uint32_t b = unit / p.Hkv, h = unit % p.Hkv;
   const uint32_t m0 = blockIdx.x * 128, T = p.T;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, col = lane % 32, half = lane / 32;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64, col = lane % 32, half = lane / 32;
   const size_t units = (size_t)p.B * p.Hkv;
-  const uint16_t* mk = p.mk + (size_t)(p.mk_per_seq ? unit : h) * p.M * D;
-  uint16_t* mv = p.mv + ((size_t)unit * p.M + m0) * D;
-
   // M is a multiple of 64, so a wavefront's 32 slots are all inside the memory or all outside
-  const int mslot = 32 * wave;
-  const bool live = m0 + mslot < p.M;
+  const uint32_t slot0 = m0 + 32 * wave;
+  const bool live = slot0 < p.M;
+  const uint16_t* mk = p.mk + ((size_t)(p.mk_per_seq ? unit : h) * p.M + slot0) * D;
+  uint16_t* mv = p.mv + ((size_t)unit * p.M + slot0) * D;
+  uint16_t* const strip = wave == 0 ? sX0 : wave == 1 ? sX1 : wave == 2 ? sT0 : sT1;
+
+  if (live) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) load_to_lds(mv + (size_t)RT::row(i, lane) * D + RT::chunk(i, lane) * 8, strip + i * 512);
+  }
   bf16x8 kb[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
     u32x4 v = {0u, 0u, 0u, 0u};
-    if (live) v = *(const u32x4*)(mk + (size_t)(m0 + mslot + col) * D + ks * 16 + half * 8);
+    if (live) v = *(const u32x4*)(mk + (size_t)col * D + ks * 16 + half * 8);
     kb[ks] = __builtin_bit_cast(bf16x8, v);
   }
-  // state product: lane column = value column, accumulator rows = slots.  The MV tile comes in (and
-  // at the end leaves) through LDS in whole rows; a lane picks its 16 x NJ elements from there.
-  f32x16 macc[NJ];
-  {
-    Tile<128, D, NT> tm;
-    tm.fetch_rows(p.mk, [&](int r) -> const uint16_t* { return m0 + r < p.M ? mv + (size_t)r * D : nullptr; });
-    tm.put(sStage, LD);
+  // state product: lane = value column, accumulator rows = slots.  Element (slot row, column) of the strip:
+  auto at = [&](int r, int jt) { return r * D + (((4 * jt + col / 8) ^ swizzle<D>(r)) * 8) + col % 8; };
+  f32x16 macc[NC];
+#pragma unroll
+  for (int jt = 0; jt < NC; ++jt) macc[jt] = zero16();
+  __builtin_amdgcn_s_waitcnt(wait_vm(0));
+  if (live) {
+#pragma unroll
+    for (int jt = 0; jt < NC; ++jt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) macc[jt][v] = bf16_val(strip[at(8 * (v / 4) + 4 * half + v % 4, jt)]);
   }
   __syncthreads();
-#pragma unroll
-  for (int jt = 0; jt < NJ; ++jt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v)
-      macc[jt][v] = bf16_val(sStage[(mslot + 8 * (v / 4) + 4 * half + (v % 4)) * LD + 32 * jt + col]);
 
   const uint32_t ntile = (T + TT - 1) / TT;
-  Tile<TT, D, NT> tx;
-  Tile<D, TT, NT> tw;
-  float tn = 0.f;
-  // Tokens past the end of the chunk load the last token instead: their weights are zero (kNoRow) and
-  // their WV^T columns are zero-filled, so whatever finite scores they get changes nothing.
-  auto fetch_tokens = [&](uint32_t t0) {
-    tx.fetch_rows(p.mk, [&](int r) -> const uint16_t* {
-      return p.wq + (((size_t)b * T + min(t0 + r, T - 1)) * p.Hkv + h) * D;
-    });
-    tw.fetch_block(p.wvt + (size_t)unit * D * p.Tpad + t0, p.Tpad);
-    if (threadIdx.x < TT) tn = p.norm_w[(size_t)unit * T + min(t0 + threadIdx.x, T - 1)].x;
+  auto pick = [](auto i, auto* a, auto* c) {
+    if constexpr (decltype(i)::v % 2 == 0) return a;
+    else return c;
   };
-  fetch_tokens(0);
-  for (uint32_t tt = 0; tt < ntile; ++tt) {
-    const uint32_t t0 = tt * TT;
-    // The token tile is staged first and the next one requested, and only then does a snapshot leave:
-    // loads and stores share one counter, so a wait for loads that follows stores waits for the
-    // stores as well - this way the snapshot's stores have the whole step to complete before the next
-    // wait (for the next token tile) comes.
-    __syncthreads();
-    tx.put(sXw, LD);
-    tw.put(sWVt, LP);
-    if (threadIdx.x < TT) sNorm[threadIdx.x] = (t0 + threadIdx.x < T) ? tn : kNoRow;
-    if (tt + 1 < ntile) fetch_tokens(t0 + TT);  // next tile, in flight during this one's products
-    if (p.has_read && (t0 % kTC) == 0) {
-      // MV at the start of sub-chunk c (c = 0: the tile just loaded, which saves a transposing pass over
-      // MV of its own), transposed ([column][slot]) for the read kernel.  A lane holds
-      // 4 consecutive slots of one column, and columns are M elements apart in memory, so the tile
-      // goes through LDS and leaves in whole 256-byte rows.  (The previous snapshot left this buffer
-      // two steps and several barriers ago.)
-      if (live) {
+  // Tokens past the end of the chunk load the last token instead: their WV^T columns are zero, so whatever
+  // finite weights they get change nothing.  Past the last tile: the last one again, never used.
+  const uint32_t xstride = p.Hkv * D, lastrow = (T - 1) % TT;
+  const uint16_t* wq = p.wq + ((size_t)b * T * p.Hkv + h) * D;
+  const uint16_t* wvt = p.wvt + (size_t)unit * p.Tpad * D;
+  auto request = [&](auto i, uint32_t tile) {
+    const uint32_t tl = min(tile, ntile - 1), over = tl == ntile - 1 ? lastrow : (uint32_t)TT - 1;
+    uint16_t *sx = pick(i, sX0, sX1), *st = pick(i, sT0, sT1);
+    const uint32_t row = min((uint32_t)col, over);
 #pragma unroll
-        for (int jt = 0; jt < NJ; ++jt)
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4)
-            store4_bf16(sSnap + (32 * jt + col) * LS + mslot + 8 * q4 + 4 * half, macc[jt][4 * q4 + 0],
-                        macc[jt][4 * q4 + 1], macc[jt][4 * q4 + 2], macc[jt][4 * q4 + 3]);
-      }
-      __syncthreads();
-      uint16_t* sn = p.snap + ((size_t)(t0 / kTC) * units + unit) * p.M * D + m0;
-      const int ch = threadIdx.x % 16;   // 16-byte chunk = 8 slots; M is a multiple of 64
-      if (m0 + 8 * ch < p.M) {
-#pragma unroll
-        for (int r = threadIdx.x / 16; r < D; r += NT / 16)
-          __builtin_nontemporal_store(*(const u32x4*)(sSnap + r * LS + 8 * ch), (u32x4*)(sn + (size_t)r * p.M + 8 * ch));
-      }
+    for (int j = 0; j < NL; ++j) {
+      const int ld = wave * NL + j;
+      load_to_lds(scalar_base(wq + (size_t)tl * TT * xstride + ld * 16) + (row * xstride + (uint32_t)half * 8u) * 2u, sx + ld * 512);
+      load_to_lds(scalar_base(wvt + (size_t)tl * kTile + ld * 512) + (uint32_t)lane * 16u, st + ld * 512);
     }
-    __syncthreads();
+    __builtin_amdgcn_global_load_lds(
+        (const __attribute__((address_space(1))) void*)(scalar_base(p.norm_w + (size_t)unit * T + tl * TT) + row * 4u),
+        (__attribute__((address_space(3))) void*)(pick(i, sN0, sN1) + 64 * wave), 4, 0, 0);
+  };
+  auto tile = [&](auto i, uint32_t tt) {
+    request(Int<decltype(i)::v + 1>{}, tt + 1);
+    if (p.has_read && live && tt % (kTC / TT) == 0) {
+      // MV at the start of sub-chunk c
+      u32x4* sn = (u32x4*)(p.snap + ((size_t)(tt / (kTC / TT)) * units + unit) * p.M * D);
 #pragma unroll
-    for (int st = 0; st < TT / 32; ++st) {
-      const int tok0 = 32 * st;
-      // scores: rows = tokens, columns = this wavefront's 32 slots
-      f32x16 sc = zero16();
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) sc = mfma_bf16(frag(sXw, LD, tok0 + col, ks * 16 + half * 8), kb[ks], sc);
-      // weights, split into hi + lo bf16 parts: words 0-1 of an operand from q4 = 2 ks, words 2-3 from 2 ks + 1
-      u32x4 ah[2], al[2];
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const f32x4 sh = *(const f32x4*)(sNorm + tok0 + 8 * q4 + 4 * half);   // shifts of the lane's 4 tokens
-        float w[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = fast_exp2(sc[4 * q4 + i] * p.wscale_l2e - sh[i]);
-        const uint32_t h0 = pack_bf16x2(w[0], w[1]), h1 = pack_bf16x2(w[2], w[3]);
-        ah[q4 / 2][2 * (q4 % 2) + 0] = h0;
-        ah[q4 / 2][2 * (q4 % 2) + 1] = h1;
-        al[q4 / 2][2 * (q4 % 2) + 0] = pack_bf16x2(w[0] - __uint_as_float(h0 << 16), w[1] - __uint_as_float(h0 & 0xFFFF0000u));
-        al[q4 / 2][2 * (q4 % 2) + 1] = pack_bf16x2(w[2] - __uint_as_float(h1 << 16), w[3] - __uint_as_float(h1 & 0xFFFF0000u));
-      }
-      // state product over the step's 32 tokens, 16 per MFMA, in the token order the weights came in:
-      // entries 0-3 of a lane's operand are tokens 16 ks + 4 half + 0..3, entries 4-7 the same + 8.
-      // All hi products of a token group before its lo products: no product waits for its predecessor.
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const bf16x8 vh = __builtin_bit_cast(bf16x8, ah[ks]), vl = __builtin_bit_cast(bf16x8, al[ks]);
-        bf16x8 bv[NJ];
-#pragma unroll
-        for (int jt = 0; jt < NJ; ++jt) {
-          const uint16_t* src = sWVt + (32 * jt + col) * LP + tok0 + 16 * ks + 4 * half;
-          const uint2 b0 = *(const uint2*)src, b1 = *(const uint2*)(src + 8);
-          bv[jt] = __builtin_bit_cast(bf16x8, (u32x4){b0.x, b0.y, b1.x, b1.y});
-        }
-#pragma unroll
-        for (int jt = 0; jt < NJ; ++jt) macc[jt] = mfma_bf16(vh, bv[jt], macc[jt]);
-#pragma unroll
-        for (int jt = 0; jt < NJ; ++jt) macc[jt] = mfma_bf16(vl, bv[jt], macc[jt]);
-      }
+        for (int jt = 0; jt < NC; ++jt)
+          __builtin_nontemporal_store(__builtin_bit_cast(u32x4, pack8(macc[jt], j)), sn + operand_chunk<D>(slot0 / 16 + j, jt, lane));
     }
+    const uint16_t *sx = pick(i, sX0, sX1), *st = pick(i, sT0, sT1);
+    const float* sn = pick(i, sN0, sN1) + 64 * wave;
+    // Regions, as in the read kernel: the next operands from LDS beside the products of the last.
+    // Scores: rows = tokens, columns = this wavefront's 32 slots
+    f32x16 sc = zero16();
+    bf16x8 f[2][4];
+    f32x4 sh[4];   // shifts of the lane's tokens
+    const bf16x8 *xt = (const bf16x8*)sx + lane, *wt = (const bf16x8*)st + lane;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) f[0][k] = xt[k * 64];
+    region();
+#pragma unroll
+    for (int bt = 0; bt < KS / 4; ++bt) {
+      if (bt + 1 < KS / 4) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[(bt + 1) & 1][k] = xt[(4 * (bt + 1) + k) * 64];
+      } else {
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) sh[q4] = *(const f32x4*)(sn + 8 * q4 + 4 * half);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) sc = mfma_bf16(f[bt & 1][k], kb[4 * bt + k], sc);
+      region();
+    }
+    // weights of 16 tokens, and what bf16 leaves of them
+    bf16x8 wh[2], wl[2];
+    auto weights = [&](int j) {
+      f32x16 lo;
+#pragma unroll
+      for (int v = 8 * j; v < 8 * j + 8; ++v) sc[v] = fast_exp2(sc[v] * p.wscale_l2e - sh[v / 4][v % 4]);
+      wh[j] = pack8(sc, j);
+      const u32x4 hw = __builtin_bit_cast(u32x4, wh[j]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        lo[8 * j + 2 * k] = sc[8 * j + 2 * k] - __uint_as_float(hw[k] << 16);
+        lo[8 * j + 2 * k + 1] = sc[8 * j + 2 * k + 1] - __uint_as_float(hw[k] & 0xFFFF0000u);
+      }
+      wl[j] = pack8(lo, j);
+    };
+    // state product over the tile's 32 tokens, 16 per MFMA.  All hi products of a token group before its lo
+    // products: no product waits for its predecessor.
+    bf16x8 bv[2][NC];
+#pragma unroll
+    for (int jt = 0; jt < NC; ++jt) bv[0][jt] = wt[jt * 64];
+    weights(0);
+    region();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if (j == 0) {
+#pragma unroll
+        for (int jt = 0; jt < NC; ++jt) bv[1][jt] = wt[(NC + jt) * 64];
+      }
+#pragma unroll
+      for (int jt = 0; jt < NC; ++jt) macc[jt] = mfma_bf16(wh[j], bv[j][jt], macc[jt]);
+#pragma unroll
+      for (int jt = 0; jt < NC; ++jt) macc[jt] = mfma_bf16(wl[j], bv[j][jt], macc[jt]);
+      if (j == 0) weights(1);
+      region();
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitLds);
+    __builtin_amdgcn_s_waitcnt(wait_vm(0));   // the next tile has arrived
+    bare_barrier();
+  };
+  request(Int<0>{}, 0);
+  __builtin_amdgcn_s_waitcnt(wait_vm(0));
+  bare_barrier();
+  uint32_t tt = 0;
+  for (; tt + 2 <= ntile; tt += 2) {
+    tile(Int<0>{}, tt);
+    tile(Int<1>{}, tt + 1);
   }
-  __syncthreads();
+  if (tt < ntile) tile(Int<0>{}, tt);
+  __builtin_amdgcn_s_waitcnt(wait_vm(0));
+  __syncthreads();   // everyone's last requests have arrived: the arrays are free
+  if (live) {
 #pragma unroll
-  for (int jt = 0; jt < NJ; ++jt)
+    for (int jt = 0; jt < NC; ++jt)
 #pragma unroll
-    for (int v = 0; v < 16; ++v)
-      sStage[(mslot + 8 * (v / 4) + 4 * half + (v % 4)) * LD + 32 * jt + col] = bf16_bits(macc[jt][v]);
-  __syncthreads();
-  {
-    constexpr int CPR = D / 8;
-    const int ch = threadIdx.x % CPR;
+      for (int v = 0; v < 16; ++v) strip[at(8 * (v / 4) + 4 * half + v % 4, jt)] = bf16_bits(macc[jt][v]);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int r = threadIdx.x / CPR; r < 128; r += NT / CPR)
-      if (m0 + r < p.M) __builtin_nontemporal_store(*(const u32x4*)(sStage + r * LD + 8 * ch), (u32x4*)(mv + (size_t)r * D + 8 * ch));
+    for (int i = 0; i < NI; ++i)
+      __builtin_nontemporal_store(*(const u32x4*)(strip + (i * 64 + lane) * 8), (u32x4*)(mv + (size_t)RT::row(i, lane) * D + RT::chunk(i, lane) * 8));
   }
 }
 
@@ -873,10 +1010,26 @@ hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
   // with a write, the state kernel leaves MV_0 transposed as the first snapshot on its way through
   if (p.has_read && !p.has_write && (e = transpose(1)) != hipSuccess) return e;
 
-  const dim3 gs = unit_grid((rows + kTC - 1) / kTC, units);
+  // Few rows of few memories leave compute units without a statistics workgroup (one fits each): split the keys, at
+  // least 256 slots a share and at most 8 shares, and merge the shares' pairs in a launch of 5 us: 3 memories x 8 heads,
+  // T = 333, M = 2112 (72 workgroups): 36 us in one share, 17 in three.
+  // The pairs (8 bytes a row and share) lie where a later launch of the chunk writes first: in the snapshots
+  // (at least 8 KB per memory and sub-chunk) or, for a chunk that only reads, in the space of WV^T (2 d bytes a token,
+  // G rows a token).
+  const uint64_t wgs = (uint64_t)((rows + kTC - 1) / kTC) * units;
+  uint32_t most = p.has_write ? kMaxStatsSplit : 2 * p.d / 8 / p.G;
+  if (most > kMaxStatsSplit) most = kMaxStatsSplit;
+  p.stats_split = 1;
+  while (p.stats_split < most && wgs * (p.stats_split + 1) <= 256 && p.M / (p.stats_split + 1) >= 256) ++p.stats_split;
+  p.stats_part = (float2*)(p.has_write ? p.snap : p.wvt);
+  const dim3 gs = unit_grid((rows + kTC - 1) / kTC * p.stats_split, units);
   if (d128) hipLaunchKernelGGL(prefill_stats_kernel<128>, gs, dim3(512), 0, s, p);
   else hipLaunchKernelGGL(prefill_stats_kernel<64>, gs, dim3(512), 0, s, p);
   if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (p.stats_split > 1) {
+    hipLaunchKernelGGL(prefill_stats_merge_kernel, unit_grid((rows + 255) / 256, units), dim3(256), 0, s, p);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
 
   auto read = [&](uint32_t c_begin, uint32_t c_count) -> hipError_t {
     p.c_begin = c_begin;

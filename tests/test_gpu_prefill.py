@@ -132,6 +132,17 @@ def test_prefill_chunk_matches_oracle(P, R, name, B, Hq, Hkv, d, M, dtype, T, mo
         assert st == (chunk + 1) * T == ref.steps
 
 
+# Edges of the chunk kernels: key tiles of 64 and 128 slots (1 to 5 of them, the last one half), token tiles of 32,
+# statistics whose keys are split over one to eight workgroups (row tiles x memories x shares <= 256, 256 slots a
+# share), reader wavefronts with no row of the chunk, both head dimensions
+@pytest.mark.parametrize("B,Hq,Hkv,d,M,T", [(1, 1, 1, 128, 64, 33), (1, 1, 1, 64, 128, 31), (1, 2, 1, 128, 192, 97),
+                                            (2, 2, 2, 128, 320, 160), (1, 1, 1, 128, 512, 129), (1, 4, 4, 64, 832, 65),
+                                            (1, 8, 1, 128, 1088, 45), (1, 1, 1, 128, 2112, 20), (3, 5, 5, 64, 2176, 140)])
+@pytest.mark.parametrize("mode", ["rw", "write_only", "read_only"])
+def test_prefill_tile_edges(P, R, B, Hq, Hkv, d, M, T, mode):
+    test_prefill_chunk_matches_oracle(P, R, f"edge_m{M}_t{T}", B, Hq, Hkv, d, M, "bf16", T, mode)
+
+
 def test_prefill_per_sequence_keys_and_scales(P, R):
     w = syn.Workload("pf_perseq", 1, 2, 4, 2, 128, 128, "bf16", 0)
     T = 96
