@@ -56,7 +56,11 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const uint16_t* __restri
 // each activation fragment it loads: the activations come from L2, where all workgroups ask for the same
 // lines at the same time, and with one weight tile per fragment that traffic (2 KB per KB of weights)
 // bounds the kernel at about 4 TB/s of weights; two tiles per fragment reach about 5.
-template <bool SWIGLU, bool XT, int WAVES, int U, int FT>
+// RT: row tiles (of 16) per workgroup.  Up to 16 rows need one, and with it half of that traffic: at 4 rows against
+// two row tiles, 11008 -> 4096 17.6 us (21.5), 4096 -> 4096 11.9 (12.7), 4096 -> 32000 47.9 (50.1), SwiGLU
+// 4096 -> 11008 30.0 (32.2), 4096 -> 12288 19.1 (19.0); at 16 rows 23.1 (25.8), 11.7 (12.7), 50.2 (52.2), 33.8
+// (34.2), 19.9 (19.3).
+template <bool SWIGLU, bool XT, int WAVES, int U, int FT, int RT>
 __global__ __launch_bounds__(64 * WAVES) void linear_kernel(const uint16_t* __restrict__ x,
                                                             const u32x4* __restrict__ w,
                                                             const u32x4* __restrict__ w2, const uint16_t* residual,
@@ -65,9 +69,10 @@ __global__ __launch_bounds__(64 * WAVES) void linear_kernel(const uint16_t* __re
   constexpr int NW2 = SWIGLU ? 2 : 1;   // weight matrices
   constexpr int NS = FT * NW2;          // weight streams of a wavefront: stream s = feature tile s / NW2 of matrix s % NW2
   constexpr int NTHR = 64 * WAVES;
-  __shared__ float sC[WAVES][32][17];
+  constexpr int ROWS = 16 * RT;
+  __shared__ float sC[WAVES][ROWS][17];
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, jl = lane % 16, kg = lane / 16;
-  const uint32_t nt0 = blockIdx.x * FT, r0 = blockIdx.y * 32, KT = K / 32;
+  const uint32_t nt0 = blockIdx.x * FT, r0 = blockIdx.y * ROWS, KT = K / 32;
   // this wavefront's share of the K tiles
   const uint32_t kt0 = (uint32_t)((uint64_t)wave * KT / WAVES), kt1 = (uint32_t)((uint64_t)(wave + 1) * KT / WAVES);
   const u32x4* wt[NS];
@@ -78,23 +83,24 @@ __global__ __launch_bounds__(64 * WAVES) void linear_kernel(const uint16_t* __re
   // Tiled activations: the two operands of K tile kt are the consecutive 1 KB tiles 2 * kt, 2 * kt + 1
   // of this row group (rows past the end are allocated, their content is never stored).
   // xstep: distance in bf16 elements between a lane's chunks of consecutive K tiles.
-  const uint32_t ra = min(r0 + jl, rows - 1), rb = min(r0 + 16 + jl, rows - 1);
-  const uint16_t* xa = XT ? x + (((size_t)blockIdx.y * KT + kt0) * 128 + lane) * 8
-                          : x + (size_t)ra * K + (size_t)kt0 * 32 + kg * 8;
-  const uint16_t* xb = XT ? xa + 64 * 8 : x + (size_t)rb * K + (size_t)kt0 * 32 + kg * 8;
+  const uint16_t* xr[RT];
+#pragma unroll
+  for (int j = 0; j < RT; ++j)
+    xr[j] = XT ? x + (((size_t)(r0 / 32) * KT + kt0) * 128 + j * 64 + lane) * 8
+               : x + (size_t)min(r0 + 16 * j + jl, rows - 1) * K + (size_t)kt0 * 32 + kg * 8;
   constexpr size_t xstep = XT ? 128 * 8 : 32;
-  f32x4 acc[NS][2];
+  f32x4 acc[NS][RT];
 #pragma unroll
   for (int s = 0; s < NS; ++s)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[s][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < RT; ++j) acc[s][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const uint32_t n_t = kt1 - kt0;
   // Rounds of U tiles: all loads of a round are issued before its first MFMA, so a round costs one memory
   // latency.  The last, partial round loads its missing tiles from the share's last tile (in bounds) and
   // zeroes their weights, which removes them from the sum.
   for (uint32_t t = 0; t < n_t; t += U) {
     const bool whole = t + U <= n_t;
-    u32x4 b[U][NS], a0[U], a1[U];
+    u32x4 b[U][NS], a[U][RT];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const size_t i = whole ? t + u : min(t + u, n_t - 1);
@@ -104,8 +110,8 @@ __global__ __launch_bounds__(64 * WAVES) void linear_kernel(const uint16_t* __re
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const size_t i = whole ? t + u : min(t + u, n_t - 1);
-      a0[u] = *(const u32x4*)(xa + i * xstep);
-      a1[u] = *(const u32x4*)(xb + i * xstep);
+#pragma unroll
+      for (int j = 0; j < RT; ++j) a[u][j] = *(const u32x4*)(xr[j] + i * xstep);
     }
     if (!whole) {
 #pragma unroll
@@ -117,19 +123,18 @@ __global__ __launch_bounds__(64 * WAVES) void linear_kernel(const uint16_t* __re
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const bf16x8 va = __builtin_bit_cast(bf16x8, a0[u]), vb = __builtin_bit_cast(bf16x8, a1[u]);
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const bf16x8 vw = __builtin_bit_cast(bf16x8, b[u][s]);
-        acc[s][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, vw, acc[s][0], 0, 0, 0);
-        acc[s][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb, vw, acc[s][1], 0, 0, 0);
-      }
+      for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int j = 0; j < RT; ++j)
+          acc[s][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[u][j]),
+                                                              __builtin_bit_cast(bf16x8, b[u][s]), acc[s][j], 0, 0, 0);
     }
   }
   // accumulator element v of a lane: token row 4 * kg + v of the row tile, feature jl.  Per feature tile
   // the partials of all wavefronts go through LDS (one matrix at a time through the same buffer) and
-  // every thread adds them in wave order for the outputs it owns (32 x 16 per tile).
-  constexpr int OPT = (512 + NTHR - 1) / NTHR;   // outputs per thread and tile
+  // every thread adds them in wave order for the outputs it owns (ROWS x 16 per tile).
+  constexpr int OPT = (ROWS * 16 + NTHR - 1) / NTHR;   // outputs per thread and tile
 #pragma unroll
   for (int f = 0; f < FT; ++f) {
     float sum[NW2][OPT];
@@ -137,13 +142,13 @@ __global__ __launch_bounds__(64 * WAVES) void linear_kernel(const uint16_t* __re
     for (int pass = 0; pass < NW2; ++pass) {
       if (f || pass) __syncthreads();
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
+      for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int v = 0; v < 4; ++v) sC[wave][16 * rt + 4 * kg + v][jl] = acc[f * NW2 + pass][rt][v];
       __syncthreads();
 #pragma unroll
       for (int q = 0; q < OPT; ++q) {
-        const uint32_t o = (threadIdx.x + q * NTHR) % 512, oi = o / 16, oj = o % 16;
+        const uint32_t o = (threadIdx.x + q * NTHR) % (ROWS * 16), oi = o / 16, oj = o % 16;
         float a = 0.f;
 #pragma unroll
         for (int k = 0; k < WAVES; ++k) a += sC[k][oi][oj];
@@ -152,8 +157,8 @@ __global__ __launch_bounds__(64 * WAVES) void linear_kernel(const uint16_t* __re
     }
 #pragma unroll
     for (int q = 0; q < OPT; ++q) {
-      const uint32_t o = threadIdx.x + q * NTHR, oi = (o % 512) / 16, oj = o % 16;
-      if (o < 512 && r0 + oi < rows) {
+      const uint32_t o = threadIdx.x + q * NTHR, oi = (o % (ROWS * 16)) / 16, oj = o % 16;
+      if (o < ROWS * 16 && r0 + oi < rows) {
         const uint32_t n = (nt0 + f) * 16 + oj;
         const int which = n >= dst.start[2] ? 2 : n >= dst.start[1] ? 1 : 0;
         const uint32_t width = dst.start[which + 1] - dst.start[which], col = n - dst.start[which];
@@ -297,18 +302,24 @@ bct_status check_linear(const void* x, const void* w, const void* out, uint32_t 
 
 using namespace bct;
 
-template <int WV, int UN, int FT>
-static void launch_linear_w(const void* x, const void* w, const void* residual, const LinearOut& dst, uint32_t rows,
-                            uint32_t K, uint32_t N, uint32_t flags, void* hip_stream) {
-  const dim3 grid(N / (16 * FT), (rows + 31) / 32), block(64 * WV);
+template <int WV, int UN, int FT, int RT>
+static void launch_linear_rt(const void* x, const void* w, const void* residual, const LinearOut& dst, uint32_t rows,
+                             uint32_t K, uint32_t N, uint32_t flags, void* hip_stream) {
+  const dim3 grid(N / (16 * FT), (rows + 16 * RT - 1) / (16 * RT)), block(64 * WV);
   if (flags & BCTM_X_TILED)
-    hipLaunchKernelGGL((linear_kernel<false, true, WV, UN, FT>), grid, block, 0, (hipStream_t)hip_stream,
+    hipLaunchKernelGGL((linear_kernel<false, true, WV, UN, FT, RT>), grid, block, 0, (hipStream_t)hip_stream,
                        (const uint16_t*)x, (const u32x4*)w, (const u32x4*)nullptr, (const uint16_t*)residual, dst, rows,
                        K, 0u);
   else
-    hipLaunchKernelGGL((linear_kernel<false, false, WV, UN, FT>), grid, block, 0, (hipStream_t)hip_stream,
+    hipLaunchKernelGGL((linear_kernel<false, false, WV, UN, FT, RT>), grid, block, 0, (hipStream_t)hip_stream,
                        (const uint16_t*)x, (const u32x4*)w, (const u32x4*)nullptr, (const uint16_t*)residual, dst, rows,
                        K, 0u);
+}
+template <int WV, int UN, int FT>
+static void launch_linear_w(const void* x, const void* w, const void* residual, const LinearOut& dst, uint32_t rows,
+                            uint32_t K, uint32_t N, uint32_t flags, void* hip_stream) {
+  if (rows <= 16) launch_linear_rt<WV, UN, FT, 1>(x, w, residual, dst, rows, K, N, flags, hip_stream);
+  else launch_linear_rt<WV, UN, FT, 2>(x, w, residual, dst, rows, K, N, flags, hip_stream);
 }
 
 // The kernel of a projection shape.  Many rows (from 128 on): the matrix-core kernel (bct_linear_rows.hip), for
@@ -327,16 +338,16 @@ static uint32_t linear_kernel_of(uint32_t rows, uint32_t N, bool swiglu) {
   return BCTM_KERNEL_STREAMING;
 }
 
-template <int WV, int UN, int FT>
+template <int WV, int UN, int FT, int RT>
 static void launch_swiglu_w(const void* x, const void* wg, const void* wu, const LinearOut& dst, uint32_t rows,
                             uint32_t K, uint32_t N, uint32_t flags, void* hip_stream) {
-  const dim3 grid(N / (16 * FT), (rows + 31) / 32), block(64 * WV);
+  const dim3 grid(N / (16 * FT), (rows + 16 * RT - 1) / (16 * RT)), block(64 * WV);
   const uint32_t ot = flags & BCTM_OUT_TILED ? 1u : 0u;
   if (flags & BCTM_X_TILED)
-    hipLaunchKernelGGL((linear_kernel<true, true, WV, UN, FT>), grid, block, 0, (hipStream_t)hip_stream,
+    hipLaunchKernelGGL((linear_kernel<true, true, WV, UN, FT, RT>), grid, block, 0, (hipStream_t)hip_stream,
                        (const uint16_t*)x, (const u32x4*)wg, (const u32x4*)wu, (const uint16_t*)nullptr, dst, rows, K, ot);
   else
-    hipLaunchKernelGGL((linear_kernel<true, false, WV, UN, FT>), grid, block, 0, (hipStream_t)hip_stream,
+    hipLaunchKernelGGL((linear_kernel<true, false, WV, UN, FT, RT>), grid, block, 0, (hipStream_t)hip_stream,
                        (const uint16_t*)x, (const u32x4*)wg, (const u32x4*)wu, (const uint16_t*)nullptr, dst, rows, K, ot);
 }
 
@@ -447,7 +458,9 @@ bct_status bctm_swiglu(const void* x, const void* w_gate, const void* w_up, void
   if (kernel == BCTM_KERNEL_TILE128 || kernel == BCTM_KERNEL_TILE256)
     return launched("swiglu", launch_linear_rows(x, w_gate, w_up, nullptr, dst, rows, K, N, flags & BCTM_X_TILED,
                                                  flags & BCTM_OUT_TILED, (hipStream_t)hip_stream));
-  launch_swiglu_w<4, 8, 1>(x, w_gate, w_up, dst, rows, K, N, flags, hip_stream);   // 36 us at 4096 -> 11008 (8 wavefronts: 38)
+  // 36 us at 32 rows, 4096 -> 11008 (8 wavefronts: 38)
+  if (rows <= 16) launch_swiglu_w<4, 8, 1, 1>(x, w_gate, w_up, dst, rows, K, N, flags, hip_stream);
+  else launch_swiglu_w<4, 8, 1, 2>(x, w_gate, w_up, dst, rows, K, N, flags, hip_stream);
   return launched("swiglu");
 }
 

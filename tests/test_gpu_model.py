@@ -93,6 +93,26 @@ def test_linear_every_workgroup_tile(M, rows, K, N, tiled):
     check_close(host(out), R.linear(x, w, res), 2.0 ** -20 * mass, f"linear {rows}x{K}x{N}")
 
 
+# the edges of the streaming kernels' one row tile (up to 16 rows), for one, two and three feature tiles and SwiGLU
+@pytest.mark.parametrize("rows", [1, 15, 16, 17, 32, 33])
+@pytest.mark.parametrize("N", [48, 16416, 12288])
+@pytest.mark.parametrize("tiled", [False, True])
+def test_linear_one_row_tile(M, rows, N, tiled):
+    K = 352
+    x, w, res = draw(1, (rows, K)), draw(2, (N, K), K ** -0.5), draw(3, (rows, N))
+    xin = M.bctm_pack_rows(dev(x)) if tiled else dev(x)
+    mass = np.abs(R.bf16_to_f64(x)) @ np.abs(R.bf16_to_f64(w)).T
+    check_close(host(M.bctm_linear(xin, M.bctm_pack_weight(dev(w)), dev(res))), R.linear(x, w, res), 2.0 ** -20 * mass,
+                f"linear {rows}x{K}x{N}")
+    if N == 48:
+        wu = draw(4, (N, K), K ** -0.5)
+        g, u = R.linear_f64(x, w), R.linear_f64(x, wu)
+        mu = np.abs(R.bf16_to_f64(x)) @ np.abs(R.bf16_to_f64(wu)).T
+        slack = 2.0 ** -20 * (1.1 * mass * np.abs(u) + (np.abs(g) + 1.0) * mu + np.abs(g * u))
+        out = M.bctm_swiglu(xin, M.bctm_pack_weight(dev(w)), M.bctm_pack_weight(dev(wu)))
+        check_close(host(out), R.swiglu(x, w, wu), slack, f"swiglu {rows}x{K}x{N}")
+
+
 def test_linear_many_rows_selects_the_right_operands(M):
     # one-hot weight rows pick input features, distinct per output feature and row: exact
     rows, K, N = 200, 256, 256
