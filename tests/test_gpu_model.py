@@ -210,6 +210,16 @@ def test_rmsnorm_tiled_out(M, rows, dim):
     assert np.array_equal(untile(t, rows, dim), plain)
 
 
+# rows around the groups of 32 and of 128 that the tiled writers go by
+@pytest.mark.parametrize("rows", [31, 32, 127, 128, 129, 255, 256, 300])
+@pytest.mark.parametrize("dim", [32, 96, 2080])
+def test_tiled_outputs_of_many_rows(M, rows, dim):
+    x, g = draw(13, (rows, dim)), draw(9, (dim,))
+    assert np.array_equal(untile(M.bctm_pack_rows(dev(x)), rows, dim), x)
+    assert np.array_equal(untile(M.bctm_rmsnorm(dev(x), dev(g), 1e-5, tiled=True), rows, dim),
+                          host(M.bctm_rmsnorm(dev(x), dev(g), 1e-5)))
+
+
 @pytest.mark.parametrize("rows,K,widths", [(32, 4096, (512, 128, 128)), (7, 320, (48, 16, 32)), (33, 64, (16, 64)),
                                            (5, 64, (6144, 3072, 3072))])
 def test_linear_split_is_bitwise_the_separate_projections(M, rows, K, widths):
