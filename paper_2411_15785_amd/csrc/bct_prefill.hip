@@ -271,29 +271,6 @@ __global__ __launch_bounds__(512, 2) void prefill_stats_kernel(const PrefillPara
                  tile1 = (uint32_t)((uint64_t)tiles * (part + 1) / p.stats_split), n = tile1 - tile0;
   const uint16_t* mk = p.mk + (size_t)(p.mk_per_seq ? unit : h) * p.M * D;
 
-  // the query rows do not change over the loop: their operand fragments stay in registers.
-  // A negative scale is moved into the row itself (negating bf16 is exact), so that below the
-  // largest raw score is also the largest scaled one and the scaling can ride in the exponent's fma.
-  float scale[2], m[2], s[2];
-  bf16x8 xb[2][KS];
-#pragma unroll
-  for (int jt = 0; jt < 2; ++jt) {
-    const uint32_t row = row0 + 64 * rh + 32 * jt + col;
-    scale[jt] = row < nw ? p.wscale_l2e : p.rscale_l2e;
-    m[jt] = kNegBig;
-    s[jt] = 0.f;
-    const uint32_t flip = scale[jt] < 0.f ? 0x80008000u : 0u;
-    scale[jt] = fabsf(scale[jt]);
-    const uint32_t rr = row - nw;
-    const uint16_t* src = row < nw ? p.wq + (((size_t)b * p.T + row) * p.Hkv + h) * D
-                                   : p.q + (((size_t)b * p.T + rr / p.G) * p.Hq + h * p.G + rr % p.G) * D;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (row < nw + nr) v = *(const u32x4*)(src + ks * 16 + half * 8);
-      xb[jt][ks] = __builtin_bit_cast(bf16x8, v ^ (u32x4){flip, flip, flip, flip});
-    }
-  }
   auto stage = [&](auto i) -> uint16_t* {
     if constexpr (decltype(i)::v % 3 == 0) return sK0;
     else if constexpr (decltype(i)::v % 3 == 1) return sK1;
@@ -309,6 +286,40 @@ __global__ __launch_bounds__(512, 2) void prefill_stats_kernel(const PrefillPara
       load_to_lds(scalar_base(mk + (size_t)slot * D + (ld % KS) * 16) + row_operand(lane, D), stage(i) + ld * 512);
     }
   };
+  // The query rows come the same way, once per workgroup, through the stage that the keys need last (the wavefronts'
+  // own loads of them, four times over and before the keys' requests: 91 us on 1890 workgroups of three tiles, so 72;
+  // B = 32, H = 32, M = 4096, T = 512 755 against 720).  They do not change over the loop: their operand fragments stay
+  // in registers.  Rows past the end: the last row again, never stored.
+  const uint32_t nrows = nw + nr;
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    const int ld = wave * NL + j;
+    const uint32_t row = min(row0 + 32 * (ld / KS) + (uint32_t)col, nrows - 1), rr = row - nw;
+    const uint16_t* src = row < nw ? p.wq + (((size_t)b * p.T + row) * p.Hkv + h) * D
+                                   : p.q + (((size_t)b * p.T + rr / p.G) * p.Hq + h * p.G + rr % p.G) * D;
+    load_to_lds(src + (ld % KS) * 16 + half * 8, sK2 + ld * 512);
+  }
+  request(Int<0>{}, 0);
+  request(Int<1>{}, 1);
+  __builtin_amdgcn_s_waitcnt(wait_vm(2 * NL));
+  bare_barrier();
+  // A negative scale is moved into the row itself (negating bf16 is exact), so that below the
+  // largest raw score is also the largest scaled one and the scaling can ride in the exponent's fma.
+  float scale[2], m[2], s[2];
+  bf16x8 xb[2][KS];
+#pragma unroll
+  for (int jt = 0; jt < 2; ++jt) {
+    scale[jt] = row0 + 64 * rh + 32 * jt + col < nw ? p.wscale_l2e : p.rscale_l2e;
+    m[jt] = kNegBig;
+    s[jt] = 0.f;
+    const uint32_t flip = scale[jt] < 0.f ? 0x80008000u : 0u;
+    scale[jt] = fabsf(scale[jt]);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      xb[jt][ks] = __builtin_bit_cast(bf16x8, *(const u32x4*)(sK2 + lane * 8 + ((2 * rh + jt) * KS + ks) * 512) ^
+                                                  (u32x4){flip, flip, flip, flip});
+  }
+  __builtin_amdgcn_s_waitcnt(kWaitLds);
   f32x16 acc[2][2];   // [tile parity][row group]
   // The products of a tile, and between them the exponentials of the tile before (from its maximum on: m is already
   // what it has to be).  OLD: there is a tile before.
@@ -349,9 +360,7 @@ __global__ __launch_bounds__(512, 2) void prefill_stats_kernel(const PrefillPara
     __builtin_amdgcn_s_waitcnt(wait_vm(NL));   // the next tile has arrived, the one after it is in flight
     bare_barrier();
   };
-  request(Int<0>{}, 0);
-  request(Int<1>{}, 1);
-  __builtin_amdgcn_s_waitcnt(wait_vm(NL));
+  __builtin_amdgcn_s_waitcnt(wait_vm(NL));   // the first keys have arrived; every wavefront has its rows
   bare_barrier();
   tile(Int<0>{}, Int<0>{}, Int<0>{}, 0);
   uint32_t t = 1;
@@ -390,6 +399,110 @@ __global__ __launch_bounds__(512, 2) void prefill_stats_kernel(const PrefillPara
     const uint32_t row = row0 + threadIdx.x;
     if (p.stats_split == 1) store_shift(p, unit, b, h, nw, nr, row, mm, ss);
     else if (row < nw + nr) p.stats_part[((size_t)unit * p.stats_split + part) * (nw + nr) + row] = make_float2(mm, ss);
+  }
+}
+
+// The same for few slots and many workgroups: one key tile at a time through registers, which leaves room for two
+// workgroups per compute unit, one of which starts or ends while the other multiplies (see launch_prefill_bf16).
+template <int D>
+__global__ __launch_bounds__(512, 4) void prefill_stats_short_kernel(const PrefillParams p) {
+  constexpr int LD = D + 8, KS = D / 16, NT = 512;
+  // the query tile is only read into registers before the loop: the key tiles reuse its memory
+  __shared__ __attribute__((aligned(16))) uint16_t sTile[128 * LD];
+  __shared__ float2 sRed[4][kTC];
+  uint16_t* const sX = sTile;
+  uint16_t* const sK = sTile;
+
+  const uint32_t uy = block_unit();
+  if (uy >= p.B * p.Hkv) return;
+  const uint32_t h = uy / p.B, b = uy % p.B, unit = b * p.Hkv + h;
+  const uint32_t nw = p.has_write ? p.T : 0u, nr = (p.has_read && p.stats_read) ? p.T * p.G : 0u;
+  const uint32_t row0 = blockIdx.x * kTC;
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, col = lane % 32, half = lane / 32;
+  // wavefront = (32 slots sg of the key tile, 64 rows rh of the row tile)
+  const int sg = wave & 3, rh = wave >> 2;
+
+  {
+    Tile<kTC, D, NT> t;
+    t.fetch_rows(p.mk, [&](int r) -> const uint16_t* {
+      uint32_t row = row0 + r;
+      if (row < nw) return p.wq + (((size_t)b * p.T + row) * p.Hkv + h) * D;
+      row -= nw;
+      if (row < nr) return p.q + (((size_t)b * p.T + row / p.G) * p.Hq + h * p.G + row % p.G) * D;
+      return nullptr;
+    });
+    t.put(sX, LD);
+  }
+  const uint16_t* mk = p.mk + (size_t)(p.mk_per_seq ? unit : h) * p.M * D;
+
+  float scale[2], m[2], s[2];
+#pragma unroll
+  for (int jt = 0; jt < 2; ++jt) {
+    scale[jt] = (row0 + 64 * rh + 32 * jt + col < nw) ? p.wscale_l2e : p.rscale_l2e;
+    m[jt] = kNegBig;
+    s[jt] = 0.f;
+  }
+  // the query rows do not change over the loop: keep their operand fragments in registers.
+  // A negative scale is moved into the row itself (negating bf16 is exact), so that below the
+  // largest raw score is also the largest scaled one and the scaling can ride in the exponent's fma.
+  __syncthreads();
+  bf16x8 xb[2][KS];
+#pragma unroll
+  for (int jt = 0; jt < 2; ++jt) {
+    const uint32_t flip = scale[jt] < 0.f ? 0x80008000u : 0u;
+    scale[jt] = fabsf(scale[jt]);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      u32x4 v = __builtin_bit_cast(u32x4, frag(sX, LD, 64 * rh + 32 * jt + col, ks * 16 + half * 8));
+      v ^= (u32x4){flip, flip, flip, flip};
+      xb[jt][ks] = __builtin_bit_cast(bf16x8, v);
+    }
+  }
+  Tile<128, D, NT> tk;
+  auto fetch_keys = [&](uint32_t m0) {
+    tk.fetch_rows(p.mk, [&](int r) -> const uint16_t* { return (m0 + r < p.M) ? mk + (size_t)(m0 + r) * D : nullptr; });
+  };
+  fetch_keys(0);
+  for (uint32_t m0 = 0; m0 < p.M; m0 += 128) {
+    __syncthreads();
+    tk.put(sK, LD);
+    if (m0 + 128 < p.M) fetch_keys(m0 + 128);  // in flight during this tile's products
+    __syncthreads();
+    if (m0 + 32 * sg < p.M) {  // M is a multiple of 64: a wavefront's 32 slots are all in or all out
+      f32x16 acc[2];
+#pragma unroll
+      for (int jt = 0; jt < 2; ++jt) acc[jt] = zero16();
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const bf16x8 a = frag(sK, LD, 32 * sg + col, ks * 16 + half * 8);
+#pragma unroll
+        for (int jt = 0; jt < 2; ++jt) acc[jt] = mfma_bf16(a, xb[jt][ks], acc[jt]);
+      }
+#pragma unroll
+      for (int jt = 0; jt < 2; ++jt) {
+        float tmax = acc[jt][0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, acc[jt][v]);
+        const float mn = fmaxf(m[jt], tmax * scale[jt]);
+        float add = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) add += fast_exp2(__builtin_fmaf(acc[jt][v], scale[jt], -mn));
+        s[jt] = s[jt] * fast_exp2(m[jt] - mn) + add;
+        m[jt] = mn;
+      }
+    }
+  }
+#pragma unroll
+  for (int jt = 0; jt < 2; ++jt) {
+    merge_stat(m[jt], s[jt], __shfl_xor(m[jt], 32, 64), __shfl_xor(s[jt], 32, 64));
+    if (half == 0) sRed[sg][64 * rh + 32 * jt + col] = make_float2(m[jt], s[jt]);
+  }
+  __syncthreads();
+  if (threadIdx.x < kTC) {
+    float mm = sRed[0][threadIdx.x].x, ss = sRed[0][threadIdx.x].y;
+#pragma unroll
+    for (int w = 1; w < 4; ++w) merge_stat(mm, ss, sRed[w][threadIdx.x].x, sRed[w][threadIdx.x].y);
+    store_shift(p, unit, b, h, nw, nr, row0 + threadIdx.x, mm, ss);
   }
 }
 
@@ -626,6 +739,8 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
   };
   const int nsb = groups(32 * rg, 32 * rg + 31);
   const bool asked = rg < groups(0, kTC - 1);
+  request(Int<0>{}, 0);
+  request(Int<1>{}, 1);
   // this wavefront's rows as operand fragments, kept in registers.  A negative read scale moves into the
   // row (negating bf16 is exact), so that the largest raw score is also the largest scaled one.
   float cs = reader ? p.rscale_l2e : p.wscale_l2e;   // scale of this wavefront's rows (log2 domain)
@@ -644,8 +759,6 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
       x[ks] = __builtin_bit_cast(bf16x8, v ^ (u32x4){flip, flip, flip, flip});
     }
   }
-  request(Int<0>{}, 0);
-  request(Int<1>{}, 1);
   tile_end();
 
   if (!reader) {
@@ -1012,7 +1125,8 @@ hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
 
   // Few rows of few memories leave compute units without a statistics workgroup (one fits each): split the keys, at
   // least 256 slots a share and at most 8 shares, and merge the shares' pairs in a launch of 5 us: 3 memories x 8 heads,
-  // T = 333, M = 2112 (72 workgroups): 36 us in one share, 17 in three.
+  // T = 333, M = 2112 (72 workgroups): 36 us in one share, 15 in three.  From 1024 slots on: 128 slots are 1.3 us of a
+  // share's time, so below that the merge (5 us, and its launch) costs what the split gives.
   // The pairs (8 bytes a row and share) lie where a later launch of the chunk writes first: in the snapshots
   // (at least 8 KB per memory and sub-chunk) or, for a chunk that only reads, in the space of WV^T (2 d bytes a token,
   // G rows a token).
@@ -1020,10 +1134,19 @@ hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
   uint32_t most = p.has_write ? kMaxStatsSplit : 2 * p.d / 8 / p.G;
   if (most > kMaxStatsSplit) most = kMaxStatsSplit;
   p.stats_split = 1;
-  while (p.stats_split < most && wgs * (p.stats_split + 1) <= 256 && p.M / (p.stats_split + 1) >= 256) ++p.stats_split;
+  while (p.M >= 1024 && p.stats_split < most && wgs * (p.stats_split + 1) <= 256 && p.M / (p.stats_split + 1) >= 256)
+    ++p.stats_split;
   p.stats_part = (float2*)(p.has_write ? p.snap : p.wvt);
   const dim3 gs = unit_grid((rows + kTC - 1) / kTC * p.stats_split, units);
-  if (d128) hipLaunchKernelGGL(prefill_stats_kernel<128>, gs, dim3(512), 0, s, p);
+  // Few slots: the kernel that fits two workgroups on a compute unit, where a workgroup's start and end are much of its
+  // time, or where its own start (one key tile, not three) is most of the launch.  us, this kernel against the other:
+  // d = 128, 1890 workgroups: M = 320 46 | 68, 1280 143 | 154, 2048 199 | 196, 3072 285 | 266; 512 workgroups: 640 22 | 26,
+  // 1280 37 | 37, 2048 57 | 53; 256: 640 14.4 | 13.7, 2048 37 | 26; 24: 128 6.4 | 7.8, 384 9.3 | 9.9.  d = 64, 1890: 320
+  // 31 | 46, 1280 81 | 93, 3072 178 | 187; 256: 640 9.1 | 9.6, 2048 22 | 19.
+  const bool brief = p.stats_split == 1 && (p.M <= 384 || (wgs > 256 && p.M <= (d128 ? 1280u : 3072u)));
+  if (brief && d128) hipLaunchKernelGGL(prefill_stats_short_kernel<128>, gs, dim3(512), 0, s, p);
+  else if (brief) hipLaunchKernelGGL(prefill_stats_short_kernel<64>, gs, dim3(512), 0, s, p);
+  else if (d128) hipLaunchKernelGGL(prefill_stats_kernel<128>, gs, dim3(512), 0, s, p);
   else hipLaunchKernelGGL(prefill_stats_kernel<64>, gs, dim3(512), 0, s, p);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (p.stats_split > 1) {
