@@ -649,7 +649,11 @@ __global__ __launch_bounds__(512) void prefill_read_only_kernel(const PrefillPar
 // needs another wavefront.  The writers are one tile ahead; one barrier per tile.  Keys and MV_c come through LDS,
 // requested two tiles ahead without a trip through registers.
 // What bounds it: 64 matrix instructions per SIMD and tile (2048 cycles) beside about as many cycles of vector work
-// for 64 exponentials per lane.
+// for 64 exponentials per lane, at the clock that the chip's power limit leaves (1.67 GHz at B = 32, H = 32, M = 4096,
+// T = 512: 2230 us; tiles staged through registers, all eight wavefronts scoring, 2650).  Forms that overlap more
+// (products between the exponentials, the next tile's scores as well) took 2290 and 2400; with
+// v_mfma_f32_16x16x32_bf16, which hides less vector work, 2430.  A launch of one round (216 workgroups, 33 tiles):
+// 67 us against 82.
 template <int D>
 __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const PrefillParams p) {
   constexpr int KS = D / 16, NC = D / 32;
