@@ -929,7 +929,10 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
 // a workgroup within 168 registers and 36 KB, so that three of them (three wavefronts per SIMD) hide each
 // other's barriers and stores; two: 2250 us against 1950 at that size, four (registers spilled): 2680.  Row-major
 // token tiles of 64 with padded rows, where a third of the LDS cycles were bank conflicts, took 2170.
-template <int D>
+// FAR: a token tile's write queries lie further apart than a lane's 32-bit byte offset reaches (see
+// launch_prefill_bf16), so their addresses are 64-bit.  Not for every chunk: 64-bit addresses spill 62 registers of
+// the d = 128 kernel, the 32-bit offsets none.
+template <int D, bool FAR>
 __global__ __launch_bounds__(256, 3) void prefill_state_kernel(const PrefillParams p) {
   constexpr int KS = D / 16, NC = D / 32;
   constexpr int TT = 32;            // tokens per tile
@@ -997,7 +1000,8 @@ __global__ __launch_bounds__(256, 3) void prefill_state_kernel(const PrefillPara
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
       const int ld = wave * NL + j;
-      load_to_lds(scalar_base(wq + (size_t)tl * TT * xstride + ld * 16) + (row * xstride + (uint32_t)half * 8u) * 2u, sx + ld * 512);
+      if constexpr (FAR) load_to_lds(wq + ((size_t)(tl * TT + row) * xstride + ld * 16 + half * 8), sx + ld * 512);
+      else load_to_lds(scalar_base(wq + (size_t)tl * TT * xstride + ld * 16) + (row * xstride + (uint32_t)half * 8u) * 2u, sx + ld * 512);
       load_to_lds(scalar_base(wvt + (size_t)tl * kTile + ld * 512) + (uint32_t)lane * 16u, st + ld * 512);
     }
     __builtin_amdgcn_global_load_lds(
@@ -1173,8 +1177,13 @@ hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
   };
   if (p.has_write) {
     const dim3 g = unit_grid((p.M + 127) / 128, units);
-    if (d128) hipLaunchKernelGGL(prefill_state_kernel<128>, g, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL(prefill_state_kernel<64>, g, dim3(256), 0, s, p);
+    // byte offset of the last lane's 16 bytes in 32 tokens' write queries: past 32 bits from 541201 heads of 128
+    // (1082402 of 64) on
+    const bool far = (31 * (uint64_t)p.Hkv * p.d + 8) * 2 > 0xFFFFFFFFu;
+    if (d128 && far) hipLaunchKernelGGL((prefill_state_kernel<128, true>), g, dim3(256), 0, s, p);
+    else if (far) hipLaunchKernelGGL((prefill_state_kernel<64, true>), g, dim3(256), 0, s, p);
+    else if (d128) hipLaunchKernelGGL((prefill_state_kernel<128, false>), g, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((prefill_state_kernel<64, false>), g, dim3(256), 0, s, p);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   // every sub-chunk reads its starting state from the transposed copies in the workspace (with a write:

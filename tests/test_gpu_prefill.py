@@ -152,6 +152,37 @@ def test_prefill_statistics_kernels(P, R, B, Hq, Hkv, d, M, T, mode):
     test_prefill_chunk_matches_oracle(P, R, f"stats_m{M}_b{B}", B, Hq, Hkv, d, M, "bf16", T, mode)
 
 
+# So many KV heads that the write queries of a 32-token tile span 4 GB: the last head count at which a
+# 32-bit byte offset reaches them all ((31 * heads * d + 8) * 2 < 2^32), and the next one.  Memories are independent, so the oracle
+# takes a few of them (62 GB on the device, drawn there).
+@pytest.mark.parametrize("Hkv", [541200, 541201])
+def test_prefill_write_queries_a_32_bit_offset_apart(P, R, Hkv):
+    import torch
+    d, M, T = 128, 64, 32
+    scale = d ** -0.5
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(5)
+
+    def draw(*shape):
+        return torch.randn(shape, generator=g, dtype=torch.bfloat16, device="cuda:0")
+
+    def some(x, dim):   # of a few heads
+        return to_np(torch.stack([x.select(dim, h) for h in (0, 1, 4097, Hkv // 2, Hkv - 2, Hkv - 1)], dim), "bf16")
+
+    gpu = P.BctCache(M, 1, Hkv, Hkv, d, torch.bfloat16, scale, scale, 0, T)
+    mk = draw(Hkv, M, d)
+    gpu.set_keys(mk)
+    mk = some(mk, 0)
+    q, wq, wv = (draw(1, T, Hkv, d) for _ in range(3))
+    out = some(gpu.prefill(q, wq, wv, T), 2)
+    mv = some(gpu.values_view(), 1)
+    q, wq, wv = (some(x, 2) for x in (q, wq, wv))
+    ref = R.RefCache(M, 1, len(mk), len(mk), d, "bf16", scale, scale, 0)
+    ref.set_keys(mk)
+    check_prefill_out(out, ref.prefill(q, wq, wv, T), "bf16", f"{Hkv} heads")
+    check_prefill_state(R, ref, mk, wq, wv, mv, T, f"{Hkv} heads")
+
+
 def test_prefill_per_sequence_keys_and_scales(P, R):
     w = syn.Workload("pf_perseq", 1, 2, 4, 2, 128, 128, "bf16", 0)
     T = 96
