@@ -152,9 +152,14 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
     bare_barrier();
   };
 
+  // The wait counts requests from the last one back, here and in the loop, so the stages' order has to stand: nothing
+  // is moved across the scheduling barriers (in the loop, bare_barrier has them).
   request(Int<0>{}, 0);
+  __builtin_amdgcn_sched_barrier(0);
   request(Int<1>{}, 1);
+  __builtin_amdgcn_sched_barrier(0);
   request(Int<2>{}, 2);
+  __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(wait_vm((S - 2) * ND));
   bare_barrier();
   const bool second = PING && wv >= 4;   // the wavefront of a SIMD that is half a step behind

@@ -299,8 +299,12 @@ __global__ __launch_bounds__(512, 2) void prefill_stats_kernel(const PrefillPara
                                    : p.q + (((size_t)b * p.T + rr / p.G) * p.Hq + h * p.G + rr % p.G) * D;
     load_to_lds(src + (ld % KS) * 16 + half * 8, sK2 + ld * 512);
   }
+  // the waits count requests from the last one back: rows, first keys, second keys stay in this order
+  region();
   request(Int<0>{}, 0);
+  region();
   request(Int<1>{}, 1);
+  region();
   __builtin_amdgcn_s_waitcnt(wait_vm(2 * NL));
   bare_barrier();
   // A negative scale is moved into the row itself (negating bf16 is exact), so that below the
