@@ -44,7 +44,6 @@ struct DecodeParams {
   uint32_t mv_u;       // 16-byte loads per lane of the MV pass
   uint32_t fused;      // 1: the whole step is one launch of decode_fused_kernel
   uint32_t fuse_norm;  // 1: the MV pass merges the per-tile statistics itself, no normaliser launch
-  uint32_t rescore;    // 1: the MV pass of a step that reads scores its slots again; no scores in memory
   float rscale_l2e, wscale_l2e;  // scale * log2(e)
   // strides (in elements) between consecutive batch entries of q/out and wq/wv;
   // [B][H][d] inputs use H*d, a token t of a [B][T][H][d] chunk uses T*H*d.
@@ -53,6 +52,8 @@ struct DecodeParams {
   // gate[b * gate_bstride + h]; null = 1.  Scales the write weights.
   const float* gate;
   uint64_t gate_bstride;
+  // last, so that the kernels that do not use it load the fields above as before
+  uint32_t rescore;    // 1: the MV pass of a step that reads scores its slots again; no scores in memory
 };
 
 // One prefill chunk of a bf16 cache: everything its launches need.
