@@ -62,8 +62,8 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const uint16_t* __restri
 // bounds the kernel at about 4 TB/s of weights; two tiles per fragment reach about 5.
 // RT: row tiles (of 16) per workgroup.  Up to 16 rows need one, and with it half of that traffic: at 4 rows against
 // two row tiles, 11008 -> 4096 17.6 us (21.5), 4096 -> 4096 11.9 (12.7), 4096 -> 32000 47.9 (50.1), SwiGLU
-// 4096 -> 11008 30.0 (32.2), 4096 -> 12288 19.1 (19.0); at 16 rows 23.1 (25.8), 11.7 (12.7), 50.2 (52.2), 33.8
-// (34.2), 19.9 (19.3).
+// 4096 -> 11008 30.0 (32.2); at 16 rows 23.1 (25.8), 11.7 (12.7), 50.2 (52.2), 33.8 (34.2).  4096 -> 12288 (three feature
+// tiles): see launch_linear_w.
 template <bool SWIGLU, bool XT, int WAVES, int U, int FT, int RT>
 __global__ __launch_bounds__(64 * WAVES) void linear_kernel(const uint16_t* __restrict__ x,
                                                             const u32x4* __restrict__ w,
@@ -331,7 +331,13 @@ static void launch_linear_rt(const void* x, const void* w, const void* residual,
 template <int WV, int UN, int FT>
 static void launch_linear_w(const void* x, const void* w, const void* residual, const LinearOut& dst, uint32_t rows,
                             uint32_t K, uint32_t N, uint32_t flags, void* hip_stream) {
-  if (rows <= 16) launch_linear_rt<WV, UN, FT, 1>(x, w, residual, dst, rows, K, N, flags, hip_stream);
+  // One row tile up to 16 rows, but for row-major activations of more than 8 rows under three feature tiles on one
+  // workgroup per compute unit: there half as many row loads in flight cost more than their traffic.  us, one row tile |
+  // two: 12288 features, 16 row-major rows, K = 4096 19.5 | 19.1, K = 8192 34.8 | 34.4, K = 2048 11.9 | 11.9; 8 rows 18.9 |
+  // 18.8, 34.3 | 34.3, 11.2 | 11.4; tiled, 16 rows 18.9 | 19.1, 33.6 | 34.2, 11.2 | 11.7.  More workgroups: 14400 features,
+  // K = 4096, 16 row-major rows 29.0 | 29.9, tiled 26.9 | 29.5.
+  const bool two = FT == 3 && !(flags & BCTM_X_TILED) && rows > 8 && N / (16 * FT) <= 256;
+  if (rows <= 16 && !two) launch_linear_rt<WV, UN, FT, 1>(x, w, residual, dst, rows, K, N, flags, hip_stream);
   else launch_linear_rt<WV, UN, FT, 2>(x, w, residual, dst, rows, K, N, flags, hip_stream);
 }
 
