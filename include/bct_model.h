@@ -61,7 +61,11 @@ bct_status bctm_pack_weight(const void* w, void* packed, uint32_t N, uint32_t K,
  * out may alias residual; x must not alias out.  Two kernels: up to 127 rows (a decode batch) the weights
  * are streamed once per 32 rows against activations read from cache; from 128 rows on (a prompt chunk), when
  * N is a multiple of 128 (bctm_swiglu: 64), a tiled matrix-core kernel runs instead, with workgroup tiles from
- * 64 x 64 to 256 x 256 chosen to fill the chip - fastest with a tiled x.  Both give the sum in fp32 with their own, fixed, summation order. */
+ * 64 x 64 to 256 x 256 chosen to fill the chip - fastest with a tiled x.  Both sum in fp32, K in one or more parts added in
+ * order.  The number of parts is fixed for a shape but depends on rows and N (bctm_linear_tile): equal calls give equal
+ * bits, a tiled and a row-major x give the same bits, and so do calls of other rows or N with as many parts; calls with
+ * other parts may differ in the last bits, a chunk's rows from the same rows alone or the parts of a bctm_linear_split
+ * from separate projections. */
 bct_status bctm_linear(const void* x, const void* w_packed, const void* residual, void* out, uint32_t rows,
                        uint32_t K, uint32_t N, uint32_t flags, void* hip_stream);
 
@@ -78,14 +82,21 @@ bct_status bctm_linear_split(const void* x, const void* w_packed, void* out0, ui
 bct_status bctm_swiglu(const void* x, const void* w_gate_packed, const void* w_up_packed, void* out, uint32_t rows,
                        uint32_t K, uint32_t N, uint32_t flags, void* hip_stream);
 
-/* Which kernel bctm_linear / bctm_linear_split (swiglu = 0) or bctm_swiglu (swiglu = 1) launches for a
- * shape: host logic only, no GPU call.  *kernel receives one of the values below. */
+/* Which kernel bctm_linear / bctm_linear_split (swiglu = 0, N their widths together) or bctm_swiglu (swiglu = 1) launches
+ * for a shape: host logic only, no GPU call.  *kernel receives one of the values below.  The last two of them
+ * name the same matrix-core kernel in two ranges of shapes; which tile it gives a workgroup there is
+ * bctm_linear_tile's answer. */
 #define BCTM_KERNEL_STREAMING 0u /* weights streamed once per 32 rows (one 16-feature tile per workgroup) */
 #define BCTM_KERNEL_STREAMING_WIDE 1u /* the same with two feature tiles per workgroup (wide output heads) */
-#define BCTM_KERNEL_TILE128 2u   /* matrix-core kernel for some hundred rows, or for features only its 128-wide tiles divide */
-#define BCTM_KERNEL_TILE256 3u   /* matrix-core kernel for many rows: 256 x 256 per workgroup where that fills the chip */
 #define BCTM_KERNEL_STREAMING_TRIPLE 4u /* streaming with three feature tiles per workgroup */
+#define BCTM_KERNEL_TILE128 2u   /* matrix-core kernel, 128 to 1023 rows or N no multiple of 256 (SwiGLU: 128) */
+#define BCTM_KERNEL_TILE256 3u   /* matrix-core kernel, from 1024 rows on and N a multiple of 256 (SwiGLU: 128) */
 bct_status bctm_linear_plan(uint32_t rows, uint32_t K, uint32_t N, uint32_t swiglu, uint32_t* kernel);
+
+/* What that launch gives one workgroup: *tile_rows token rows x *tile_features features, K summed in *k_parts parts.
+ * flags: BCTM_X_TILED as in the call.  Host logic only, the launches go by the same functions. */
+bct_status bctm_linear_tile(uint32_t rows, uint32_t K, uint32_t N, uint32_t swiglu, uint32_t flags, uint32_t* tile_rows,
+                            uint32_t* tile_features, uint32_t* k_parts);
 
 /* ids[r] = index of the largest logits[r][:] (the lowest index among equal maxima). */
 bct_status bctm_argmax(const void* logits, int32_t* ids, uint32_t rows, uint32_t N, void* hip_stream);

@@ -20,6 +20,15 @@ __device__ __forceinline__ size_t tiled_chunk(uint32_t r, uint32_t k, uint32_t K
   return ((((size_t)(r / 32) * (K / 32) + k / 32) * 2 + (r % 32) / 16) * 64) + 16 * ((k % 32) / 8) + r % 16;
 }
 
+// What a projection launch gives each workgroup: rows x features (SwiGLU: of the product), and in how many parts K is
+// summed (each a chain of its own, the parts added in order).
+struct LinearTile {
+  uint32_t rows, features, k_parts;
+};
+
+// The tile of launch_linear_rows for a shape: host logic, what that launch itself goes by.
+LinearTile linear_rows_tile(uint32_t rows, uint32_t N, bool swiglu);
+
 // The matrix-core projection of many rows (bct_linear_rows.hip).  w2 non-null: SwiGLU of w and w2.  x_tiled /
 // out_tiled: activations in the tiled order.  N is a multiple of 128 (SwiGLU: 64), K of 32.
 hipError_t launch_linear_rows(const void* x, const void* w, const void* w2, const void* residual, const LinearOut& dst,

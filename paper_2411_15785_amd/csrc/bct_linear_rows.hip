@@ -268,7 +268,8 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
   }
 }
 
-// The tile of a shape.  The time of a launch is the number of rounds its workgroups take on 256 compute units
+// The tile of a shape.  It decides in how many parts K is summed as well, so a result's last bits depend on the
+// row and feature counts (bctm_linear_tile tells).  The time of a launch is the number of rounds its workgroups take on 256 compute units
 // times the K steps times what a step of a resident workgroup takes; measured us per K step at 640 and 16384
 // rows, K = 11008 / 4096:
 //   256 x 256             one workgroup per compute unit  0.46 (few) - 0.69 (chip full)
@@ -328,6 +329,18 @@ void launch_rows(const void* x, const void* w, const void* w2, const void* resid
 }
 
 }  // namespace
+
+LinearTile linear_rows_tile(uint32_t rows, uint32_t N, bool swiglu) {
+  const uint32_t per = swiglu ? 2 : 1;   // B columns of a feature
+  switch (rows_shape(rows, per * N)) {
+    case kTile256: return {256, 256 / per, 1};
+    case kTile128x256: return {128, 256 / per, 1};
+    case kTile128: return {128, 128 / per, 1};
+    case kTile128K2: return {128, 128 / per, 2};
+    case kTile64K2: return {64, 64 / per, 2};
+  }
+  return {0, 0, 0};
+}
 
 hipError_t launch_linear_rows(const void* x, const void* w, const void* w2, const void* residual, const LinearOut& dst,
                               uint32_t rows, uint32_t K, uint32_t N, bool x_tiled, bool out_tiled, hipStream_t s) {

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const uint16_t* __restri
 // RT: row tiles (of 16) per workgroup.  Up to 16 rows need one, and with it half of that traffic: at 4 rows against
 // two row tiles, 11008 -> 4096 17.6 us (21.5), 4096 -> 4096 11.9 (12.7), 4096 -> 32000 47.9 (50.1), SwiGLU
 // 4096 -> 11008 30.0 (32.2); at 16 rows 23.1 (25.8), 11.7 (12.7), 50.2 (52.2), 33.8 (34.2).  4096 -> 12288 (three feature
-// tiles): see launch_linear_w.
+// tiles): see streaming_row_tiles.
 template <bool SWIGLU, bool XT, int WAVES, int U, int FT, int RT>
 __global__ __launch_bounds__(64 * WAVES) void linear_kernel(const uint16_t* __restrict__ x,
                                                             const u32x4* __restrict__ w,
@@ -328,22 +328,27 @@ static void launch_linear_rt(const void* x, const void* w, const void* residual,
                        (const uint16_t*)x, (const u32x4*)w, (const u32x4*)nullptr, (const uint16_t*)residual, dst, rows,
                        K, 0u);
 }
-template <int WV, int UN, int FT>
-static void launch_linear_w(const void* x, const void* w, const void* residual, const LinearOut& dst, uint32_t rows,
-                            uint32_t K, uint32_t N, uint32_t flags, void* hip_stream) {
+// Row tiles of a streaming launch with FT feature tiles a workgroup.
+static uint32_t streaming_row_tiles(uint32_t FT, uint32_t rows, uint32_t N, uint32_t flags) {
   // One row tile up to 16 rows, but for row-major activations of more than 8 rows under three feature tiles on one
   // workgroup per compute unit: there half as many row loads in flight cost more than their traffic.  us, one row tile |
   // two: 12288 features, 16 row-major rows, K = 4096 19.5 | 19.1, K = 8192 34.8 | 34.4, K = 2048 11.9 | 11.9; 8 rows 18.9 |
   // 18.8, 34.3 | 34.3, 11.2 | 11.4; tiled, 16 rows 18.9 | 19.1, 33.6 | 34.2, 11.2 | 11.7.  More workgroups: 14400 features,
   // K = 4096, 16 row-major rows 29.0 | 29.9, tiled 26.9 | 29.5.
   const bool two = FT == 3 && !(flags & BCTM_X_TILED) && rows > 8 && N / (16 * FT) <= 256;
-  if (rows <= 16 && !two) launch_linear_rt<WV, UN, FT, 1>(x, w, residual, dst, rows, K, N, flags, hip_stream);
+  return rows <= 16 && !two ? 1 : 2;
+}
+template <int WV, int UN, int FT>
+static void launch_linear_w(const void* x, const void* w, const void* residual, const LinearOut& dst, uint32_t rows,
+                            uint32_t K, uint32_t N, uint32_t flags, void* hip_stream) {
+  if (streaming_row_tiles(FT, rows, N, flags) == 1)
+    launch_linear_rt<WV, UN, FT, 1>(x, w, residual, dst, rows, K, N, flags, hip_stream);
   else launch_linear_rt<WV, UN, FT, 2>(x, w, residual, dst, rows, K, N, flags, hip_stream);
 }
 
 // The kernel of a projection shape.  Many rows (from 128 on): the matrix-core kernel (bct_linear_rows.hip), for
-// feature counts its 128-feature (SwiGLU: 64) tiles cover exactly; from 1024 rows on with tiles of up to
-// 256 x 256 where the feature count allows.
+// feature counts its 128-feature (SwiGLU: 64) tiles cover exactly; its two values name ranges of shapes, the tile
+// inside it is linear_rows_tile's choice.
 // Few rows: the streaming kernel; measured at 32 rows (weights in TB/s): K = 4096, N = 4096 / 12288: 16
 // wavefronts, one feature tile 3.6 / 4.0 against 2.8 / 3.8 for two tiles (too few workgroups); N = 32000:
 // two tiles 5.0 against 4.3.
@@ -355,6 +360,12 @@ static uint32_t linear_kernel_of(uint32_t rows, uint32_t N, bool swiglu) {
   // features (W_q | W_wq | W_wv at 4096 each) are exactly 256 workgroups, 19.5 us against 24.3
   if (!swiglu && N % 48 == 0 && N / 48 >= 256) return BCTM_KERNEL_STREAMING_TRIPLE;
   return BCTM_KERNEL_STREAMING;
+}
+
+// What the launches below and above give a workgroup; the wavefronts of a workgroup share K.
+static LinearTile streaming_tile(uint32_t kernel, uint32_t rows, uint32_t N, bool swiglu, uint32_t flags) {
+  const uint32_t ft = kernel == BCTM_KERNEL_STREAMING_TRIPLE ? 3 : kernel == BCTM_KERNEL_STREAMING_WIDE ? 2 : 1;
+  return {16 * streaming_row_tiles(ft, rows, N, flags), 16 * ft, swiglu ? 4u : ft > 1 ? 8u : 16u};
 }
 
 template <int WV, int UN, int FT, int RT>
@@ -479,7 +490,7 @@ bct_status bctm_swiglu(const void* x, const void* w_gate, const void* w_up, void
     return launched("swiglu", launch_linear_rows(x, w_gate, w_up, nullptr, dst, rows, K, N, flags & BCTM_X_TILED,
                                                  flags & BCTM_OUT_TILED, (hipStream_t)hip_stream));
   // 36 us at 32 rows, 4096 -> 11008 (8 wavefronts: 38)
-  if (rows <= 16) launch_swiglu_w<4, 8, 1, 1>(x, w_gate, w_up, dst, rows, K, N, flags, hip_stream);
+  if (streaming_row_tiles(1, rows, N, flags) == 1) launch_swiglu_w<4, 8, 1, 1>(x, w_gate, w_up, dst, rows, K, N, flags, hip_stream);
   else launch_swiglu_w<4, 8, 1, 2>(x, w_gate, w_up, dst, rows, K, N, flags, hip_stream);
   return launched("swiglu");
 }
@@ -488,6 +499,21 @@ bct_status bctm_linear_plan(uint32_t rows, uint32_t K, uint32_t N, uint32_t swig
   if (!kernel || rows == 0 || K == 0 || N == 0) return mfail(BCT_ERR_INVALID_ARG, "NULL pointer or zero size");
   if (K % 32 != 0 || N % 16 != 0) return mfail(BCT_ERR_UNSUPPORTED, "K must be a multiple of 32 and N of 16");
   *kernel = linear_kernel_of(rows, N, swiglu != 0);
+  return BCT_OK;
+}
+
+bct_status bctm_linear_tile(uint32_t rows, uint32_t K, uint32_t N, uint32_t swiglu, uint32_t flags, uint32_t* tile_rows,
+                            uint32_t* tile_features, uint32_t* k_parts) {
+  if (!tile_rows || !tile_features || !k_parts || rows == 0 || K == 0 || N == 0)
+    return mfail(BCT_ERR_INVALID_ARG, "NULL pointer or zero size");
+  if (K % 32 != 0 || N % 16 != 0) return mfail(BCT_ERR_UNSUPPORTED, "K must be a multiple of 32 and N of 16");
+  const uint32_t kernel = linear_kernel_of(rows, N, swiglu != 0);
+  const LinearTile t = kernel == BCTM_KERNEL_TILE128 || kernel == BCTM_KERNEL_TILE256
+                           ? linear_rows_tile(rows, N, swiglu != 0)
+                           : streaming_tile(kernel, rows, N, swiglu != 0, flags);
+  *tile_rows = t.rows;
+  *tile_features = t.features;
+  *k_parts = t.k_parts;
   return BCT_OK;
 }
 

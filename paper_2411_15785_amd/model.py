@@ -15,7 +15,7 @@ from . import binding
 from .binding import BCT_OK, BctCache, BctError, _dptr, _stream_ptr, _torch
 
 MODEL_EXPORTS = ["bctm_embed", "bctm_rmsnorm", "bctm_pack_weight", "bctm_pack_rows", "bctm_linear", "bctm_linear_split",
-                 "bctm_swiglu", "bctm_linear_plan",
+                 "bctm_swiglu", "bctm_linear_plan", "bctm_linear_tile",
                  "bctm_argmax", "bctm_last_error"]
 
 BCTM_KERNEL_STREAMING, BCTM_KERNEL_STREAMING_WIDE, BCTM_KERNEL_TILE128, BCTM_KERNEL_TILE256 = 0, 1, 2, 3
@@ -42,6 +42,7 @@ def mlib() -> ctypes.CDLL:
     L.bctm_linear_split.argtypes = [vp, vp, vp, u32, vp, u32, vp, u32, u32, u32, u32, vp]
     L.bctm_swiglu.argtypes = [vp, vp, vp, vp, u32, u32, u32, u32, vp]
     L.bctm_linear_plan.argtypes = [u32, u32, u32, u32, ctypes.POINTER(u32)]
+    L.bctm_linear_tile.argtypes = [u32, u32, u32, u32, u32] + [ctypes.POINTER(u32)] * 3
     L.bctm_argmax.argtypes = [vp, vp, u32, u32, vp]
     for n in MODEL_EXPORTS[:-1]:
         getattr(L, n).restype = ctypes.c_int
@@ -93,6 +94,14 @@ def bctm_linear_plan(rows, K, N, swiglu=False):
     k = ctypes.c_uint32(0)
     _ck(mlib().bctm_linear_plan(rows, K, N, 1 if swiglu else 0, ctypes.byref(k)), "bctm_linear_plan")
     return k.value
+
+
+def bctm_linear_tile(rows, K, N, swiglu=False, tiled=False):
+    """(rows, features, parts of K) that the launch of this shape gives one workgroup; tiled: x is a TiledRows."""
+    v = [ctypes.c_uint32(0) for _ in range(3)]
+    _ck(mlib().bctm_linear_tile(rows, K, N, 1 if swiglu else 0, BCTM_X_TILED if tiled else 0,
+                                *(ctypes.byref(a) for a in v)), "bctm_linear_tile")
+    return tuple(a.value for a in v)
 
 
 class TiledRows:

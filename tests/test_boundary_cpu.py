@@ -86,7 +86,7 @@ def test_model_entry_points_check_arguments_before_touching_the_gpu(L):
 
 def test_projection_kernel_choice():
     """bctm_linear_plan: which kernel a projection shape runs in (host logic).  The 7B-shaped stack: a decode
-    batch streams the weights; a prompt chunk takes the matrix-core kernel, 256 x 256 where the shape allows."""
+    batch streams the weights; a prompt chunk takes the matrix-core kernel (its tile: test_projection_tile)."""
     from paper_2411_15785_amd import model as Mo
     S, SW, T128, T256 = (Mo.BCTM_KERNEL_STREAMING, Mo.BCTM_KERNEL_STREAMING_WIDE, Mo.BCTM_KERNEL_TILE128,
                          Mo.BCTM_KERNEL_TILE256)
@@ -110,6 +110,30 @@ def test_projection_kernel_choice():
     assert ML.bctm_linear_plan(4, 72, 32, 0, ctypes.byref(k)) == P.BCT_ERR_UNSUPPORTED
     assert ML.bctm_linear_plan(4, 64, 32, 0, None) == P.BCT_ERR_INVALID_ARG
     assert ML.bctm_linear_plan(0, 64, 32, 0, ctypes.byref(k)) == P.BCT_ERR_INVALID_ARG
+
+
+def test_projection_tile():
+    """bctm_linear_tile: rows x features per workgroup and the parts that K is summed in, as launched (host logic)."""
+    from paper_2411_15785_amd import model as Mo
+    tile = Mo.bctm_linear_tile
+    # streaming: row tiles of 16; 1, 2 or 3 feature tiles; K over the workgroup's wavefronts
+    assert tile(4, 11008, 4096) == (16, 16, 16) and tile(17, 11008, 4096) == (32, 16, 16)
+    assert tile(16, 4096, 32000) == (16, 32, 8) and tile(127, 4096, 32000) == (32, 32, 8)
+    assert tile(8, 4096, 12288) == (16, 48, 8) and tile(9, 4096, 12288) == (32, 48, 8)
+    assert tile(9, 4096, 12288, tiled=True) == (16, 48, 8) and tile(9, 4096, 14400) == (16, 48, 8)
+    assert tile(16, 4096, 11008, swiglu=True) == (16, 16, 4) and tile(32, 4096, 11008, swiglu=True) == (32, 16, 4)
+    assert tile(4096, 4096, 96, swiglu=True) == (32, 16, 4)
+    # the matrix-core kernel's five tiles, plain and SwiGLU (half as many features of two matrices)
+    assert tile(128, 4096, 128) == (64, 64, 2) and tile(640, 11008, 4096) == (128, 128, 2)
+    assert tile(1024, 4096, 4096) == (128, 128, 2) and tile(1030, 4096, 4096) == (128, 256, 1)
+    assert tile(640, 4096, 12288) == (128, 256, 1) and tile(1000, 4096, 32768) == (256, 256, 1)
+    assert tile(1030, 4096, 4224) == (128, 128, 1) and tile(16384, 11008, 4096) == (256, 256, 1)
+    assert tile(16384, 4096, 11008, swiglu=True) == (256, 128, 1) and tile(128, 4096, 64, swiglu=True) == (64, 32, 2)
+    ML = Mo.mlib()
+    k = [ctypes.byref(ctypes.c_uint32(0)) for _ in range(3)]
+    assert ML.bctm_linear_tile(4, 72, 32, 0, 0, *k) == P.BCT_ERR_UNSUPPORTED
+    assert ML.bctm_linear_tile(0, 64, 32, 0, 0, *k) == P.BCT_ERR_INVALID_ARG
+    assert ML.bctm_linear_tile(4, 64, 32, 0, 0, k[0], None, k[2]) == P.BCT_ERR_INVALID_ARG
 
 
 def desc(**kw):

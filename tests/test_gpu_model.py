@@ -235,6 +235,25 @@ def test_linear_split_is_bitwise_the_separate_projections(M, rows, K, widths):
             assert np.array_equal(host(o), host(M.bctm_linear(x, M.bctm_pack_weight(w))))
 
 
+# Chunks, where the widths together and each width alone take other workgroup tiles: bitwise where K is summed in as many
+# parts, else both within the rounding of fp32 sums (one bf16 spacing + 2^-20 of the products' absolute sum)
+@pytest.mark.parametrize("rows,K,widths", [(128, 160, (512, 128, 128)), (640, 288, (4096, 4096, 4096)),
+                                           (640, 4096, (2048, 1024, 1024)), (1030, 96, (4096, 128))])
+def test_linear_split_of_a_chunk(M, rows, K, widths):
+    import torch
+    x, ws = draw(1, (rows, K)), [draw(20 + i, (n, K), K ** -0.5) for i, n in enumerate(widths)]
+    outs = [torch.empty((rows, n), dtype=torch.bfloat16, device="cuda") for n in widths]
+    M.bctm_linear_split(M.bctm_pack_rows(dev(x)), M.bctm_pack_weight(*[dev(w) for w in ws]), outs)
+    parts = M.bctm_linear_tile(rows, K, sum(widths))[2]
+    for o, w, n in zip(outs, ws, widths):
+        alone = M.bctm_linear(dev(x), M.bctm_pack_weight(dev(w)))
+        if M.bctm_linear_tile(rows, K, n)[2] == parts:
+            assert np.array_equal(host(o), host(alone))
+        mass = np.abs(R.bf16_to_f64(x)) @ np.abs(R.bf16_to_f64(w)).T
+        check_close(host(o), R.linear(x, w), 2.0 ** -20 * mass, f"split {rows}x{K}x{n}")
+        check_close(host(alone), R.linear(x, w), 2.0 ** -20 * mass, f"alone {rows}x{K}x{n}")
+
+
 def test_linear_in_place_residual(M):
     rows, K, N = 7, 256, 128
     x, w, res = draw(1, (rows, K)), draw(2, (N, K), K ** -0.5), draw(3, (rows, N))
