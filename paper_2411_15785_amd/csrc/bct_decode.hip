@@ -395,12 +395,14 @@ void plan_decode(DecodeParams& p, int dtype) {
 
 template <int D, int NT>
 static hipError_t launch_scores_mfma(const DecodeParams& p, hipStream_t s) {
-  if (p.rescore) {
-    const uint32_t stiles = p.M / (32 * NT), blocks = (p.B * p.R + 15) / 16;
-    uint32_t zs = (uint32_t)((2048 + (uint64_t)stiles * p.Hkv - 1) / ((uint64_t)stiles * p.Hkv));
-    if (zs > blocks) zs = blocks;
-    hipLaunchKernelGGL((stats_mfma_bf16_kernel<D, 2 * NT>), dim3(stiles, p.Hkv, zs), dim3(64), 0, s, p);
-    return hipGetLastError();
+  if constexpr (D == 128) {   // plan_mv_pass re-scores with d = 128 only
+    if (p.rescore) {
+      const uint32_t stiles = p.M / (32 * NT), blocks = (p.B * p.R + 15) / 16;
+      uint32_t zs = (uint32_t)((2048 + (uint64_t)stiles * p.Hkv - 1) / ((uint64_t)stiles * p.Hkv));
+      if (zs > blocks) zs = blocks;
+      hipLaunchKernelGGL((stats_mfma_bf16_kernel<D, 2 * NT>), dim3(stiles, p.Hkv, zs), dim3(64), 0, s, p);
+      return hipGetLastError();
+    }
   }
   const uint32_t tiles = p.M / (32 * NT);
   const uint32_t rbs = (p.B * p.R + 31) / 32;
