@@ -206,6 +206,10 @@ typedef struct bct_plan_info {
 } bct_plan_info;
 bct_status bct_plan_query(const bct_cache_desc* desc, bct_plan_info* info);
 
+/* *rescores = 1 if the MV pass (section 3.2 steps 4-5 and the read) of such a step scores its slots again instead of
+ * reading stored scores: large grids of several query heads per KV head.  Host logic only, as above. */
+bct_status bct_plan_rescores(const bct_cache_desc* desc, uint32_t* rescores);
+
 /* Device addresses of the two regions inside cache_mem, MK first, then MV (section 3.1's two
  * sequences), for zero-copy views of the state: the bounded-cache layout in HBM as the caller sees it. */
 bct_status bct_cache_regions(const bct_cache* c, void** mk_dev, size_t* mk_bytes,

@@ -542,6 +542,16 @@ bct_status bct_plan_query(const bct_cache_desc* desc, bct_plan_info* info) {
   return BCT_OK;
 }
 
+bct_status bct_plan_rescores(const bct_cache_desc* desc, uint32_t* rescores) {
+  const bct_status st = check_desc(desc);
+  if (st != BCT_OK) return st;
+  if (!rescores) return fail(BCT_ERR_INVALID_ARG, "rescores is NULL");
+  bct::DecodeParams p;
+  fill_plan(desc, p);
+  *rescores = p.fused ? 0u : p.rescore;
+  return BCT_OK;
+}
+
 bct_status bct_cache_regions(const bct_cache* c, void** mk_dev, size_t* mk_bytes, void** mv_dev, size_t* mv_bytes) {
   if (!c) return fail(BCT_ERR_INVALID_ARG, "cache handle is NULL");
   if (mk_dev) *mk_dev = c->mk;

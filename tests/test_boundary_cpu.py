@@ -243,6 +243,16 @@ def test_launch_plans_of_the_five_workloads(L):
     st, f4 = P.bct_plan_query(P.make_desc(w4.M, w4.B, w4.Hq, w4.Hkv, w4.d, P.BCT_F32, w4.scale, w4.scale))
     assert st == P.BCT_OK and f4["mv_workgroup"] == 512          # fp32 storage keeps the vector-ALU read
     assert c4["launches"] == 4
+    # scores again in the MV pass: several query heads, bf16, d = 128, shared keys, more than 16384 workgroups of 64 slots
+    def again(M, B, G, d=128, dt=P.BCT_BF16, flags=0):
+        st, v = P.bct_plan_rescores(P.make_desc(M, B, 8 * G, 8, d, dt, 0.1, 0.1, flags))
+        assert st == P.BCT_OK
+        return v
+    assert again(8192, 64, 4) == 1 and again(8192, 16, 4) == 0 and again(8192, 17, 3) == 1
+    assert again(8192, 64, 2) == 0 and again(8192, 64, 4, d=64) == 0 and again(8192, 64, 4, dt=P.BCT_F32) == 0
+    assert again(8192, 64, 4, flags=P.BCT_MK_PER_SEQUENCE) == 0
+    assert P.bct_plan_rescores(desc(capacity_M=100))[0] == P.BCT_ERR_UNSUPPORTED
+    assert L.bct_plan_rescores(ctypes.byref(desc()), None) == P.BCT_ERR_INVALID_ARG
     c5 = plan("cfg5")            # 128 partials per row, two per lane of the MV pass: no normaliser launch
     assert c5["slots_per_stat"] == 128 and c5["normaliser_launch"] == 0 and c5["launches"] == 3
     c5 = plan("cfg5")
