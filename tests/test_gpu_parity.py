@@ -172,6 +172,38 @@ def test_one_step_of_a_large_grid_with_several_query_heads(P, R, B, G, M, mode):
     test_one_step_from_common_state(P, R, f"large_grid_g{G}_m{M}", B, 8 * G, 8, 128, M, "bf16", mode, 0)
 
 
+# The same with statistics tiles of 32, 64 and 128 slots, step sizes on the write row, and scales of either sign; the oracle
+# holds the first and the last sequence
+@pytest.mark.parametrize("B,Hkv,G,M,tile,rs,ws,gated", [(2100, 8, 3, 64, 32, -0.09, 0.12, True),
+                                                        (18, 16, 4, 4096, 64, 0.0884, -0.0884, False),
+                                                        (17, 16, 8, 4096, 64, 0.0884, 0.0884, True),
+                                                        (9, 16, 4, 8192, 128, 0.0884, 0.0884, True),
+                                                        (9, 16, 3, 8192, 128, -0.05, -0.1, False)])
+def test_scores_again_with_every_statistics_tile(P, R, B, Hkv, G, M, tile, rs, ws, gated):
+    import torch
+    w = syn.Workload(f"again_g{G}_m{M}", 1, B, Hkv * G, Hkv, 128, M, "bf16", 0)
+    bs = [0, B - 1]
+    ref, gpu, mk, _, _ = make_pair(w, R.RefCache, P.BctCache, batch_subset=bs, read_scale=rs, write_scale=ws)
+    gpu.randomize_values(7, 1.0)
+    before = gpu.values_view().clone()
+    ref.set_values(to_np(before[bs], "bf16"))
+    assert P.bct_plan_rescores(gpu.desc) == (P.BCT_OK, 1) and P.bct_plan_query(gpu.desc)[1]["slots_per_stat"] == tile
+    q, wq, wv = step_np(w, 0)
+    eta = None
+    if gated:
+        eta = syn.normal(3, 9, 77, (B, Hkv)).astype(np.float32)   # of either sign
+        eta[:, ::5] = 0.0
+    o_ref = ref.decode_step(sub(q, bs), sub(wq, bs), sub(wv, bs), gate=sub(eta, bs))
+    o_gpu = gpu.decode_step(to_dev(q, "bf16"), to_dev(wq, "bf16"), to_dev(wv, "bf16"),
+                            gate=None if eta is None else torch.from_numpy(eta).cuda())
+    check_out(to_np(o_gpu, "bf16")[bs], o_ref, "bf16", w.name)
+    got = gpu.values_view()
+    check_state_one_step(to_np(got[bs], "bf16"), ref.values(), "bf16", w.name, before=to_np(before[bs], "bf16"))
+    assert np.array_equal(to_np(gpu.keys_view(), "bf16"), mk)
+    if gated:
+        assert torch.equal(got[:, ::5].view(torch.int16), before[:, ::5].view(torch.int16))   # step size zero: not moved
+
+
 @pytest.mark.parametrize("dtype,G", [("bf16", 1), ("f32", 2)])
 def test_more_memories_than_one_grid_dimension_holds(P, R, dtype, G):
     """66000 memories (batch 1100 x 60 KV heads): launches indexed by memory spill from grid.y into grid.z.
