@@ -134,9 +134,9 @@ Sizes compute_sizes(const bct_cache_desc* d, uint32_t max_T) {
   z.off_pf_norm_w = z.off_pf_norm_r = z.off_pf_wvt = z.off_pf_snap = off;
   if (max_T > 0 && d->dtype == BCT_BF16) {
     z.off_pf_norm_w = off;
-    off += align_up(units * max_T * sizeof(float2), 256);
+    off += align_up(units * max_T * sizeof(float), 256);
     z.off_pf_norm_r = off;
-    off += align_up(units * max_T * p.G * sizeof(float2), 256);
+    off += align_up(units * max_T * p.G * sizeof(float), 256);
     const size_t nb = (max_T + bct::kPrefillSubChunk - 1) / bct::kPrefillSubChunk;
     z.off_pf_wvt = off;
     off += align_up(units * d->head_dim * nb * bct::kPrefillSubChunk * sz, 256);
@@ -466,7 +466,7 @@ bct_status bct_prefill_gated(bct_cache* c, const void* q, const void* k_new, con
   pp.out = (uint16_t*)out;
   pp.gate = gate;
   pp.norm_w = (float*)(c->ws + c->off_pf_norm_w);
-  pp.norm_r = (float2*)(c->ws + c->off_pf_norm_r);
+  pp.norm_r = (float*)(c->ws + c->off_pf_norm_r);
   pp.snap = (uint16_t*)(c->ws + c->off_pf_snap);
   pp.wvt = (uint16_t*)(c->ws + c->off_pf_wvt);
   pp.B = c->plan.B;

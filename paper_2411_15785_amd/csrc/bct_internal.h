@@ -65,7 +65,7 @@ struct PrefillParams {
   const uint16_t* wv;  // [B][T][Hkv][d] or null
   uint16_t* out;       // [B][T][Hq][d] or null
   float* norm_w;       // [B*Hkv][T]   shift of each write row: max + log2(sum of exp2(score - max))
-  float2* norm_r;      // [B*Hkv][T*G] (the same, unused) of each read row, for a chunk that only reads
+  float* norm_r;       // [B*Hkv][T*G] the same of each read row, for a chunk that only reads
   uint16_t* snap;      // [ceil(T/128)][B*Hkv] MV at the start of each sub-chunk as operand tiles (M x d); a chunk that
                        // only reads: one copy of MV as [B*Hkv][d][M]
   uint16_t* wvt;       // [B*Hkv] WV as operand tiles (Tpad x d), zero beyond T

@@ -244,7 +244,7 @@ __device__ __forceinline__ void store_shift(const PrefillParams& p, uint32_t uni
     const float le = p.gate ? __log2f(fabsf(p.gate[((size_t)b * p.T + row) * p.Hkv + h])) : 0.f;
     p.norm_w[(size_t)unit * p.T + row] = m + __log2f(s) - le;
   } else if (row - nw < nr) {
-    p.norm_r[(size_t)unit * p.T * p.G + (row - nw)] = make_float2(m + __log2f(s), 0.f);
+    p.norm_r[(size_t)unit * p.T * p.G + (row - nw)] = m + __log2f(s);
   }
 }
 
@@ -572,7 +572,7 @@ __global__ __launch_bounds__(512) void prefill_read_only_kernel(const PrefillPar
   float nrm_r;
   {
     const uint32_t rho = rho0 + 32 * rj + col, t = t0 + rho / G;
-    nrm_r = t < T ? p.norm_r[(size_t)unit * T * G + (size_t)t * G + rho % G].x : kNoRow;
+    nrm_r = t < T ? p.norm_r[(size_t)unit * T * G + (size_t)t * G + rho % G] : kNoRow;
   }
   // product step: wavefront = (32 output rows, half of the value columns)
   constexpr int NOC = D / 64;                      // 32-column tiles per wavefront in the output product
