@@ -395,7 +395,8 @@ void plan_decode(DecodeParams& p, int dtype) {
 
 template <int D, int NT>
 static hipError_t launch_scores_mfma(const DecodeParams& p, hipStream_t s) {
-  if constexpr (D == 128) {   // plan_mv_pass re-scores with d = 128 only
+  // plan_mv_pass re-scores with d = 128 only, and with less keys than would make the tiles 128 slots
+  if constexpr (D == 128 && NT < 4) {
     if (p.rescore) {
       const uint32_t stiles = p.M / (32 * NT), blocks = (p.B * p.R + 15) / 16;
       uint32_t zs = (uint32_t)((2048 + (uint64_t)stiles * p.Hkv - 1) / ((uint64_t)stiles * p.Hkv));

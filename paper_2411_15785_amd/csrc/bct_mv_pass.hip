@@ -236,14 +236,24 @@ void plan_mv_pass(DecodeParams& p, int dtype) {
   // to the launch.
   const uint64_t wgs = (uint64_t)p.B * p.Hkv * p.S;
   p.fuse_norm = (p.n_tiles <= kMaxMergedTiles && (!gqa || wgs <= 16384)) ? 1u : 0u;
-  // Such a grid also scores its slots again instead of reading scores: what 1 + G fp32 scores per slot cost on their
-  // way through memory then exceeds the keys' extra trip from L2.  Whole step, us, scores through memory ->
-  // scored again (several caches in turn, so that scratch does not stay in the last-level cache): B = 64, Hkv = 8,
-  // G = 4, M = 8192 (65536 workgroups) 442 -> 418; B = 32 223 -> 212; G = 8: B = 64, M = 3072 206 -> 192, B = 36,
-  // M = 4096 (18432 workgroups) 160 -> 145; 16384 workgroups (B = 16, Hkv = 16, G = 4) 117 -> 118, 8192 80 -> 83.
+  // A large grid of that pass may score its slots again instead of reading stored scores.  For it: 1 + G fp32 scores a slot
+  // are not written and read.  Against it: every workgroup reads its 64 keys again, which is cheap from its XCD's L2 (4 MB)
+  // and dear from beyond.  Workgroup ids go to the eight XCDs in turn, split index first, so from one sequence to the
+  // next a slot range comes back to as many XCDs as 8 / gcd(S * Hkv, 8), and an XCD sees 1 / gcd of the keys.  The step with
+  // stored scores / re-scored, 150 shapes with G = 3 to 8 and up to 100000 workgroups, caches with workspaces of their
+  // own taking turns | one workspace for all (which the last-level cache keeps):
+  //   an XCD's keys up to 2.5 MB, scratch (scores + partial outputs) from 256 MB  1.06 to 1.16 | 1.02 to 1.19
+  //                               scratch 192 to 256 MB  1.05 to 1.09 | 0.98 to 1.04 (B = 64, Hkv = 8, G = 4, M = 8192:
+  //                                                      441 -> 417 us | 403 -> 406)
+  //                               scratch 100 to 192 MB  1.00 to 1.07 | 0.98 to 1.01, below 0.98 to 1.06 | 0.98 to 1.00
+  //   3 MB 0.98 to 1.02 | 0.88 to 0.99, more 0.82 to 0.99 | 0.80 to 0.99 (B = 62, Hkv = 15, G = 3, M = 4032, all keys
+  //   on every XCD: 360 -> 445 us in one workspace)
   // With one query head per KV head (2 scores per slot) it loses at every size: 345 -> 378 us for the pass at
   // B = 32, H = 32, M = 4096.
-  p.rescore = gqa && wgs > 16384 ? 1u : 0u;
+  const uint64_t scratch = wgs * (256u * (1 + p.G) + (p.S > 1 ? 512u * p.G : 0u));   // 64 slots a workgroup
+  const uint64_t cycle = (uint64_t)p.S * p.Hkv, xcd_keys = (uint64_t)p.Hkv * p.M * 256u /
+                                                           (cycle % 8 == 0 ? 8 : cycle % 4 == 0 ? 4 : cycle % 2 == 0 ? 2 : 1);
+  p.rescore = gqa && scratch >= (192u << 20) && xcd_keys <= (5u << 19) ? 1u : 0u;
 }
 
 template <typename DT, int D, int GT, int BS, int U, bool NORM>

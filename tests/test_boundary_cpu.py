@@ -243,12 +243,17 @@ def test_launch_plans_of_the_five_workloads(L):
     st, f4 = P.bct_plan_query(P.make_desc(w4.M, w4.B, w4.Hq, w4.Hkv, w4.d, P.BCT_F32, w4.scale, w4.scale))
     assert st == P.BCT_OK and f4["mv_workgroup"] == 512          # fp32 storage keeps the vector-ALU read
     assert c4["launches"] == 4
-    # scores again in the MV pass: several query heads, bf16, d = 128, shared keys, more than 16384 workgroups of 64 slots
-    def again(M, B, G, d=128, dt=P.BCT_BF16, flags=0):
-        st, v = P.bct_plan_rescores(P.make_desc(M, B, 8 * G, 8, d, dt, 0.1, 0.1, flags))
+    # scores again in the MV pass: several query heads, bf16, d = 128, shared keys, 192 MB of scores and partial outputs
+    # (per workgroup of 64 slots 256 (1 + G) + 512 G bytes), 2.5 MB of keys on an XCD (1 / gcd(splits x heads, 8) of them)
+    def again(M, B, G, d=128, dt=P.BCT_BF16, flags=0, H=8):
+        st, v = P.bct_plan_rescores(P.make_desc(M, B, H * G, H, d, dt, 0.1, 0.1, flags))
         assert st == P.BCT_OK
         return v
-    assert again(8192, 64, 4) == 1 and again(8192, 16, 4) == 0 and again(8192, 17, 3) == 1
+    assert again(8192, 64, 4) == 1 and again(8192, 60, 4) == 1 and again(8192, 59, 4) == 0 and again(8192, 16, 4) == 0
+    assert again(64, 10922, 8) == 0 and again(64, 10923, 8) == 1                 # no partial outputs: one split
+    assert again(10240, 64, 8) == 1 and again(10304, 64, 8) == 0                 # 2.5 MB of keys on an XCD
+    assert again(8192, 64, 8, H=7) == 1 and again(8128, 64, 8, H=7) == 0         # 1/8 of the keys; all of them
+    assert again(4992, 101, 8, H=7) == 0 and again(4992, 101, 8, H=4) == 1        # half of 9 MB; 1/8 of 5 MB
     assert again(8192, 64, 2) == 0 and again(8192, 64, 4, d=64) == 0 and again(8192, 64, 4, dt=P.BCT_F32) == 0
     assert again(8192, 64, 4, flags=P.BCT_MK_PER_SEQUENCE) == 0
     assert P.bct_plan_rescores(desc(capacity_M=100))[0] == P.BCT_ERR_UNSUPPORTED

@@ -165,20 +165,21 @@ def test_one_step_from_common_state(P, R, name, B, Hq, Hkv, d, M, dtype, mode, f
         assert st == t + 1
 
 
-# Several query heads per KV head over more than 16384 workgroups of 64 slots: the MV pass scores its slots again.
+# Several query heads per KV head over more than 16384 workgroups of 64 slots: the normaliser is a launch of its own.
 @pytest.mark.parametrize("B,G,M,mode", [(2100, 3, 64, "rw"), (2100, 3, 64, "read_only"), (2100, 4, 64, "write_only"),
                                         (420, 8, 320, "rw")])
 def test_one_step_of_a_large_grid_with_several_query_heads(P, R, B, G, M, mode):
     test_one_step_from_common_state(P, R, f"large_grid_g{G}_m{M}", B, 8 * G, 8, 128, M, "bf16", mode, 0)
 
 
-# The same with statistics tiles of 32, 64 and 128 slots, step sizes on the write row, and scales of either sign; the oracle
-# holds the first and the last sequence
-@pytest.mark.parametrize("B,Hkv,G,M,tile,rs,ws,gated", [(2100, 8, 3, 64, 32, -0.09, 0.12, True),
-                                                        (18, 16, 4, 4096, 64, 0.0884, -0.0884, False),
-                                                        (17, 16, 8, 4096, 64, 0.0884, 0.0884, True),
-                                                        (9, 16, 4, 8192, 128, 0.0884, 0.0884, True),
-                                                        (9, 16, 3, 8192, 128, -0.05, -0.1, False)])
+# Grids large enough for the MV pass to score its slots again, with either statistics tile, one split and several, step
+# sizes on the write row, and scales of either sign; the oracle holds the first and the last sequence
+@pytest.mark.parametrize("B,Hkv,G,M,tile,rs,ws,gated", [(2000, 8, 8, 128, 32, -0.09, 0.12, True),
+                                                        (1000, 3, 4, 1344, 32, 0.0884, 0.0884, False),
+                                                        (61, 16, 4, 4096, 64, 0.0884, -0.0884, False),
+                                                        (31, 16, 8, 4096, 64, 0.0884, 0.0884, True),
+                                                        (80, 8, 3, 8192, 64, -0.05, -0.1, True),
+                                                        (10923, 8, 8, 64, 32, 0.0884, 0.0884, False)])
 def test_scores_again_with_every_statistics_tile(P, R, B, Hkv, G, M, tile, rs, ws, gated):
     import torch
     w = syn.Workload(f"again_g{G}_m{M}", 1, B, Hkv * G, Hkv, 128, M, "bf16", 0)
