@@ -1155,7 +1155,11 @@ hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
   // d = 128, 1890 workgroups: M = 320 46 | 68, 1280 143 | 154, 2048 199 | 196, 3072 285 | 266; 512 workgroups: 640 22 | 26,
   // 1280 37 | 37, 2048 57 | 53; 256: 640 14.4 | 13.7, 2048 37 | 26; 24: 128 6.4 | 7.8, 384 9.3 | 9.9.  d = 64, 1890: 320
   // 31 | 46, 1280 81 | 93, 3072 178 | 187; 256: 640 9.1 | 9.6, 2048 22 | 19.
-  const bool brief = p.stats_split == 1 && (p.M <= 384 || (wgs > 256 && p.M <= (d128 ? 1280u : 3072u)));
+  // One round of workgroups, whole read-only chunk: d = 64, 32 workgroups: 512 19.6 | 20.2, 768 25.1 | 25.3, 896 27.7 | 26.7;
+  // 255: 512 28.6 | 29.6, 768 33.4 | 34.6, 896 36.8 | 36.6; d = 128, 32: 384 23.8 | 24.2, 448 26.7 | 26.8, 576 31.9 | 31.3; 255:
+  // 320 32.9 | 33.0, 384 35.3 | 35.0, 448 39.2 | 38.5.
+  const bool brief =
+      p.stats_split == 1 && (p.M <= (d128 ? 384u : 768u) || (wgs > 256 && p.M <= (d128 ? 1280u : 3072u)));
   if (brief && d128) hipLaunchKernelGGL(prefill_stats_short_kernel<128>, gs, dim3(512), 0, s, p);
   else if (brief) hipLaunchKernelGGL(prefill_stats_short_kernel<64>, gs, dim3(512), 0, s, p);
   else if (d128) hipLaunchKernelGGL(prefill_stats_kernel<128>, gs, dim3(512), 0, s, p);

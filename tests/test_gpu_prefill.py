@@ -143,10 +143,11 @@ def test_prefill_tile_edges(P, R, B, Hq, Hkv, d, M, T, mode):
     test_prefill_chunk_matches_oracle(P, R, f"edge_m{M}_t{T}", B, Hq, Hkv, d, M, "bf16", T, mode)
 
 
-# Either statistics kernel at the border between them: 384 slots and the next size (one share each), up to 256 workgroups
-# and more
+# Either statistics kernel at the border between them: 384 slots (d = 64: 768) and the next size (one share each), up to 256
+# workgroups and more
 @pytest.mark.parametrize("B,Hq,Hkv,d,M,T", [(1, 2, 1, 128, 384, 140), (1, 2, 1, 128, 448, 140), (1, 1, 1, 64, 448, 70),
-                                            (13, 20, 20, 64, 448, 3), (13, 20, 20, 128, 448, 3)])
+                                            (13, 20, 20, 64, 448, 3), (13, 20, 20, 128, 448, 3), (1, 2, 1, 64, 768, 140),
+                                            (1, 2, 1, 64, 832, 140), (13, 20, 20, 64, 832, 3)])
 @pytest.mark.parametrize("mode", ["rw", "read_only"])
 def test_prefill_statistics_kernels(P, R, B, Hq, Hkv, d, M, T, mode):
     test_prefill_chunk_matches_oracle(P, R, f"stats_m{M}_b{B}", B, Hq, Hkv, d, M, "bf16", T, mode)
