@@ -181,7 +181,9 @@ __global__ __launch_bounds__(64 * WAVES) void linear_kernel(const uint16_t* __re
 // The row of a workgroup.  Workgroups go to the eight XCDs in turn; a 128-byte line of the tiled order holds 8 inputs
 // of 8 consecutive rows, and rows in launch order would leave parts of every line in eight L2s.  So 16 consecutive
 // rows (1 KB tiles) are those of one XCD, for as many whole groups of 128 rows as there are.  16384 rows x 4096:
-// 80 us against 139 (8 rows per workgroup: 110), 2048 rows 10.3 against 16.3; bound by memory (268 MB).
+// 80 us against 139 (8 rows per workgroup: 110), 2048 rows 10.3 against 16.3.  That is 3.4 TB/s, not the rate of memory: the
+// same 268 MB take pack_rows_kernel 52 us.  A workgroup here holds one row of 8 KB and waits twice, for the row and
+// for the sum.
 __device__ __forceinline__ uint32_t tiled_row(uint32_t block, uint32_t rows) {
   if (block >= rows / 128 * 128) return block;
   return (block / 128 * 8 + block % 8) * 16 + block / 8 % 16;

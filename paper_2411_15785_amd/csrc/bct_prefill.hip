@@ -653,8 +653,11 @@ __global__ __launch_bounds__(512) void prefill_read_only_kernel(const PrefillPar
 // needs another wavefront.  The writers are one tile ahead; one barrier per tile.  Keys and MV_c come through LDS,
 // requested two tiles ahead without a trip through registers.
 // What bounds it: 64 matrix instructions per SIMD and tile (2048 cycles) beside about as many cycles of vector work
-// for 64 exponentials per lane, at the clock that the chip's power limit leaves (1.67 GHz at B = 32, H = 32, M = 4096,
-// T = 512: 2230 us; tiles staged through registers, all eight wavefronts scoring, 2650).  Forms that overlap more
+// for 64 exponentials per lane, at 1.67 GHz under load (B = 32, H = 32, M = 4096, T = 512: 2230 us; tiles staged through
+// registers, all eight wavefronts scoring, 2650), the matrix pipe busy half of the cycles.  And a stall: at d = 128 a reader
+// needs four registers more than its 256, the compiler keeps one query operand in scratch and reloads it in one of
+// the three tiles that the loop is unrolled by, and the wait for it is for everything in flight - the keys and values
+// that the tile has just requested two tiles ahead - while the barrier holds the other wavefronts.  (d = 64 fits.)  Forms that overlap more
 // (products between the exponentials, the next tile's scores as well) took 2290 and 2400; with
 // v_mfma_f32_16x16x32_bf16, which hides less vector work, 2430.  A launch of one round (216 workgroups, 33 tiles):
 // 67 us against 82.
@@ -930,9 +933,10 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
 // wavefront's slots stay in registers.
 // With reads the kernel is partly bound by memory (MV in and out and a copy of MV per sub-chunk: 6.4 GB of the 8.4 a
 // chunk moves at B = 32, H = 32, M = 4096, T = 512), without by its matrix and vector work.  A token tile of 32 keeps
-// a workgroup within 168 registers and 36 KB, so that three of them (three wavefronts per SIMD) hide each
+// a workgroup within 168 registers and 34 KB, so that three of them (three wavefronts per SIMD) hide each
 // other's barriers and stores; two: 2250 us against 1950 at that size, four (registers spilled): 2680.  Row-major
-// token tiles of 64 with padded rows, where a third of the LDS cycles were bank conflicts, took 2170.
+// token tiles of 64 with padded rows, where a third of the LDS cycles were bank conflicts, took 2170.  The wait that ends a
+// tile is for all requests; in every fourth tile that includes the snapshot's stores, issued after them.
 // FAR: a token tile's write queries lie further apart than a lane's 32-bit byte offset reaches (see
 // launch_prefill_bf16), so their addresses are 64-bit.  Not for every chunk: 64-bit addresses spill 62 registers of
 // the d = 128 kernel, the 32-bit offsets none.
@@ -1132,7 +1136,7 @@ hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
     return hipGetLastError();
   };
   if (p.has_write && (e = transpose(0)) != hipSuccess) return e;
-  // with a write, the state kernel leaves MV_0 transposed as the first snapshot on its way through
+  // with a write, the state kernel leaves MV_0 as the first snapshot on its way through
   if (p.has_read && !p.has_write && (e = transpose(1)) != hipSuccess) return e;
 
   // Few rows of few memories leave compute units without a statistics workgroup (one fits each): split the keys, at
@@ -1194,9 +1198,9 @@ hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
     else hipLaunchKernelGGL((prefill_state_kernel<64, false>), g, dim3(256), 0, s, p);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  // every sub-chunk reads its starting state from the transposed copies in the workspace (with a write:
-  // copy c is what the state kernel left when it reached sub-chunk c, MV_0 for c = 0; without a write:
-  // the one copy of MV made above serves all of them), so one launch serves all sub-chunks
+  // every sub-chunk reads its starting state from a copy of MV in the workspace (with a write: copy c, in operand
+  // tiles, is what the state kernel left when it reached sub-chunk c, MV_0 for c = 0; without a write: the one
+  // transposed copy made above serves all of them), so one launch serves all sub-chunks
   if (p.has_read && (e = read(0, nb)) != hipSuccess) return e;
   return hipSuccess;
 }
