@@ -653,7 +653,7 @@ __global__ __launch_bounds__(512) void prefill_read_only_kernel(const PrefillPar
 // needs another wavefront.  The writers are one tile ahead; one barrier per tile.  Keys and MV_c come through LDS,
 // requested two tiles ahead without a trip through registers.
 // What bounds it: 64 matrix instructions per SIMD and tile (2048 cycles) beside about as many cycles of vector work
-// for 64 exponentials per lane, at 1.67 GHz under load (B = 32, H = 32, M = 4096, T = 512: 2230 us; tiles staged through
+// for 64 exponentials per lane, at 1.7-1.8 GHz under load (B = 32, H = 32, M = 4096, T = 512: 2230 us; tiles staged through
 // registers, all eight wavefronts scoring, 2650), the matrix pipe busy half of the cycles.  And a stall: at d = 128 a reader
 // needs four registers more than its 256, the compiler keeps one query operand in scratch and reloads it in one of
 // the three tiles that the loop is unrolled by, and the wait for it is for everything in flight - the keys and values
