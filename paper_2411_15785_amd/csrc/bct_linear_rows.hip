@@ -34,14 +34,16 @@ namespace {
 
 // KS groups of WR x WC wavefronts; a wavefront owns 16 * MI token rows x 16 * NJ B-tile columns (SwiGLU: gate and
 // up tiles alternate, so half as many output features); group g sums the K steps [KT * g / KS, ...).
-template <bool SWIGLU, bool XT, int MI, int NJ, int WR, int WC, int KS>
+// PAIR (row-major activations): the two K steps of a line are requested together, see request_rows.
+template <bool SWIGLU, bool XT, bool PAIR, int MI, int NJ, int WR, int WC, int KS>
 __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
     const uint16_t* __restrict__ x, const u32x4* __restrict__ w, const u32x4* __restrict__ w2, const uint16_t* residual,
     LinearOut dst, uint32_t rows, uint32_t K, uint32_t NT, uint32_t out_tiled) {
   constexpr int NW = WR * WC;                      // wavefronts of a group
   constexpr int TA = MI * WR, TB = NJ * WC, TT = TA + TB;  // 1 KB tiles of a K step: activations, weights
-  constexpr int ND = TT / NW;                      // of them per wavefront
-  static_assert(TT % NW == 0, "tiles must divide among the wavefronts");
+  constexpr int ND = TT / NW, NA = TA / NW, NB = TB / NW;  // of them per wavefront
+  static_assert(TA % NW == 0 && TB % NW == 0, "tiles must divide among the wavefronts");
+  static_assert(!PAIR || !XT, "tiled activations have no half lines");
   constexpr int S = 4;                             // LDS stages
   constexpr bool PING = NW * KS == 8;              // two wavefronts per SIMD that take turns
   constexpr uint32_t HB = 4;                       // row tiles of a band
@@ -113,14 +115,29 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
   // one index into the stage each: the compiler loses track of which array an access belongs to when the
   // address is a long chain
   const int put0 = (grp * TT + wave) * 64, geta = (grp * TT + MI * wr) * 64 + lane, getb = (grp * TT + TA + NJ * wc) * 64 + lane;
-  auto request = [&](auto c, uint32_t kt) {
+  auto at = [&](uint32_t kt) { return min(kfirst + kt, KT - 1); };   // past the end: the last step again, never multiplied
+  auto request = [&](auto c, uint32_t kt, auto first, auto last) {   // loads first .. last - 1 of step kt
     u32x4* s = stage(c);
-    const uint32_t k = min(kfirst + kt, KT - 1);   // past the end: the last step again, never multiplied
+    const uint32_t k = at(kt);
 #pragma unroll
-    for (int j = 0; j < ND; ++j) load_to_lds(src[j] + (size_t)k * step[j], s + put0 + NW * 64 * j);
+    for (int j = decltype(first)::v; j < decltype(last)::v; ++j) load_to_lds(src[j] + (size_t)k * step[j], s + put0 + NW * 64 * j);
   };
-  // K step kt from stage c; requests step kt + S - 1 into the stage whose reads all wavefronts have finished
-  // (they waited for them before the barrier that ended their step kt - 1)
+  // PAIR: a row's 64 bytes of a K step are half a line; the two steps of a line are requested together, before its other
+  // half is evicted.
+  auto request_rows = [&](auto c, uint32_t kt) {
+    u32x4 *s0 = stage(c), *s1 = stage(Int<decltype(c)::v + 1>{});
+    const uint32_t k0 = at(kt), k1 = at(kt + 1);
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
+      load_to_lds(src[j] + (size_t)k0 * step[j], s0 + put0 + NW * 64 * j);
+      load_to_lds(src[j] + (size_t)k1 * step[j], s1 + put0 + NW * 64 * j);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // before the weights that are requested next: the waits count on it
+  };
+  // K step kt from stage c; requests step kt + S - 1 (PAIR: of the activations, in even steps, kt + 2 and kt + 3) into
+  // stages whose reads all wavefronts have finished (they waited for them before the barrier that ended their step
+  // kt - 1).  Left in flight at the end: what steps kt + 2 and kt + 3 need (PAIR: after an odd step only their weights,
+  // as the activations of kt + 1 came with those of kt + 2).
   auto k_step = [&](auto c, uint32_t kt, auto last) {
     u32x4* s = stage(c);
     bf16x8 a[MI], b[NJ];
@@ -128,10 +145,13 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
     for (int i = 0; i < NJ; ++i) b[i] = __builtin_bit_cast(bf16x8, s[getb + 64 * i]);
 #pragma unroll
     for (int i = 0; i < MI; ++i) a[i] = __builtin_bit_cast(bf16x8, s[geta + 64 * i]);
-    request(Int<decltype(c)::v + S - 1>{}, kt + S - 1);
+    constexpr bool even = decltype(c)::v % 2 == 0;   // of kt as well
+    constexpr int left = (S - 2) * (PAIR && !even ? NB : ND);
+    if constexpr (PAIR && even) request_rows(Int<decltype(c)::v + 2>{}, kt + 2);
+    request(Int<decltype(c)::v + S - 1>{}, kt + S - 1, Int<PAIR ? NA : 0>{}, Int<ND>{});
     if constexpr (PING) {
       __builtin_amdgcn_s_waitcnt(kWaitLds);
-      __builtin_amdgcn_s_waitcnt(wait_vm((S - 2) * ND));
+      __builtin_amdgcn_s_waitcnt(wait_vm(left));
       bare_barrier();
     }
     auto products = [&] {
@@ -147,20 +167,21 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
     if constexpr (!PING) {
       // the operands have been read: a wavefront's products wait for them and come before the barrier
       __builtin_amdgcn_s_waitcnt(kWaitLds);
-      __builtin_amdgcn_s_waitcnt(wait_vm((S - 2) * ND));
+      __builtin_amdgcn_s_waitcnt(wait_vm(left));
     }
     bare_barrier();
   };
 
   // The wait counts requests from the last one back, here and in the loop, so the stages' order has to stand: nothing
   // is moved across the scheduling barriers (in the loop, bare_barrier has them).
-  request(Int<0>{}, 0);
+  if constexpr (PAIR) request_rows(Int<0>{}, 0);
+  request(Int<0>{}, 0, Int<PAIR ? NA : 0>{}, Int<ND>{});
   __builtin_amdgcn_sched_barrier(0);
-  request(Int<1>{}, 1);
+  request(Int<1>{}, 1, Int<PAIR ? NA : 0>{}, Int<ND>{});
   __builtin_amdgcn_sched_barrier(0);
-  request(Int<2>{}, 2);
+  request(Int<2>{}, 2, Int<PAIR ? NA : 0>{}, Int<ND>{});
   __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(wait_vm((S - 2) * ND));
+  __builtin_amdgcn_s_waitcnt(wait_vm((S - 2) * (PAIR ? NB : ND)));
   bare_barrier();
   const bool second = PING && wv >= 4;   // the wavefront of a SIMD that is half a step behind
   if (second) bare_barrier();
@@ -306,11 +327,11 @@ RowsShape rows_shape(uint32_t rows, uint32_t bcols) {
   return best;
 }
 
-template <bool SWIGLU, bool XT, int MI, int NJ, int WR, int WC, int KS>
+template <bool SWIGLU, bool XT, int MI, int NJ, int WR, int WC, int KS, bool PAIR = false>
 void launch_shape(const void* x, const void* w, const void* w2, const void* residual, const LinearOut& dst, uint32_t rows,
                   uint32_t K, uint32_t bcols, bool out_tiled, hipStream_t s) {
   const uint32_t NT = bcols / (16 * NJ * WC), RT = (rows + 16 * MI * WR - 1) / (16 * MI * WR);
-  hipLaunchKernelGGL((linear_rows_kernel<SWIGLU, XT, MI, NJ, WR, WC, KS>), dim3(8 * ((RT * NT + 7) / 8)),
+  hipLaunchKernelGGL((linear_rows_kernel<SWIGLU, XT, PAIR, MI, NJ, WR, WC, KS>), dim3(8 * ((RT * NT + 7) / 8)),
                      dim3(64 * WR * WC * KS), 0, s, (const uint16_t*)x, (const u32x4*)w, (const u32x4*)w2,
                      (const uint16_t*)residual, dst, rows, K, NT, out_tiled ? 1u : 0u);
 }
@@ -319,7 +340,18 @@ template <bool SWIGLU, bool XT>
 void launch_rows(const void* x, const void* w, const void* w2, const void* residual, const LinearOut& dst, uint32_t rows,
                  uint32_t K, uint32_t N, bool out_tiled, hipStream_t s) {
   const uint32_t bcols = SWIGLU ? 2 * N : N;
-  switch (rows_shape(rows, bcols)) {
+  const RowsShape shape = rows_shape(rows, bcols);
+  if constexpr (!SWIGLU && !XT) {
+    // Row-major activations under 128 x 128 tiles (feature counts that 256 does not divide), many of them, and weights
+    // that the last-level cache does not keep: in pairs.  us, in pairs | step by step, 70 shapes: 2894 rows, 10400 -> 11904
+    // 872 | 972; 7647, 9120 -> 13184 2217 | 2411; 1172, 9792 -> 23936 794 | 839; 3463, 4416 -> 27520 1109 | 1205; 781, 5440 ->
+    // 22912 300 | 298.  Fewer weights: 2236, 4288 -> 17280 415 | 390; K below 4000 up to 13 % slower.  Fewer
+    // tiles (the activations of odd steps come later): 677, 10688 -> 11392 328 | 301.
+    const uint64_t tiles = (uint64_t)((rows + 127) / 128) * (N / 128);
+    if (shape == kTile128 && (uint64_t)K * N >= (100u << 20) && tiles >= 850)
+      return launch_shape<false, false, 4, 4, 2, 2, 1, true>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
+  }
+  switch (shape) {
     case kTile256: return launch_shape<SWIGLU, XT, 8, 4, 2, 4, 1>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
     case kTile128x256: return launch_shape<SWIGLU, XT, 4, 4, 2, 4, 1>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
     case kTile128: return launch_shape<SWIGLU, XT, 4, 4, 2, 2, 1>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);

@@ -235,6 +235,27 @@ def test_linear_split_is_bitwise_the_separate_projections(M, rows, K, widths):
             assert np.array_equal(host(o), host(M.bctm_linear(x, M.bctm_pack_weight(w))))
 
 
+# Row-major activations whose K steps are requested in pairs (wide weights of an odd multiple of 128 features, many tiles), with
+# every remainder of the four stages and ragged last rows: the bits of the tiled activations' kernel, and the oracle's values
+# for the first and last features
+@pytest.mark.parametrize("rows,K", [(512, 3200), (400, 3232), (513, 3264), (511, 3296)])
+def test_linear_rows_in_pairs(M, rows, K):
+    import torch
+    N = 32896
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    x = torch.randn((rows, K), generator=g, dtype=torch.bfloat16, device="cuda")
+    w = torch.randn((N, K), generator=g, dtype=torch.bfloat16, device="cuda").mul_(K ** -0.5)
+    assert M.bctm_linear_tile(rows, K, N) == (128, 128, 1)
+    wp = M.bctm_pack_weight(w)
+    out = M.bctm_linear(x, wp)
+    assert torch.equal(out.view(torch.int16), M.bctm_linear(M.bctm_pack_rows(x), wp).view(torch.int16))
+    for part in (slice(0, 160), slice(N - 160, N)):
+        xh, wh = host(x), host(w[part].contiguous())
+        mass = np.abs(R.bf16_to_f64(xh)) @ np.abs(R.bf16_to_f64(wh)).T
+        check_close(host(out[:, part].contiguous()), R.linear(xh, wh), 2.0 ** -20 * mass, f"pairs {rows}x{K}")
+
+
 # Chunks, where the widths together and each width alone take other workgroup tiles: bitwise where K is summed in as many
 # parts, else both within the rounding of fp32 sums (one bf16 spacing + 2^-20 of the products' absolute sum)
 @pytest.mark.parametrize("rows,K,widths", [(128, 160, (512, 128, 128)), (640, 288, (4096, 4096, 4096)),
