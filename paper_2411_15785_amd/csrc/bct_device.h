@@ -97,12 +97,23 @@ __device__ __forceinline__ void load_to_lds(const void* g, void* lds) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
                                    (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
 }
-// The same address, opaque to the compiler: with it as the scalar base of a lane's 32-bit offset a request needs one
-// vector register for its address, where the compiler would keep a 64-bit address per lane and request.
-__device__ __forceinline__ const char* scalar_base(const void* p) {
-  const char* q = (const char*)p;
-  asm("" : "+s"(q));
-  return q;
+// BYTES (16 or 4) per lane to LDS at lds + BYTES * lane, lds the same in every lane: from base, the same in every lane, +
+// offset bytes; or from an address per lane.  Written out because the compiler takes its own instruction for an access to
+// LDS in flight and answers it with a wait for all LDS reads before the next use of one, and adds the offset to a 64-bit
+// address in vector registers.  It counts as an outstanding vector-memory operation, which the compiler does not know:
+// whoever requests waits for it (wait_vm); the compiler's own waits only become stricter by it.
+template <int BYTES = 16>
+__device__ __forceinline__ void lds_request(const void* base, uint32_t offset, void* lds) {
+  static_assert(BYTES == 16 || BYTES == 4, "one of two instructions");
+  const uint32_t to = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+  if constexpr (BYTES == 4)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(offset), "s"(base), "s"(to) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(to) : "memory", "m0");
+}
+__device__ __forceinline__ void lds_request(const void* lane_address, void* lds) {
+  const uint32_t to = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(lane_address), "s"(to) : "memory", "m0");
 }
 // A barrier that waits for nothing else: requests into LDS stay in flight across it.
 __device__ __forceinline__ void bare_barrier() {

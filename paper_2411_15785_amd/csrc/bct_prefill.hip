@@ -21,7 +21,7 @@
 // (C[i][j] += sum_k A[i][k] B[j][k]); the accumulator of lane l holds column j = l % 32 and rows
 // i = 8*(v/4) + 4*(l/32) + v%4.  Operands that are contracted the other way than they lie in memory (MV over slots, WV
 // over tokens) are kept in the workspace as operand tiles (below), in the order in which a lane's accumulator
-// registers become the next product's operand.  Tiles come to LDS by load_to_lds, one or two tiles ahead,
+// registers become the next product's operand.  Tiles come to LDS by lds_request, one or two tiles ahead,
 // and LDS reads are issued a region ahead of the products that use them.
 //
 // Precision: scores in fp32 from exact bf16 products; softmax weights are
@@ -131,15 +131,11 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& a, int j) {
                                             pack_bf16x2(a[8 * j + 4], a[8 * j + 5]), pack_bf16x2(a[8 * j + 6], a[8 * j + 7])});
 }
 
-// Rows contracted along their own elements (keys, write queries) come to LDS as operand tiles of 32 rows x 16
-// elements: load instruction ks of 32 rows brings, per lane, the 16 bytes that the lane then reads as its operand
-// (row l % 32, elements 16 ks + 8 (l / 32) ..), at 1 KB * ks + 16 l, so that every LDS read is linear and its address
-// a constant away from the lane's.  Byte offset of a lane in the rows, from element 16 ks of the first one; rows are
-// `stride` elements apart:
-__device__ __forceinline__ uint32_t row_operand(uint32_t lane, uint32_t stride) {
-  return ((lane % 32) * stride + (lane / 32) * 8) * 2;
-}
-// ... and a tile that comes and goes in whole rows: the 16-byte chunk c of row r at position c ^ swizzle(r) of the row
+// Rows contracted along their own elements (keys, write queries), and MV on its way in and out, lie in LDS row after
+// row, the 16-byte chunk c of row r at position c ^ swizzle(r) of the row.  So a load instruction brings whole rows (4 of
+// 256 bytes): neighbouring lanes ask for neighbouring chunks.  The address unit takes four such lanes a cycle, 64 bytes;
+// of lanes that ask in the order of an operand, each for another row, one: a 64-slot tile of keys took 1024 cycles of it, a
+// third of what the read kernel needs for the tile, and 256 in whole rows.
 template <int D>
 __device__ __forceinline__ int swizzle(int r) {
   return D == 128 ? r % 16 : (r / 2) % 8;
@@ -154,6 +150,19 @@ struct RowTile {
   // load instruction n of a tile: this lane's row and chunk
   static __device__ __forceinline__ int row(int n, int lane) { return n * RPL + lane / CPR; }
   static __device__ __forceinline__ int chunk(int n, int lane) { return (lane % CPR) ^ swizzle<D>(row(n, lane)); }
+  // byte offset of that chunk from the instruction's first row, rows in memory one after another
+  static __device__ __forceinline__ uint32_t source(int n, int lane) { return (uint32_t)((lane / CPR) * D * 2 + chunk(n, lane) * 16); }
+  // this lane's operand ks (row lane % 32 of 32, elements 16 ks + 8 (lane / 32) ..) of 32 rows at `rows`: 16 lanes
+  // read 16 different chunk columns, no two in one bank.  at: operand_at(lane).  The exclusive or is opaque: the compiler
+  // would keep its D / 16 results in registers.
+  static __device__ __forceinline__ uint32_t operand_at(int lane) {
+    return (uint32_t)((lane % 32) * D * 2 + ((lane / 32) ^ swizzle<D>(lane % 32)) * 16);
+  }
+  static __device__ __forceinline__ bf16x8 operand(const uint16_t* rows, int ks, uint32_t at) {
+    uint32_t a = at;
+    if (ks) asm volatile("v_xor_b32 %0, %1, %2" : "=v"(a) : "n"(32 * ks), "v"(at));
+    return *(const bf16x8*)((const char*)rows + a);
+  }
 };
 
 // max over the two lanes l, l ^ 32 (v_permlane32_swap: no LDS crossbar)
@@ -250,6 +259,7 @@ __device__ __forceinline__ void store_shift(const PrefillParams& p, uint32_t uni
 
 template <int D>
 __global__ __launch_bounds__(512, 2) void prefill_stats_kernel(const PrefillParams p) {
+  typedef RowTile<D> RT;
   constexpr int KS = D / 16;
   constexpr int kTile = 128 * D;           // elements of a key tile
   constexpr int NL = kTile / 512 / 8;      // its load instructions per wavefront
@@ -281,9 +291,9 @@ __global__ __launch_bounds__(512, 2) void prefill_stats_kernel(const PrefillPara
     const uint32_t m0 = (tile0 + min(t, n - 1)) * 128;
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
-      const int ld = wave * NL + j;
-      const uint32_t slot = min(m0 + 32 * (ld / KS), p.M - 32);
-      load_to_lds(scalar_base(mk + (size_t)slot * D + (ld % KS) * 16) + row_operand(lane, D), stage(i) + ld * 512);
+      const int ld = wave * NL + j, row = ld * RT::RPL;
+      const uint32_t slot = min(m0 + row / 32 * 32, p.M - 32) + row % 32;
+      lds_request(mk + (size_t)slot * D, RT::source(ld, lane), stage(i) + ld * 512);
     }
   };
   // The query rows come the same way, once per workgroup, through the stage that the keys need last (the wavefronts'
@@ -294,10 +304,10 @@ __global__ __launch_bounds__(512, 2) void prefill_stats_kernel(const PrefillPara
 #pragma unroll
   for (int j = 0; j < NL; ++j) {
     const int ld = wave * NL + j;
-    const uint32_t row = min(row0 + 32 * (ld / KS) + (uint32_t)col, nrows - 1), rr = row - nw;
+    const uint32_t row = min(row0 + (uint32_t)RT::row(ld, lane), nrows - 1), rr = row - nw;
     const uint16_t* src = row < nw ? p.wq + (((size_t)b * p.T + row) * p.Hkv + h) * D
                                    : p.q + (((size_t)b * p.T + rr / p.G) * p.Hq + h * p.G + rr % p.G) * D;
-    load_to_lds(src + (ld % KS) * 16 + half * 8, sK2 + ld * 512);
+    lds_request(src + RT::chunk(ld, lane) * 8, sK2 + ld * 512);
   }
   // the waits count requests from the last one back: rows, first keys, second keys stay in this order
   region();
@@ -309,6 +319,7 @@ __global__ __launch_bounds__(512, 2) void prefill_stats_kernel(const PrefillPara
   bare_barrier();
   // A negative scale is moved into the row itself (negating bf16 is exact), so that below the
   // largest raw score is also the largest scaled one and the scaling can ride in the exponent's fma.
+  const uint32_t at = RT::operand_at(lane);
   float scale[2], m[2], s[2];
   bf16x8 xb[2][KS];
 #pragma unroll
@@ -320,7 +331,7 @@ __global__ __launch_bounds__(512, 2) void prefill_stats_kernel(const PrefillPara
     scale[jt] = fabsf(scale[jt]);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      xb[jt][ks] = __builtin_bit_cast(bf16x8, *(const u32x4*)(sK2 + lane * 8 + ((2 * rh + jt) * KS + ks) * 512) ^
+      xb[jt][ks] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, RT::operand(sK2 + (2 * rh + jt) * 32 * D, ks, at)) ^
                                                   (u32x4){flip, flip, flip, flip});
   }
   __builtin_amdgcn_s_waitcnt(kWaitLds);
@@ -330,10 +341,9 @@ __global__ __launch_bounds__(512, 2) void prefill_stats_kernel(const PrefillPara
   auto tile = [&](auto i, auto par, auto old, uint32_t t) {
     constexpr int P = decltype(par)::v;
     request(Int<decltype(i)::v + 2>{}, t + 2);
-    const bf16x8* k = (const bf16x8*)(stage(i) + sg * KS * 512) + lane;
     bf16x8 f[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) f[ks] = k[ks * 64];
+    for (int ks = 0; ks < KS; ++ks) f[ks] = RT::operand(stage(i) + sg * 32 * D, ks, at);
     acc[P][0] = zero16();
     acc[P][1] = zero16();
     float add[2] = {0.f, 0.f};
@@ -652,21 +662,21 @@ __global__ __launch_bounds__(512) void prefill_read_only_kernel(const PrefillPar
 // factor are the lane's own, and what is accumulated (32 rows x d columns and 32 rows x 128 tokens) never
 // needs another wavefront.  The writers are one tile ahead; one barrier per tile.  Keys and MV_c come through LDS,
 // requested two tiles ahead without a trip through registers.
-// What bounds it: 64 matrix instructions per SIMD and tile (2048 cycles) beside about as many cycles of vector work
-// for 64 exponentials per lane, at 1.7-1.8 GHz under load (B = 32, H = 32, M = 4096, T = 512: 2230 us; tiles staged through
-// registers, all eight wavefronts scoring, 2650), the matrix pipe busy half of the cycles.  And a stall: at d = 128 a reader
-// needs four registers more than its 256, the compiler keeps one query operand in scratch and reloads it in one of
-// the three tiles that the loop is unrolled by, and the wait for it is for everything in flight - the keys and values
-// that the tile has just requested two tiles ahead - while the barrier holds the other wavefronts.  (d = 64 fits.)  Forms that overlap more
-// (products between the exponentials, the next tile's scores as well) took 2290 and 2400; with
-// v_mfma_f32_16x16x32_bf16, which hides less vector work, 2430.  A launch of one round (216 workgroups, 33 tiles):
-// 67 us against 82.
+// What bounds it: a reader and a writer share a SIMD's issue slots.  A tile of 64 slots is 64 matrix instructions there (2048
+// cycles) beside 1300 cycles of vector instructions, and the older wavefront always goes first; it takes 3050 cycles at
+// 1.65 GHz (B = 32, H = 32, M = 4096, T = 512: 2100 us) and as many at 2.1 GHz (216 workgroups of one round, 33 tiles: 59).  A
+// reader alone takes 2700.  Before, keys came as operand tiles (see RowTile), every wavefront requested its share, a
+// reader kept one operand in scratch and the sum's terms until after the products: 3300 cycles, 2270 us, 67.  The
+// requests are the writers' because the address unit takes a request in 16 cycles and holds up whoever asks.  Built, right
+// and not kept, us for the two sizes: a block's weights between the next 32 slots' score products 2220, 65; operands from
+// LDS a region earlier 2180, 65; writers with a higher priority 3720 cycles a tile; requests after the scores 3940.
 template <int D>
 __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const PrefillParams p) {
+  typedef RowTile<D> RT;
   constexpr int KS = D / 16, NC = D / 32;
   constexpr float kTau = 8.f;
   constexpr int kTile = 64 * D;                 // elements of a 64-slot tile
-  constexpr int NL = kTile / 512 / 8;           // its load instructions per wavefront
+  constexpr int NL = kTile / 512 / 4;           // its load instructions per writer
   // three stages each; separate arrays, so that the compiler knows what a request into one does not touch
   __shared__ __attribute__((aligned(16))) uint16_t sK0[kTile], sK1[kTile], sK2[kTile];
   __shared__ __attribute__((aligned(16))) uint16_t sV0[kTile], sV1[kTile], sV2[kTile];
@@ -684,40 +694,41 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
   const uint16_t* mk = p.mk + (size_t)(p.mk_per_seq ? unit : h) * p.M * D;
   const uint16_t* mvc = p.snap + ((size_t)c * units + unit) * p.M * D;   // MV_c as operand tiles
 
-  auto stage_k = [&](auto i) -> uint16_t* {
+  auto stage_k = [&](auto i) __attribute__((always_inline)) -> uint16_t* {
     if constexpr (decltype(i)::v % 3 == 0) return sK0;
     else if constexpr (decltype(i)::v % 3 == 1) return sK1;
     else return sK2;
   };
-  auto stage_v = [&](auto i) -> uint16_t* {
+  auto stage_v = [&](auto i) __attribute__((always_inline)) -> uint16_t* {
     if constexpr (decltype(i)::v % 3 == 0) return sV0;
     else if constexpr (decltype(i)::v % 3 == 1) return sV1;
     else return sV2;
   };
-  auto request = [&](auto i, uint32_t tile) {
+  auto request = [&](auto i, uint32_t tile) __attribute__((always_inline)) {
     const uint32_t t = min(tile, n - 1);   // past the end: the last tile again, never used
     const uint16_t *k = mk + (size_t)t * kTile, *v = mvc + (size_t)t * kTile;
 #pragma unroll
-    for (int j = 0; j < NL; ++j) {   // 32 slots' operand tiles, then the other 32's
-      const int ld = wave * NL + j;
-      load_to_lds(scalar_base(k + (ld / KS) * 32 * D + (ld % KS) * 16) + row_operand(lane, D), stage_k(i) + ld * 512);
+    for (int j = 0; j < NL; ++j) {
+      const int ld = (wave & 3) * NL + j;
+      lds_request(k + ld * 512, RT::source(ld, lane), stage_k(i) + ld * 512);
     }
     __builtin_amdgcn_sched_barrier(0);   // the keys are needed a tile before the values: see tile_end
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
-      const int ld = wave * NL + j;
-      load_to_lds(scalar_base(v + ld * 512) + (uint32_t)lane * 16u, stage_v(i) + ld * 512);
+      const int ld = (wave & 3) * NL + j;
+      lds_request(v + ld * 512, (uint32_t)lane * 16u, stage_v(i) + ld * 512);
     }
   };
   // 32 slots of the tile (blk = 0, 1) against this wavefront's 32 rows: lane = row, register v = slot
   // 8 (v / 4) + 4 half + v % 4 of the 32
   // LDS operands are requested a region ahead of the products that use them (region(): the scheduler keeps its
   // order; left to itself it waits out an LDS latency before every second product).
-  auto scores = [&](const uint16_t* k, const bf16x8* x, f32x16* s) {
+  const uint32_t at = RT::operand_at(lane);
+  auto scores = [&](const uint16_t* k, const bf16x8* x, f32x16* s) __attribute__((always_inline)) {
     bf16x8 f[2][4];
-    auto load = [&](int bt) {
+    auto load = [&](int bt) __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) f[bt & 1][i] = *(const bf16x8*)(k + lane * 8 + ((i & 1) * KS + 2 * bt + i / 2) * 512);
+      for (int i = 0; i < 4; ++i) f[bt & 1][i] = RT::operand(k + (i & 1) * 32 * D, 2 * bt + i / 2, at);
     };
     s[0] = zero16();
     s[1] = zero16();
@@ -733,7 +744,7 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
   };
   // End of tile i: this wavefront's LDS accesses are done; of its requests the values of tile i + 2 may still be on
   // their way, the keys of i + 2 (for the writers) and the values of i + 1 have arrived
-  auto tile_end = [&] {
+  auto tile_end = [&]() __attribute__((always_inline)) {
     __builtin_amdgcn_s_waitcnt(kWaitLds);
     __builtin_amdgcn_s_waitcnt(wait_vm(NL));
     bare_barrier();
@@ -744,14 +755,16 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
   // A row's own token and the earlier ones of the sub-chunk are all it can read: of the four groups of 32 write
   // tokens a reader needs the first nsb (none: its rows are all past the chunk's end), the workgroup those
   // whose writer is asked
-  auto groups = [&](uint32_t first_row, uint32_t last_row) -> int {
+  auto groups = [&](uint32_t first_row, uint32_t last_row) __attribute__((always_inline)) -> int {
     const uint32_t left = T - t0;   // tokens of the sub-chunk, at least one
     return (rho0 + first_row) / G >= left ? 0 : (int)(min((rho0 + last_row) / G, left - 1) / 32 + 1);
   };
   const int nsb = groups(32 * rg, 32 * rg + 31);
   const bool asked = rg < groups(0, kTC - 1);
-  request(Int<0>{}, 0);
-  request(Int<1>{}, 1);
+  if (!reader) {
+    request(Int<0>{}, 0);
+    request(Int<1>{}, 1);
+  }
   // this wavefront's rows as operand fragments, kept in registers.  A negative read scale moves into the
   // row (negating bf16 is exact), so that the largest raw score is also the largest scaled one.
   float cs = reader ? p.rscale_l2e : p.wscale_l2e;   // scale of this wavefront's rows (log2 domain)
@@ -774,7 +787,7 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
 
   if (!reader) {
     const float shift = present ? p.norm_w[(size_t)unit * T + rtok] : kNoRow;
-    auto weights = [&](auto i, uint32_t it) {
+    auto weights = [&](auto i, uint32_t it) __attribute__((always_inline)) {
       f32x16 s[2];
       scores(stage_k(i), x, s);
 #pragma unroll
@@ -785,7 +798,7 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
         for (int j = 0; j < 2; ++j) sW[(((it & 1) * 4 + rg) * 4 + 2 * k + j) * 64 + lane] = pack8(s[k], j);
       }
     };
-    auto tile = [&](auto i, uint32_t it) {
+    auto tile = [&](auto i, uint32_t it) __attribute__((always_inline)) {
       request(Int<decltype(i)::v + 2>{}, it + 2);
       if (asked) weights(Int<decltype(i)::v + 1>{}, it + 1);   // past the end: of whatever tile is there, never used
       tile_end();
@@ -810,12 +823,12 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
 #pragma unroll
   for (int sb = 0; sb < 4; ++sb) aacc[sb] = zero16();
   float shift = kNegBig, zsum = 0.f;
-  auto tile = [&](auto i, uint32_t it) {
+  auto tile = [&](auto i, uint32_t it) __attribute__((always_inline)) {
     f32x16 s[2];
     scores(stage_k(i), x, s);
     float tm = fmaxf(s[0][0], s[1][0]);
 #pragma unroll
-    for (int v = 1; v < 16; ++v) tm = fmaxf(tm, fmaxf(s[0][v], s[1][v]));
+    for (int v = 1; v < 16; ++v) tm = fmaxf(fmaxf(tm, s[0][v]), s[1][v]);
     tm = max_of_halves(tm) * cs;
     const bool moves = tm > shift + kTau;        // also the first tile (shift = kNegBig, nothing accumulated yet)
     if (__builtin_amdgcn_ballot_w64(moves)) {    // bring what has been accumulated to the new shifts
@@ -836,12 +849,13 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
     constexpr int NF = NC > 4 ? NC : 4;
     bf16x8 f[2][NF], pw[4];     // pw: the row's weights, 16 slots each
     float add = 0.f;
-    auto weights = [&](int j) {
+    auto weights = [&](int j) __attribute__((always_inline)) {
 #pragma unroll
       for (int v = 8 * (j & 1); v < 8 * (j & 1) + 8; ++v) {
         s[j / 2][v] = fast_exp2(__builtin_fmaf(s[j / 2][v], cs, -shift));
         add += s[j / 2][v];
       }
+      asm volatile("" : "+v"(add));   // added here: moved behind the products, the terms take 32 registers
       pw[j] = pack8(s[j / 2], j & 1);
     };
 #pragma unroll
@@ -875,8 +889,7 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
         region();
       }
   };
-  auto step = [&](auto i, uint32_t it) {
-    request(Int<decltype(i)::v + 2>{}, it + 2);
+  auto step = [&](auto i, uint32_t it) __attribute__((always_inline)) {
     if (nsb > 0) tile(i, it);
     tile_end();
   };
@@ -935,7 +948,8 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
 // chunk moves at B = 32, H = 32, M = 4096, T = 512), without by its matrix and vector work.  A token tile of 32 keeps
 // a workgroup within 168 registers and 34 KB, so that three of them (three wavefronts per SIMD) hide each
 // other's barriers and stores; two: 2250 us against 1950 at that size, four (registers spilled): 2680.  Row-major
-// token tiles of 64 with padded rows, where a third of the LDS cycles were bank conflicts, took 2170.  The wait that ends a
+// token tiles of 64 with padded rows, where a third of the LDS cycles were bank conflicts, took 2170.  With write queries as operand
+// tiles (see RowTile) 1950 to 1970, in whole rows 1870.  The wait that ends a
 // tile is for all requests; in every fourth tile that includes the snapshot's stores, issued after them.
 // FAR: a token tile's write queries lie further apart than a lane's 32-bit byte offset reaches (see
 // launch_prefill_bf16), so their addresses are 64-bit.  Not for every chunk: 64-bit addresses spill 62 registers of
@@ -968,7 +982,7 @@ __global__ __launch_bounds__(256, 3) void prefill_state_kernel(const PrefillPara
 
   if (live) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i) load_to_lds(mv + (size_t)RT::row(i, lane) * D + RT::chunk(i, lane) * 8, strip + i * 512);
+    for (int i = 0; i < NI; ++i) lds_request(mv, RT::row(i, lane) * D * 2 + RT::chunk(i, lane) * 16, strip + i * 512);
   }
   bf16x8 kb[KS];
 #pragma unroll
@@ -978,7 +992,7 @@ __global__ __launch_bounds__(256, 3) void prefill_state_kernel(const PrefillPara
     kb[ks] = __builtin_bit_cast(bf16x8, v);
   }
   // state product: lane = value column, accumulator rows = slots.  Element (slot row, column) of the strip:
-  auto at = [&](int r, int jt) { return r * D + (((4 * jt + col / 8) ^ swizzle<D>(r)) * 8) + col % 8; };
+  auto cell = [&](int r, int jt) { return r * D + (((4 * jt + col / 8) ^ swizzle<D>(r)) * 8) + col % 8; };
   f32x16 macc[NC];
 #pragma unroll
   for (int jt = 0; jt < NC; ++jt) macc[jt] = zero16();
@@ -987,11 +1001,11 @@ __global__ __launch_bounds__(256, 3) void prefill_state_kernel(const PrefillPara
 #pragma unroll
     for (int jt = 0; jt < NC; ++jt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) macc[jt][v] = bf16_val(strip[at(8 * (v / 4) + 4 * half + v % 4, jt)]);
+      for (int v = 0; v < 16; ++v) macc[jt][v] = bf16_val(strip[cell(8 * (v / 4) + 4 * half + v % 4, jt)]);
   }
   __syncthreads();
 
-  const uint32_t ntile = (T + TT - 1) / TT;
+  const uint32_t ntile = (T + TT - 1) / TT, at = RT::operand_at(lane);
   auto pick = [](auto i, auto* a, auto* c) {
     if constexpr (decltype(i)::v % 2 == 0) return a;
     else return c;
@@ -1004,17 +1018,15 @@ __global__ __launch_bounds__(256, 3) void prefill_state_kernel(const PrefillPara
   auto request = [&](auto i, uint32_t tile) {
     const uint32_t tl = min(tile, ntile - 1), over = tl == ntile - 1 ? lastrow : (uint32_t)TT - 1;
     uint16_t *sx = pick(i, sX0, sX1), *st = pick(i, sT0, sT1);
-    const uint32_t row = min((uint32_t)col, over);
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
       const int ld = wave * NL + j;
-      if constexpr (FAR) load_to_lds(wq + ((size_t)(tl * TT + row) * xstride + ld * 16 + half * 8), sx + ld * 512);
-      else load_to_lds(scalar_base(wq + (size_t)tl * TT * xstride + ld * 16) + (row * xstride + (uint32_t)half * 8u) * 2u, sx + ld * 512);
-      load_to_lds(scalar_base(wvt + (size_t)tl * kTile + ld * 512) + (uint32_t)lane * 16u, st + ld * 512);
+      const uint32_t row = min((uint32_t)RT::row(ld, lane), over), ch = (uint32_t)RT::chunk(ld, lane) * 8u;
+      if constexpr (FAR) lds_request(wq + ((size_t)(tl * TT + row) * xstride + ch), sx + ld * 512);
+      else lds_request(wq + (size_t)tl * TT * xstride, (row * xstride + ch) * 2u, sx + ld * 512);
+      lds_request(wvt + (size_t)tl * kTile + ld * 512, (uint32_t)lane * 16u, st + ld * 512);
     }
-    __builtin_amdgcn_global_load_lds(
-        (const __attribute__((address_space(1))) void*)(scalar_base(p.norm_w + (size_t)unit * T + tl * TT) + row * 4u),
-        (__attribute__((address_space(3))) void*)(pick(i, sN0, sN1) + 64 * wave), 4, 0, 0);
+    lds_request<4>(p.norm_w + (size_t)unit * T + tl * TT, min((uint32_t)col, over) * 4u, pick(i, sN0, sN1) + 64 * wave);
   };
   auto tile = [&](auto i, uint32_t tt) {
     request(Int<decltype(i)::v + 1>{}, tt + 1);
@@ -1034,15 +1046,15 @@ __global__ __launch_bounds__(256, 3) void prefill_state_kernel(const PrefillPara
     f32x16 sc = zero16();
     bf16x8 f[2][4];
     f32x4 sh[4];   // shifts of the lane's tokens
-    const bf16x8 *xt = (const bf16x8*)sx + lane, *wt = (const bf16x8*)st + lane;
+    const bf16x8* wt = (const bf16x8*)st + lane;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) f[0][k] = xt[k * 64];
+    for (int k = 0; k < 4; ++k) f[0][k] = RT::operand(sx, k, at);
     region();
 #pragma unroll
     for (int bt = 0; bt < KS / 4; ++bt) {
       if (bt + 1 < KS / 4) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) f[(bt + 1) & 1][k] = xt[(4 * (bt + 1) + k) * 64];
+        for (int k = 0; k < 4; ++k) f[(bt + 1) & 1][k] = RT::operand(sx, 4 * (bt + 1) + k, at);
       } else {
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) sh[q4] = *(const f32x4*)(sn + 8 * q4 + 4 * half);
@@ -1105,7 +1117,7 @@ __global__ __launch_bounds__(256, 3) void prefill_state_kernel(const PrefillPara
 #pragma unroll
     for (int jt = 0; jt < NC; ++jt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) strip[at(8 * (v / 4) + 4 * half + v % 4, jt)] = bf16_bits(macc[jt][v]);
+      for (int v = 0; v < 16; ++v) strip[cell(8 * (v / 4) + 4 * half + v % 4, jt)] = bf16_bits(macc[jt][v]);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
