@@ -181,28 +181,35 @@ __global__ __launch_bounds__(64 * WAVES) void linear_kernel(const uint16_t* __re
 // The row of a workgroup.  Workgroups go to the eight XCDs in turn; a 128-byte line of the tiled order holds 8 inputs
 // of 8 consecutive rows, and rows in launch order would leave parts of every line in eight L2s.  So 16 consecutive
 // rows (1 KB tiles) are those of one XCD, for as many whole groups of 128 rows as there are.  16384 rows x 4096:
-// 80 us against 139 (8 rows per workgroup: 110), 2048 rows 10.3 against 16.3.  That is 3.4 TB/s, not the rate of memory: the
-// same 268 MB take pack_rows_kernel 52 us.  A workgroup here holds one row of 8 KB and waits twice, for the row and
-// for the sum.
+// 80 us against 139 (8 rows per workgroup: 110), 2048 rows 10.3 against 16.3.  That is 3.5 TB/s, not the rate of memory: the
+// same 268 MB take pack_rows_kernel 52 us.  A workgroup here holds one row of 8 KB and waits for it and for the sum.
 __device__ __forceinline__ uint32_t tiled_row(uint32_t block, uint32_t rows) {
   if (block >= rows / 128 * 128) return block;
   return (block / 128 * 8 + block % 8) * 16 + block / 8 % 16;
 }
 
-// One workgroup per row; a thread keeps its (up to eight) 16-byte chunks of the row in registers between
-// the sum of squares and the scaling, so the row is read once.
+// One workgroup per row; a thread keeps its NV 16-byte chunks of the row in registers between the sum of squares and the
+// scaling.  The gains are requested with the row, so that it waits for memory once (us, with the row | after the sum | after
+// it and eight chunks a thread for every width: 4 x 4096 2.5 | 2.6 | 2.9, 640 x 4096 4.5 | 4.7 | 5.1, 4096 x 8192 39 | 44 | 46,
+// 16384 x 12288 259 | 283 | 296); LATE: after the sum, see rmsnorm_late.
+template <int NV, bool LATE>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const uint16_t* x, const uint16_t* gain, uint16_t* out,
                                                       uint32_t rows, uint32_t dim, float eps, uint32_t out_tiled) {
   __shared__ float s_part[4];
   const uint32_t row = out_tiled ? tiled_row(blockIdx.x, rows) : blockIdx.x;
   const uint16_t* xr = x + (size_t)row * dim;
-  u32x4 v[8];
+  u32x4 v[NV], gv[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    // chunks past the end: the first one again, not counted and not stored
+    const uint32_t c = (threadIdx.x + i * 256) * 8, from = c < dim ? c : 0u;
+    v[i] = *(const u32x4*)(xr + from);
+    if (!LATE) gv[i] = *(const u32x4*)(gain + from);
+  }
   float ss = 0.f;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const uint32_t c = (threadIdx.x + i * 256) * 8;
-    if (c < dim) {
-      v[i] = *(const u32x4*)(xr + c);
+  for (int i = 0; i < NV; ++i) {
+    if ((threadIdx.x + i * 256) * 8 < dim) {
       float f[8];
       unpack16<BF16>(v[i], f);
 #pragma unroll
@@ -215,12 +222,12 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const uint16_t* x, const u
   ss = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
   const float r = 1.0f / sqrtf(ss / (float)dim + eps);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < NV; ++i) {
     const uint32_t c = (threadIdx.x + i * 256) * 8;
     if (c < dim) {
       float f[8], g[8];
       unpack16<BF16>(v[i], f);
-      unpack16<BF16>(*(const u32x4*)(gain + c), g);
+      unpack16<BF16>(LATE ? *(const u32x4*)(gain + c) : gv[i], g);
 #pragma unroll
       for (int e = 0; e < 8; ++e) f[e] = f[e] * r * g[e];
       const u32x4 o = pack16_round<BF16>(f);
@@ -303,6 +310,11 @@ bct_status launched(const char* what, hipError_t e = hipGetLastError()) {
   snprintf(g_merr, sizeof(g_merr), "%s launch failed: %s", what, hipGetErrorString(e));
   return BCT_ERR_HIP;
 }
+// Narrow rows that together leave the caches: the gains after the sum.  us, with the row | after the sum: 16384 x 4096 90 |
+// 76, 8192 x 4096 45 | 39, 16384 x 2048 36.2 | 34.5; below 32 M elements 8192 x 3072 21.6 | 21.4, 4096 x 4096 15.2 | 15.7, 16384 x 1024
+// 15.4 | 15.4; wider 16384 x 5120 97 | 101, 8192 x 6144 54 | 64.
+bool rmsnorm_late(uint32_t rows, uint32_t dim) { return dim <= 4096 && (uint64_t)rows * dim >= (32u << 20); }
+
 bool al16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 bct_status check_linear(const void* x, const void* w, const void* out, uint32_t rows, uint32_t K, uint32_t N) {
@@ -406,8 +418,12 @@ bct_status bctm_rmsnorm(const void* x, const void* gain, void* out, uint32_t row
     return mfail(BCT_ERR_UNSUPPORTED, "tiled activations need a multiple of 32 columns");
   if ((flags & BCTM_OUT_TILED) && x == out) return mfail(BCT_ERR_INVALID_ARG, "a tiled output cannot overwrite x");
   if (!al16(x) || !al16(gain) || !al16(out)) return mfail(BCT_ERR_MISALIGNED, "pointers must be 16-byte aligned");
-  hipLaunchKernelGGL(rmsnorm_kernel, dim3(rows), dim3(256), 0, (hipStream_t)hip_stream, (const uint16_t*)x,
-                     (const uint16_t*)gain, (uint16_t*)out, rows, dim, eps, flags & BCTM_OUT_TILED);
+  const bool late = rmsnorm_late(rows, dim);
+  const auto kernel = dim <= 2048 ? (late ? rmsnorm_kernel<1, true> : rmsnorm_kernel<1, false>)
+                      : dim <= 4096 ? (late ? rmsnorm_kernel<2, true> : rmsnorm_kernel<2, false>)
+                      : dim <= 8192 ? rmsnorm_kernel<4, false> : rmsnorm_kernel<8, false>;
+  hipLaunchKernelGGL(kernel, dim3(rows), dim3(256), 0, (hipStream_t)hip_stream, (const uint16_t*)x, (const uint16_t*)gain,
+                     (uint16_t*)out, rows, dim, eps, flags & BCTM_OUT_TILED);
   return launched("rmsnorm");
 }
 

@@ -9,6 +9,7 @@ far inside it).  Arg-max and embedding are integer / byte work: bit-exact.
 """
 import numpy as np
 import pytest
+import torch
 
 import bct_synth as syn
 from _util import bf16_ulp, to_dev, to_np
@@ -328,6 +329,26 @@ def test_rmsnorm(M, rows, dim):
     out = M.bctm_rmsnorm(dev(x), dev(g), 1e-5)
     ref = R.rmsnorm(x, g, 1e-5)
     check_close(host(out), ref, 2.0 ** -20 * np.abs(R.bf16_to_f64(ref)), f"rmsnorm {rows}x{dim}")
+
+
+# widths around the numbers of 16-byte chunks that a thread holds (1, 2, 4, 8)
+@pytest.mark.parametrize("dim", [2040, 2048, 2056, 4096, 4104, 8192, 8200, 16376])
+def test_rmsnorm_chunks_of_a_thread(M, dim):
+    x, g = draw(8, (2, dim), 3.0), syn.pack(1.0 + 0.1 * syn.normal(11, 9, 9, (dim,)), "bf16")
+    ref = R.rmsnorm(x, g, 1e-5)
+    check_close(host(M.bctm_rmsnorm(dev(x), dev(g), 1e-5)), ref, 2.0 ** -20 * np.abs(R.bf16_to_f64(ref)), f"rmsnorm 2x{dim}")
+
+
+# so many elements that the gains are requested after the sum of squares: a row's bits do not depend on it
+@pytest.mark.parametrize("rows,dim", [(16400, 2048), (8225, 4088), (8193, 4096)])
+def test_rmsnorm_of_many_rows(M, rows, dim):
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(rows)
+    x = torch.randn((rows, dim), generator=gen, dtype=torch.bfloat16, device="cuda:0")
+    g = torch.randn((dim,), generator=gen, dtype=torch.bfloat16, device="cuda:0")
+    out = M.bctm_rmsnorm(x, g, 1e-5)
+    for r in (0, rows // 2, rows - 40):
+        assert torch.equal(out[r:r + 40], M.bctm_rmsnorm(x[r:r + 40].contiguous(), g, 1e-5))
 
 
 def test_embed_and_argmax_are_exact(M):
