@@ -161,17 +161,37 @@ def bct_strerror(st: int) -> str:
 
 # ------------------------------------------------------------------ tensor-level convenience
 
+# A small step takes 5 us on the GPU, so the way to it is kept short: no context manager where the device is current
+# already, no stream object, pointers as plain integers (every pointer parameter is declared c_void_p).  us a call, with
+# those | without: decode_step of 4 memories of 64 x 64 10.3 | 6.1, a 512-wide MLP of one row 29 | 18.
+
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _stream_ptr():
-    return ctypes.c_void_p(_torch().cuda.current_stream().cuda_stream)
+    torch = _torch()
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _launch(fn, device, *args):
+    """fn(*args, the current stream of `device`), with that device current."""
+    torch = _torch()
+    if device.type == "cuda" and device.index == torch.cuda.current_device():
+        return fn(*args, torch._C._cuda_getCurrentRawStream(device.index))
+    with torch.cuda.device(device):
+        return fn(*args, _stream_ptr())
 
 
 class BctCache:
@@ -193,6 +213,8 @@ class BctCache:
         ws = 1.0 / math.sqrt(head_dim) if write_scale is None else write_scale
         self.desc = make_desc(capacity_M, batch, n_q_heads, n_kv_heads, head_dim, code, rs, ws, flags)
         self.M, self.B, self.Hq, self.Hkv, self.d = capacity_M, batch, n_q_heads, n_kv_heads, head_dim
+        self._q_shape, self._kv_shape = (batch, n_q_heads, head_dim), (batch, n_kv_heads, head_dim)
+        self._gate_shape = (batch, n_kv_heads)
         self.flags = flags
         self.max_prefill_T = max_prefill_T
         self._h = None
@@ -233,15 +255,12 @@ class BctCache:
     def _check(self, t, shape, name):
         if t is None:
             return
-        if t.dtype != self.torch_dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous() \
-                or t.device != self.device:
+        if t.dtype is not self.torch_dtype or t.shape != shape or not t.is_contiguous() or t.device != self.device:
             raise ValueError(f"{name}: expected contiguous {self.torch_dtype} {tuple(shape)} on {self.device}, "
                              f"got {t.dtype} {tuple(t.shape)} on {t.device}")
 
     def _call(self, name, *args):
-        torch = _torch()
-        with torch.cuda.device(self.device):
-            st = getattr(lib(), name)(self._h, *args, _stream_ptr())
+        st = _launch(getattr(lib(), name), self.device, self._h, *args)
         if st != BCT_OK:
             raise BctError(st, name)
 
@@ -270,22 +289,20 @@ class BctCache:
         self._call("bct_cache_import_sequence", ctypes.c_uint32(b), _dptr(mk), _dptr(mv))
 
     def _check_gate(self, gate, shape):
-        torch = _torch()
-        if gate is not None and (gate.dtype != torch.float32 or tuple(gate.shape) != tuple(shape)
+        if gate is not None and (gate.dtype is not _torch().float32 or gate.shape != shape
                                  or not gate.is_contiguous() or gate.device != self.device):
             raise ValueError(f"gate: expected contiguous float32 {tuple(shape)} on {self.device}")
 
     def decode_step(self, q, k_new, v_new, out=None, gate=None):
         """One token per sequence; returns out [B][Hq][d] (None for a write-only step).
         gate: float32 [B][Hkv] step sizes of the write, or None."""
-        torch = _torch()
-        self._check_gate(gate, (self.B, self.Hkv))
-        self._check(q, (self.B, self.Hq, self.d), "q")
-        self._check(k_new, (self.B, self.Hkv, self.d), "k_new")
-        self._check(v_new, (self.B, self.Hkv, self.d), "v_new")
+        self._check_gate(gate, self._gate_shape)
+        self._check(q, self._q_shape, "q")
+        self._check(k_new, self._kv_shape, "k_new")
+        self._check(v_new, self._kv_shape, "v_new")
         if q is not None and out is None:
-            out = torch.empty_like(q)
-        self._check(out, (self.B, self.Hq, self.d), "out")
+            out = _torch().empty_like(q)
+        self._check(out, self._q_shape, "out")
         if gate is None:
             self._call("bct_decode_step", _dptr(q), _dptr(k_new), _dptr(v_new), _dptr(out))
         else:
@@ -327,13 +344,11 @@ class BctCache:
         if q is not None and out is None:
             out = torch.empty_like(q)
         self._check(out, (self.B, T, self.Hq, self.d), "out")
-        torch = _torch()
-        with torch.cuda.device(self.device):
-            if gate is None:
-                st = lib().bct_prefill(self._h, _dptr(q), _dptr(k_new), _dptr(v_new), T, _dptr(out), _stream_ptr())
-            else:
-                st = lib().bct_prefill_gated(self._h, _dptr(q), _dptr(k_new), _dptr(v_new), _dptr(gate), T,
-                                             _dptr(out), _stream_ptr())
+        if gate is None:
+            st = _launch(lib().bct_prefill, self.device, self._h, _dptr(q), _dptr(k_new), _dptr(v_new), T, _dptr(out))
+        else:
+            st = _launch(lib().bct_prefill_gated, self.device, self._h, _dptr(q), _dptr(k_new), _dptr(v_new), _dptr(gate), T,
+                         _dptr(out))
         if st != BCT_OK:
             raise BctError(st, "bct_prefill")
         return out

@@ -12,7 +12,7 @@ import math
 from dataclasses import dataclass
 
 from . import binding
-from .binding import BCT_OK, BctCache, BctError, _dptr, _stream_ptr, _torch
+from .binding import BCT_OK, BctCache, BctError, _dptr, _launch, _torch
 
 MODEL_EXPORTS = ["bctm_embed", "bctm_rmsnorm", "bctm_pack_weight", "bctm_pack_rows", "bctm_linear", "bctm_linear_split",
                  "bctm_swiglu", "bctm_linear_plan", "bctm_linear_tile",
@@ -83,9 +83,8 @@ def bctm_embed(ids, table, out=None):
     _bf16_2d(out, "out", table.shape[1])
     if out.shape[0] != ids.numel():
         raise ValueError("out: one row per id")
-    with torch.cuda.device(table.device):
-        _ck(mlib().bctm_embed(_dptr(ids), _dptr(table), _dptr(out), ids.numel(), table.shape[0], table.shape[1],
-                              _stream_ptr()), "bctm_embed")
+    _ck(_launch(mlib().bctm_embed, table.device, _dptr(ids), _dptr(table), _dptr(out), ids.numel(), table.shape[0],
+                table.shape[1]), "bctm_embed")
     return out
 
 
@@ -120,15 +119,13 @@ class TiledRows:
 
 
 def bctm_pack_rows(x, out=None):
-    torch = _torch()
     _bf16_2d(x, "x")
     rows, K = x.shape
     if out is None:
         out = TiledRows(rows, K, x.device)
     if (out.rows, out.K) != (rows, K):
         raise ValueError("out: tiled buffer of x's shape")
-    with torch.cuda.device(x.device):
-        _ck(mlib().bctm_pack_rows(_dptr(x), _dptr(out.data), rows, K, _stream_ptr()), "bctm_pack_rows")
+    _ck(_launch(mlib().bctm_pack_rows, x.device, _dptr(x), _dptr(out.data), rows, K), "bctm_pack_rows")
     return out
 
 
@@ -152,9 +149,8 @@ def bctm_rmsnorm(x, gain, eps, out=None, tiled=False):
         if out.shape[0] != x.shape[0]:
             raise ValueError("out: x's shape")
         dst = out
-    with torch.cuda.device(x.device):
-        _ck(mlib().bctm_rmsnorm(_dptr(x), _dptr(gain), _dptr(dst), x.shape[0], x.shape[1], eps,
-                                BCTM_OUT_TILED if tiled else 0, _stream_ptr()), "bctm_rmsnorm")
+    _ck(_launch(mlib().bctm_rmsnorm, x.device, _dptr(x), _dptr(gain), _dptr(dst), x.shape[0], x.shape[1],
+                eps, BCTM_OUT_TILED if tiled else 0), "bctm_rmsnorm")
     return out
 
 
@@ -174,11 +170,9 @@ def bctm_pack_weight(*ws):
     N = sum(w.shape[0] for w in ws)
     data = torch.empty(N * K, dtype=torch.bfloat16, device=ws[0].device)
     off = 0
-    with torch.cuda.device(ws[0].device):
-        for w in ws:
-            _ck(mlib().bctm_pack_weight(_dptr(w), _dptr(data[off:]), w.shape[0], K, _stream_ptr()),
-                "bctm_pack_weight")
-            off += w.shape[0] * K
+    for w in ws:
+        _ck(_launch(mlib().bctm_pack_weight, ws[0].device, _dptr(w), _dptr(data[off:]), w.shape[0], K), "bctm_pack_weight")
+        off += w.shape[0] * K
     return PackedWeight(data, N, K)
 
 
@@ -210,9 +204,8 @@ def bctm_linear(x, w, residual=None, out=None):
         _bf16_2d(residual, "residual", N)
     if out.shape[0] != rows or (residual is not None and residual.shape[0] != rows):
         raise ValueError("out / residual: one row per row of x")
-    with torch.cuda.device(xd.device):
-        _ck(mlib().bctm_linear(_dptr(xd), _dptr(w.data), _dptr(residual), _dptr(out), rows, K, N, xf,
-                               _stream_ptr()), "bctm_linear")
+    _ck(_launch(mlib().bctm_linear, xd.device, _dptr(xd), _dptr(w.data), _dptr(residual), _dptr(out), rows, K,
+                N, xf), "bctm_linear")
     return out
 
 
@@ -227,10 +220,8 @@ def bctm_linear_split(x, w, outs):
         if o.shape[0] != rows:
             raise ValueError("outs: one row per row of x")
     o2, n2 = (outs[2], outs[2].shape[1]) if len(outs) == 3 else (None, 0)
-    torch = _torch()
-    with torch.cuda.device(xd.device):
-        _ck(mlib().bctm_linear_split(_dptr(xd), _dptr(w.data), _dptr(outs[0]), outs[0].shape[1], _dptr(outs[1]),
-                                     outs[1].shape[1], _dptr(o2), n2, rows, K, xf, _stream_ptr()), "bctm_linear_split")
+    _ck(_launch(mlib().bctm_linear_split, xd.device, _dptr(xd), _dptr(w.data), _dptr(outs[0]), outs[0].shape[1],
+                _dptr(outs[1]), outs[1].shape[1], _dptr(o2), n2, rows, K, xf), "bctm_linear_split")
     return outs
 
 
@@ -256,9 +247,8 @@ def bctm_swiglu(x, w_gate, w_up, out=None, tiled=False):
         if out.shape[0] != rows:
             raise ValueError("out: one row per row of x")
         dst = out
-    with torch.cuda.device(xd.device):
-        _ck(mlib().bctm_swiglu(_dptr(xd), _dptr(w_gate.data), _dptr(w_up.data), _dptr(dst), rows, K, N,
-                               xf | (BCTM_OUT_TILED if tiled else 0), _stream_ptr()), "bctm_swiglu")
+    _ck(_launch(mlib().bctm_swiglu, xd.device, _dptr(xd), _dptr(w_gate.data), _dptr(w_up.data), _dptr(dst), rows,
+                K, N, xf | (BCTM_OUT_TILED if tiled else 0)), "bctm_swiglu")
     return out
 
 
@@ -269,9 +259,7 @@ def bctm_argmax(logits, out=None):
         out = torch.empty(logits.shape[0], dtype=torch.int32, device=logits.device)
     if out.dtype != torch.int32 or tuple(out.shape) != (logits.shape[0],) or not out.is_contiguous():
         raise ValueError("out: a contiguous int32 vector, one entry per row")
-    with torch.cuda.device(logits.device):
-        _ck(mlib().bctm_argmax(_dptr(logits), _dptr(out), logits.shape[0], logits.shape[1], _stream_ptr()),
-            "bctm_argmax")
+    _ck(_launch(mlib().bctm_argmax, logits.device, _dptr(logits), _dptr(out), logits.shape[0], logits.shape[1]), "bctm_argmax")
     return out
 
 
