@@ -670,6 +670,8 @@ __global__ __launch_bounds__(512) void prefill_read_only_kernel(const PrefillPar
 // requests are the writers' because the address unit takes a request in 16 cycles and holds up whoever asks.  Built, right
 // and not kept, us for the two sizes: a block's weights between the next 32 slots' score products 2220, 65; operands from
 // LDS a region earlier 2180, 65; writers with a higher priority 3720 cycles a tile; requests after the scores 3940.
+// The rows leave whole (see the end): 8-byte pieces of 32 rows a store and a token group's operands when they were needed took
+// 1.5 us more of a workgroup (B = 45, Hkv = 21, M = 320, T = 166, five tiles: 296 us for the chunk, now 286).
 template <int D>
 __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const PrefillParams p) {
   typedef RowTile<D> RT;
@@ -907,8 +909,16 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
   // A'[s] = (s <= token of the row) ? sum_m e[row][m] ww[s][m] : 0, and with it the tokens of the sub-chunk itself
   const int tl = (int)((rho0 + srow) / G);  // the row's token within the sub-chunk
   const bf16x8* wvt = (const bf16x8*)(p.wvt + ((size_t)unit * p.Tpad + t0) * D);
+  bf16x8 wf[2][2 * NC];   // operands of 32 tokens, requested while the 32 before are multiplied
+  auto tokens = [&](int sb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < 2 * NC; ++k) wf[sb & 1][k] = wvt[operand_chunk<D>(2 * sb + k / NC, k % NC, lane)];
+  };
+  tokens(0);
 #pragma unroll
   for (int sb = 0; sb < 4; ++sb) {   // a group that was not multiplied holds zeros
+    if (sb < 3) tokens(sb + 1);
+    region();
 #pragma unroll
     for (int v = 0; v < 16; ++v)
       if (32 * sb + 8 * (v / 4) + 4 * half + v % 4 > tl) aacc[sb][v] = 0.f;
@@ -916,19 +926,28 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
     for (int j = 0; j < 2; ++j) {
       const bf16x8 a = pack8(aacc[sb], j);
 #pragma unroll
-      for (int jt = 0; jt < NC; ++jt) oacc[jt] = mfma_bf16(wvt[operand_chunk<D>(2 * sb + j, jt, lane)], a, oacc[jt]);
+      for (int jt = 0; jt < NC; ++jt) oacc[jt] = mfma_bf16(wf[sb & 1][j * NC + jt], a, oacc[jt]);
     }
+    region();
   }
   const float z = zsum + __shfl_xor(zsum, 32, 64), inv = 1.0f / z;   // the normaliser of everything accumulated
-  if (present) {
-    // 8-byte stores: a row's pieces come one after another, and once per M slots
-    uint16_t* o = p.out + (((size_t)b * T + rtok) * p.Hq + h * G + (rho0 + srow) % G) * D + 4 * half;
+  // A lane has pieces of 8 bytes of its row; the rows leave whole, through this wavefront's 32 rows of LDS.  The key stages are
+  // free: the requests that the writers may still have in flight are for values.
+  uint16_t* const strip = (rg < 2 ? sK0 : sK1) + (rg % 2) * 32 * D;
 #pragma unroll
-    for (int jt = 0; jt < NC; ++jt)
+  for (int jt = 0; jt < NC; ++jt)
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4)
-        store4_bf16(o + 32 * jt + 8 * q4, oacc[jt][4 * q4 + 0] * inv, oacc[jt][4 * q4 + 1] * inv,
-                    oacc[jt][4 * q4 + 2] * inv, oacc[jt][4 * q4 + 3] * inv);
+    for (int q4 = 0; q4 < 4; ++q4)
+      store4_bf16(strip + col * D + ((4 * jt + q4) ^ swizzle<D>(col)) * 8 + 4 * half, oacc[jt][4 * q4 + 0] * inv,
+                  oacc[jt][4 * q4 + 1] * inv, oacc[jt][4 * q4 + 2] * inv, oacc[jt][4 * q4 + 3] * inv);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int i = 0; i < D / 16; ++i) {
+    const uint32_t rho = rho0 + 32 * rg + RT::row(i, lane), tk = t0 + rho / G;
+    if (tk < T)
+      *(u32x4*)(p.out + (((size_t)b * T + tk) * p.Hq + h * G + rho % G) * D + RT::chunk(i, lane) * 8) =
+          *(const u32x4*)(strip + (i * 64 + lane) * 8);
   }
 }
 
