@@ -24,7 +24,7 @@
 // Where 256 x 256 tiles are too few for 256 compute units, smaller tiles follow; and where even 128 x 128 tiles
 // leave every compute unit at most one workgroup of four wavefronts, two groups of wavefronts share a
 // tile, each with half of the inputs, and are the two that take turns on a SIMD (see rows_shape for the choice
-// and the measurements).
+// and the measurements).  128 x 512 fills rounds where 256 wastes rows.
 #include "bct_device.h"
 #include "bct_linear.h"
 
@@ -294,13 +294,18 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
 // times the K steps times what a step of a resident workgroup takes; measured us per K step at 640 and 16384
 // rows, K = 11008 / 4096:
 //   256 x 256             one workgroup per compute unit  0.46 (few) - 0.69 (chip full)
+//   128 x 512             one                             0.80
 //   128 x 256             one                             0.34 - 0.44
 //   128 x 128             two of four wavefronts          0.26 alone on its compute unit, 0.46 for a pair
 //   128 x 128, K in two   one                             0.19 - 0.25
 //   64 x 64, K in two     two                             0.11 alone, 0.19 for a pair
 // so 256 x 256 wins where the chip is full (4 rounds of it against 16 of 128 x 128), the others where its
-// workgroups are few: 640 rows x 11008 -> 4096 takes 157, 117, 88, 67, 94 us in this order.
-enum RowsShape { kTile256, kTile128x256, kTile128, kTile128K2, kTile64K2 };
+// workgroups are few: 640 rows x 11008 -> 4096 takes 157 us in 256 x 256, 117, 88, 67, 94 in the last four.  128 x 512 has the
+// work of 256 x 256 and 5 / 4 of its loads; it is there for row counts that 256 wastes, where it saves a round of
+// workgroups: us without | with it, K = 4096, 640 rows SwiGLU -> 11008 (430 | 215 tiles) 120 | 107, 557 rows -> 24576 122 | 109, 1045
+// -> 13824 116 | 104, 1838 -> 26112 346 | 306, 2936 -> 22528 424 | 392; where the rule leaves it, 5437 -> 20992 685 | 672, 3668 -> 35328
+// 784 | 815, 5193 -> 37888 1159 | 1269.
+enum RowsShape { kTile256, kTile128x512, kTile128x256, kTile128, kTile128K2, kTile64K2 };
 
 RowsShape rows_shape(uint32_t rows, uint32_t bcols) {
   auto tiles = [&](uint32_t bm, uint32_t bn) { return (uint64_t)((rows + bm - 1) / bm) * (bcols / bn); };
@@ -324,6 +329,7 @@ RowsShape rows_shape(uint32_t rows, uint32_t bcols) {
     take(kTile128x256, one(tiles(128, 256), 44));
     take(kTile256, one(tiles(256, 256), 69));
   }
+  if (bcols % 512 == 0) take(kTile128x512, one(tiles(128, 512), 80));
   return best;
 }
 
@@ -353,6 +359,7 @@ void launch_rows(const void* x, const void* w, const void* w2, const void* resid
   }
   switch (shape) {
     case kTile256: return launch_shape<SWIGLU, XT, 8, 4, 2, 4, 1>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
+    case kTile128x512: return launch_shape<SWIGLU, XT, 4, 8, 2, 4, 1>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
     case kTile128x256: return launch_shape<SWIGLU, XT, 4, 4, 2, 4, 1>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
     case kTile128: return launch_shape<SWIGLU, XT, 4, 4, 2, 2, 1>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
     case kTile128K2: return launch_shape<SWIGLU, XT, 4, 4, 2, 2, 2>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
@@ -366,6 +373,7 @@ LinearTile linear_rows_tile(uint32_t rows, uint32_t N, bool swiglu) {
   const uint32_t per = swiglu ? 2 : 1;   // B columns of a feature
   switch (rows_shape(rows, per * N)) {
     case kTile256: return {256, 256 / per, 1};
+    case kTile128x512: return {128, 512 / per, 1};
     case kTile128x256: return {128, 256 / per, 1};
     case kTile128: return {128, 128 / per, 1};
     case kTile128K2: return {128, 128 / per, 2};

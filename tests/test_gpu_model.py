@@ -257,6 +257,49 @@ def test_linear_rows_in_pairs(M, rows, K):
         check_close(host(out[:, part].contiguous()), R.linear(xh, wh), 2.0 ** -20 * mass, f"pairs {rows}x{K}")
 
 
+# The 128 x 512 tile: row counts that 256 wastes.  One to five K steps, a last row tile of 1 and of 45 rows, a residual, outputs
+# whose border lies inside a tile; row-major and tiled inputs bit for bit the same.
+@pytest.mark.parametrize("rows,K", [(557, 32), (513, 96), (640, 160)])
+def test_linear_tile_of_512_features(M, rows, K):
+    N = 23552
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    x = torch.randn((rows, K), generator=g, dtype=torch.bfloat16, device="cuda")
+    w = torch.randn((N, K), generator=g, dtype=torch.bfloat16, device="cuda").mul_(K ** -0.5)
+    res = torch.randn((rows, N), generator=g, dtype=torch.bfloat16, device="cuda")
+    assert M.bctm_linear_tile(rows, K, N) == (128, 512, 1)
+    wp, xt = M.bctm_pack_weight(w), M.bctm_pack_rows(x)
+    out, plain = M.bctm_linear(x, wp, res), M.bctm_linear(xt, wp)
+    assert torch.equal(out.view(torch.int16), M.bctm_linear(xt, wp, res).view(torch.int16))
+    outs = [torch.empty((rows, n), dtype=torch.bfloat16, device="cuda") for n in (11792, 256, 11504)]
+    M.bctm_linear_split(xt, wp, outs)
+    assert torch.equal(torch.cat(outs, 1).view(torch.int16), plain.view(torch.int16))
+    for part in (slice(0, 520), slice(11776, 12060), slice(N - 520, N)):
+        xh, wh, rh = host(x), host(w[part].contiguous()), host(res[:, part].contiguous())
+        mass = np.abs(R.bf16_to_f64(xh)) @ np.abs(R.bf16_to_f64(wh)).T + np.abs(R.bf16_to_f64(rh))
+        check_close(host(out[:, part].contiguous()), R.linear(xh, wh, rh), 2.0 ** -20 * mass, f"512 features {rows}x{K}")
+
+
+@pytest.mark.parametrize("rows,K", [(557, 32), (640, 160)])
+def test_swiglu_tile_of_512_features(M, rows, K):
+    N = 11776
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    x = torch.randn((rows, K), generator=g, dtype=torch.bfloat16, device="cuda")
+    wg = torch.randn((N, K), generator=g, dtype=torch.bfloat16, device="cuda").mul_(2.0 * K ** -0.5)
+    wu = torch.randn((N, K), generator=g, dtype=torch.bfloat16, device="cuda").mul_(K ** -0.5)
+    assert M.bctm_linear_tile(rows, K, N, swiglu=True) == (128, 256, 1)
+    pg, pu = M.bctm_pack_weight(wg), M.bctm_pack_weight(wu)
+    out = M.bctm_swiglu(x, pg, pu)
+    assert np.array_equal(untile(M.bctm_swiglu(M.bctm_pack_rows(x), pg, pu, tiled=True), rows, N), host(out))
+    for part in (slice(0, 300), slice(N - 300, N)):
+        xh, gh, uh = host(x), host(wg[part].contiguous()), host(wu[part].contiguous())
+        xa, a, u = np.abs(R.bf16_to_f64(xh)), R.linear_f64(xh, gh), R.linear_f64(xh, uh)
+        mg, mu = xa @ np.abs(R.bf16_to_f64(gh)).T, xa @ np.abs(R.bf16_to_f64(uh)).T
+        slack = 2.0 ** -20 * (1.1 * mg * np.abs(u) + (np.abs(a) + 1.0) * mu + np.abs(a * u))   # as in test_swiglu
+        check_close(host(out[:, part].contiguous()), R.swiglu(xh, gh, uh), slack, f"swiglu, 512 features {rows}x{K}")
+
+
 # Chunks, where the widths together and each width alone take other workgroup tiles: bitwise where K is summed in as many
 # parts, else both within the rounding of fp32 sums (one bf16 spacing + 2^-20 of the products' absolute sum)
 @pytest.mark.parametrize("rows,K,widths", [(128, 160, (512, 128, 128)), (640, 288, (4096, 4096, 4096)),
