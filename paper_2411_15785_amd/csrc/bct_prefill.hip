@@ -1222,7 +1222,7 @@ hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
     const dim3 g = unit_grid((p.M + 127) / 128, units);
     // byte offset of the last lane's 16 bytes in 32 tokens' write queries: past 32 bits from 541201 heads of 128
     // (1082402 of 64) on
-    const bool far = (31 * (uint64_t)p.Hkv * p.d + 8) * 2 > 0xFFFFFFFFu;
+    const bool far = (31 * (uint64_t)p.Hkv * p.d + p.d - 8) * 2 > 0xFFFFFFFFu;
     if (d128 && far) hipLaunchKernelGGL((prefill_state_kernel<128, true>), g, dim3(256), 0, s, p);
     else if (far) hipLaunchKernelGGL((prefill_state_kernel<64, true>), g, dim3(256), 0, s, p);
     else if (d128) hipLaunchKernelGGL((prefill_state_kernel<128, false>), g, dim3(256), 0, s, p);
