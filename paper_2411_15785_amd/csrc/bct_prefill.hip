@@ -667,7 +667,8 @@ __global__ __launch_bounds__(512) void prefill_read_only_kernel(const PrefillPar
 // 1.65 GHz (B = 32, H = 32, M = 4096, T = 512: 2100 us) and as many at 2.1 GHz (216 workgroups of one round, 33 tiles: 59).  A
 // reader alone takes 2700.  Before, keys came as operand tiles (see RowTile), every wavefront requested its share, a
 // reader kept one operand in scratch and the sum's terms until after the products: 3300 cycles, 2270 us, 67.  The
-// requests are the writers' because the address unit takes a request in 16 cycles and holds up whoever asks.  Built, right
+// requests are the writers' because the address unit takes a request in 16 cycles and holds up whoever asks (which of them:
+// see `idle`).  Built, right
 // and not kept, us for the two sizes: a block's weights between the next 32 slots' score products 2220, 65; operands from
 // LDS a region earlier 2180, 65; writers with a higher priority 3720 cycles a tile; requests after the scores 3940.
 // The rows leave whole (see the end): 8-byte pieces of 32 rows a store and a token group's operands when they were needed took
@@ -706,18 +707,19 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
     else if constexpr (decltype(i)::v % 3 == 1) return sV1;
     else return sV2;
   };
-  auto request = [&](auto i, uint32_t tile) __attribute__((always_inline)) {
+  // nl of the tile's 4 NL load instructions of either matrix, `first` and the ones after it
+  auto request = [&](auto nl, auto i, uint32_t tile, int first) __attribute__((always_inline)) {
     const uint32_t t = min(tile, n - 1);   // past the end: the last tile again, never used
     const uint16_t *k = mk + (size_t)t * kTile, *v = mvc + (size_t)t * kTile;
 #pragma unroll
-    for (int j = 0; j < NL; ++j) {
-      const int ld = (wave & 3) * NL + j;
+    for (int j = 0; j < decltype(nl)::v; ++j) {
+      const int ld = first + j;
       lds_request(k + ld * 512, RT::source(ld, lane), stage_k(i) + ld * 512);
     }
     __builtin_amdgcn_sched_barrier(0);   // the keys are needed a tile before the values: see tile_end
 #pragma unroll
-    for (int j = 0; j < NL; ++j) {
-      const int ld = (wave & 3) * NL + j;
+    for (int j = 0; j < decltype(nl)::v; ++j) {
+      const int ld = first + j;
       lds_request(v + ld * 512, (uint32_t)lane * 16u, stage_v(i) + ld * 512);
     }
   };
@@ -746,9 +748,9 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
   };
   // End of tile i: this wavefront's LDS accesses are done; of its requests the values of tile i + 2 may still be on
   // their way, the keys of i + 2 (for the writers) and the values of i + 1 have arrived
-  auto tile_end = [&]() __attribute__((always_inline)) {
+  auto tile_end = [&](auto nl) __attribute__((always_inline)) {
     __builtin_amdgcn_s_waitcnt(kWaitLds);
-    __builtin_amdgcn_s_waitcnt(wait_vm(NL));
+    __builtin_amdgcn_s_waitcnt(wait_vm(decltype(nl)::v));
     bare_barrier();
   };
 
@@ -762,10 +764,21 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
     return (rho0 + first_row) / G >= left ? 0 : (int)(min((rho0 + last_row) / G, left - 1) / 32 + 1);
   };
   const int nsb = groups(32 * rg, 32 * rg + 31);
-  const bool asked = rg < groups(0, kTC - 1);
+  const int nasked = groups(0, kTC - 1);
+  const bool asked = rg < nasked;
+  // Who requests: every writer a quarter of a tile; where some writers have no weights to make (96 tokens or fewer to read) two
+  // of those half each or the only one all of it, so that nobody who computes waits for the address unit.  Us, with quarters
+  // always and so: B = 40, H = 37, M = 7680, d = 64, 4 tokens 1820 and 1702 (the read 720 and 602); B = 8, H = 8, M = 4096, d = 128, 20 tokens
+  // 141.9 and 134.4; B = 1, H = 7, M = 9216, d = 64, 90 tokens 170.0 and 152.7; B = 4, H = 8, M = 4096, d = 128, 80 tokens 127.8 and 124.7.
+  const int idle = 4 - nasked;
+  auto begin = [&](auto nl, int first) __attribute__((always_inline)) {
+    request(nl, Int<0>{}, 0, first);
+    request(nl, Int<1>{}, 1, first);
+  };
   if (!reader) {
-    request(Int<0>{}, 0);
-    request(Int<1>{}, 1);
+    if (idle == 0) begin(Int<NL>{}, rg * NL);
+    else if (idle == 1 && rg == 3) begin(Int<4 * NL>{}, 0);
+    else if (idle >= 2 && rg >= 2) begin(Int<2 * NL>{}, (rg - 2) * 2 * NL);
   }
   // this wavefront's rows as operand fragments, kept in registers.  A negative read scale moves into the
   // row (negating bf16 is exact), so that the largest raw score is also the largest scaled one.
@@ -785,7 +798,9 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
       x[ks] = __builtin_bit_cast(bf16x8, v ^ (u32x4){flip, flip, flip, flip});
     }
   }
-  tile_end();
+  if (idle == 1) tile_end(Int<4 * NL>{});
+  else if (idle >= 2) tile_end(Int<2 * NL>{});
+  else tile_end(Int<NL>{});
 
   if (!reader) {
     const float shift = present ? p.norm_w[(size_t)unit * T + rtok] : kNoRow;
@@ -800,21 +815,28 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
         for (int j = 0; j < 2; ++j) sW[(((it & 1) * 4 + rg) * 4 + 2 * k + j) * 64 + lane] = pack8(s[k], j);
       }
     };
-    auto tile = [&](auto i, uint32_t it) __attribute__((always_inline)) {
-      request(Int<decltype(i)::v + 2>{}, it + 2);
-      if (asked) weights(Int<decltype(i)::v + 1>{}, it + 1);   // past the end: of whatever tile is there, never used
-      tile_end();
+    // nl: the writer's requests of either matrix and tile, none (then all of them are others')
+    auto walk = [&](auto nl, auto weighs, int first) __attribute__((always_inline)) {
+      auto tile = [&](auto i, uint32_t it) __attribute__((always_inline)) {
+        if constexpr (decltype(nl)::v > 0) request(nl, Int<decltype(i)::v + 2>{}, it + 2, first);
+        if (decltype(weighs)::v && asked) weights(Int<decltype(i)::v + 1>{}, it + 1);   // past the end: of whatever tile is there, never used
+        tile_end(nl);
+      };
+      if (decltype(weighs)::v && asked) weights(Int<0>{}, 0);
+      tile_end(nl);
+      uint32_t it = 0;
+      for (; it + 3 <= n; it += 3) {
+        tile(Int<0>{}, it);
+        tile(Int<1>{}, it + 1);
+        tile(Int<2>{}, it + 2);
+      }
+      if (it < n) tile(Int<0>{}, it);
+      if (it + 1 < n) tile(Int<1>{}, it + 1);
     };
-    if (asked) weights(Int<0>{}, 0);
-    tile_end();
-    uint32_t it = 0;
-    for (; it + 3 <= n; it += 3) {
-      tile(Int<0>{}, it);
-      tile(Int<1>{}, it + 1);
-      tile(Int<2>{}, it + 2);
-    }
-    if (it < n) tile(Int<0>{}, it);
-    if (it + 1 < n) tile(Int<1>{}, it + 1);
+    if (idle == 0) walk(Int<NL>{}, Int<1>{}, rg * NL);
+    else if (idle == 1 && rg == 3) walk(Int<4 * NL>{}, Int<0>{}, 0);
+    else if (idle >= 2 && rg >= 2) walk(Int<2 * NL>{}, Int<0>{}, (rg - 2) * 2 * NL);
+    else walk(Int<0>{}, Int<1>{}, 0);
     __builtin_amdgcn_s_waitcnt(wait_vm(0));
     return;   // no barrier follows
   }
@@ -893,9 +915,9 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
   };
   auto step = [&](auto i, uint32_t it) __attribute__((always_inline)) {
     if (nsb > 0) tile(i, it);
-    tile_end();
+    tile_end(Int<NL>{});
   };
-  tile_end();   // the writers' first tile
+  tile_end(Int<NL>{});   // the writers' first tile
   uint32_t it = 0;
   for (; it + 3 <= n; it += 3) {
     step(Int<0>{}, it);

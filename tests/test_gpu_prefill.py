@@ -145,6 +145,15 @@ def test_prefill_tile_edges(P, R, B, Hq, Hkv, d, M, T, mode):
 
 # Either statistics kernel at the border between them: 384 slots (d = 64: 768) and the next size (one share each), up to 256
 # workgroups and more
+# one to four groups of 32 write tokens asked for in the last sub-chunk (which decides who requests the tiles), one to
+# seven tiles, workgroups of one launch with different numbers of them
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,M,T", [(1, 1, 64, 4), (2, 2, 128, 32), (1, 1, 192, 33), (2, 2, 256, 64), (1, 1, 320, 65), (2, 2, 64, 96),
+                                        (1, 1, 448, 97), (4, 1, 256, 200), (3, 1, 320, 128), (8, 2, 128, 50)])
+def test_prefill_groups_asked_for(P, R, Hq, Hkv, d, M, T):
+    test_prefill_chunk_matches_oracle(P, R, "groups", 2, Hq, Hkv, d, M, "bf16", T, "rw")
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,d,M,T", [(1, 2, 1, 128, 384, 140), (1, 2, 1, 128, 448, 140), (1, 1, 1, 64, 448, 70),
                                             (13, 20, 20, 64, 448, 3), (13, 20, 20, 128, 448, 3), (1, 2, 1, 64, 768, 140),
                                             (1, 2, 1, 64, 832, 140), (13, 20, 20, 64, 832, 3)])
