@@ -101,19 +101,25 @@ __device__ __forceinline__ void load_to_lds(const void* g, void* lds) {
 // offset bytes; or from an address per lane.  Written out because the compiler takes its own instruction for an access to
 // LDS in flight and answers it with a wait for all LDS reads before the next use of one, and adds the offset to a 64-bit
 // address in vector registers.  It counts as an outstanding vector-memory operation, which the compiler does not know:
-// whoever requests waits for it (wait_vm); the compiler's own waits only become stricter by it.
+// whoever requests waits for it (wait_vm); the compiler's own waits only become stricter by it.  The LDS address is an
+// operand bound to m0, so the compiler sets it.  Nor does the compiler know the distances that the load needs: 1 wait
+// state from a write of m0, 5 from a vector instruction that writes its scalar base (v_readfirstlane, a spilled register's
+// v_readlane).  So the load takes a copy of the base, made here by the scalar unit, which needs no distance on either
+// side and is the one instruction after m0 as well.  (s_nop 4 instead: write-only chunk of B = 32, H = 32, M = 4096, T = 512
+// 2200 us against 2180.)
 template <int BYTES = 16>
 __device__ __forceinline__ void lds_request(const void* base, uint32_t offset, void* lds) {
   static_assert(BYTES == 16 || BYTES == 4, "one of two instructions");
   const uint32_t to = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+  const void* from;
   if constexpr (BYTES == 4)
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(offset), "s"(base), "s"(to) : "memory", "m0");
+    asm volatile("s_mov_b64 %0, %2\n\tglobal_load_lds_dword %1, %0" : "=&s"(from) : "v"(offset), "s"(base), "{m0}"(to) : "memory");
   else
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(to) : "memory", "m0");
+    asm volatile("s_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0" : "=&s"(from) : "v"(offset), "s"(base), "{m0}"(to) : "memory");
 }
 __device__ __forceinline__ void lds_request(const void* lane_address, void* lds) {
   const uint32_t to = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(lane_address), "s"(to) : "memory", "m0");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(lane_address), "{m0}"(to) : "memory");
 }
 // A barrier that waits for nothing else: requests into LDS stay in flight across it.
 __device__ __forceinline__ void bare_barrier() {
