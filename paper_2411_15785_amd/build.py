@@ -24,6 +24,11 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
 FLAGS += os.environ.get("BCT_EXTRA_HIPCC_FLAGS", "").split()
 
 
+def diagnostics(stderr: str) -> str:
+    """What the compiler said, without the host pass's line that it does not know the GPU's feature."""
+    return "\n".join(l for l in stderr.splitlines() if l.strip() and "'-packed-fp32-ops' is not a recognized feature" not in l)
+
+
 def _compile(src: str, verbose: bool) -> str:
     obj = os.path.join(OBJ_DIR, os.path.basename(src) + ".o")
     cmd = [HIPCC, *FLAGS, "-c", src, "-o", obj]
@@ -32,8 +37,9 @@ def _compile(src: str, verbose: bool) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{r.stdout}\n{r.stderr}")
-    if verbose and r.stderr.strip():
-        print(r.stderr, flush=True)
+    said = diagnostics(r.stderr)   # warnings, whether verbose or not
+    if said:
+        print(said, flush=True)
     return obj
 
 

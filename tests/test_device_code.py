@@ -1,5 +1,6 @@
-"""What the compiler makes of the device code, without a GPU: no warnings, and the requests into LDS that are written
-out in assembly keep the distances that the hardware asks for (the compiler does not look inside)."""
+"""What the compiler makes of the device code, without a GPU: no warnings (and a build shows those there are), and the
+requests into LDS that are written out in assembly keep the distances that the hardware asks for (the compiler does
+not look inside)."""
 import os
 import re
 import subprocess
@@ -23,6 +24,18 @@ def prefill_isa(tmp_path_factory):
 def test_device_compile_has_no_warnings(prefill_isa):
     warnings = [l for l in prefill_isa[0].splitlines() if "warning:" in l]
     assert not warnings, f"{len(warnings)} warnings, the first: {warnings[0]}"
+
+
+def test_build_shows_the_compilers_warnings(tmp_path, monkeypatch, capsys):
+    cc = tmp_path / "cc"
+    cc.write_text("#!/bin/sh\n"
+                  "echo \"'-packed-fp32-ops' is not a recognized feature for this target (ignoring feature)\" >&2\n"
+                  "echo 'x.hip:3:5: warning: unused variable' >&2\n")
+    cc.chmod(0o755)
+    monkeypatch.setattr(build, "HIPCC", str(cc))
+    monkeypatch.setattr(build, "OBJ_DIR", str(tmp_path))
+    build._compile("x.hip", verbose=False)
+    assert capsys.readouterr().out == "x.hip:3:5: warning: unused variable\n"
 
 
 # A load must not come within 5 wait states of a vector instruction's write of its scalar base, nor within 1 of a write
