@@ -166,19 +166,27 @@ def bct_strerror(st: int) -> str:
 # those | without: decode_step of 4 memories of 64 x 64 10.3 | 6.1, a 512-wide MLP of one row 29 | 18.
 
 _torch_module = None
+_raw_stream = None   # device index -> address of torch's current stream there
+
+
+def _raw_stream_of(torch):
+    """torch's own short way to a stream's address, which is private; where a torch has none, by way of a stream object."""
+    return getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
+        (lambda index: torch.cuda.current_stream(index).cuda_stream)
 
 
 def _torch():
-    global _torch_module
+    global _torch_module, _raw_stream
     if _torch_module is None:
         import torch
+        _raw_stream = _raw_stream_of(torch)
         _torch_module = torch
     return _torch_module
 
 
 def _stream_ptr():
     torch = _torch()
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dptr(t):
@@ -189,7 +197,7 @@ def _launch(fn, device, *args):
     """fn(*args, the current stream of `device`), with that device current."""
     torch = _torch()
     if device.type == "cuda" and device.index == torch.cuda.current_device():
-        return fn(*args, torch._C._cuda_getCurrentRawStream(device.index))
+        return fn(*args, _raw_stream(device.index))
     with torch.cuda.device(device):
         return fn(*args, _stream_ptr())
 

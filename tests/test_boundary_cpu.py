@@ -3,6 +3,7 @@ include/bct.h declares, and validates its arguments before the first HIP call.""
 import ctypes
 import os
 import re
+import types
 
 import pytest
 
@@ -266,3 +267,55 @@ def test_launch_plans_of_the_five_workloads(L):
     st, _ = P.bct_plan_query(desc(capacity_M=100))
     assert st == P.BCT_ERR_UNSUPPORTED
     assert L.bct_plan_query(ctypes.byref(desc()), None) == P.BCT_ERR_INVALID_ARG
+
+
+class _TorchOfTwoDevices:
+    """As much of torch as a launch asks for: two devices, stream 100 + i current on device i."""
+
+    def __init__(self, private):
+        self.current, self.entered = 0, []
+        outer = self
+
+        class Device:
+            def __init__(self, device):
+                self.to = outer.current if device.index is None else device.index
+
+            def __enter__(self):
+                outer.entered.append(self.to)
+                self.back, outer.current = outer.current, self.to
+
+            def __exit__(self, *_):
+                outer.current = self.back
+
+        def stream(index):
+            return 100 + index
+        self._C = types.SimpleNamespace(**({"_cuda_getCurrentRawStream": stream} if private else {}))
+        self.cuda = types.SimpleNamespace(device=Device, current_device=lambda: outer.current,
+                                          current_stream=lambda index: types.SimpleNamespace(cuda_stream=stream(index)))
+
+
+@pytest.mark.parametrize("private", [True, False])
+def test_launches_go_to_the_device_of_their_tensors(monkeypatch, private):
+    """_launch, without a GPU: the device that is current is not entered, another one is, and left again however the call
+    ends; the stream is the called device's; a torch without the private function serves as well."""
+    torch = _TorchOfTwoDevices(private)
+    monkeypatch.setattr(binding, "_torch_module", torch)
+    monkeypatch.setattr(binding, "_raw_stream", binding._raw_stream_of(torch))
+    dev = lambda index: types.SimpleNamespace(type="cuda", index=index)
+    seen = lambda *args: (torch.current, args)
+    assert binding._launch(seen, dev(0), 7, None) == (0, (7, None, 100)) and torch.entered == []
+    assert binding._launch(seen, dev(1), 7) == (1, (7, 101)) and torch.entered == [1] and torch.current == 0
+    assert binding._launch(seen, dev(None)) == (0, (100,)) and torch.entered == [1, 0]
+    with pytest.raises(ZeroDivisionError):
+        binding._launch(lambda s: 1 // 0, dev(1))
+    assert torch.current == 0
+    torch.current = 1
+    assert binding._stream_ptr() == 101
+    assert binding._launch(seen, dev(0)) == (0, (100,)) and torch.current == 1
+
+
+def test_every_pointer_parameter_is_declared(L):
+    """Pointers go to the library as plain integers, which ctypes cuts to 32 bits where no argument type is declared."""
+    from paper_2411_15785_amd import model
+    ML = model.mlib()
+    assert [n for n in binding.EXPORTS + model.MODEL_EXPORTS if getattr(ML, n).argtypes is None] == []
