@@ -129,7 +129,9 @@ __device__ __forceinline__ void bare_barrier() {
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("" ::: "memory");
 }
-// s_waitcnt operands: at most n vector-memory operations outstanding / no LDS operation outstanding
+// s_waitcnt operands: at most n vector-memory operations outstanding / no LDS operation outstanding.  The counter has six
+// bits: a wavefront keeps at most kMostVm operations outstanding.
+constexpr int kMostVm = 63;
 constexpr int wait_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
 constexpr int kWaitLds = 15 | (7 << 4) | (0 << 8) | (3 << 14);
 

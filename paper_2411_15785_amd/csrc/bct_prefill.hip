@@ -771,8 +771,13 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
   // always and so: B = 40, H = 37, M = 7680, d = 64, 4 tokens 1820 and 1702 (the read 720 and 602); B = 8, H = 8, M = 4096, d = 128, 20 tokens
   // 141.9 and 134.4; B = 1, H = 7, M = 9216, d = 64, 90 tokens 170.0 and 152.7; B = 4, H = 8, M = 4096, d = 128, 80 tokens 127.8 and 124.7.
   const int idle = 4 - nasked;
+  // Outstanding: two tiles here, then three matrices' requests (the values of a tile and all of the one after the next).
+  // One idle writer at d = 128 starts with 64, more than the counter holds: it waits for the first.
+  static_assert(3 * 4 * NL <= kMostVm, "a lone requester's tiles in flight");
   auto begin = [&](auto nl, int first) __attribute__((always_inline)) {
+    constexpr int kAll = 4 * decltype(nl)::v;
     request(nl, Int<0>{}, 0, first);
+    if constexpr (kAll > kMostVm) __builtin_amdgcn_s_waitcnt(wait_vm(kMostVm - kAll / 2));
     request(nl, Int<1>{}, 1, first);
   };
   if (!reader) {
