@@ -766,8 +766,9 @@ __global__ __launch_bounds__(512, 2) void prefill_read_online_kernel(const Prefi
   const int nsb = groups(32 * rg, 32 * rg + 31);
   const int nasked = groups(0, kTC - 1);
   const bool asked = rg < nasked;
-  // Who requests: every writer a quarter of a tile; where some writers have no weights to make (96 tokens or fewer to read) two
-  // of those half each or the only one all of it, so that nobody who computes waits for the address unit.  Us, with quarters
+  // Who requests (every workgroup has a row, so at least one writer is asked): every writer a quarter of a tile; where some
+  // writers have no weights to make (96 tokens or fewer to read) two of those half each or the only one all of it, so that
+  // nobody who computes waits for the address unit.  Us, with quarters
   // always and so: B = 40, H = 37, M = 7680, d = 64, 4 tokens 1820 and 1702 (the read 720 and 602); B = 8, H = 8, M = 4096, d = 128, 20 tokens
   // 141.9 and 134.4; B = 1, H = 7, M = 9216, d = 64, 90 tokens 170.0 and 152.7; B = 4, H = 8, M = 4096, d = 128, 80 tokens 127.8 and 124.7.
   const int idle = 4 - nasked;
@@ -1232,9 +1233,14 @@ hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
 
-  auto read = [&](uint32_t c_begin, uint32_t c_count) -> hipError_t {
-    p.c_begin = c_begin;
-    const dim3 g = unit_grid(c_count * p.G, units);
+  // Row tiles of 128 read rows (T * G rows): G of each whole sub-chunk, as many as have a row of the last one.  All G of a
+  // last sub-chunk of few tokens would be workgroups that walk the whole memory for nothing: us a chunk, all G | those
+  // with a row: G = 8, Hkv = 8, M = 4096, d = 128: B = 8, T = 4 203 | 130, B = 32, T = 130 1631 | 1229 (a chunk that only reads
+  // 174 | 106, 1534 | 1106); B = 32, M = 2048, d = 64, T = 10 296 | 89.
+  auto read = [&]() -> hipError_t {
+    p.c_begin = 0;
+    const uint32_t left = p.T - (nb - 1) * kTC;
+    const dim3 g = unit_grid((nb - 1) * p.G + (left * p.G + kTC - 1) / kTC, units);
     const dim3 rblock(512);
     if (p.has_write) {
       if (d128) hipLaunchKernelGGL((prefill_read_online_kernel<128>), g, rblock, 0, s, p);
@@ -1259,7 +1265,7 @@ hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
   // every sub-chunk reads its starting state from a copy of MV in the workspace (with a write: copy c, in operand
   // tiles, is what the state kernel left when it reached sub-chunk c, MV_0 for c = 0; without a write: the one
   // transposed copy made above serves all of them), so one launch serves all sub-chunks
-  if (p.has_read && (e = read(0, nb)) != hipSuccess) return e;
+  if (p.has_read && (e = read()) != hipSuccess) return e;
   return hipSuccess;
 }
 

@@ -143,8 +143,6 @@ def test_prefill_tile_edges(P, R, B, Hq, Hkv, d, M, T, mode):
     test_prefill_chunk_matches_oracle(P, R, f"edge_m{M}_t{T}", B, Hq, Hkv, d, M, "bf16", T, mode)
 
 
-# Either statistics kernel at the border between them: 384 slots (d = 64: 768) and the next size (one share each), up to 256
-# workgroups and more
 # one to four groups of 32 write tokens asked for in the last sub-chunk (which decides who requests the tiles), one to
 # seven tiles, workgroups of one launch with different numbers of them
 @pytest.mark.parametrize("d", [64, 128])
@@ -154,6 +152,17 @@ def test_prefill_groups_asked_for(P, R, Hq, Hkv, d, M, T):
     test_prefill_chunk_matches_oracle(P, R, "groups", 2, Hq, Hkv, d, M, "bf16", T, "rw")
 
 
+# Last sub-chunks whose read rows (tokens x query heads of a KV head) fill part of one 128-row tile, exactly one, one and one
+# row more, and all G: each launch has as many row tiles as have a row
+@pytest.mark.parametrize("Hq,Hkv,d,T", [(8, 1, 128, 4), (8, 1, 64, 15), (16, 2, 128, 16), (8, 1, 64, 17), (16, 2, 64, 130), (8, 1, 128, 144),
+                                        (8, 1, 128, 256), (9, 3, 128, 171), (9, 3, 64, 170), (5, 1, 128, 129), (8, 1, 64, 1), (7, 1, 128, 147)])
+@pytest.mark.parametrize("mode", ["rw", "read_only"])
+def test_prefill_row_tiles_of_the_last_sub_chunk(P, R, Hq, Hkv, d, T, mode):
+    test_prefill_chunk_matches_oracle(P, R, f"rows_t{T}", 2, Hq, Hkv, d, 192, "bf16", T, mode)
+
+
+# Either statistics kernel at the border between them: 384 slots (d = 64: 768) and the next size (one share each), up to 256
+# workgroups and more
 @pytest.mark.parametrize("B,Hq,Hkv,d,M,T", [(1, 2, 1, 128, 384, 140), (1, 2, 1, 128, 448, 140), (1, 1, 1, 64, 448, 70),
                                             (13, 20, 20, 64, 448, 3), (13, 20, 20, 128, 448, 3), (1, 2, 1, 64, 768, 140),
                                             (1, 2, 1, 64, 832, 140), (13, 20, 20, 64, 832, 3)])
