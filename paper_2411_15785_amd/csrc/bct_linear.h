@@ -27,7 +27,7 @@ struct LinearTile {
 };
 
 // The tile of launch_linear_rows for a shape: host logic, what that launch itself goes by.
-LinearTile linear_rows_tile(uint32_t rows, uint32_t N, bool swiglu);
+LinearTile linear_rows_tile(uint32_t rows, uint32_t K, uint32_t N, bool swiglu, bool x_tiled);
 
 // The matrix-core projection of many rows (bct_linear_rows.hip).  w2 non-null: SwiGLU of w and w2.  x_tiled /
 // out_tiled: activations in the tiled order.  N is a multiple of 128 (SwiGLU: 64), K of 32.

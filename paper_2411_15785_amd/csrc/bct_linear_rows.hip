@@ -292,7 +292,7 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
 // The tile of a shape.  It decides in how many parts K is summed as well, so a result's last bits depend on the
 // row and feature counts (bctm_linear_tile tells).  The time of a launch is the number of rounds its workgroups take on 256 compute units
 // times the K steps times what a step of a resident workgroup takes; measured us per K step at 640 and 16384
-// rows, K = 11008 / 4096:
+// rows, K = 11008 / 4096, one set of weights again and again, so out of the caches:
 //   256 x 256             one workgroup per compute unit  0.46 (few) - 0.69 (chip full)
 //   128 x 512             one                             0.80
 //   128 x 256             one                             0.34 - 0.44
@@ -300,14 +300,20 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
 //   128 x 128, K in two   one                             0.19 - 0.25
 //   64 x 64, K in two     two                             0.11 alone, 0.19 for a pair
 // so 256 x 256 wins where the chip is full (4 rounds of it against 16 of 128 x 128), the others where its
-// workgroups are few: 640 rows x 11008 -> 4096 takes 157 us in 256 x 256, 117, 88, 67, 94 in the last four.  128 x 512 has the
-// work of 256 x 256 and 5 / 4 of its loads; it is there for row counts that 256 wastes, where it saves a round of
-// workgroups: us without | with it, K = 4096, 640 rows SwiGLU -> 11008 (430 | 215 tiles) 120 | 107, 557 rows -> 24576 122 | 109, 1045
-// -> 13824 116 | 104, 1838 -> 26112 346 | 306, 2936 -> 22528 424 | 392; where the rule leaves it, 5437 -> 20992 685 | 672, 3668 -> 35328
-// 784 | 815, 5193 -> 37888 1159 | 1269.
+// workgroups are few: 640 rows x 11008 -> 4096 takes 157 us in 256 x 256, 117, 88, 67, 94 in the last four (with weights from
+// memory, as a stack of layers has them, the 67 are 96).
+// 128 x 512 has the work of 256 x 256 and 5 / 4 of its loads; it is there for row counts that 256 wastes, where it saves
+// a round of workgroups.  With weights from memory, us without | with it, tiled x: against 128 x 256 838 rows, 4096 -> 53248
+// 367 | 326, 384, 8192 -> 37376 242 | 212; against 128 x 128 526, 4096 -> 66560 366 | 314, 319, 4096 -> 69632 239 | 216 (a predicted 2 %:
+// the price of many pairs is low).  Against 256 x 256 it depends on K: up to 4096 885, 4096 -> 66560 426 | 414, 3690, 2048 ->
+// 22528 280 | 269, 1057, 512 -> 68608 111 | 102 (44 shapes, 0.986 to 1.12 times as fast); from 5120 on a step of 256 x 256 takes 0.62 to
+// 0.68, of 128 x 512 0.78 to 0.83, and with one round of six or seven saved it loses: 1658, 8192 -> 24576 SwiGLU 1019 | 1070, 4654,
+// 11008 -> 20992 1626 | 1676 (15 shapes, 0.95 to 1.015; on another box 0.96 to 1.0), hence 83 there; one of five: 2135, 11008 -> 14592 SwiGLU 1103 | 1071 (7, 0.98 to
+// 1.045).  A row-major x waits longer for its rows, and the wider tile wins in all 37 shapes: 4654, 11008 -> 20992 2105 | 1841, 1911,
+// 1024 -> 50176 218 | 212.
 enum RowsShape { kTile256, kTile128x512, kTile128x256, kTile128, kTile128K2, kTile64K2 };
 
-RowsShape rows_shape(uint32_t rows, uint32_t bcols) {
+RowsShape rows_shape(uint32_t rows, uint32_t bcols, uint32_t K, bool x_tiled) {
   auto tiles = [&](uint32_t bm, uint32_t bn) { return (uint64_t)((rows + bm - 1) / bm) * (bcols / bn); };
   // hundredths of a us per K step: one workgroup per compute unit at a time; two, a last one may have it alone
   auto one = [](uint64_t t, uint64_t cost) { return (t + 255) / 256 * cost; };
@@ -329,7 +335,8 @@ RowsShape rows_shape(uint32_t rows, uint32_t bcols) {
     take(kTile128x256, one(tiles(128, 256), 44));
     take(kTile256, one(tiles(256, 256), 69));
   }
-  if (bcols % 512 == 0) take(kTile128x512, one(tiles(128, 512), 80));
+  // (dear only against 256 x 256, which sums K in one part as well: the parts do not depend on x's order)
+  if (bcols % 512 == 0) take(kTile128x512, one(tiles(128, 512), best == kTile256 && x_tiled && K > 4096 ? 83 : 80));
   return best;
 }
 
@@ -346,7 +353,7 @@ template <bool SWIGLU, bool XT>
 void launch_rows(const void* x, const void* w, const void* w2, const void* residual, const LinearOut& dst, uint32_t rows,
                  uint32_t K, uint32_t N, bool out_tiled, hipStream_t s) {
   const uint32_t bcols = SWIGLU ? 2 * N : N;
-  const RowsShape shape = rows_shape(rows, bcols);
+  const RowsShape shape = rows_shape(rows, bcols, K, XT);
   if constexpr (!SWIGLU && !XT) {
     // Row-major activations under 128 x 128 tiles (feature counts that 256 does not divide), many of them, and weights
     // that the last-level cache does not keep: in pairs.  us, in pairs | step by step, 70 shapes: 2894 rows, 10400 -> 11904
@@ -369,9 +376,9 @@ void launch_rows(const void* x, const void* w, const void* w2, const void* resid
 
 }  // namespace
 
-LinearTile linear_rows_tile(uint32_t rows, uint32_t N, bool swiglu) {
+LinearTile linear_rows_tile(uint32_t rows, uint32_t K, uint32_t N, bool swiglu, bool x_tiled) {
   const uint32_t per = swiglu ? 2 : 1;   // B columns of a feature
-  switch (rows_shape(rows, per * N)) {
+  switch (rows_shape(rows, per * N, K, x_tiled)) {
     case kTile256: return {256, 256 / per, 1};
     case kTile128x512: return {128, 512 / per, 1};
     case kTile128x256: return {128, 256 / per, 1};

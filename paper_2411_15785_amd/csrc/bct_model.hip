@@ -527,7 +527,7 @@ bct_status bctm_linear_tile(uint32_t rows, uint32_t K, uint32_t N, uint32_t swig
   if (K % 32 != 0 || N % 16 != 0) return mfail(BCT_ERR_UNSUPPORTED, "K must be a multiple of 32 and N of 16");
   const uint32_t kernel = linear_kernel_of(rows, N, swiglu != 0);
   const LinearTile t = kernel == BCTM_KERNEL_TILE128 || kernel == BCTM_KERNEL_TILE256
-                           ? linear_rows_tile(rows, N, swiglu != 0)
+                           ? linear_rows_tile(rows, K, N, swiglu != 0, (flags & BCTM_X_TILED) != 0)
                            : streaming_tile(kernel, rows, N, swiglu != 0, flags);
   *tile_rows = t.rows;
   *tile_features = t.features;

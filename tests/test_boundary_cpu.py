@@ -137,6 +137,26 @@ def test_projection_tile():
     assert ML.bctm_linear_tile(4, 64, 32, 0, 0, k[0], None, k[2]) == P.BCT_ERR_INVALID_ARG
 
 
+def test_projection_tile_of_512_features():
+    """128 x 512 against 256 x 256: for tiled inputs of more than 4096 only where it saves a round of five or fewer; K is summed in as
+    many parts for either order of x."""
+    from paper_2411_15785_amd import model as Mo
+    tile = Mo.bctm_linear_tile
+    for rows, K, N, swiglu in [(1658, 8192, 24576, True), (1642, 8192, 47616, False), (4654, 11008, 20992, False),
+                               (2149, 5120, 37888, False), (5969, 11008, 6912, True), (4654, 4128, 20992, False)]:
+        per = 2 if swiglu else 1
+        assert tile(rows, K, N, swiglu, tiled=True) == (256, 256 // per, 1)
+        assert tile(rows, K, N, swiglu) == (128, 512 // per, 1)
+        assert tile(rows, 4096, N, swiglu, tiled=True) == (128, 512 // per, 1)
+    for rows, K, N, swiglu in [(2135, 11008, 14592, True), (4948, 8192, 13312, False), (838, 11008, 53248, False), (319, 8192, 69632, False)]:
+        assert tile(rows, K, N, swiglu, tiled=True) == tile(rows, K, N, swiglu) == (128, 256 if swiglu else 512, 1)
+    for rows in range(128, 9000, 61):
+        for N in range(256, 40000, 1280):
+            for K in (4096, 8192):
+                for swiglu in (False, True):
+                    assert tile(rows, K, N, swiglu, tiled=True)[2] == tile(rows, K, N, swiglu)[2]
+
+
 def desc(**kw):
     d = dict(capacity_M=4096, batch=32, n_q_heads=32, n_kv_heads=32, head_dim=128, dtype=P.BCT_BF16,
              read_scale=0.0884, write_scale=0.0884, flags=0)

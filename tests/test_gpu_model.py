@@ -280,6 +280,18 @@ def test_linear_tile_of_512_features(M, rows, K):
         check_close(host(out[:, part].contiguous()), R.linear(xh, wh, rh), 2.0 ** -20 * mass, f"512 features {rows}x{K}")
 
 
+# Row counts and K for which a tiled x takes 256 x 256 and a row-major one 128 x 512: the same bits
+def test_linear_orders_of_x_with_different_tiles(M):
+    rows, K, N = 2149, 4128, 37888
+    assert M.bctm_linear_tile(rows, K, N, tiled=True) == (256, 256, 1) and M.bctm_linear_tile(rows, K, N) == (128, 512, 1)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    x = torch.randn((rows, K), generator=g, dtype=torch.bfloat16, device="cuda")
+    wp = M.bctm_pack_weight(torch.randn((N, K), generator=g, dtype=torch.bfloat16, device="cuda").mul_(K ** -0.5))
+    res = torch.randn((rows, N), generator=g, dtype=torch.bfloat16, device="cuda")
+    assert torch.equal(M.bctm_linear(x, wp, res).view(torch.int16), M.bctm_linear(M.bctm_pack_rows(x), wp, res).view(torch.int16))
+
+
 @pytest.mark.parametrize("rows,K", [(557, 32), (640, 160)])
 def test_swiglu_tile_of_512_features(M, rows, K):
     N = 11776
