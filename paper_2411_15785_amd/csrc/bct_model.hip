@@ -181,7 +181,7 @@ __global__ __launch_bounds__(64 * WAVES) void linear_kernel(const uint16_t* __re
 // The row of a workgroup.  Workgroups go to the eight XCDs in turn; a 128-byte line of the tiled order holds 8 inputs
 // of 8 consecutive rows, and rows in launch order would leave parts of every line in eight L2s.  So 16 consecutive
 // rows (1 KB tiles) are those of one XCD, for as many whole groups of 128 rows as there are.  16384 rows x 4096:
-// 80 us against 139 (8 rows per workgroup: 110), 2048 rows 10.3 against 16.3.  That is 3.5 TB/s, not the rate of memory: the
+// 80 us against 139 (8 rows per workgroup: 110), 2048 rows 10.3 against 16.3.  That is 3.4 TB/s, not the rate of memory: the
 // same 268 MB take pack_rows_kernel 52 us.  A workgroup here holds one row of 8 KB and waits for it and for the sum.
 __device__ __forceinline__ uint32_t tiled_row(uint32_t block, uint32_t rows) {
   if (block >= rows / 128 * 128) return block;
@@ -189,27 +189,37 @@ __device__ __forceinline__ uint32_t tiled_row(uint32_t block, uint32_t rows) {
 }
 
 // One workgroup per row; a thread keeps its NV 16-byte chunks of the row in registers between the sum of squares and the
-// scaling.  The gains are requested with the row, so that it waits for memory once (us, with the row | after the sum | after
-// it and eight chunks a thread for every width: 4 x 4096 2.5 | 2.6 | 2.9, 640 x 4096 4.5 | 4.7 | 5.1, 4096 x 8192 39 | 44 | 46,
-// 16384 x 12288 259 | 283 | 296); LATE: after the sum, see rmsnorm_late.
-template <int NV, bool LATE>
+// scaling.  When the gains and the chunks are requested depends on the size (rmsnorm_form):
+//   kGainsWithRow   all at once, so that a workgroup waits for memory once.  us, so | gains after the sum | after it and
+//                   eight chunks a thread for every width: 4 x 4096 2.5 | 2.6 | 2.9, 640 x 4096 4.5 | 4.7 | 5.1, 4096 x 8192 39 |
+//                   44 | 46, 16384 x 12288 259 | 283 | 296
+//   kGainsLate      the gains after the sum: less in flight
+//   kChunkByChunk   so, and a chunk is requested when the one before has arrived: the workgroups of 16 rows that write one
+//                   line of the tiled order stay closer together, and fewer lines leave the L2 in parts
+enum RmsForm { kGainsWithRow, kGainsLate, kChunkByChunk };
+
+template <int NV, RmsForm FORM>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const uint16_t* x, const uint16_t* gain, uint16_t* out,
                                                       uint32_t rows, uint32_t dim, float eps, uint32_t out_tiled) {
   __shared__ float s_part[4];
   const uint32_t row = out_tiled ? tiled_row(blockIdx.x, rows) : blockIdx.x;
   const uint16_t* xr = x + (size_t)row * dim;
   u32x4 v[NV], gv[NV];
+  if constexpr (FORM != kChunkByChunk) {
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    // chunks past the end: the first one again, not counted and not stored
-    const uint32_t c = (threadIdx.x + i * 256) * 8, from = c < dim ? c : 0u;
-    v[i] = *(const u32x4*)(xr + from);
-    if (!LATE) gv[i] = *(const u32x4*)(gain + from);
+    for (int i = 0; i < NV; ++i) {
+      // chunks past the end: the first one again, not counted and not stored
+      const uint32_t c = (threadIdx.x + i * 256) * 8, from = c < dim ? c : 0u;
+      v[i] = *(const u32x4*)(xr + from);
+      if (FORM == kGainsWithRow) gv[i] = *(const u32x4*)(gain + from);
+    }
   }
   float ss = 0.f;
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    if ((threadIdx.x + i * 256) * 8 < dim) {
+    const uint32_t c = (threadIdx.x + i * 256) * 8;
+    if (c < dim) {
+      if constexpr (FORM == kChunkByChunk) v[i] = *(const u32x4*)(xr + c);
       float f[8];
       unpack16<BF16>(v[i], f);
 #pragma unroll
@@ -227,7 +237,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const uint16_t* x, const u
     if (c < dim) {
       float f[8], g[8];
       unpack16<BF16>(v[i], f);
-      unpack16<BF16>(LATE ? *(const u32x4*)(gain + c) : gv[i], g);
+      unpack16<BF16>(FORM == kGainsWithRow ? gv[i] : *(const u32x4*)(gain + c), g);
 #pragma unroll
       for (int e = 0; e < 8; ++e) f[e] = f[e] * r * g[e];
       const u32x4 o = pack16_round<BF16>(f);
@@ -310,10 +320,25 @@ bct_status launched(const char* what, hipError_t e = hipGetLastError()) {
   snprintf(g_merr, sizeof(g_merr), "%s launch failed: %s", what, hipGetErrorString(e));
   return BCT_ERR_HIP;
 }
-// Narrow rows that together leave the caches: the gains after the sum.  us, with the row | after the sum: 16384 x 4096 90 |
-// 76, 8192 x 4096 45 | 39, 16384 x 2048 36.2 | 34.5; below 32 M elements 8192 x 3072 21.6 | 21.4, 4096 x 4096 15.2 | 15.7, 16384 x 1024
-// 15.4 | 15.4; wider 16384 x 5120 97 | 101, 8192 x 6144 54 | 64.
-bool rmsnorm_late(uint32_t rows, uint32_t dim) { return dim <= 4096 && (uint64_t)rows * dim >= (32u << 20); }
+// The form of a size, by what it measured: us, kGainsWithRow | kGainsLate | kChunkByChunk, the same buffers again and again
+// (x and out in the last-level cache where they fit) / buffers from memory.
+// Row-major outputs: 4096 x 4096 11.5 | 12.0 | 12.2 / 14.1 | 14.6 | 14.8; 16384 x 2048 20.8 | 21.3 | - / 24.2 | 25.2 | -; 16384 x
+// 4096 38.7 | 38.9 | 38.9 / 46.0 | 47.2 | 46.6; 32768 x 5120 116 | 115 | 118 / 115 | 115 | 117; 16384 x 12288 139 | 141 | 154.
+// Tiled outputs, from 8 M elements on.  Up to 4096 wide: 1024 x 4096 5.83 | 5.93 | 6.02 / 6.50 | 6.99 | 7.11; 2048 9.27 | 9.40 | 9.60
+// / 11.9 | 10.6 | 10.7; 6144 21.8 | 22.0 | 23.0 / 34.3 | 31.1 | 32.6; 9000 x 3584 26.6 | 26.0 | 27.9 / 42.8 | 38.2 | 39.3; 16384 - | 52.7
+// | 50.5 / - | 81.9 | 79.7; 32768 - | 164 | 157 / - | 166 | 154; but 32768 x 3584 - | 128 | 135 / - | 129 | 135 (the border lies at 4000:
+// 24000 rows 108 | 112 / 113 | 113, 50000 236 | 234 / 237 | 233); 8192 x 1024 8.8 | 9.3 | 9.3 / 12.5 | 11.8 | 11.7, 12000 12.3 | 12.3 | 12.1
+// / 19.0 | 17.7 | 17.4, 32768 x 2048 - | 47.7 | 47.5 / - | 72.4 | 73.8.
+// Wider: 9000 x 4224 33.7 | 34.8 | 34.8 / 52.1 | 51.3 | 50.9; 14000 x 5120 89.7 | 93.5 | 84.1 / 88.2 | 91.2 | 86.9; 50000 x 5120 351 | 343
+// | 312; 16384 x 6144 116 | 132 | 120 / 118 | 136 | 120; 24000 180 | 206 | 174 / 181 | 205 | 175; 50000 425 | 442 | 363; 32768 x 7168 295 |
+// 344 | 298; 32768 x 8192 338 | 410 | 354.  Not chosen by: 2048 rows of 8192 or 12288 from memory, 21.8 | 22.8 | 20.3, from the
+// cache 16.6 | 17.9 | 19.4.
+RmsForm rmsnorm_form(uint32_t rows, uint32_t dim, bool out_tiled) {
+  const uint64_t n = (uint64_t)rows * dim, M = 1u << 20;
+  if (!out_tiled) return kGainsWithRow;
+  if (dim <= 4000 || (dim <= 4096 && n < 48 * M)) return n >= (dim > 2048 ? 8 : 10) * M ? kGainsLate : kGainsWithRow;
+  return dim <= 6144 && n >= (dim <= 5120 ? 48 : 128) * M ? kChunkByChunk : kGainsWithRow;
+}
 
 bool al16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
@@ -418,10 +443,13 @@ bct_status bctm_rmsnorm(const void* x, const void* gain, void* out, uint32_t row
     return mfail(BCT_ERR_UNSUPPORTED, "tiled activations need a multiple of 32 columns");
   if ((flags & BCTM_OUT_TILED) && x == out) return mfail(BCT_ERR_INVALID_ARG, "a tiled output cannot overwrite x");
   if (!al16(x) || !al16(gain) || !al16(out)) return mfail(BCT_ERR_MISALIGNED, "pointers must be 16-byte aligned");
-  const bool late = rmsnorm_late(rows, dim);
-  const auto kernel = dim <= 2048 ? (late ? rmsnorm_kernel<1, true> : rmsnorm_kernel<1, false>)
-                      : dim <= 4096 ? (late ? rmsnorm_kernel<2, true> : rmsnorm_kernel<2, false>)
-                      : dim <= 8192 ? rmsnorm_kernel<4, false> : rmsnorm_kernel<8, false>;
+  const RmsForm form = rmsnorm_form(rows, dim, (flags & BCTM_OUT_TILED) != 0);
+  const auto kernel = dim <= 2048   ? (form == kGainsLate ? rmsnorm_kernel<1, kGainsLate> : rmsnorm_kernel<1, kGainsWithRow>)
+                      : dim <= 4096 ? (form == kChunkByChunk ? rmsnorm_kernel<2, kChunkByChunk>
+                                       : form == kGainsLate  ? rmsnorm_kernel<2, kGainsLate>
+                                                             : rmsnorm_kernel<2, kGainsWithRow>)
+                      : dim <= 8192 ? (form == kChunkByChunk ? rmsnorm_kernel<4, kChunkByChunk> : rmsnorm_kernel<4, kGainsWithRow>)
+                                    : rmsnorm_kernel<8, kGainsWithRow>;
   hipLaunchKernelGGL(kernel, dim3(rows), dim3(256), 0, (hipStream_t)hip_stream, (const uint16_t*)x, (const uint16_t*)gain,
                      (uint16_t*)out, rows, dim, eps, flags & BCTM_OUT_TILED);
   return launched("rmsnorm");

@@ -394,9 +394,12 @@ def test_rmsnorm_chunks_of_a_thread(M, dim):
     check_close(host(M.bctm_rmsnorm(dev(x), dev(g), 1e-5)), ref, 2.0 ** -20 * np.abs(R.bf16_to_f64(ref)), f"rmsnorm 2x{dim}")
 
 
-# so many elements that the gains are requested after the sum of squares: a row's bits do not depend on it, nor on the
-# order of the output (the last group of 128 rows, whose rows go to the XCDs otherwise, is a partial one)
-@pytest.mark.parametrize("rows,dim", [(16400, 2048), (8225, 4088), (8193, 4096)])
+# so many elements that, for a tiled output, the gains are requested after the sum of squares, or the chunks one by one:
+# a row's bits do not depend on it, nor on the order of the output (the last group of 128 rows, whose rows go to the XCDs
+# otherwise, is a partial one).  Borders at 8, 10, 48 and 128 M elements and at widths of 2048, 4000, 4096, 5120 and 6144
+@pytest.mark.parametrize("rows,dim", [(16400, 2048), (8225, 4088), (8193, 4096), (2049, 4096), (10250, 1024), (12600, 4000),
+                                      (12300, 4032), (12300, 4096), (11950, 4224), (9840, 5120), (26100, 5152), (21900, 6144),
+                                      (21900, 6176)])
 def test_rmsnorm_of_many_rows(M, rows, dim):
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(rows)
