@@ -662,9 +662,11 @@ __global__ __launch_bounds__(512) void prefill_read_only_kernel(const PrefillPar
 // factor are the lane's own, and what is accumulated (32 rows x d columns and 32 rows x 128 tokens) never
 // needs another wavefront.  The writers are one tile ahead; one barrier per tile.  Keys and MV_c come through LDS,
 // requested two tiles ahead without a trip through registers.
-// What bounds it: a reader and a writer share a SIMD's issue slots.  A tile of 64 slots is 64 matrix instructions there (2048
-// cycles) beside 1300 cycles of vector instructions, and the older wavefront always goes first; it takes 3050 cycles at
-// 1.65 GHz (B = 32, H = 32, M = 4096, T = 512: 2100 us) and as many at 2.1 GHz (216 workgroups of one round, 33 tiles: 59).  A
+// What bounds it: the SIMD that has most to multiply (d = 128: a writer 16 products a tile, a reader 32 and 4 for each group of
+// 32 tokens it can read, so 52, 56, 60 and 64 for G = 1; the barrier waits for the 64), and that a reader and a writer share
+// its issue slots.  A tile of 64 slots is up to 2048 cycles of matrix instructions
+// beside 1300 cycles of vector instructions, and the older wavefront always goes first; it takes 3050 cycles at
+// 1.65 GHz (B = 32, H = 32, M = 4096, T = 512: 2100 us) and as many at 2.1 GHz (192 workgroups of one round, 33 tiles: 59).  A
 // reader alone takes 2700.  Before, keys came as operand tiles (see RowTile), every wavefront requested its share, a
 // reader kept one operand in scratch and the sum's terms until after the products: 3300 cycles, 2270 us, 67.  The
 // requests are the writers' because the address unit takes a request in 16 cycles and holds up whoever asks (which of them:

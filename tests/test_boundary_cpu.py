@@ -124,7 +124,7 @@ def test_projection_tile():
     assert tile(9, 4096, 12288, tiled=True) == (16, 48, 8) and tile(9, 4096, 14400) == (16, 48, 8)
     assert tile(16, 4096, 11008, swiglu=True) == (16, 16, 4) and tile(32, 4096, 11008, swiglu=True) == (32, 16, 4)
     assert tile(4096, 4096, 96, swiglu=True) == (32, 16, 4)
-    # the matrix-core kernel's five tiles, plain and SwiGLU (half as many features of two matrices)
+    # the matrix-core kernel's tiles (128 x 512: below), plain and SwiGLU (half as many features of two matrices)
     assert tile(128, 4096, 128) == (64, 64, 2) and tile(640, 11008, 4096) == (128, 128, 2)
     assert tile(1024, 4096, 4096) == (128, 128, 2) and tile(1030, 4096, 4096) == (128, 256, 1)
     assert tile(640, 4096, 12288) == (128, 256, 1) and tile(1000, 4096, 32768) == (256, 256, 1)

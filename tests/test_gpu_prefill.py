@@ -172,7 +172,7 @@ def test_prefill_statistics_kernels(P, R, B, Hq, Hkv, d, M, T, mode):
 
 
 # So many KV heads that the write queries of a 32-token tile span 4 GB: the last head count at which a
-# 32-bit byte offset reaches them all ((31 * heads * d + 8) * 2 < 2^32), and the next one.  Memories are independent, so the oracle
+# 32-bit byte offset reaches them all ((31 * heads * d + d - 8) * 2 < 2^32), and the next one.  Memories are independent, so the oracle
 # takes a few of them (62 GB on the device, drawn there).
 @pytest.mark.parametrize("Hkv", [541200, 541201])
 def test_prefill_write_queries_a_32_bit_offset_apart(P, R, Hkv):
