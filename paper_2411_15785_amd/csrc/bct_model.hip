@@ -195,7 +195,8 @@ __device__ __forceinline__ uint32_t tiled_row(uint32_t block, uint32_t rows) {
 //                   44 | 46, 16384 x 12288 259 | 283 | 296
 //   kGainsLate      the gains after the sum: less in flight
 //   kChunkByChunk   so, and a chunk is requested when the one before has arrived: the workgroups of 16 rows that write one
-//                   line of the tiled order stay closer together, and fewer lines leave the L2 in parts
+//                   line of the tiled order stay closer together, and fewer lines leave the L2 in parts (16384 x 4096, 134 MB
+//                   of output: 168 MB written, with the gains late 212)
 enum RmsForm { kGainsWithRow, kGainsLate, kChunkByChunk };
 
 template <int NV, RmsForm FORM>

@@ -1238,7 +1238,8 @@ hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
   // Row tiles of 128 read rows (T * G rows): G of each whole sub-chunk, as many as have a row of the last one.  All G of a
   // last sub-chunk of few tokens would be workgroups that walk the whole memory for nothing: us a chunk, all G | those
   // with a row: G = 8, Hkv = 8, M = 4096, d = 128: B = 8, T = 4 203 | 130, B = 32, T = 130 1631 | 1229 (a chunk that only reads
-  // 174 | 106, 1534 | 1106); B = 32, M = 2048, d = 64, T = 10 296 | 89.
+  // 174 | 106, 1534 | 1106); B = 32, M = 2048, d = 64, T = 10 296 | 89.  (Workgroups that return at once do not help: with G = 8 one
+  // in eight has a row, and workgroups go to the eight XCDs in turn, so that one XCD would do all the work: 205.)
   auto read = [&]() -> hipError_t {
     p.c_begin = 0;
     const uint32_t left = p.T - (nb - 1) * kTC;
