@@ -307,10 +307,10 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
 // 367 | 326, 384, 8192 -> 37376 242 | 212; against 128 x 128 526, 4096 -> 66560 366 | 314, 319, 4096 -> 69632 239 | 216 (a predicted 2 %:
 // the price of many pairs is low).  Against 256 x 256 it depends on K: up to 4096 885, 4096 -> 66560 426 | 414, 3690, 2048 ->
 // 22528 280 | 269, 1057, 512 -> 68608 111 | 102 (44 shapes, 0.986 to 1.12 times as fast); from 5120 on a step of 256 x 256 takes 0.62 to
-// 0.68, of 128 x 512 0.78 to 0.83, and with one round of six or seven saved it loses: 1658, 8192 -> 24576 SwiGLU 1019 | 1070, 4654,
-// 11008 -> 20992 1626 | 1676 (15 shapes, 0.95 to 1.015; on another box 0.96 to 1.0), hence 83 there; one of five: 2135, 11008 -> 14592 SwiGLU 1103 | 1071 (7, 0.98 to
-// 1.045).  A row-major x waits longer for its rows, and the wider tile wins in all 37 shapes: 4654, 11008 -> 20992 2105 | 1841, 1911,
-// 1024 -> 50176 218 | 212.
+// 0.68, of 128 x 512 0.78 to 0.83, and where it saves one round of six or seven it loses: 1658, 8192 -> 24576 SwiGLU 1019 | 1070,
+// 4654, 11008 -> 20992 1626 | 1676 (15 shapes, 0.95 to 1.015; on another card 0.96 to 1.0), hence 83 there, which leaves it one of
+// five: 2135, 11008 -> 14592 SwiGLU 1103 | 1071 (7 shapes, 0.98 to 1.045).  A row-major x waits longer for its rows, and the wider
+// tile wins in all 37 shapes: 4654, 11008 -> 20992 2105 | 1841, 1911, 1024 -> 50176 218 | 212.
 enum RowsShape { kTile256, kTile128x512, kTile128x256, kTile128, kTile128K2, kTile64K2 };
 
 RowsShape rows_shape(uint32_t rows, uint32_t bcols, uint32_t K, bool x_tiled) {

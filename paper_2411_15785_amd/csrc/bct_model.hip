@@ -190,11 +190,11 @@ __device__ __forceinline__ uint32_t tiled_row(uint32_t block, uint32_t rows) {
 
 // One workgroup per row; a thread keeps its NV 16-byte chunks of the row in registers between the sum of squares and the
 // scaling.  When the gains and the chunks are requested depends on the size (rmsnorm_form):
-//   kGainsWithRow   all at once, so that a workgroup waits for memory once.  us, so | gains after the sum | after it and
+//   kGainsWithRow   all at once, so that a workgroup waits for memory once.  us, this | gains after the sum | after it and
 //                   eight chunks a thread for every width: 4 x 4096 2.5 | 2.6 | 2.9, 640 x 4096 4.5 | 4.7 | 5.1, 4096 x 8192 39 |
 //                   44 | 46, 16384 x 12288 259 | 283 | 296
 //   kGainsLate      the gains after the sum: less in flight
-//   kChunkByChunk   so, and a chunk is requested when the one before has arrived: the workgroups of 16 rows that write one
+//   kChunkByChunk   as that, and a chunk is requested when the one before has arrived: the workgroups of 16 rows that write one
 //                   line of the tiled order stay closer together, and fewer lines leave the L2 in parts (16384 x 4096, 134 MB
 //                   of output: 168 MB written, with the gains late 212)
 enum RmsForm { kGainsWithRow, kGainsLate, kChunkByChunk };
