@@ -71,9 +71,9 @@ def dominant_kernel(plan, rescores, w):
     gt = 1 if w.G <= 1 else 2 if w.G <= 2 else 4 if w.G <= 4 else 8
     if plan["one_launch"]:
         return f"decode_fused_kernel<{dt},{w.d},{gt}>"
-    if w.dtype == "bf16" and w.d == 128 and w.G > 2:
+    if w.dtype == "bf16" and w.G > 2:
         again = "true" if rescores else "false"
-        return f"mv_pass_gqa_kernel<true,{plan['mv_workgroup']},{norm},{plan['mv_loads_per_lane']},{again}>"
+        return f"mv_pass_gqa_kernel<true,{plan['mv_workgroup']},{norm},{plan['mv_loads_per_lane']},{again},{w.d}>"
     return f"mv_pass_kernel<{dt},{w.d},{gt},true,true,{plan['mv_workgroup']},{plan['mv_loads_per_lane']},{norm}>"
 
 

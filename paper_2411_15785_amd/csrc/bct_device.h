@@ -135,6 +135,12 @@ constexpr int kMostVm = 63;
 constexpr int wait_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
 constexpr int kWaitLds = 15 | (7 << 4) | (0 << 8) | (3 << 14);
 
+// The workgroup's LDS writes so far are there for all its wavefronts; vector-memory operations stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_s_waitcnt(kWaitLds);
+  bare_barrier();
+}
+
 template <int I>
 struct Int {
   static constexpr int v = I;
@@ -206,6 +212,71 @@ __device__ __forceinline__ f32x4 score16(const u32x4* key, const u32x4* query) {
     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, key[ks]), __builtin_bit_cast(bf16x8, query[ks]),
                                                 c, 0, 0, 0);
   return c;
+}
+
+// out[g][column] += sum over slots of weight[g][slot] * MV[slot][column] on v_mfma_f32_16x16x32_bf16, for eight slots of
+// every lane.  raw: the lane's 16-byte chunk (8 columns) of its eight consecutive slots.  Lane l is row / column c = l % 16 of
+// the operands and their eight entries 8 * (l / 16) of the contraction.
+// LPS = 16 lanes to a slot row: the contraction runs over the wavefront's 32 slots; operand e, a transposition in the lane,
+// is element e of chunk c.  acc[e], element v of a lane: query head 4 * (l / 16) + v, column 8 c + e.
+// LPS = 8: lanes l and l ^ 8 hold the same chunk of different slots.  They exchange halves, so that lanes c < 8 have
+// elements 0 to 3 and lanes c >= 8 elements 4 to 7 of both groups of slots: two contractions over 32 slots, part j the
+// slots of lanes with l / 8 % 2 = j.  acc[e]: column 8 (c % 8) + 4 (c / 8) + e.
+// hi, lo: per part the weights of head c for the slots 8 * (l / 16) .. of the part, as bf16 parts whose sum has fp32 grade.
+template <int LPS>
+struct ReadShape {
+  static constexpr int kParts = 16 / LPS, kProducts = LPS / 2;
+  static __device__ __forceinline__ uint32_t column(uint32_t c) { return LPS == 16 ? 8 * c : 8 * (c % 8) + 4 * (c / 8); }
+};
+__device__ __forceinline__ f32x4 mfma_hi_lo(u32x4 hi, u32x4 lo, u32x4 b, f32x4 c) {
+  const bf16x8 bv = __builtin_bit_cast(bf16x8, b);
+  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, hi), bv, c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, lo), bv, c, 0, 0, 0);
+}
+template <int LPS>
+__device__ __forceinline__ void mfma_read(const u32x4* raw, const u32x4* hi, const u32x4* lo, f32x4* acc) {
+  // element e % 2 of word w of the eight slots
+  auto operand = [](const uint32_t* w, int odd) -> u32x4 {
+    u32x4 t;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      t[i] = odd ? ((w[2 * i] >> 16) | (w[2 * i + 1] & 0xFFFF0000u)) : ((w[2 * i] & 0xFFFFu) | (w[2 * i + 1] << 16));
+    return t;
+  };
+  if constexpr (LPS == 16) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      uint32_t w[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) w[u] = raw[u][e / 2];
+      acc[e] = mfma_hi_lo(hi[0], lo[0], operand(w, e % 2), acc[e]);
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      // row_ror:8 is the lane l ^ 8; the bank mask names the lanes that take from it, the others keep their own word
+      uint32_t a[8], b[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        a[u] = (uint32_t)__builtin_amdgcn_update_dpp((int)raw[u][k], (int)raw[u][2 + k], 0x128, 0xF, 0xC, false);
+        b[u] = (uint32_t)__builtin_amdgcn_update_dpp((int)raw[u][2 + k], (int)raw[u][k], 0x128, 0xF, 0x3, false);
+      }
+#pragma unroll
+      for (int o = 0; o < 2; ++o) {
+        acc[2 * k + o] = mfma_hi_lo(hi[0], lo[0], operand(a, o), acc[2 * k + o]);
+        acc[2 * k + o] = mfma_hi_lo(hi[1], lo[1], operand(b, o), acc[2 * k + o]);
+      }
+    }
+  }
+}
+// Eight fp32 weights as bf16 operands: their roundings, and what the roundings left.
+__device__ __forceinline__ void split_hi_lo(const float* w, u32x4& hi, u32x4& lo) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t h = pack_bf16x2(w[2 * i], w[2 * i + 1]);
+    hi[i] = h;
+    lo[i] = pack_bf16x2(w[2 * i] - __uint_as_float(h << 16), w[2 * i + 1] - __uint_as_float(h & 0xFFFF0000u));
+  }
 }
 
 // One wavefront merges the per-tile (max, sum of exp2(score - max)) pairs of a row, up to 128 of them (lane l

@@ -213,14 +213,16 @@ static constexpr MvShape kWide = {512, 8};   // 64 KB per workgroup
 static constexpr uint64_t kWholeMinBytes = 32u << 10, kWholeMaxBytes = 256u << 10;
 static constexpr uint64_t kWholeMinUnits = 192, kWholeMaxTotal = 64ull << 20;
 
-// bf16, d = 128, G > 2: the MFMA read (bct_mv_pass_gqa.hip), again 16 KB one-shot workgroups.  Measured at
+// bf16, G > 2: the MFMA read (bct_mv_pass_gqa.hip), again 16 KB one-shot workgroups.  Measured at
 // B = 64, Hkv = 8, G = 4, M = 8192 (MV pass alone): 128 threads 351 us, 256 threads 386 us, 512 threads 415 us,
 // against 429 us for the vector-ALU read in its best shape (512 x 8); the smaller workgroups leave more
 // partial outputs to sum (merge 21 us against 7 us).  16 loads per lane: 128 threads 397 us, 64 threads 357 us.
+// d = 64 against the vector-ALU read in its shape (512 x 8), whole step: G = 4: 32 memories of 2048 slots 17.5 -> 14.4, 256 of
+// 2048 44.9 -> 42.5, 1024 of 16384 1077 -> 948; G = 3, 512 of 8192 247 -> 213; G = 8, 256 of 8192 300 -> 144.
 static constexpr MvShape kGqa = {128, 8};
 
 void plan_mv_pass(DecodeParams& p, int dtype) {
-  const bool gqa = p.G > 2 && dtype == 1 && p.d == 128;
+  const bool gqa = p.G > 2 && dtype == 1;
   MvShape s = (p.G <= 2) ? kSmall : gqa ? kGqa : kWide;
   const uint64_t mem = (uint64_t)p.M * p.d * (dtype == 0 ? 4u : 2u), units = (uint64_t)p.B * p.Hkv;
   if (p.G <= 1 && mem > kWholeMinBytes && mem <= kWholeMaxBytes && units >= kWholeMinUnits && units * mem <= kWholeMaxTotal)
@@ -253,7 +255,7 @@ void plan_mv_pass(DecodeParams& p, int dtype) {
   const uint64_t scratch = wgs * (256u * (1 + p.G) + (p.S > 1 ? 512u * p.G : 0u));   // 64 slots a workgroup
   const uint64_t cycle = (uint64_t)p.S * p.Hkv, xcd_keys = (uint64_t)p.Hkv * p.M * 256u /
                                                            (cycle % 8 == 0 ? 8 : cycle % 4 == 0 ? 4 : cycle % 2 == 0 ? 2 : 1);
-  p.rescore = gqa && scratch >= (192u << 20) && xcd_keys <= (5u << 19) ? 1u : 0u;
+  p.rescore = gqa && p.d == 128 && scratch >= (192u << 20) && xcd_keys <= (5u << 19) ? 1u : 0u;
 }
 
 template <typename DT, int D, int GT, int BS, int U, bool NORM>
@@ -288,23 +290,22 @@ static bool launch_shape(const DecodeParams& p, hipStream_t s) {
     else launch_mode<DT, D, 2, 256, 4>(p, s);
     return true;
   }
-  if (p.mv_bs == kWide.bs && p.mv_u == kWide.u && G > 2) {
-    if (!p.has_read) launch_mode<DT, D, 1, 512, 8>(p, s);
-    else if (G <= 4) launch_mode<DT, D, 4, 512, 8>(p, s);
-    else launch_mode<DT, D, 8, 512, 8>(p, s);
-    return true;
-  }
-  if (p.mv_u == 8 && G > 2 && !p.has_read) {   // write-only step of a cache whose reads take the MFMA pass
-    if (p.mv_bs == 256) launch_mode<DT, D, 1, 256, 8>(p, s);
-    else if (p.mv_bs == 128) launch_mode<DT, D, 1, 128, 8>(p, s);
-    else return false;
+  if constexpr (DT::kElemsPerVec == 4) {
+    if (p.mv_bs == kWide.bs && p.mv_u == kWide.u && G > 2) {
+      if (!p.has_read) launch_mode<DT, D, 1, 512, 8>(p, s);
+      else if (G <= 4) launch_mode<DT, D, 4, 512, 8>(p, s);
+      else launch_mode<DT, D, 8, 512, 8>(p, s);
+      return true;
+    }
+  } else if (p.mv_bs == kGqa.bs && p.mv_u == kGqa.u && G > 2 && !p.has_read) {
+    launch_mode<DT, D, 1, 128, 8>(p, s);   // write-only step of a cache whose reads take the MFMA pass
     return true;
   }
   return false;
 }
 
 hipError_t launch_stream(const DecodeParams& p, int dtype, hipStream_t s) {
-  if (dtype == 1 && p.d == 128 && p.G > 2 && p.has_read) return launch_stream_gqa(p, s);
+  if (dtype == 1 && p.G > 2 && p.has_read) return launch_stream_gqa(p, s);
   bool ok;
   if (dtype == 0) ok = (p.d == 128) ? launch_shape<F32, 128>(p, s) : launch_shape<F32, 64>(p, s);
   else ok = (p.d == 128) ? launch_shape<BF16, 128>(p, s) : launch_shape<BF16, 64>(p, s);

@@ -1,4 +1,4 @@
-// The MV pass for several query heads per KV head (bf16, d = 128, G > 2; gfx950).
+// The MV pass for several query heads per KV head (bf16, G > 2; gfx950).
 //
 // The update of MV is the same read-modify-write stream as in bct_mv_pass.hip.
 // What changes is the read: with G query heads the output is
@@ -7,18 +7,13 @@
 // bound by those FMAs (and by every one of the 16 lanes of a slot row computing
 // all G softmax weights again), not by memory.  Here the contraction over the
 // wavefront's 32 slots runs on v_mfma_f32_16x16x32_bf16:
-//   B operand = MV_new (exactly the bf16 values just stored): lane (sub, sl)
-//     holds columns 8 sub .. 8 sub + 7 of the slots 8 sl .. 8 sl + 7; an in-lane
-//     8 x 8 transpose of 16-bit elements turns its 8 row registers into 8
-//     operands, operand e = column 8 sub + e for the lane's 8 slots: column
-//     index of the MFMA = sub, contraction entries 8 (l / 16) + u = the slots;
-//   A operand = the softmax weights: lane (sub, sl) computes the weights of ONE
-//     query head, g = sub, for its 8 slots (lanes sub >= G hold zeros), split
-//     into hi + lo bf16 parts (two MFMAs) so that the weights keep fp32 grade;
-//   accumulator e of lane (sub, sl): out[g = 4 sl + v][column 8 sub + e].
-// The MFMA also sums over the four lane groups, so no lane exchange is needed.
+//   B operand = MV_new (exactly the bf16 values just stored), A operand = the softmax weights: mfma_read.  A lane computes
+//     the weights of ONE query head (row l % 16; rows >= G hold zeros), split into hi + lo bf16 parts (two products) so that
+//     they keep fp32 grade.
+// The products also sum over the lane groups, so no lane exchange of sums is needed.  d = 64, G = 8, 256 memories of 8192
+// slots: 155 us the step against 300 with the read on the vector ALU.
 //
-// RESCORE (keys shared by the batch): the scores are not read from memory but computed again from the
+// RESCORE (d = 128, keys shared by the batch): the scores are not read from memory but computed again from the
 // workgroup's 16 KB of keys (from L2: every sequence's workgroups read the same table): two v_mfma_f32_16x16x32_bf16 per 32 inputs,
 // key row 4 a + c of group n = slot 8 a + 4 n + c, column g = query head g, column 15 = the write row.  Lane
 // (sub, sl) then holds, in the two groups, exactly the scores of head g = sub for its 8 slots, the A
@@ -31,30 +26,31 @@ namespace bct {
 
 namespace {
 
-typedef float f32x4v __attribute__((ext_vector_type(4)));
-
-template <bool WRITE, int BS, bool NORM, int U, bool RESCORE>
+template <bool WRITE, int BS, bool NORM, int U, bool RESCORE, int D>
 __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
-  constexpr int D = 128, NB = U / 8, NW = BS / 64, SPB = NW * 4 * U;   // a wavefront covers 4 U slots
+  constexpr int LPS = D / 8, SPI = 64 / LPS, PARTS = ReadShape<LPS>::kParts;   // lanes per slot row, slots per load instruction
+  constexpr int NB = U / 8, NW = BS / 64, SPB = NW * SPI * U;
   constexpr uint32_t W = WRITE ? 1u : 0u;
   __shared__ float s_red[NW * kMaxG * D];
 
-  static_assert(!RESCORE || U == 8, "a lane's slots are two MFMA groups of four");
+  static_assert(!RESCORE || (U == 8 && PARTS == 1), "a lane's slots are two MFMA groups of four");
+  static_assert(PARTS == 1 || NB == 1, "a part's slots are eight, one block of loads");
   const uint32_t split = blockIdx.x, unit = block_unit();
   if (unit >= p.B * p.Hkv) return;
   const uint32_t b = unit / p.Hkv, h = unit % p.Hkv;
   const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
-  const int sub = lane % 16, sl = lane / 16;
+  const int sub = lane % LPS, sl = lane / LPS;   // 16-byte chunk of a slot row, group of U slots
+  const int col = lane % 16, kg = lane / 16;     // query head (row of A), group of eight entries of the contraction
   const uint32_t R = p.R, G = p.G, M = p.M;
 
-  // M is a multiple of 64: the 32 slots of a wavefront are all inside the memory or all outside
-  const uint32_t slot0 = split * SPB + wave * (4 * U) + sl * U;
+  // M is a multiple of 64: the SPI * U (32 or 64) slots of a wavefront are all inside the memory or all outside
+  const uint32_t slot0 = split * SPB + wave * (SPI * U) + sl * U;
   const bool active = slot0 < M;
   uint16_t* mv = (uint16_t*)p.mv + ((size_t)unit * M + slot0) * D + sub * 8;
 
   // RESCORE: the keys and this lane's query row (column sub), requested before MV
   u32x4 kf[RESCORE ? 2 : 1][4], xq[4];
-  const bool wcol = WRITE && sub == 15;
+  const bool wcol = WRITE && col == 15;
   if (RESCORE) {
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) xq[ks] = (u32x4){0u, 0u, 0u, 0u};
@@ -81,7 +77,7 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
     for (int u = 0; u < U; ++u) raw[u] = __builtin_nontemporal_load((const u32x4*)(mv + (size_t)u * D));
   }
 
-  // (max, 1/sum) of the write row and of this lane's read row (query head g = sub)
+  // (max, 1/sum) of the write row and of this lane's read row (query head g = col)
   float2 nw = make_float2(0.f, 0.f), nr = make_float2(0.f, 0.f);
   if (NORM) {
     // all rows' pairs are requested before the first is reduced (rows past R repeat row 0 and are dropped)
@@ -99,20 +95,22 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
           if (p.gate) inv *= p.gate[(size_t)b * p.gate_bstride + h];
           nw = make_float2(mx, inv);
         }
-        if (r == W + (uint32_t)sub && r >= W) nr = make_float2(mx, inv);
+        if (r == W + (uint32_t)col && r >= W) nr = make_float2(mx, inv);
       }
     }
   } else {
     if (WRITE) nw = p.norm[(size_t)unit * R];
-    if ((uint32_t)sub < G) nr = p.norm[(size_t)unit * R + W + sub];
+    if ((uint32_t)col < G) nr = p.norm[(size_t)unit * R + W + col];
   }
 
   // rw: the lane's weights as an A operand (zero in lanes without a query head); ww: the write weights of its slots, with
   // stored scores only where they are used (here as well, the pass takes 1-2 % longer)
   const float* sc = p.scores + (size_t)unit * R * M + slot0;  // row r at sc + r * M
-  float rw[U], ww[U];
+  float rw[PARTS][U], ww[U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) rw[u] = 0.f;
+  for (int j = 0; j < PARTS; ++j)
+#pragma unroll
+    for (int u = 0; u < U; ++u) rw[j][u] = 0.f;
   if (RESCORE) {
 #pragma unroll
     for (int u = 0; u < U; ++u) ww[u] = 0.f;
@@ -126,37 +124,36 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
         for (int v = 0; v < 4; ++v) {
           const float e = fast_exp2(c[v] * scale - n2.x) * n2.y;
           if (WRITE) ww[4 * n + v] = row_lane<15>(e);
-          rw[4 * n + v] = (uint32_t)sub < G ? e : 0.f;
+          rw[0][4 * n + v] = (uint32_t)col < G ? e : 0.f;
         }
       }
     }
   } else {
-    if (active && (uint32_t)sub < G) {
+    if (active && (uint32_t)col < G) {
+      // this lane's entries of the contraction: its own slots with one part, with two those of both groups
+      const float* from = PARTS == 1 ? sc : p.scores + (size_t)unit * R * M + split * SPB + wave * (SPI * U) + kg * (PARTS * U);
 #pragma unroll
-      for (int k = 0; k < U / 4; ++k) {
-        const f32x4v a = *(const f32x4v*)(sc + (size_t)(W + sub) * M + 4 * k);
+      for (int j = 0; j < PARTS; ++j)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) rw[4 * k + i] = fast_exp2(a[i] - nr.x) * nr.y;
-      }
+        for (int k = 0; k < U / 4; ++k) {
+          const f32x4 a = *(const f32x4*)(from + (size_t)(W + col) * M + j * U + 4 * k);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) rw[j][4 * k + i] = fast_exp2(a[i] - nr.x) * nr.y;
+        }
     }
   }
   // hi + lo bf16 parts of the lane's weights, 8 slots per block: the A operands
-  u32x4 ahi[NB], alo[NB];
+  u32x4 ahi[NB][PARTS], alo[NB][PARTS];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-    for (int w2 = 0; w2 < 4; ++w2) {
-      const float r0 = rw[8 * nb + 2 * w2], r1 = rw[8 * nb + 2 * w2 + 1];
-      const uint32_t hw = pack_bf16x2(r0, r1);
-      ahi[nb][w2] = hw;
-      alo[nb][w2] = pack_bf16x2(r0 - __uint_as_float(hw << 16), r1 - __uint_as_float(hw & 0xFFFF0000u));
-    }
+    for (int j = 0; j < PARTS; ++j) split_hi_lo(&rw[j][8 * nb], ahi[nb][j], alo[nb][j]);
 
   if (WRITE && active) {
     if (!RESCORE) {
 #pragma unroll
       for (int k = 0; k < U / 4; ++k) {
-        const f32x4v a = *(const f32x4v*)(sc + 4 * k);
+        const f32x4 a = *(const f32x4*)(sc + 4 * k);
 #pragma unroll
         for (int i = 0; i < 4; ++i) ww[4 * k + i] = fast_exp2(a[i] - nw.x) * nw.y;
       }
@@ -175,33 +172,18 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
     }
   }
 
-  // in-lane transpose of the 8 x 8 block of bf16 (slot u, column e) and the products
-  f32x4v acc[8];
+  constexpr int NP = ReadShape<LPS>::kProducts;
+  f32x4 acc[NP];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    f32x4v z = {0.f, 0.f, 0.f, 0.f};
+  for (int e = 0; e < NP; ++e) acc[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      u32x4 t;
-#pragma unroll
-      for (int w2 = 0; w2 < 4; ++w2) {
-        const uint32_t lo = raw[8 * nb + 2 * w2][e / 2], hi = raw[8 * nb + 2 * w2 + 1][e / 2];
-        t[w2] = (e % 2 == 0) ? ((lo & 0xFFFFu) | (hi << 16)) : ((lo >> 16) | (hi & 0xFFFF0000u));
-      }
-      const bf16x8 bv = __builtin_bit_cast(bf16x8, t);
-      z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ahi[nb]), bv, z, 0, 0, 0);
-      z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, alo[nb]), bv, z, 0, 0, 0);
-    }
-    acc[e] = z;
-  }
-
-  // accumulator e, element v of lane (sub, sl): query head 4 sl + v, column 8 sub + e
+  for (int nb = 0; nb < NB; ++nb) mfma_read<LPS>(raw + 8 * nb, ahi[nb], alo[nb], acc);
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    const uint32_t g = 4 * sl + v;
+    const uint32_t g = 4 * kg + v;
     if (g < G) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) s_red[(wave * kMaxG + g) * D + 8 * sub + e] = acc[e][v];
+      for (int e = 0; e < NP; ++e) s_red[(wave * kMaxG + g) * D + ReadShape<LPS>::column(col) + e] = acc[e][v];
     }
   }
   __syncthreads();
@@ -221,27 +203,33 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
 
 }  // namespace
 
-template <int BS, int U>
+template <int BS, int U, int D>
 static void launch_gqa_bs(const DecodeParams& p, hipStream_t s) {
   const dim3 grid = unit_grid(p.S, (uint64_t)p.B * p.Hkv), block(BS);
+  if constexpr (D == 128) {
+    if (p.rescore) {
+      if (p.has_write) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U, true, D>), grid, block, 0, s, p);
+      else hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, false, U, true, D>), grid, block, 0, s, p);
+      return;
+    }
+  }
   if (p.has_write) {
-    if (p.rescore) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U, true>), grid, block, 0, s, p);
-    else if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, true, U, false>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U, false>), grid, block, 0, s, p);
+    if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, true, U, false, D>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U, false, D>), grid, block, 0, s, p);
   } else {
-    if (p.rescore) hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, false, U, true>), grid, block, 0, s, p);
-    else if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, true, U, false>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, false, U, false>), grid, block, 0, s, p);
+    if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, true, U, false, D>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, false, U, false, D>), grid, block, 0, s, p);
   }
 }
 
-// bf16, d = 128, G > 2, a step with a read.  The launch shape is the plan's: 128 threads, 8 loads per lane
-// (the kernel is written for any multiple of 8 loads; 16 measured slower, see plan_mv_pass).
+// bf16, G > 2, a step with a read.  The launch shape is the plan's: 128 threads, 8 loads per lane
+// (with d = 128 the kernel is written for any multiple of 8 loads; 16 measured slower, see plan_mv_pass).
 hipError_t launch_stream_gqa(const DecodeParams& p, hipStream_t s) {
-  if (p.d != 128 || p.G <= 2 || p.G > kMaxG || !p.has_read) return hipErrorInvalidConfiguration;
+  if (p.G <= 2 || p.G > kMaxG || !p.has_read) return hipErrorInvalidConfiguration;
   if (p.mv_bs != 128 || p.mv_u != 8) return hipErrorInvalidConfiguration;
-  if (p.rescore && p.fuse_norm) return hipErrorInvalidConfiguration;
-  launch_gqa_bs<128, 8>(p, s);
+  if (p.rescore && (p.fuse_norm || p.d != 128)) return hipErrorInvalidConfiguration;
+  if (p.d == 128) launch_gqa_bs<128, 8, 128>(p, s);
+  else launch_gqa_bs<128, 8, 64>(p, s);
   return hipGetLastError();
 }
 

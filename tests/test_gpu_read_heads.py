@@ -1,0 +1,36 @@
+"""The streaming step's matrix-core read of several query heads with 64 columns: edges of its 64-slot wavefronts and
+128-slot workgroups, against the oracle."""
+import pytest
+
+import bct_synth as syn
+from _util import make_pair, sub, to_dev, to_np
+from test_gpu_parity import check_out, check_state_one_step
+
+pytestmark = pytest.mark.gpu
+
+
+# one wavefront of two with slots, a partial last workgroup, whole ones; statistics merged in the pass and by their own launch
+@pytest.mark.parametrize("B,Hkv,G,M,seq", [(1, 1, 3, 64, 0), (3, 2, 4, 192, 0), (2, 3, 5, 1024, 1), (5, 1, 8, 2112, 0),
+                                           (24, 43, 3, 2048, 0)])
+def test_steps_from_a_common_state(B, Hkv, G, M, seq):
+    import paper_2411_15785_amd as P
+    from oracle import bct_ref as R
+    w = syn.Workload("heads", 1, B, Hkv * G, Hkv, 64, M, "bf16", 3)
+    few = [0, B - 1] if B > 8 else None
+    ref, gpu, mk, mv, bs = make_pair(w, R.RefCache, P.BctCache, flags=seq | P.BCT_STEP_STREAMING, mv0=True, batch_subset=few)
+    st, plan = P.bct_plan_query(gpu.desc)
+    assert st == P.BCT_OK and plan["mv_workgroup"] == 128 and plan["mv_loads_per_lane"] == 8
+    assert plan["normaliser_launch"] == (1 if B * Hkv * M > 16384 * 128 else 0)
+    for t, (read, write) in enumerate(((True, True), (False, True), (True, False))):
+        q, wq, wv = syn.make_step(w, t)
+        q, wq, wv = q if read else None, wq if write else None, wv if write else None
+        before = ref.values()
+        whole = to_np(gpu.values_view(), "bf16").copy()
+        whole[bs] = before
+        gpu.set_values(to_dev(whole, "bf16"))
+        o_ref = ref.decode_step(sub(q, bs), sub(wq, bs), sub(wv, bs))
+        o = gpu.decode_step(to_dev(q, "bf16"), to_dev(wq, "bf16"), to_dev(wv, "bf16"))
+        what = f"M={M} G={G} read={read} write={write}"
+        if read:
+            check_out(to_np(o, "bf16")[bs], o_ref, "bf16", what)
+        check_state_one_step(to_np(gpu.values_view(), "bf16")[bs], ref.values(), "bf16", what, before=before)
