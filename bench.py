@@ -63,14 +63,25 @@ def cpu_baseline(w, seconds_budget=20.0):
     }
 
 
-def dominant_kernel(plan, rescores, w):
+def dominant_kernel(plan, rescores, whole, w):
     """The instantiation of the MV pass (or the one-launch step) that this plan launches for a step with a
     write and a read, spelled as rocprofv3 prints its template arguments."""
     dt = "BF16" if w.dtype == "bf16" else "F32"
     norm = "false" if plan["normaliser_launch"] else "true"
     gt = 1 if w.G <= 1 else 2 if w.G <= 2 else 4 if w.G <= 4 else 8
+    wgs, threads = whole
+    if wgs:
+        if w.dtype == "bf16" and w.G > 2:
+            gt = 8
+        slots = threads * 16 // (w.d // wgs * (2 if w.dtype == "bf16" else 4))
+        loads = next(u for u in (4, 8, 16) if w.M <= u * slots)
+        if threads == 1024:
+            loads = 16
+        elif w.dtype == "bf16" and w.G > 2:
+            loads = max(loads, 8)
+        return f"decode_whole_kernel<{dt},{w.d},{gt},{loads},{wgs},{threads}>"
     if plan["one_launch"]:
-        return f"decode_fused_kernel<{dt},{w.d},{gt}>"
+        return f"decode_fused_kernel<{dt},{w.d}>"
     if w.dtype == "bf16" and w.G > 2:
         again = "true" if rescores else "false"
         return f"mv_pass_gqa_kernel<true,{plan['mv_workgroup']},{norm},{plan['mv_loads_per_lane']},{again},{w.d}>"
@@ -119,10 +130,11 @@ def config_leg(name, pkg, syn, torch, np, reps=5):
     gbs = nbytes / (t_us * 1e-6) / 1e9
     _, plan = pkg.bct_plan_query(c.desc)
     _, rescores = pkg.bct_plan_rescores(c.desc)
+    whole = pkg.bct_plan_whole(c.desc)[1:]
     leg = {"shape": f"B={w.B}, Hq={w.Hq}, Hkv={w.Hkv}, d={w.d}, M={w.M}, {w.dtype}", "us_per_layer_step": t_us,
            "us_replays": us, "launch": f"HIP graph of {n} steps, median of {reps} replays",
            "algorithmic_bytes": nbytes, "GB/s": gbs, "frac_of_hbm_peak": gbs / HBM_PEAK_GBS,
-           "tokens_per_s_one_layer": w.B / (t_us * 1e-6), "kernel": dominant_kernel(plan, rescores, w), "plan": plan}
+           "tokens_per_s_one_layer": w.B / (t_us * 1e-6), "kernel": dominant_kernel(plan, rescores, whole, w), "plan": plan}
     if T:
         pq, pwq, pwv = (to_dev(a) for a in syn.make_step(w, 0, 0, T=T))
         pout = torch.empty_like(pq)
@@ -408,7 +420,7 @@ def main():
     achieved = mv_pass_bytes / (ms_mv * 1e-3) / 1e9 if ms_mv > 0 else None
     layer_ms = ms_per_step / L
     _, plan = pkg.bct_plan_query(desc)
-    kernel = dominant_kernel(plan, pkg.bct_plan_rescores(desc)[1], w)
+    kernel = dominant_kernel(plan, pkg.bct_plan_rescores(desc)[1], pkg.bct_plan_whole(desc)[1:], w)
     # HBM bytes per launch of that kernel from rocprofv3 counters: a RECORDED profile (profiles/), valid only
     # for the kernel instantiation it was taken on; another plan means another kernel and no figure
     traffic, traffic_src = None, None

@@ -54,8 +54,8 @@ typedef enum { BCT_F32 = 0, BCT_BF16 = 1 } bct_dtype;
 
 enum {
   BCT_MK_PER_SEQUENCE = 1u, /* desc.flags: one key table per batch element */
-  BCT_STEP_STREAMING = 2u   /* desc.flags: always take the four-launch decode step, also for a cache small
-                             * enough for the one-launch step (same results to the stated tolerances;
+  BCT_STEP_STREAMING = 2u   /* desc.flags: always take the decode step of several launches, also for a cache small
+                             * enough for a one-launch step (same results to the stated tolerances;
                              * for comparing the two) */
 };
 
@@ -195,8 +195,9 @@ bct_status bct_cache_steps(const bct_cache* c, uint64_t* steps);
  * descriptor: how many launches, and the shape of the pass over MV.  Host logic only (no GPU needed);
  * for inspection, tests and for naming the kernel a measurement belongs to. */
 typedef struct bct_plan_info {
-  uint32_t launches;          /* kernels per decode step with both a write and a read: 1, 3 or 4       */
-  uint32_t one_launch;        /* 1: the small-cache single-workgroup step                               */
+  uint32_t launches;          /* kernels per decode step with both a write and a read: 1 to 4          */
+  uint32_t one_launch;        /* 1: the whole step is one launch; the fields below then describe the
+                               * launches that BCT_STEP_STREAMING would take instead                    */
   uint32_t scores_mfma;       /* 1: scores by MFMA (bf16, keys shared by the batch), else dot products  */
   uint32_t slots_per_stat;    /* slots per (max, sum) partial of the scores pass                        */
   uint32_t normaliser_launch; /* 1: the partials are merged by a launch of their own                    */
@@ -209,6 +210,10 @@ bct_status bct_plan_query(const bct_cache_desc* desc, bct_plan_info* info);
 /* *rescores = 1 if the MV pass (section 3.2 steps 4-5 and the read) of such a step scores its slots again instead of
  * reading stored scores: large grids of several query heads per KV head.  Host logic only, as above. */
 bct_status bct_plan_rescores(const bct_cache_desc* desc, uint32_t* rescores);
+
+/* *workgroups = how many workgroups of *threads threads take one memory through the whole step (sections 3.2 and 3.4, and
+ * the read) in one launch, or 0 where several launches or the smallest caches' own one do.  Host logic only, as above. */
+bct_status bct_plan_whole(const bct_cache_desc* desc, uint32_t* workgroups, uint32_t* threads);
 
 /* Device addresses of the two regions inside cache_mem, MK first, then MV (section 3.1's two
  * sequences), for zero-copy views of the state: the bounded-cache layout in HBM as the caller sees it. */

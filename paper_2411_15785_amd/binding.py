@@ -32,7 +32,7 @@ EXPORTS = [
     "bct_cache_randomize_values", "bct_cache_export_sequence", "bct_cache_import_sequence", "bct_plan_query", "bct_cache_import", "bct_cache_steps",
     "bct_cache_regions", "bct_cache_destroy", "bct_strerror", "bct_last_error", "bct_stream_copy",
     "bct_profile_enable", "bct_profile_read", "bct_decode_step_static", "bct_static_scratch_bytes",
-    "bct_decode_step_keyed", "bct_plan_rescores",
+    "bct_decode_step_keyed", "bct_plan_rescores", "bct_plan_whole",
 ]
 
 
@@ -87,6 +87,7 @@ def lib() -> ctypes.CDLL:
     L.bct_prefill.argtypes = [vp, vp, vp, vp, u32, vp, vp]
     L.bct_plan_query.argtypes = [dp, ctypes.POINTER(bct_plan_info)]
     L.bct_plan_rescores.argtypes = [dp, ctypes.POINTER(u32)]
+    L.bct_plan_whole.argtypes = [dp, ctypes.POINTER(u32), ctypes.POINTER(u32)]
     L.bct_cache_randomize_values.argtypes = [vp, u64, ctypes.c_float, vp]
     L.bct_cache_export_sequence.argtypes = [vp, u32, vp, vp, vp]
     L.bct_cache_import_sequence.argtypes = [vp, u32, vp, vp, vp]
@@ -149,6 +150,13 @@ def bct_plan_rescores(desc):
     v = ctypes.c_uint32(0)
     st = lib().bct_plan_rescores(ctypes.byref(desc) if desc is not None else None, ctypes.byref(v))
     return st, v.value
+
+
+def bct_plan_whole(desc):
+    """-> (status, workgroups per memory, threads of each): the step of this descriptor as one launch, 0 if it is not."""
+    n, t = ctypes.c_uint32(), ctypes.c_uint32()
+    st = lib().bct_plan_whole(ctypes.byref(desc) if desc is not None else None, ctypes.byref(n), ctypes.byref(t))
+    return st, n.value, t.value
 
 
 def bct_last_error() -> str:

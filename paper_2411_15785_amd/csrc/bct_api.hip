@@ -28,6 +28,7 @@ struct bct_cache {
   uint64_t steps;
   bool keys_set;
   bct::DecodeParams plan;  // shape, strides and launch plan; pointers filled per call
+  bct::WholePlan whole;
   // optional per-launch timing: 4 events per recorded step
   std::vector<hipEvent_t> prof_ev;
   uint32_t prof_cap = 0, prof_n = 0;
@@ -89,7 +90,7 @@ struct Sizes {
   size_t ws_decode_bytes;
 };
 
-void fill_plan(const bct_cache_desc* d, bct::DecodeParams& p) {
+bct::WholePlan fill_plan(const bct_cache_desc* d, bct::DecodeParams& p) {
   memset(&p, 0, sizeof(p));
   p.B = d->batch;
   p.Hq = d->n_q_heads;
@@ -106,7 +107,10 @@ void fill_plan(const bct_cache_desc* d, bct::DecodeParams& p) {
   p.R = 1 + p.G;
   p.has_write = p.has_read = 1;
   bct::plan_decode(p, d->dtype);
-  if (d->flags & BCT_STEP_STREAMING) p.fused = 0u;
+  bct::WholePlan w = bct::plan_whole(p, d->dtype);
+  if (d->flags & BCT_STEP_STREAMING) w = bct::WholePlan{0u, 0u};
+  if (w.workgroups || (d->flags & BCT_STEP_STREAMING)) p.fused = 0u;
+  return w;
 }
 
 Sizes compute_sizes(const bct_cache_desc* d, uint32_t max_T) {
@@ -188,11 +192,13 @@ bct_status run_decode(bct_cache* c, char* ws, const void* q, const void* k_new, 
   hipError_t e;
   hipEvent_t* ev = (c->prof_n < c->prof_cap) ? &c->prof_ev[(size_t)c->prof_n * 4] : nullptr;
   if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return hip_fail(e, "event record");
-  if (key_new) p.fused = 0u;   // the one-launch step has no key update: take the streaming launches
-  if (p.fused) {
+  if (key_new) p.fused = 0u;   // that one-launch step has no key update
+  if (p.fused || c->whole.workgroups) {
     // a small cache: the whole step in one launch (timed as the MV pass)
     if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return hip_fail(e, "event record");
-    if ((e = bct::launch_fused(p, c->desc.dtype, s)) != hipSuccess) return hip_fail(e, "fused step launch");
+    e = p.fused ? bct::launch_fused(p, s)
+                : bct::launch_whole(p, c->whole, bct::KeyWrite{c->mk, key_new, key_gate}, c->desc.dtype, s);
+    if (e != hipSuccess) return hip_fail(e, "one-launch step");
     if (ev && (e = hipEventRecord(ev[2], s)) != hipSuccess) return hip_fail(e, "event record");
   } else {
     if ((e = bct::launch_scores(p, c->desc.dtype, s)) != hipSuccess) return hip_fail(e, "scores launch");
@@ -294,7 +300,7 @@ bct_status bct_cache_init(const bct_cache_desc* desc, uint32_t max_prefill_T, vo
   c->ws_decode_bytes = z.ws_decode_bytes;
   c->steps = 0;
   c->keys_set = false;
-  fill_plan(desc, c->plan);
+  c->whole = fill_plan(desc, c->plan);
   {
     // set-up time is where the static scratch's address is looked up on this device (a caller of
     // bct_decode_step_static may be unable to make such a call later, e.g. under graph capture)
@@ -530,15 +536,15 @@ bct_status bct_plan_query(const bct_cache_desc* desc, bct_plan_info* info) {
   if (st != BCT_OK) return st;
   if (!info) return fail(BCT_ERR_INVALID_ARG, "info is NULL");
   bct::DecodeParams p;
-  fill_plan(desc, p);
-  info->one_launch = p.fused;
+  const bool one = fill_plan(desc, p).workgroups || p.fused;
+  info->one_launch = one ? 1u : 0u;
   info->scores_mfma = (desc->dtype == BCT_BF16 && !p.mk_per_seq) ? 1u : 0u;
   info->slots_per_stat = p.stat_tile;
-  info->normaliser_launch = (!p.fused && !p.fuse_norm) ? 1u : 0u;
+  info->normaliser_launch = (!one && !p.fuse_norm) ? 1u : 0u;
   info->mv_workgroup = p.mv_bs;
   info->mv_loads_per_lane = p.mv_u;
   info->mv_splits = p.S;
-  info->launches = p.fused ? 1u : 2u + info->normaliser_launch + (p.S > 1 ? 1u : 0u);
+  info->launches = one ? 1u : 2u + info->normaliser_launch + (p.S > 1 ? 1u : 0u);
   return BCT_OK;
 }
 
@@ -547,8 +553,19 @@ bct_status bct_plan_rescores(const bct_cache_desc* desc, uint32_t* rescores) {
   if (st != BCT_OK) return st;
   if (!rescores) return fail(BCT_ERR_INVALID_ARG, "rescores is NULL");
   bct::DecodeParams p;
-  fill_plan(desc, p);
-  *rescores = p.fused ? 0u : p.rescore;
+  const bool one = fill_plan(desc, p).workgroups || p.fused;
+  *rescores = one ? 0u : p.rescore;
+  return BCT_OK;
+}
+
+bct_status bct_plan_whole(const bct_cache_desc* desc, uint32_t* workgroups, uint32_t* threads) {
+  const bct_status st = check_desc(desc);
+  if (st != BCT_OK) return st;
+  if (!workgroups || !threads) return fail(BCT_ERR_INVALID_ARG, "workgroups or threads is NULL");
+  bct::DecodeParams p;
+  const bct::WholePlan w = fill_plan(desc, p);
+  *workgroups = w.workgroups;
+  *threads = w.threads;
   return BCT_OK;
 }
 

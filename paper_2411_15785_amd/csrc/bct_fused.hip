@@ -6,49 +6,52 @@
 // dependency "the softmax normaliser of all M slots before any slot is
 // written" (section 3.2 steps 2 and 4) is a workgroup barrier instead of a
 // launch boundary:
-//   A. scores of the write query and the G read queries against all M keys
+//   A. scores of the write query and the read query against all M keys
 //      (log2 domain) into LDS;
 //   B. per row: max and sum over the M slots, then the scores are replaced in
 //      place by the softmax weights (the write row times the token's step
 //      size, if one is given);
 //   C. one pass over MV: load, fma(ww[m], wv, MV[m,:]), round, store, and
-//      accumulate rw[g][m] times the value just stored (section 3.4 equation,
+//      accumulate rw[m] times the value just stored (section 3.4 equation,
 //      then the read);
-//   D. the G output rows are summed over the lanes and wavefronts in a fixed
+//   D. the output row is summed over the lanes and wavefronts in a fixed
 //      order and stored.
-// Chosen by plan_decode for M <= kFusedMaxM and at most kFusedMaxUnits memories
-// (one resident round of workgroups); BCT_STEP_STREAMING in the descriptor's flags turns it off.
+// Left for what decode_whole_kernel (bct_whole.hip) does not do better: fp32, one query head per KV head, 257 to 512
+// memories of at most 128 slots (512 memories of 64 slots: d = 64 6.3 us against 6.7, d = 128 with keys per sequence 12.9
+// against 14.0).  Its workgroups of 256 threads and few registers are one resident round there.
+// BCT_STEP_STREAMING in the descriptor's flags turns it off.
 #include "bct_device.h"
 #include "bct_internal.h"
 
 namespace bct {
 
-template <typename DT, int D, int GT>
+template <typename DT, int D>
 __global__ __launch_bounds__(256) void decode_fused_kernel(const DecodeParams p) {
   typedef typename DT::elem elem;
   constexpr int E = DT::kElemsPerVec;
   constexpr int LPS = D / E;       // lanes per slot row (16 bytes each)
   constexpr int SPP = 256 / LPS;   // slots per pass of the workgroup
   constexpr int UC = 4;            // slots a lane has in flight in step C
+  constexpr uint32_t kRows = 2;    // write and read
 
-  __shared__ __attribute__((aligned(16))) float s_w[kMaxRows][kFusedMaxM];
-  __shared__ float2 s_norm[kMaxRows];
-  __shared__ float s_red[4 * GT * D];
+  __shared__ __attribute__((aligned(16))) float s_w[kRows][kFusedMaxM];
+  __shared__ float2 s_norm[kRows];
+  __shared__ float s_red[4 * D];
 
   const uint32_t unit = blockIdx.x, b = unit / p.Hkv, h = unit % p.Hkv;
   const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
   const int sub = tid % LPS, sl = tid / LPS;
-  const uint32_t R = p.R, G = p.G, M = p.M, W = p.has_write;
+  const uint32_t R = p.R, M = p.M, W = p.has_write;
 
   // ---- A: scores.  The query rows stay in registers (this lane's 16 bytes of each).
   {
     const elem* mk = (const elem*)p.mk + (size_t)(p.mk_per_seq ? unit : h) * M * D + sub * E;
-    float xf[kMaxRows][E], scale[kMaxRows];
+    float xf[kRows][E], scale[kRows];
 #pragma unroll
-    for (uint32_t r = 0; r < kMaxRows; ++r) {
+    for (uint32_t r = 0; r < kRows; ++r) {
       if (r < R) {
         const elem* x = (W && r == 0) ? (const elem*)p.wq + (size_t)b * p.kv_bstride + (size_t)h * D
-                                      : (const elem*)p.q + (size_t)b * p.q_bstride + (size_t)(h * G + (r - W)) * D;
+                                      : (const elem*)p.q + (size_t)b * p.q_bstride + (size_t)h * D;
         unpack16<DT>(*(const u32x4*)(x + sub * E), xf[r]);
         scale[r] = (W && r == 0) ? p.wscale_l2e : p.rscale_l2e;
       }
@@ -68,7 +71,7 @@ __global__ __launch_bounds__(256) void decode_fused_kernel(const DecodeParams p)
           float kf[E];
           unpack16<DT>(kraw[u], kf);
 #pragma unroll
-          for (uint32_t r = 0; r < kMaxRows; ++r) {
+          for (uint32_t r = 0; r < kRows; ++r) {
             if (r < R) {
               float dot = 0.f;
 #pragma unroll
@@ -112,11 +115,9 @@ __global__ __launch_bounds__(256) void decode_fused_kernel(const DecodeParams p)
     const elem* wv = (const elem*)p.wv + (size_t)b * p.kv_bstride + (size_t)h * D;
     unpack16<DT>(*(const u32x4*)(wv + sub * E), wvf);
   }
-  float acc[GT][E];
+  float acc[E];
 #pragma unroll
-  for (int g = 0; g < GT; ++g)
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[g][e] = 0.f;
+  for (int e = 0; e < E; ++e) acc[e] = 0.f;
   for (uint32_t s0 = sl; s0 < M; s0 += SPP * UC) {
     u32x4 raw[UC];
 #pragma unroll
@@ -137,60 +138,35 @@ __global__ __launch_bounds__(256) void decode_fused_kernel(const DecodeParams p)
           *(u32x4*)(mv + (size_t)slot * D) = pack16_round<DT>(x);  // x now holds the stored values
         }
         if (p.has_read) {
+          const float rw = s_w[W][slot];
 #pragma unroll
-          for (int g = 0; g < GT; ++g) {
-            if ((uint32_t)g < G) {
-              const float rw = s_w[W + g][slot];
-#pragma unroll
-              for (int e = 0; e < E; ++e) acc[g][e] = __builtin_fmaf(rw, x[e], acc[g][e]);
-            }
-          }
+          for (int e = 0; e < E; ++e) acc[e] = __builtin_fmaf(rw, x[e], acc[e]);
         }
       }
     }
   }
 
-  // ---- D: output rows
+  // ---- D: the output row
   if (p.has_read) {
 #pragma unroll
-    for (int g = 0; g < GT; ++g)
-#pragma unroll
-      for (int e = 0; e < E; ++e) acc[g][e] = xor_sum<LPS, 32>(acc[g][e]);
+    for (int e = 0; e < E; ++e) acc[e] = xor_sum<LPS, 32>(acc[e]);
     if (lane / LPS == 0) {
 #pragma unroll
-      for (int g = 0; g < GT; ++g)
-#pragma unroll
-        for (int e = 0; e < E; ++e) s_red[(wave * GT + g) * D + sub * E + e] = acc[g][e];
+      for (int e = 0; e < E; ++e) s_red[wave * D + sub * E + e] = acc[e];
     }
     __syncthreads();
-    for (uint32_t i = tid; i < G * D; i += 256) {
-      const uint32_t g = i / D, j = i % D;
-      const float v = (s_red[(0 * GT + g) * D + j] + s_red[(1 * GT + g) * D + j]) +
-                      (s_red[(2 * GT + g) * D + j] + s_red[(3 * GT + g) * D + j]);
-      store_elem((elem*)p.out, (size_t)b * p.q_bstride + (size_t)(h * G + g) * D + j, v);
+    for (uint32_t j = tid; j < D; j += 256) {
+      const float v = (s_red[j] + s_red[D + j]) + (s_red[2 * D + j] + s_red[3 * D + j]);
+      store_elem((elem*)p.out, (size_t)b * p.q_bstride + (size_t)h * D + j, v);
     }
   }
 }
 
-template <typename DT, int D>
-static void launch_fused_g(const DecodeParams& p, hipStream_t s) {
+hipError_t launch_fused(const DecodeParams& p, hipStream_t s) {
+  if (p.M > kFusedMaxM || p.G != 1) return hipErrorInvalidConfiguration;
   const dim3 grid(p.B * p.Hkv), block(256);
-  const uint32_t G = p.has_read ? p.G : 1u;
-  if (G <= 1) hipLaunchKernelGGL((decode_fused_kernel<DT, D, 1>), grid, block, 0, s, p);
-  else if (G <= 2) hipLaunchKernelGGL((decode_fused_kernel<DT, D, 2>), grid, block, 0, s, p);
-  else if (G <= 4) hipLaunchKernelGGL((decode_fused_kernel<DT, D, 4>), grid, block, 0, s, p);
-  else hipLaunchKernelGGL((decode_fused_kernel<DT, D, 8>), grid, block, 0, s, p);
-}
-
-hipError_t launch_fused(const DecodeParams& p, int dtype, hipStream_t s) {
-  if (p.M > kFusedMaxM || p.G > kMaxG) return hipErrorInvalidConfiguration;
-  if (dtype == 0) {
-    if (p.d == 128) launch_fused_g<F32, 128>(p, s);
-    else launch_fused_g<F32, 64>(p, s);
-  } else {
-    if (p.d == 128) launch_fused_g<BF16, 128>(p, s);
-    else launch_fused_g<BF16, 64>(p, s);
-  }
+  if (p.d == 128) hipLaunchKernelGGL((decode_fused_kernel<F32, 128>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((decode_fused_kernel<F32, 64>), grid, block, 0, s, p);
   return hipGetLastError();
 }
 

@@ -12,14 +12,22 @@ namespace bct {
 constexpr uint32_t kMaxG = 8;          // query heads per KV head
 constexpr uint32_t kMaxRows = 1 + kMaxG;  // score rows per memory: write + G reads
 constexpr uint32_t kMinStatTile = 32;  // smallest slot tile with its own (max, sum) partial
-// A cache this small is stepped by one launch, one workgroup per memory: up to this many
-// slots and this many memories (one resident round of workgroups).  Measured inside a HIP graph
-// (bf16 d = 128 / fp32 d = 64, 4 to 512 memories): M = 64: 6.5-7.9 us against 7.0-10.9 us for
-// the four launches, M = 128: equal or better, M = 256: 15-21 us against 9-23 us (a single
-// workgroup has too few loads in flight to stream a larger memory), so the limit is 128.
-// Launched eagerly the one launch also saves three launch overheads (config 1: 11 us against 25).
+// decode_fused_kernel, one workgroup per memory: up to this many slots and this many memories (one resident round of
+// workgroups).  Beyond 128 slots a workgroup of 256 threads has too few loads in flight (M = 256: 15-21 us against 9-23 us
+// for the streaming launches); plan_whole says which of these steps decode_whole_kernel takes.
 constexpr uint32_t kFusedMaxM = 128;
 constexpr uint32_t kFusedMaxUnits = 512;
+
+// decode_whole_kernel with `threads` a workgroup: MV loads per lane for columns of col_bytes of M slots (at most
+// kWholeMaxLoads), bytes of LDS (at most kLdsBytes): two key tiles of 16 rows per wavefront, R fp32 weights a slot, statistics.
+constexpr uint32_t kWholeMaxLoads = 16, kLdsBytes = 160u << 10;
+inline uint32_t whole_loads(uint32_t threads, uint32_t col_bytes, uint32_t M) {
+  const uint32_t slots = threads * 16 / col_bytes;
+  return (M + slots - 1) / slots;
+}
+inline size_t whole_lds_bytes(uint32_t threads, uint32_t row_bytes, uint32_t R, uint32_t M) {
+  return (size_t)threads / 64 * 32 * row_bytes + ((size_t)R * M + threads / 64 * 32) * sizeof(float);
+}
 
 // One decode step of one layer: everything its launches need.
 struct DecodeParams {
@@ -87,9 +95,22 @@ hipError_t launch_prefill_bf16(const PrefillParams& p, hipStream_t s);
 hipError_t launch_scores(const DecodeParams& p, int dtype, hipStream_t s);
 hipError_t launch_normalise(const DecodeParams& p, hipStream_t s);
 hipError_t launch_stream(const DecodeParams& p, int dtype, hipStream_t s);
-hipError_t launch_stream_gqa(const DecodeParams& p, hipStream_t s);   // bf16, d = 128, G > 2, with a read
+hipError_t launch_stream_gqa(const DecodeParams& p, hipStream_t s);   // bf16, G > 2, with a read
 hipError_t launch_merge(const DecodeParams& p, int dtype, hipStream_t s);
-hipError_t launch_fused(const DecodeParams& p, int dtype, hipStream_t s);
+hipError_t launch_fused(const DecodeParams& p, hipStream_t s);   // fp32, G = 1
+// A step that is one launch of decode_whole_kernel: `workgroups` (0: it is not) of `threads` threads per memory.
+struct WholePlan {
+  uint32_t workgroups, threads;
+};
+// Of a step that writes keys in that launch: the keys, the key write vectors [B][Hkv][d] (null: none), their step sizes
+// [B][Hkv] (strides of the gate) or null.
+struct KeyWrite {
+  void* mk;
+  const void* wk;
+  const float* gate;
+};
+WholePlan plan_whole(const DecodeParams& p, int dtype);
+hipError_t launch_whole(const DecodeParams& p, const WholePlan& w, const KeyWrite& kw, int dtype, hipStream_t s);
 hipError_t launch_fill_zero(void* dst, size_t n_bytes, hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t n_bytes, hipStream_t s);
 hipError_t launch_randomize(void* dst, size_t n_bytes, int dtype, uint64_t seed, float amplitude, hipStream_t s);

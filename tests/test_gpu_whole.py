@@ -1,0 +1,126 @@
+"""The decode step that takes whole memories through one launch: where it is chosen, at the edges of its tiles and
+loads, against the oracle and against the streaming launches of the same step."""
+import numpy as np
+import pytest
+
+import bct_synth as syn
+from _util import bf16_ulp, f64, make_pair, to_dev, to_np
+from test_gpu_parity import check_out, check_state_one_step
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    import paper_2411_15785_amd as pkg
+    pkg.lib()
+    return pkg
+
+
+@pytest.fixture(scope="module")
+def R():
+    from oracle import bct_ref
+    return bct_ref
+
+
+# B, Hq, Hkv, d, M, dtype, per-sequence keys, workgroups per memory, threads.  A tile of keys is 16 slots for each of 8 or 16
+# wavefronts (M / 16 tiles: one, two, three and more rounds, the last one partial), a lane has 4, 8 or 16 loads.
+CASES = [
+    (1, 1, 1, 128, 64, "bf16", 0, 2, 512),       # 4 tiles for 8 wavefronts, one memory
+    (3, 5, 5, 128, 192, "bf16", 0, 2, 512),      # 12 tiles; 15 memories x 2: a partial row of XCDs
+    (2, 6, 2, 128, 320, "bf16", 0, 2, 512),      # three query heads, eight lanes to a slot row
+    (9, 16, 16, 128, 320, "bf16", 0, 1, 512),    # 144 memories: one workgroup each, 16 lanes to a slot row
+    (9, 16, 16, 128, 576, "bf16", 0, 1, 1024),   # beyond 512 slots
+    (4, 18, 18, 128, 1984, "bf16", 0, 2, 1024),  # most loads, 124 tiles for 16 wavefronts
+    (5, 32, 16, 128, 448, "bf16", 0, 2, 512),    # two query heads
+    (9, 128, 16, 128, 448, "bf16", 0, 1, 512),   # eight, matrix-core read, last block of loads half used
+    (2, 35, 5, 64, 704, "bf16", 0, 1, 512),      # seven, 64 columns
+    (1, 3, 3, 64, 768, "bf16", 0, 1, 512),
+    (2, 4, 4, 128, 64, "f32", 0, 2, 512),
+    (9, 32, 16, 128, 256, "f32", 0, 1, 512),     # 32 lanes to a slot row
+    (2, 15, 5, 64, 320, "f32", 0, 1, 512),
+    (5, 104, 13, 64, 512, "f32", 0, 1, 512),
+    (2, 3, 3, 128, 320, "bf16", 1, 1, 512),
+    (3, 8, 2, 64, 192, "bf16", 1, 1, 512),
+    (2, 6, 2, 128, 192, "f32", 1, 1, 512),
+]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,M,dtype,seq,wgs,threads", CASES)
+def test_step_against_oracle_and_streaming(P, R, B, Hq, Hkv, d, M, dtype, seq, wgs, threads):
+    """Both, write alone, read alone; step sizes; keys that move, where each sequence has its own."""
+    import torch
+    w = syn.Workload("whole", 1, B, Hq, Hkv, d, M, dtype, 4)
+    ref, gpu, mk, mv, bs = make_pair(w, R.RefCache, P.BctCache, flags=seq, mv0=True)
+    _, stream, *_ = make_pair(w, R.RefCache, P.BctCache, flags=seq | P.BCT_STEP_STREAMING, mv0=True)
+    assert P.bct_plan_whole(gpu.desc) == (P.BCT_OK, wgs, threads) and P.bct_plan_whole(stream.desc)[1] == 0
+    eta = np.abs(syn.unpack(syn.make_step(w, 7)[0], dtype).astype(np.float32))[:, :Hkv, 0].copy()
+    dev = lambda a: to_dev(a, dtype)
+    gate = torch.from_numpy(eta).to("cuda:0")
+    steps = [("both", True, True, None), ("write", False, True, None), ("read", True, False, None), ("gated", True, True, eta)]
+    for t, (what, read, write, g) in enumerate(steps):
+        q, wq, wv = syn.make_step(w, t)
+        q, wq, wv = q if read else None, wq if write else None, wv if write else None
+        before = ref.values()
+        kw, kg = ({}, {}) if g is None else ({"gate": g}, {"gate": gate})
+        o_ref = ref.decode_step(q, wq, wv, **kw)
+        outs = []
+        for c in (gpu, stream):
+            c.set_values(dev(before))
+            o = c.decode_step(dev(q), dev(wq), dev(wv), **kg)
+            check_state_one_step(to_np(c.values_view(), dtype), ref.values(), dtype, what, before=before)
+            outs.append(to_np(o, dtype) if read else None)
+        if read:
+            for o in outs:
+                check_out(o, o_ref, dtype, what)
+            # two correct sums of one step: each within two spacings of the oracle's (fp32: 1e-5), so within four
+            a, b = (f64(o, dtype) for o in outs)
+            worst = np.max(np.abs(a - b), axis=-1)
+            peak = np.max(np.abs(b), axis=-1)
+            assert np.all(worst <= (2e-5 * peak if dtype == "f32" else 4 * bf16_ulp(peak))), what
+    assert np.array_equal(to_np(gpu.keys_view(), dtype), mk)
+    if seq:
+        q, wq, wv = syn.make_step(w, 9)
+        wk = syn.make_step(w, 10)[2]
+        kappa = torch.full((B, Hkv), 0.25, device="cuda:0")
+        for c in (gpu, stream):
+            c.set_values(dev(mv))
+            o = c.decode_step_keyed(dev(q), dev(wq), dev(wv), dev(wk), gate=gate, key_gate=kappa)
+            check_out(to_np(o, dtype), _keyed(ref, mk, mv, q, wq, wv, wk, eta, 0.25), dtype, "keyed")
+            check_state_one_step(to_np(c.values_view(), dtype), ref.values(), dtype, "keyed MV", before=mv)
+            check_state_one_step(to_np(c.keys_view(), dtype), ref.keys(), dtype, "keyed MK", before=mk)
+
+
+def _keyed(ref, mk, mv, q, wq, wv, wk, eta, kappa):
+    ref.set_keys(mk)
+    ref.set_values(mv)
+    return ref.decode_step_keyed(q, wq, wv, wk, gate=eta, kgate=np.full(eta.shape, kappa, np.float32))
+
+
+def test_repeats_itself_and_graphs(P):
+    """Equal inputs give equal bits, launched or replayed."""
+    import torch
+    for (B, Hq, Hkv, d, M, dtype) in ((3, 16, 4, 128, 320, "bf16"), (4, 40, 40, 128, 256, "bf16"), (2, 4, 4, 64, 64, "f32")):
+        w = syn.Workload("whole_bits", 1, B, Hq, Hkv, d, M, dtype, 2)
+        cs = []
+        for _ in range(2):
+            c = P.BctCache(M, B, Hq, Hkv, d, torch.float32 if dtype == "f32" else torch.bfloat16, w.scale, w.scale)
+            assert P.bct_plan_whole(c.desc)[1] > 0
+            c.set_keys(to_dev(syn.make_keys(w), dtype))
+            cs.append(c)
+        ins = [to_dev(a, dtype) for a in syn.make_step(w, 0)]
+        o = [torch.empty_like(ins[0]) for _ in range(2)]
+        graph = torch.cuda.CUDAGraph()
+        cs[1].decode_step(*ins, o[1])
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            cs[1].decode_step(*ins, o[1])
+        cs[1].set_values(None)
+        for _ in range(3):
+            cs[0].decode_step(*ins, o[0])
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(o[0].view(torch.uint8), o[1].view(torch.uint8))
+            assert torch.equal(cs[0].values_view().view(torch.uint8), cs[1].values_view().view(torch.uint8))
