@@ -60,7 +60,7 @@ bct_status bctm_pack_weight(const void* w, void* packed, uint32_t N, uint32_t K,
  * K a multiple of 32, N a multiple of 16; fp32 accumulation (MFMA), one rounding to bf16 at the end.
  * out may alias residual; x must not alias out.  Two kernels: up to 127 rows (a decode batch) the weights
  * are streamed once per 32 rows against activations read from cache; from 128 rows on (a prompt chunk), when
- * N is a multiple of 128 (bctm_swiglu: 64), a tiled matrix-core kernel runs instead, with workgroup tiles from
+ * N is a multiple of 128 (bctm_swiglu: 64) or N * rows is large (bctm_linear_plan), a tiled matrix-core kernel runs instead, with workgroup tiles from
  * 64 x 64 to 256 x 256 and 128 x 512 chosen to fill the chip - fastest with a tiled x.  Both sum in fp32, K in one or more parts added in
  * order.  The tile depends on rows, N, K and x's order, the number of parts on rows and N alone (bctm_linear_tile): equal calls give equal
  * bits, a tiled and a row-major x give the same bits, and so do calls of other rows or N with as many parts; calls with

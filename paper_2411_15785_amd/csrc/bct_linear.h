@@ -30,7 +30,7 @@ struct LinearTile {
 LinearTile linear_rows_tile(uint32_t rows, uint32_t K, uint32_t N, bool swiglu, bool x_tiled);
 
 // The matrix-core projection of many rows (bct_linear_rows.hip).  w2 non-null: SwiGLU of w and w2.  x_tiled /
-// out_tiled: activations in the tiled order.  N is a multiple of 128 (SwiGLU: 64), K of 32.
+// out_tiled: activations in the tiled order.  N is a multiple of 16 (out_tiled: 32), K of 32.
 hipError_t launch_linear_rows(const void* x, const void* w, const void* w2, const void* residual, const LinearOut& dst,
                               uint32_t rows, uint32_t K, uint32_t N, bool x_tiled, bool out_tiled, hipStream_t s);
 

@@ -93,9 +93,10 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
         step[j] = 64;
       }
     } else {
-      const uint32_t bt = tile - TA;
-      if (SWIGLU) src[j] = (const char*)(((bt % 2) ? w2 : w) + (size_t)(nt * (TB / 2) + bt / 2) * KT * 64 + lane);
-      else src[j] = (const char*)(w + (size_t)(nt * TB + bt) * KT * 64 + lane);
+      // features past the end: the last ones again, not stored
+      const uint32_t bt = tile - TA, most = dst.start[3] / 16 - 1;
+      if (SWIGLU) src[j] = (const char*)(((bt % 2) ? w2 : w) + (size_t)min(nt * (TB / 2) + bt / 2, most) * KT * 64 + lane);
+      else src[j] = (const char*)(w + (size_t)min(nt * TB + bt, most) * KT * 64 + lane);
       step[j] = 1024;
     }
   }
@@ -261,11 +262,11 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
     for (int ps = 0; ps < 16 / RPP; ++ps) {
       const int rr = ps * RPP + lane / CPR;
       const uint32_t row = r0 + wr * (16 * MI) + (grp * MO + i) * 16 + rr;
-      if (rr < 16 && row < rows) {
+      const uint32_t n = nt * BNF + wc * (BNF / WC) + 8 * cc;
+      if (rr < 16 && row < rows && n < dst.start[3]) {
         float y[8];
         *(f32x4*)&y[0] = *(const f32x4*)&e[rr][8 * cc];
         *(f32x4*)&y[4] = *(const f32x4*)&e[rr][8 * cc + 4];
-        const uint32_t n = nt * BNF + wc * (BNF / WC) + 8 * cc;
         const int which = n >= dst.start[2] ? 2 : n >= dst.start[1] ? 1 : 0;
         const uint32_t width = dst.start[which + 1] - dst.start[which], col = n - dst.start[which];
         const size_t oo = (size_t)row * width + col;
@@ -311,10 +312,12 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
 // 4654, 11008 -> 20992 1626 | 1676 (15 shapes, 0.95 to 1.015; on another card 0.96 to 1.0), hence 83 there, which leaves it one of
 // five: 2135, 11008 -> 14592 SwiGLU 1103 | 1071 (7 shapes, 0.98 to 1.045).  A row-major x waits longer for its rows, and the wider
 // tile wins in all 37 shapes: 4654, 11008 -> 20992 2105 | 1841, 1911, 1024 -> 50176 218 | 212.
+// A count of columns that 128 does not divide leaves the last tile of every row of tiles partly used, in any shape: all of them
+// are open to it, at what their whole tiles cost.
 enum RowsShape { kTile256, kTile128x512, kTile128x256, kTile128, kTile128K2, kTile64K2 };
 
 RowsShape rows_shape(uint32_t rows, uint32_t bcols, uint32_t K, bool x_tiled) {
-  auto tiles = [&](uint32_t bm, uint32_t bn) { return (uint64_t)((rows + bm - 1) / bm) * (bcols / bn); };
+  auto tiles = [&](uint32_t bm, uint32_t bn) { return (uint64_t)((rows + bm - 1) / bm) * ((bcols + bn - 1) / bn); };
   // hundredths of a us per K step: one workgroup per compute unit at a time; two, a last one may have it alone
   auto one = [](uint64_t t, uint64_t cost) { return (t + 255) / 256 * cost; };
   auto two = [](uint64_t t, uint64_t alone, uint64_t pair) {
@@ -331,19 +334,20 @@ RowsShape rows_shape(uint32_t rows, uint32_t bcols, uint32_t K, bool x_tiled) {
   };
   take(kTile128K2, one(tiles(128, 128), 25));
   take(kTile64K2, two(tiles(64, 64), 11, 19));
-  if (bcols % 256 == 0) {
+  const bool ragged = bcols % 128 != 0;
+  if (bcols % 256 == 0 || ragged) {
     take(kTile128x256, one(tiles(128, 256), 44));
     take(kTile256, one(tiles(256, 256), 69));
   }
   // (dear only against 256 x 256, which sums K in one part as well: the parts do not depend on x's order)
-  if (bcols % 512 == 0) take(kTile128x512, one(tiles(128, 512), best == kTile256 && x_tiled && K > 4096 ? 83 : 80));
+  if (bcols % 512 == 0 || ragged) take(kTile128x512, one(tiles(128, 512), best == kTile256 && x_tiled && K > 4096 ? 83 : 80));
   return best;
 }
 
 template <bool SWIGLU, bool XT, int MI, int NJ, int WR, int WC, int KS, bool PAIR = false>
 void launch_shape(const void* x, const void* w, const void* w2, const void* residual, const LinearOut& dst, uint32_t rows,
                   uint32_t K, uint32_t bcols, bool out_tiled, hipStream_t s) {
-  const uint32_t NT = bcols / (16 * NJ * WC), RT = (rows + 16 * MI * WR - 1) / (16 * MI * WR);
+  const uint32_t NT = (bcols + 16 * NJ * WC - 1) / (16 * NJ * WC), RT = (rows + 16 * MI * WR - 1) / (16 * MI * WR);
   hipLaunchKernelGGL((linear_rows_kernel<SWIGLU, XT, PAIR, MI, NJ, WR, WC, KS>), dim3(8 * ((RT * NT + 7) / 8)),
                      dim3(64 * WR * WC * KS), 0, s, (const uint16_t*)x, (const u32x4*)w, (const u32x4*)w2,
                      (const uint16_t*)residual, dst, rows, K, NT, out_tiled ? 1u : 0u);
@@ -360,7 +364,7 @@ void launch_rows(const void* x, const void* w, const void* w2, const void* resid
     // 872 | 972; 7647, 9120 -> 13184 2217 | 2411; 1172, 9792 -> 23936 794 | 839; 3463, 4416 -> 27520 1109 | 1205; 781, 5440 ->
     // 22912 300 | 298.  Fewer weights: 2236, 4288 -> 17280 415 | 390; K below 4000 up to 13 % slower.  Fewer
     // tiles (the activations of odd steps come later): 677, 10688 -> 11392 328 | 301.
-    const uint64_t tiles = (uint64_t)((rows + 127) / 128) * (N / 128);
+    const uint64_t tiles = (uint64_t)((rows + 127) / 128) * ((N + 127) / 128);
     if (shape == kTile128 && (uint64_t)K * N >= (100u << 20) && tiles >= 850)
       return launch_shape<false, false, 4, 4, 2, 2, 1, true>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
   }

@@ -386,14 +386,20 @@ static void launch_linear_w(const void* x, const void* w, const void* residual, 
   else launch_linear_rt<WV, UN, FT, 2>(x, w, residual, dst, rows, K, N, flags, hip_stream);
 }
 
-// The kernel of a projection shape.  Many rows (from 128 on): the matrix-core kernel (bct_linear_rows.hip), for
-// feature counts its 128-feature (SwiGLU: 64) tiles cover exactly; its two values name ranges of shapes, the tile
-// inside it is linear_rows_tile's choice.
+// The kernel of a projection shape.  Many rows (from 128 on): the matrix-core kernel (bct_linear_rows.hip); its two values
+// name ranges of shapes, the tile inside it is linear_rows_tile's choice.  Feature counts that no tile divides take it as
+// well, with a last tile that is partly used, once the streaming kernel, which reads the weights again for every 32 rows, has
+// more than one round of workgroups (of inputs beyond 8192: two).  us, streaming | matrix-core, weights from memory:
+//   709 rows, 11264 -> 2912 332 | 94; 2381, 1664 -> 1344 142 | 20; 4096, 4096 -> 4128 959 | 157; 8192, 5088 -> 5088 3679 | 361;
+//   SwiGLU 1500, 4000 -> 1504 188 | 54; 640, 1024 -> 2848 42 | 14; 256, 1024 -> 736 (368 workgroups) 11.8 | 6.9, 256, 5120 -> 736
+//   23.6 | 19.3, SwiGLU 27 | 24; 200, 5120 -> 480 (210) 12.9 | 19.0, SwiGLU 15.8 | 20.8; 256, 11008 -> 736 39 | 47, -> 1504 (752) 67 | 45
+// Not below 128 features, where no tile is half used, and not beyond 16384.
 // Few rows: the streaming kernel; measured at 32 rows (weights in TB/s): K = 4096, N = 4096 / 12288: 16
 // wavefronts, one feature tile 3.6 / 4.0 against 2.8 / 3.8 for two tiles (too few workgroups); N = 32000:
 // two tiles 5.0 against 4.3.
-static uint32_t linear_kernel_of(uint32_t rows, uint32_t N, bool swiglu) {
-  if (rows >= 128 && N % (swiglu ? 64u : 128u) == 0)
+static uint32_t linear_kernel_of(uint32_t rows, uint32_t K, uint32_t N, bool swiglu) {
+  const bool ragged = N >= 128 && N <= 16384 && (uint64_t)(N / 16) * ((rows + 31) / 32) > (!swiglu && K > 8192 ? 512u : 256u);
+  if (rows >= 128 && (N % (swiglu ? 64u : 128u) == 0 || ragged))
     return (rows >= 1024 && N % (swiglu ? 128u : 256u) == 0) ? BCTM_KERNEL_TILE256 : BCTM_KERNEL_TILE128;
   if (!swiglu && N >= 16384 && N % 32 == 0) return BCTM_KERNEL_STREAMING_WIDE;
   // three feature tiles per workgroup when that still leaves a workgroup for every compute unit: 12288
@@ -483,7 +489,7 @@ bct_status bctm_pack_weight(const void* w, void* packed, uint32_t N, uint32_t K,
 
 static bct_status launch_linear(const void* x, const void* w, const void* residual, const LinearOut& dst,
                                 uint32_t rows, uint32_t K, uint32_t N, uint32_t flags, void* hip_stream) {
-  const uint32_t kernel = linear_kernel_of(rows, N, false);
+  const uint32_t kernel = linear_kernel_of(rows, K, N, false);
   if (kernel == BCTM_KERNEL_TILE128 || kernel == BCTM_KERNEL_TILE256)
     return launched("linear", launch_linear_rows(x, w, nullptr, residual, dst, rows, K, N, flags & BCTM_X_TILED, false,
                                                  (hipStream_t)hip_stream));
@@ -532,7 +538,7 @@ bct_status bctm_swiglu(const void* x, const void* w_gate, const void* w_up, void
     return mfail(BCT_ERR_UNSUPPORTED, "tiled activations need a multiple of 32 columns");
   if (!al16(w_up)) return mfail(BCT_ERR_MISALIGNED, "pointers must be 16-byte aligned");
   const LinearOut dst = {{(uint16_t*)out, nullptr, nullptr}, {0u, N, N, N}};
-  const uint32_t kernel = linear_kernel_of(rows, N, true);
+  const uint32_t kernel = linear_kernel_of(rows, K, N, true);
   if (kernel == BCTM_KERNEL_TILE128 || kernel == BCTM_KERNEL_TILE256)
     return launched("swiglu", launch_linear_rows(x, w_gate, w_up, nullptr, dst, rows, K, N, flags & BCTM_X_TILED,
                                                  flags & BCTM_OUT_TILED, (hipStream_t)hip_stream));
@@ -545,7 +551,7 @@ bct_status bctm_swiglu(const void* x, const void* w_gate, const void* w_up, void
 bct_status bctm_linear_plan(uint32_t rows, uint32_t K, uint32_t N, uint32_t swiglu, uint32_t* kernel) {
   if (!kernel || rows == 0 || K == 0 || N == 0) return mfail(BCT_ERR_INVALID_ARG, "NULL pointer or zero size");
   if (K % 32 != 0 || N % 16 != 0) return mfail(BCT_ERR_UNSUPPORTED, "K must be a multiple of 32 and N of 16");
-  *kernel = linear_kernel_of(rows, N, swiglu != 0);
+  *kernel = linear_kernel_of(rows, K, N, swiglu != 0);
   return BCT_OK;
 }
 
@@ -554,7 +560,7 @@ bct_status bctm_linear_tile(uint32_t rows, uint32_t K, uint32_t N, uint32_t swig
   if (!tile_rows || !tile_features || !k_parts || rows == 0 || K == 0 || N == 0)
     return mfail(BCT_ERR_INVALID_ARG, "NULL pointer or zero size");
   if (K % 32 != 0 || N % 16 != 0) return mfail(BCT_ERR_UNSUPPORTED, "K must be a multiple of 32 and N of 16");
-  const uint32_t kernel = linear_kernel_of(rows, N, swiglu != 0);
+  const uint32_t kernel = linear_kernel_of(rows, K, N, swiglu != 0);
   const LinearTile t = kernel == BCTM_KERNEL_TILE128 || kernel == BCTM_KERNEL_TILE256
                            ? linear_rows_tile(rows, K, N, swiglu != 0, (flags & BCTM_X_TILED) != 0)
                            : streaming_tile(kernel, rows, N, swiglu != 0, flags);

@@ -339,3 +339,15 @@ def test_every_pointer_parameter_is_declared(L):
     from paper_2411_15785_amd import model
     ML = model.mlib()
     assert [n for n in binding.EXPORTS + model.MODEL_EXPORTS if getattr(ML, n).argtypes is None] == []
+
+
+def test_projection_of_ragged_feature_counts():
+    """Feature counts that no tile divides: the matrix-core kernel beyond a round of streaming workgroups (two of long sums)."""
+    from paper_2411_15785_amd import model as Mo
+    S, T128, plan = Mo.BCTM_KERNEL_STREAMING, Mo.BCTM_KERNEL_TILE128, Mo.bctm_linear_plan
+    assert plan(709, 11264, 2912) == T128 and plan(1500, 4000, 1504, swiglu=True) == T128 and plan(127, 4096, 12336) == S + 4
+    assert plan(256, 4096, 512 + 16) == T128 and plan(256, 4096, 496) == S          # 264 and 248 workgroups
+    assert plan(256, 11008, 1024 + 16) == T128 and plan(256, 11008, 1008) == S      # 520 and 504
+    assert plan(256, 11008, 544, swiglu=True) == T128 and plan(256, 11008, 480, swiglu=True) == S
+    assert plan(4096, 4096, 112) == S and plan(4096, 4096, 144) == T128             # at least one tile of features
+    assert plan(4096, 4096, 16384) == Mo.BCTM_KERNEL_TILE256 and plan(4096, 4096, 16400) == S
