@@ -9,7 +9,8 @@
 //     RW = softmax_rows(read_scale  * Q  . MK^T)   [T*G x M]
 //     MV_end   = round(MV_start + WW^T . WV)                       (section 3.4 eq., summed over t)
 //     out_t    = RW_t . (MV_start + sum_{s<=t} ww_s^T wv_s)         (read after the token's own write)
-// Tokens are grouped in sub-chunks of 128.  For sub-chunk c,
+// A chunk of few tokens is one pass over MK and MV (prefill_pass_kernel).  Otherwise tokens are grouped in sub-chunks of 128.
+// For sub-chunk c,
 //     out_c = RW_c . MV_c + tril(RW_c . WW_c^T) . WV_c,   MV_c = MV at the start of the sub-chunk,
 // where the state kernel, which walks the sub-chunks in order with its MV tile
 // in fp32 registers, leaves MV_c (rounded to bf16, as an MFMA operand has to be)
@@ -1175,45 +1176,481 @@ __global__ __launch_bounds__(256, 3) void prefill_state_kernel(const PrefillPara
   }
 }
 
+// ------------------------------------------------------------------ chunks of few tokens
+
+// With one sub-chunk MV_c is MV itself, and with few tokens the products are small beside the bytes: one pass over MK and
+// MV does the read and the update (prefill_pass_kernel).  Before it, one launch makes the statistics of the write rows and puts
+// the operands of the chunk's rows in order, since every workgroup of the pass wants them (prefill_begin_kernel); after
+// it, the outputs of the slot ranges are added (prefill_pass_merge_kernel), if there are several.
+//
+// Operand tiles of the write queries and of the read rows: tile (group of 32 rows, 16 inputs ks), lane l: row l % 32, inputs
+// 16 ks + 8 (l / 32) ..; rows that do not exist are zero.  A negative read scale moves into the read rows.  WV as in
+// prefill_transpose_kernel, 32 NT tokens.
+struct PassParams {
+  PrefillParams c;
+  uint16_t *wvt, *wqt, *qt;   // [units][..]
+  float2* pairs;              // [units][shares][T] (max, sum) of a token's write scores over a share of the slots
+  float* part;                // [units][splits][rows][d] outputs of a range of slots, not normalised
+  float2* mz;                 // [units][splits][rows] their shift and sum of weights
+  uint32_t rows;              // T G
+  uint32_t shares, share_tiles;   // of 128 slots
+  uint32_t splits;            // of 128 slots
+};
+
+template <int D, int NT, int NR>
+__global__ __launch_bounds__(256) void prefill_begin_kernel(const PassParams q) {
+  constexpr int LD = D + 8, KS = D / 16, kRows = 32 * D, NI = kRows / 512;
+  typedef RowTile<D> RT;
+  __shared__ __attribute__((aligned(16))) uint16_t sT[4 * kRows];   // a wavefront's 32 key rows each, or 64 rows of WV
+  __shared__ float2 sPair[NT][4][32];
+  static_assert(64 * LD <= 4 * kRows, "WV");
+  const PrefillParams& p = q.c;
+  const uint32_t unit = block_unit();
+  if (unit >= p.B * p.Hkv) return;
+  const uint32_t b = unit / p.Hkv, h = unit % p.Hkv, T = p.T;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64, col = lane % 32, half = lane / 32;
+  if (blockIdx.x < q.shares) {
+    // statistics of a share: a wavefront takes every fourth 32 slots of it; lane = token, register = slot
+    bf16x8 x[NT][KS];
+#pragma unroll
+    for (int g = 0; g < NT; ++g)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if ((uint32_t)(32 * g + col) < T) v = *(const u32x4*)(p.wq + (((size_t)b * T + 32 * g + col) * p.Hkv + h) * D + ks * 16 + half * 8);
+        x[g][ks] = __builtin_bit_cast(bf16x8, v);
+      }
+    const uint16_t* mk = p.mk + (size_t)(p.mk_per_seq ? unit : h) * p.M * D;
+    const uint32_t first = blockIdx.x * q.share_tiles * 128 + 32 * wave, end = min((blockIdx.x + 1) * q.share_tiles * 128, p.M);
+    float m[NT], sum[NT];
+#pragma unroll
+    for (int g = 0; g < NT; ++g) {
+      m[g] = kNegBig;
+      sum[g] = 0.f;
+    }
+    uint16_t* const strip = sT + wave * kRows;
+    const uint32_t at = RT::operand_at(lane);
+    auto request = [&](uint32_t slot) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) lds_request(mk + (size_t)slot * D + i * 512, RT::source(i, lane), strip + i * 512);
+    };
+    if (first < end) request(first);
+    for (uint32_t slot = first; slot < end; slot += 128) {
+      __builtin_amdgcn_s_waitcnt(wait_vm(0));
+      asm volatile("" ::: "memory");
+      region();
+      bf16x8 kb[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kb[ks] = RT::operand(strip, ks, at);
+      __builtin_amdgcn_s_waitcnt(kWaitLds);   // the rows have been read: the next ones may come
+      asm volatile("" ::: "memory");
+      region();
+      if (slot + 128 < end) request(slot + 128);
+#pragma unroll
+      for (int g = 0; g < NT; ++g) {
+        f32x16 s = zero16();
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) s = mfma_bf16(kb[ks], x[g][ks], s);
+        float t = kNegBig, add = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          s[v] *= p.wscale_l2e;
+          t = fmaxf(t, s[v]);
+        }
+        t = fmaxf(m[g], t);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) add += fast_exp2(s[v] - t);
+        sum[g] = sum[g] * fast_exp2(m[g] - t) + add;
+        m[g] = t;
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < NT; ++g) {
+      merge_stat(m[g], sum[g], __shfl_xor(m[g], 32, 64), __shfl_xor(sum[g], 32, 64));
+      if (half == 0) sPair[g][wave][col] = make_float2(m[g], sum[g]);
+    }
+    __syncthreads();
+    if (threadIdx.x < T) {
+      const int g = threadIdx.x / 32, c = threadIdx.x % 32;
+      float2 r = sPair[g][0][c];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) merge_stat(r.x, r.y, sPair[g][w][c].x, sPair[g][w][c].y);
+      q.pairs[((size_t)unit * q.shares + blockIdx.x) * T + threadIdx.x] = r;
+    }
+    return;
+  }
+  Tile<64, D> t;
+  t.fetch_rows(p.wv, [&](int r) -> const uint16_t* { return r < (int)T ? p.wv + (((size_t)b * T + r) * p.Hkv + h) * D : nullptr; });
+  if (p.gate) {   // the sign of a step size: see prefill_transpose_kernel
+#pragma unroll
+    for (int i = 0; i < Tile<64, D>::N; ++i) {
+      const uint32_t tk = threadIdx.x / Tile<64, D>::CPR + i * Tile<64, D>::RPP;
+      const uint32_t flip = tk < T && p.gate[((size_t)b * T + tk) * p.Hkv + h] < 0.f ? 0x80008000u : 0u;
+      t.v[i] ^= (u32x4){flip, flip, flip, flip};
+    }
+  }
+  t.put(sT, LD);
+  const uint32_t rflip = p.rscale_l2e < 0.f ? 0x80008000u : 0u;
+  for (int i = threadIdx.x; i < (NT + NR) * KS * 64; i += 256) {
+    const int l = i % 64, ks = i / 64 % KS, g = i / 64 / KS;   // row group: the write queries', then the read rows'
+    const bool wr = g < NT;
+    const uint32_t row = (wr ? g : g - NT) * 32 + l % 32, k = ks * 16 + l / 32 * 8;
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (wr && row < T) v = *(const u32x4*)(p.wq + (((size_t)b * T + row) * p.Hkv + h) * D + k);
+    if (!wr && row < q.rows)
+      v = *(const u32x4*)(p.q + (((size_t)b * T + row / p.G) * p.Hq + h * p.G + row % p.G) * D + k) ^ (u32x4){rflip, rflip, rflip, rflip};
+    u32x4* to = wr ? (u32x4*)q.wqt + (size_t)unit * NT * KS * 64 + i : (u32x4*)q.qt + (size_t)unit * NR * KS * 64 + (i - NT * KS * 64);
+    *to = v;
+  }
+  __syncthreads();
+  u32x4* dst = (u32x4*)q.wvt + (size_t)unit * NT * 32 * D / 8;
+  for (int i = threadIdx.x; i < NT * 32 * D / 8; i += 256) {
+    const int l = i % 64, tile = i / 64, hf = l / 32;
+    const int j = 32 * (tile % (D / 32)) + l % 32, t8 = 16 * (tile / (D / 32)) + 4 * hf;
+    uint32_t e[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) e[k] = sT[(t8 + (k / 4) * 8 + k % 4) * LD + j];
+    dst[i] = (u32x4){e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+  }
+}
+
+// One workgroup walks its range of slots 128 at a time, a wavefront 32 of them: keys as operands in registers, MV through
+// LDS in whole rows and back as operand tiles.  Up to 32 NT tokens and 32 NR read rows.
+//   1. scores of the read rows against this wavefront's slots (lane = row, register = slot); a row's largest of the 128
+//      moves its shift; weights of the write tokens (lane = token);
+//   2. weights, sums and MV of all wavefronts meet in LDS as operand tiles;
+//   3. a wavefront makes 32 columns of 32 read rows: += RW . MV + mask(RW . WW^T) . WV;
+//   4. the state, as in prefill_state_kernel: the same products in the same order, so MV has the same bits.
+// A workgroup is one chain of these steps, 6 us alone and 10 beside another one, and two fit a compute unit (d = 64: three, 10 %
+// faster than two): 3456 of them (B = 3, H = 36, M = 4096, T = 10) take 74 us, 4.6 TB/s.  Keys in operand order from memory instead of
+// in whole rows: 78; the operands of the rows from memory where they are used, not staged: 92; walking several tiles in a
+// workgroup with the next one's loads in flight: spills.
+template <int D, int NT, int NR>
+__global__ __launch_bounds__(256, D == 64 && NR == 1 ? 3 : D == 64 || NR == 1 ? 2 : 1) void prefill_pass_kernel(const PassParams q) {
+  constexpr int KS = D / 16, NC = D / 32;
+  constexpr int kRows = 32 * D;       // elements of a wavefront's slots
+  constexpr int NI = kRows / 512;     // load instructions of them
+  constexpr int NK = (NR * NC + 3) / 4;   // blocks of 32 rows x 32 columns of a wavefront
+  typedef RowTile<D> RT;
+  __shared__ __attribute__((aligned(16))) uint16_t sMV[4 * kRows];   // rows on the way in and out, operand tiles between
+  __shared__ __attribute__((aligned(16))) bf16x8 sW[NT * 4 * 2 * 64], sP[NR * 4 * 2 * 64];   // [group][wavefront][16 slots][lane]
+  __shared__ __attribute__((aligned(16))) u32x4 sX[NT * KS * 64], sQ[NR * KS * 64], sV[NT * 2 * NC * 64];
+  __shared__ float sMax[NR][4][32], sSum[NR][4][32];
+  __shared__ __attribute__((aligned(16))) float sShift[NT * 32];
+  const PrefillParams& p = q.c;
+  const uint32_t unit = block_unit();
+  if (unit >= p.B * p.Hkv) return;
+  const uint32_t b = unit / p.Hkv, h = unit % p.Hkv, split = blockIdx.x, T = p.T;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64, col = lane % 32, half = lane / 32;
+  const uint32_t first = split * 128, end = min(first + 128, p.M);
+  const uint16_t* mk = p.mk + (size_t)(p.mk_per_seq ? unit : h) * p.M * D;
+  uint16_t* mv = p.mv + (size_t)unit * p.M * D;
+  uint16_t* const strip = sMV + wave * kRows;
+
+  // the rows' operands, a quarter of the tiles a wavefront: older than the loads below, so they are there when those are
+#pragma unroll
+  for (int i = 0; i < (NT + NR) * KS / 4 + NT * NC / 2; ++i) {
+    const int k = i * 4 + wave;
+    const char* from = k < NT * KS         ? (const char*)q.wqt + ((size_t)unit * NT * KS + k) * 1024
+                       : k < (NT + NR) * KS ? (const char*)q.qt + ((size_t)unit * NR * KS + (k - NT * KS)) * 1024
+                                            : (const char*)q.wvt + ((size_t)unit * NT * 2 * NC + (k - (NT + NR) * KS)) * 1024;
+    u32x4* to = k < NT * KS ? sX + k * 64 : k < (NT + NR) * KS ? sQ + (k - NT * KS) * 64 : sV + (k - (NT + NR) * KS) * 64;
+    lds_request(from, (uint32_t)lane * 16u, to);
+  }
+  // M is a multiple of 64, so a wavefront's 32 slots are all inside the memory or all outside.  Keys in whole rows through
+  // the strip, then MV through registers: it is needed later.
+  const uint32_t slot0 = first + 32 * wave;
+  const bool live = slot0 < end;
+  if (live) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) lds_request(mk + (size_t)slot0 * D + i * 512, RT::source(i, lane), strip + i * 512);
+  }
+  float2 pair[kMaxStatsSplit];   // requested together; past the end the last share again, not counted
+  if (threadIdx.x < T) {
+#pragma unroll
+    for (uint32_t k = 0; k < kMaxStatsSplit; ++k) pair[k] = q.pairs[((size_t)unit * q.shares + min(k, q.shares - 1)) * T + threadIdx.x];
+  }
+  asm volatile("" ::: "memory");
+  u32x4 mn[NI];
+  if (live) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) mn[i] = __builtin_nontemporal_load((const u32x4*)(mv + (size_t)slot0 * D + i * 512) + lane);
+  }
+  asm volatile("" ::: "memory");
+  // a token's shift, from the pairs of all shares: max + log2(sum) - log2 |step size| (see store_shift)
+  if (threadIdx.x < NT * 32) {
+    float s = kNoRow;
+    if (threadIdx.x < T) {
+      float m = kNegBig, sum = 0.f;
+#pragma unroll
+      for (uint32_t k = 0; k < kMaxStatsSplit; ++k)
+        if (k < q.shares) merge_stat(m, sum, pair[k].x, pair[k].y);
+      const float le = p.gate ? __log2f(fabsf(p.gate[((size_t)b * T + threadIdx.x) * p.Hkv + h])) : 0.f;
+      s = m + __log2f(sum) - le;
+    }
+    sShift[threadIdx.x] = s;
+  }
+  if (live) __builtin_amdgcn_s_waitcnt(wait_vm(NI));   // all but MV
+  else __builtin_amdgcn_s_waitcnt(wait_vm(0));
+  lds_barrier();
+
+  const float cs = fabsf(p.rscale_l2e);
+  auto against = [&](const u32x4* rows, const bf16x8* kb) -> f32x16 {   // lane = row, register v = slot 8 (v / 4) + 4 half + v % 4
+    f32x16 s = zero16();
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) s = mfma_bf16(kb[ks], __builtin_bit_cast(bf16x8, rows[ks * 64 + lane]), s);
+    return s;
+  };
+  f32x16 oacc[NK];
+  float shift[NR], zsum[NR];
+#pragma unroll
+  for (int k = 0; k < NK; ++k) oacc[k] = zero16();
+#pragma unroll
+  for (int g = 0; g < NR; ++g) {
+    shift[g] = kNegBig;
+    zsum[g] = 0.f;
+  }
+
+  {
+    // element (slot row, this lane's column of the 32 of jt) of the strip
+    auto cell = [&](int r, int jt) { return r * D + (((4 * jt + col / 8) ^ swizzle<D>(r)) * 8) + col % 8; };
+    // 1
+    bf16x8 kb[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const bf16x8 v = RT::operand(strip, ks, RT::operand_at(lane));
+      kb[ks] = live ? v : __builtin_bit_cast(bf16x8, (u32x4){0u, 0u, 0u, 0u});
+    }
+    f32x16 s[NR];
+#pragma unroll
+    for (int g = 0; g < NR; ++g) {
+      s[g] = against(sQ + g * KS * 64, kb);
+      float tm = s[g][0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) tm = fmaxf(tm, s[g][v]);
+      tm = max_of_halves(tm);
+      if (half == 0) sMax[g][wave][col] = live ? tm * cs : kNegBig;
+    }
+#pragma unroll
+    for (int g = 0; g < NT; ++g) {
+      f32x16 w = against(sX + g * KS * 64, kb);
+      const float sh = sShift[32 * g + col];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) w[v] = live ? fast_exp2(__builtin_fmaf(w[v], p.wscale_l2e, -sh)) : 0.f;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) sW[((g * 4 + wave) * 2 + j) * 64 + lane] = pack8(w, j);
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitLds);   // the keys have been read
+    asm volatile("" ::: "memory");
+    // 2: MV to the strip in whole rows, and out of it as operand tiles (rows = columns of MV, contracted over slots)
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      *(u32x4*)(strip + RT::row(i, lane) * D + RT::chunk(i, lane) * 8) = live ? mn[i] : (u32x4){0u, 0u, 0u, 0u};
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    u32x4 mo[NC][2];
+#pragma unroll
+    for (int jt = 0; jt < NC; ++jt)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        uint32_t e[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) e[k] = strip[cell(16 * j + 8 * (k / 4) + 4 * half + k % 4, jt)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) mo[jt][j][k] = e[2 * k] | (e[2 * k + 1] << 16);
+      }
+    __builtin_amdgcn_s_waitcnt(kWaitLds);
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int jt = 0; jt < NC; ++jt)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) *(u32x4*)(strip + ((jt * 2 + j) * 64 + lane) * 8) = mo[jt][j];
+    lds_barrier();
+#pragma unroll
+    for (int g = 0; g < NR; ++g) {
+      const float to = fmaxf(fmaxf(sMax[g][0][col], sMax[g][1][col]), fmaxf(sMax[g][2][col], sMax[g][3][col]));
+      shift[g] = to;
+      float sum = 0.f;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        s[g][v] = live ? fast_exp2(__builtin_fmaf(s[g][v], cs, -to)) : 0.f;
+        sum += s[g][v];
+      }
+      sum += __shfl_xor(sum, 32, 64);
+      if (half == 0) sSum[g][wave][col] = sum;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) sP[((g * 4 + wave) * 2 + j) * 64 + lane] = pack8(s[g], j);
+    }
+    lds_barrier();
+    // 3
+#pragma unroll
+    for (int g = 0; g < NR; ++g) zsum[g] = (sSum[g][0][col] + sSum[g][1][col]) + (sSum[g][2][col] + sSum[g][3][col]);
+#pragma unroll
+    for (int k0 = 0; k0 < NK; ++k0) {
+      const int k = k0 * 4 + wave, g = k / NC, jt = k % NC;
+      if (k < NR * NC && 32u * g < q.rows) {
+        const bf16x8* pw = sP + g * 4 * 2 * 64 + lane;
+        f32x16 o = zero16();
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            o = mfma_bf16(*(const bf16x8*)(sMV + w * kRows + ((jt * 2 + j) * 64 + lane) * 8), pw[(w * 2 + j) * 64], o);
+        const int tl = (int)((32 * g + col) / p.G);   // the row's token
+#pragma unroll
+        for (int tg = 0; tg < NT; ++tg) {
+          const bf16x8* ww = sW + tg * 4 * 2 * 64 + lane;
+          f32x16 a = zero16();
+#pragma unroll
+          for (int w = 0; w < 8; ++w) a = mfma_bf16(ww[w * 64], pw[w * 64], a);
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            if (32 * tg + 8 * (v / 4) + 4 * half + v % 4 > tl) a[v] = 0.f;
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            o = mfma_bf16(__builtin_bit_cast(bf16x8, sV[operand_chunk<D>(2 * tg + j, jt, lane)]), pack8(a, j), o);
+        }
+        oacc[k0] = o;
+      }
+    }
+    // 4
+    f32x16 macc[NC];
+#pragma unroll
+    for (int jt = 0; jt < NC; ++jt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const uint32_t w = mo[jt][v / 8][v % 8 / 2];
+        macc[jt][v] = __uint_as_float(v % 2 ? w & 0xFFFF0000u : w << 16);
+      }
+#pragma unroll
+    for (int tg = 0; tg < NT; ++tg) {
+      f32x16 sc = zero16();
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) sc = mfma_bf16(__builtin_bit_cast(bf16x8, sX[(tg * KS + ks) * 64 + lane]), kb[ks], sc);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        f32x16 lo;
+#pragma unroll
+        for (int q4 = 2 * j; q4 < 2 * j + 2; ++q4) {
+          const f32x4 sh = *(const f32x4*)(sShift + 32 * tg + 8 * q4 + 4 * half);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) sc[4 * q4 + v] = fast_exp2(sc[4 * q4 + v] * p.wscale_l2e - sh[v]);
+        }
+        const bf16x8 wh = pack8(sc, j);
+        const u32x4 hw = __builtin_bit_cast(u32x4, wh);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          lo[8 * j + 2 * k] = sc[8 * j + 2 * k] - __uint_as_float(hw[k] << 16);
+          lo[8 * j + 2 * k + 1] = sc[8 * j + 2 * k + 1] - __uint_as_float(hw[k] & 0xFFFF0000u);
+        }
+        const bf16x8 wl = pack8(lo, j);
+        bf16x8 bv[NC];
+#pragma unroll
+        for (int jt = 0; jt < NC; ++jt) bv[jt] = __builtin_bit_cast(bf16x8, sV[operand_chunk<D>(2 * tg + j, jt, lane)]);
+#pragma unroll
+        for (int jt = 0; jt < NC; ++jt) macc[jt] = mfma_bf16(wh, bv[jt], macc[jt]);
+#pragma unroll
+        for (int jt = 0; jt < NC; ++jt) macc[jt] = mfma_bf16(wl, bv[jt], macc[jt]);
+      }
+    }
+    lds_barrier();   // the operand tiles have been read
+    if (live) {
+#pragma unroll
+      for (int jt = 0; jt < NC; ++jt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) strip[cell(8 * (v / 4) + 4 * half + v % 4, jt)] = bf16_bits(macc[jt][v]);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        __builtin_nontemporal_store(*(const u32x4*)(strip + RT::row(i, lane) * D + RT::chunk(i, lane) * 8), (u32x4*)(mv + (size_t)slot0 * D + i * 512) + lane);
+      __builtin_amdgcn_s_waitcnt(kWaitLds);   // the strip has been read
+      asm volatile("" ::: "memory");
+    }
+  }
+
+#pragma unroll
+  for (int k0 = 0; k0 < NK; ++k0) {
+    const int k = k0 * 4 + wave, g = k / NC, jt = k % NC;
+    const uint32_t rho = 32 * g + col;
+    if (k < NR * NC && rho < q.rows) {
+      const f32x16 o = oacc[k0];
+      const float sh = NR == 2 && g ? shift[NR - 1] : shift[0], z = NR == 2 && g ? zsum[NR - 1] : zsum[0];
+      if (q.splits == 1) {
+        const float inv = 1.0f / z;
+        uint16_t* to = p.out + (((size_t)b * T + rho / p.G) * p.Hq + h * p.G + rho % p.G) * D + 32 * jt + 4 * half;
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) store4_bf16(to + 8 * q4, o[4 * q4] * inv, o[4 * q4 + 1] * inv, o[4 * q4 + 2] * inv, o[4 * q4 + 3] * inv);
+      } else {
+        const size_t at = ((size_t)unit * q.splits + split) * q.rows + rho;
+        float* to = q.part + at * D + 32 * jt + 4 * half;
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) *(f32x4*)(to + 8 * q4) = (f32x4){o[4 * q4], o[4 * q4 + 1], o[4 * q4 + 2], o[4 * q4 + 3]};
+        if (jt == 0 && half == 0) q.mz[at] = make_float2(sh, z);
+      }
+    }
+  }
+}
+
+// out[row] = sum over the slot tiles of exp2(shift_s - shift) part_s / sum of the same of their sums, shift the largest.  One
+// workgroup = one row; group k of D / 4 lanes takes the tiles k, k + groups, ..; the groups are added in order.
+template <int D>
+__global__ __launch_bounds__(256) void prefill_pass_merge_kernel(const PassParams q) {
+  constexpr int L = D / 4, NG = 256 / L;
+  __shared__ f32x4 sO[NG][L];
+  __shared__ float sZ[NG], sM[4];
+  const PrefillParams& p = q.c;
+  const uint32_t unit = block_unit(), rho = blockIdx.x;
+  if (unit >= p.B * p.Hkv) return;
+  const uint32_t b = unit / p.Hkv, h = unit % p.Hkv;
+  const int tid = threadIdx.x, g = tid / L, l = tid % L;
+  const float2* mz = q.mz + (size_t)unit * q.splits * q.rows + rho;
+  float m = kNegBig;
+  for (uint32_t s = tid; s < q.splits; s += 256) m = fmaxf(m, mz[(size_t)s * q.rows].x);
+  m = xor_max<1, 32>(m);
+  if (tid % 64 == 0) sM[tid / 64] = m;
+  __syncthreads();
+  m = fmaxf(fmaxf(sM[0], sM[1]), fmaxf(sM[2], sM[3]));
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  float z = 0.f;
+#pragma unroll 4
+  for (uint32_t s = g; s < q.splits; s += NG) {
+    const float2 v = mz[(size_t)s * q.rows];
+    const float f = fast_exp2(v.x - m);
+    z = __builtin_fmaf(v.y, f, z);
+    o += *(const f32x4*)(q.part + (((size_t)unit * q.splits + s) * q.rows + rho) * D + 4 * l) * f;
+  }
+  sO[g][l] = o;
+  if (l == 0) sZ[g] = z;
+  __syncthreads();
+  if (g == 0) {
+#pragma unroll
+    for (int k = 1; k < NG; ++k) {
+      o += sO[k][l];
+      z += sZ[k];
+    }
+    const float inv = 1.0f / z;
+    store4_bf16(p.out + (((size_t)b * p.T + rho / p.G) * p.Hq + h * p.G + rho % p.G) * D + 4 * l, o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+  }
+}
+
 // ------------------------------------------------------------------ host side
 
-hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
-  PrefillParams p = p0;
+// The shifts of the write rows, or of the read rows of a chunk that only reads (p.stats_read).
+static hipError_t launch_stats(PrefillParams& p, hipStream_t s) {
   const uint32_t units = p.B * p.Hkv;
-  // a chunk that writes normalises its read rows on the fly (prefill_read_online_kernel): statistics of
-  // the write rows only
-  p.stats_read = (p.has_read && !p.has_write) ? 1u : 0u;
   const uint32_t rows = (p.has_write ? p.T : 0u) + (p.stats_read ? p.T * p.G : 0u);
-  const uint32_t nb = (p.T + kTC - 1) / kTC;
   const bool d128 = p.d == 128;
-  const dim3 block(256);
-  hipError_t e;
-
-  p.Tpad = nb * kTC;
-  auto transpose = [&](int which) -> hipError_t {
-    const dim3 g = unit_grid((which == 0 ? p.Tpad : p.M) / 64, units);
-    if (d128) hipLaunchKernelGGL(prefill_transpose_kernel<128>, g, block, 0, s, p, which);
-    else hipLaunchKernelGGL(prefill_transpose_kernel<64>, g, block, 0, s, p, which);
-    return hipGetLastError();
-  };
-  if (p.has_write && (e = transpose(0)) != hipSuccess) return e;
-  // with a write, the state kernel leaves MV_0 as the first snapshot on its way through
-  if (p.has_read && !p.has_write && (e = transpose(1)) != hipSuccess) return e;
-
   // Few rows of few memories leave compute units without a statistics workgroup (one fits each): split the keys, at
   // least 256 slots a share and at most 8 shares, and merge the shares' pairs in a launch of 5 us: 3 memories x 8 heads,
   // T = 333, M = 2112 (72 workgroups): 36 us in one share, 15 in three.  From 1024 slots on: 128 slots are 1.3 us of a
   // share's time, so below that the merge (5 us, and its launch) costs what the split gives.
-  // The pairs (8 bytes a row and share) lie where a later launch of the chunk writes first: in the snapshots
-  // (at least 8 KB per memory and sub-chunk) or, for a chunk that only reads, in the space of WV^T (2 d bytes a token,
-  // G rows a token).
   const uint64_t wgs = (uint64_t)((rows + kTC - 1) / kTC) * units;
   uint32_t most = p.has_write ? kMaxStatsSplit : 2 * p.d / 8 / p.G;
   if (most > kMaxStatsSplit) most = kMaxStatsSplit;
   p.stats_split = 1;
   while (p.M >= 1024 && p.stats_split < most && wgs * (p.stats_split + 1) <= 256 && p.M / (p.stats_split + 1) >= 256)
     ++p.stats_split;
-  p.stats_part = (float2*)(p.has_write ? p.snap : p.wvt);
   const dim3 gs = unit_grid((rows + kTC - 1) / kTC * p.stats_split, units);
   // Few slots: the kernel that fits two workgroups on a compute unit, where a workgroup's start and end are much of its
   // time, or where its own start (one key tile, not three) is most of the launch.  us, this kernel against the other:
@@ -1229,11 +1666,94 @@ hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
   else if (brief) hipLaunchKernelGGL(prefill_stats_short_kernel<64>, gs, dim3(512), 0, s, p);
   else if (d128) hipLaunchKernelGGL(prefill_stats_kernel<128>, gs, dim3(512), 0, s, p);
   else hipLaunchKernelGGL(prefill_stats_kernel<64>, gs, dim3(512), 0, s, p);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (p.stats_split > 1) {
-    hipLaunchKernelGGL(prefill_stats_merge_kernel, unit_grid((rows + 255) / 256, units), dim3(256), 0, s, p);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (p.stats_split == 1) return hipGetLastError();
+  {
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
+  hipLaunchKernelGGL(prefill_stats_merge_kernel, unit_grid((rows + 255) / 256, units), dim3(256), 0, s, p);
+  return hipGetLastError();
+}
+
+template <int D, int NT, int NR>
+static hipError_t launch_pass(const PassParams& q, hipStream_t s) {
+  const uint32_t units = q.c.B * q.c.Hkv;
+  hipLaunchKernelGGL((prefill_begin_kernel<D, NT, NR>), unit_grid(q.shares + 1, units), dim3(256), 0, s, q);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((prefill_pass_kernel<D, NT, NR>), unit_grid(q.splits, units), dim3(256), 0, s, q);
+  if ((e = hipGetLastError()) != hipSuccess || q.splits == 1) return e;
+  hipLaunchKernelGGL((prefill_pass_merge_kernel<D>), unit_grid(q.rows, units), dim3(256), 0, s, q);
+  return hipGetLastError();
+}
+
+// A chunk of few tokens in one pass: up to 32 read rows of a memory always; up to 64 rows (and tokens), whose workgroups are
+// alone on a compute unit with d = 128, where a memory is one workgroup or the memories are few, so that the others' chains over
+// a whole memory leave the chip idle.  us a chunk, transpose, statistics, state and read launches | begin, pass and merge (430
+// shapes): d = 128, G = 1: 3 memories of 192 slots, T = 5 24.6 | 13.6; 44 of 12864, T = 6 343 | 122; 108 of 4096, T = 10 176 | 98; 512
+// of 4096, T = 32 564 | 426; d = 64: 234 of 3904, G = 4, T = 4 161 | 100, 1024 of 192, T = 32 68.7 | 64.5 (the smallest gain up to 32 rows).
+// Up to 64 rows: d = 128, 6 of 12800, T = 55 255 | 60; 28 of 1088, T = 38 49 | 27; 1024 of 128, G = 4, T = 16 93 | 67; but 208 of 1152,
+// T = 41 104 | 141; 128 of 6976, G = 3, T = 19 323 | 387; 66 of 576, T = 47 41.6 | 40.2; d = 64, 232 of 1088, T = 45 64.5 | 68.2.
+// Its scratch lies where the other launches keep WV and the copies of MV, which are one after another: of a chunk of up to
+// 128 tokens 2 d (128 + M) bytes per memory.
+static bool pass_params(const PrefillParams& p, PassParams& q, int& nt, int& nr) {
+  if (!p.has_write || !p.has_read || p.T > 64 || p.T * p.G > 64) return false;
+  const uint64_t units = (uint64_t)p.B * p.Hkv, D = p.d;
+  const uint32_t tiles = (p.M + 127) / 128;
+  q.c = p;
+  q.rows = p.T * p.G;
+  if (q.rows > 32 && tiles > 1 && units > 64) return false;
+  nt = p.T > 32 ? 2 : 1;
+  nr = q.rows > 32 ? 2 : 1;
+  q.splits = tiles;
+  q.share_tiles = (tiles + kMaxStatsSplit - 1) / kMaxStatsSplit;
+  q.shares = (tiles + q.share_tiles - 1) / q.share_tiles;
+  const uint64_t wvt = units * nt * 32 * D * 2, qt = units * nr * 32 * D * 2, pairs = units * q.shares * p.T * 8;
+  const uint64_t part = q.splits > 1 ? units * q.splits * q.rows : 0;
+  if (2 * wvt + qt + pairs + part * (4 * D + 8) > units * (128 + p.M) * D * 2) return false;
+  q.wvt = p.wvt;
+  q.wqt = q.wvt + wvt / 2;
+  q.qt = q.wqt + wvt / 2;
+  q.part = (float*)(q.qt + qt / 2);
+  q.mz = (float2*)(q.part + part * D);
+  q.pairs = q.mz + part;
+  return true;
+}
+
+hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {
+  {
+    PassParams q;
+    int nt, nr;
+    if (pass_params(p0, q, nt, nr)) {
+      if (p0.d == 128) return nt == 2 ? launch_pass<128, 2, 2>(q, s) : nr == 2 ? launch_pass<128, 1, 2>(q, s) : launch_pass<128, 1, 1>(q, s);
+      return nt == 2 ? launch_pass<64, 2, 2>(q, s) : nr == 2 ? launch_pass<64, 1, 2>(q, s) : launch_pass<64, 1, 1>(q, s);
+    }
+  }
+  PrefillParams p = p0;
+  const uint32_t units = p.B * p.Hkv;
+  // a chunk that writes normalises its read rows on the fly (prefill_read_online_kernel): statistics of
+  // the write rows only
+  p.stats_read = (p.has_read && !p.has_write) ? 1u : 0u;
+  const uint32_t nb = (p.T + kTC - 1) / kTC;
+  const bool d128 = p.d == 128;
+  const dim3 block(256);
+  hipError_t e;
+  p.Tpad = nb * kTC;
+  auto transpose = [&](int which) -> hipError_t {
+    const dim3 g = unit_grid((which == 0 ? p.Tpad : p.M) / 64, units);
+    if (d128) hipLaunchKernelGGL(prefill_transpose_kernel<128>, g, block, 0, s, p, which);
+    else hipLaunchKernelGGL(prefill_transpose_kernel<64>, g, block, 0, s, p, which);
+    return hipGetLastError();
+  };
+  if (p.has_write && (e = transpose(0)) != hipSuccess) return e;
+  // with a write, the state kernel leaves MV_0 as the first snapshot on its way through
+  if (p.has_read && !p.has_write && (e = transpose(1)) != hipSuccess) return e;
+
+  // the pairs of a split launch (8 bytes a row and share) lie where a later launch of the chunk writes first: in the
+  // snapshots (at least 8 KB per memory and sub-chunk) or, for a chunk that only reads, in the space of WV^T (2 d bytes a
+  // token, G rows a token)
+  p.stats_part = (float2*)(p.has_write ? p.snap : p.wvt);
+  if ((e = launch_stats(p, s)) != hipSuccess) return e;
 
   // Row tiles of 128 read rows (T * G rows): G of each whole sub-chunk, as many as have a row of the last one.  All G of a
   // last sub-chunk of few tokens would be workgroups that walk the whole memory for nothing: us a chunk, all G | those
