@@ -58,7 +58,10 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
   const uint32_t RT = (rows + BM - 1) / BM, total = RT * NT, per = (total + 7) / 8;
   const uint32_t vid = (blockIdx.x % 8) * per + blockIdx.x / 8;
   if (vid >= total) return;   // the grid is 8 * per workgroups: every id below total comes up once
-  const uint32_t nfull = RT / HB;
+  // The last band takes the remainder as well (HB to 2 * HB - 1 row tiles): a band of one row tile of its own would read
+  // every weight for that row tile alone.  us, own band | this: 320 rows, 11008 -> 4096 89.5 | 82.5, 4096 -> 12288 73 | 67,
+  // SwiGLU 4096 -> 11008 120 | 111, 640 rows 107 | 102.
+  const uint32_t nfull = RT < 2 * HB ? 0u : RT / HB - 1;
   uint32_t rt, nt;
   if (vid < nfull * HB * NT) {
     const uint32_t band = vid / (HB * NT), rem = vid % (HB * NT);
@@ -299,10 +302,16 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
 //   128 x 256             one                             0.34 - 0.44
 //   128 x 128             two of four wavefronts          0.26 alone on its compute unit, 0.46 for a pair
 //   128 x 128, K in two   one                             0.19 - 0.25
+//   128 x 64, K in two    one                             0.16
 //   64 x 64, K in two     two                             0.11 alone, 0.19 for a pair
 // so 256 x 256 wins where the chip is full (4 rounds of it against 16 of 128 x 128), the others where its
 // workgroups are few: 640 rows x 11008 -> 4096 takes 157 us in 256 x 256, 117, 88, 67, 94 in the last four (with weights from
 // memory, as a stack of layers has them, the 67 are 96).
+// A compute unit gets 50 to 60 GB/s of operands then, however many stages are in flight (5 or 8 stages instead of 4:
+// the same times), so the fewest bytes per compute unit win among the shapes that have one round of workgroups, and 128 x 64 is
+// for where 64 x 64 would be pairs and 128 x 128 would leave compute units idle.  us, weights from memory, without | with it: 320
+// rows, 11008 -> 4096 82.9 | 62.4, 4096 -> 4096 30.9 | 25.9, 5120 -> 5120 41.7 | 37.9; 384 85.2 | 70.4, 31.8 | 28.3, 42.4 | 36.3; 512
+// 86.9 | 73.6, 33.5 | 29.8; 192, 2048 -> 6144 18.6 | 16.4; 1024, 2048 -> 2048 17.6 | 16.5; 700, 2048 -> 2048 15.3 | 15.6.
 // 128 x 512 has the work of 256 x 256 and 5 / 4 of its loads; it is there for row counts that 256 wastes, where it saves
 // a round of workgroups.  With weights from memory, us without | with it, tiled x: against 128 x 256 838 rows, 4096 -> 53248
 // 367 | 326, 384, 8192 -> 37376 242 | 212; against 128 x 128 526, 4096 -> 66560 366 | 314, 319, 4096 -> 69632 239 | 216 (a predicted 2 %:
@@ -314,7 +323,7 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
 // tile wins in all 37 shapes: 4654, 11008 -> 20992 2105 | 1841, 1911, 1024 -> 50176 218 | 212.
 // A count of columns that 128 does not divide leaves the last tile of every row of tiles partly used, in any shape: all of them
 // are open to it, at what their whole tiles cost.
-enum RowsShape { kTile256, kTile128x512, kTile128x256, kTile128, kTile128K2, kTile64K2 };
+enum RowsShape { kTile256, kTile128x512, kTile128x256, kTile128, kTile128K2, kTile128x64K2, kTile64K2 };
 
 RowsShape rows_shape(uint32_t rows, uint32_t bcols, uint32_t K, bool x_tiled) {
   auto tiles = [&](uint32_t bm, uint32_t bn) { return (uint64_t)((rows + bm - 1) / bm) * ((bcols + bn - 1) / bn); };
@@ -333,6 +342,7 @@ RowsShape rows_shape(uint32_t rows, uint32_t bcols, uint32_t K, bool x_tiled) {
     }
   };
   take(kTile128K2, one(tiles(128, 128), 25));
+  take(kTile128x64K2, one(tiles(128, 64), 16));
   take(kTile64K2, two(tiles(64, 64), 11, 19));
   const bool ragged = bcols % 128 != 0;
   if (bcols % 256 == 0 || ragged) {
@@ -374,6 +384,7 @@ void launch_rows(const void* x, const void* w, const void* w2, const void* resid
     case kTile128x256: return launch_shape<SWIGLU, XT, 4, 4, 2, 4, 1>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
     case kTile128: return launch_shape<SWIGLU, XT, 4, 4, 2, 2, 1>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
     case kTile128K2: return launch_shape<SWIGLU, XT, 4, 4, 2, 2, 2>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
+    case kTile128x64K2: return launch_shape<SWIGLU, XT, 2, 4, 4, 1, 2>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
     case kTile64K2: return launch_shape<SWIGLU, XT, 2, 2, 2, 2, 2>(x, w, w2, residual, dst, rows, K, bcols, out_tiled, s);
   }
 }
@@ -388,6 +399,7 @@ LinearTile linear_rows_tile(uint32_t rows, uint32_t K, uint32_t N, bool swiglu, 
     case kTile128x256: return {128, 256 / per, 1};
     case kTile128: return {128, 128 / per, 1};
     case kTile128K2: return {128, 128 / per, 2};
+    case kTile128x64K2: return {128, 64 / per, 2};
     case kTile64K2: return {64, 64 / per, 2};
   }
   return {0, 0, 0};

@@ -35,7 +35,7 @@ def test_linear(M, rows, K, N, tile):
     assert np.array_equal(*bits)
 
 
-@pytest.mark.parametrize("rows,K,N,tile", [(128, 96, 6176, (64, 32, 2)), (130, 32, 6176, (128, 64, 2)), (150, 64, 12320, (128, 128, 1)),
+@pytest.mark.parametrize("rows,K,N,tile", [(128, 96, 2080, (64, 32, 2)), (128, 96, 6176, (128, 32, 2)), (130, 32, 6176, (128, 64, 2)), (150, 64, 12320, (128, 128, 1)),
                                            (300, 32, 12320, (256, 128, 1)), (520, 32, 12320, (128, 256, 1)),
                                            (700, 32, 12320, (128, 64, 1)), (1030, 1024, 160, (64, 32, 2))])
 def test_swiglu(M, rows, K, N, tile):
