@@ -253,9 +253,19 @@ void plan_mv_pass(DecodeParams& p, int dtype) {
   // With one query head per KV head (2 scores per slot) it loses at every size: 345 -> 378 us for the pass at
   // B = 32, H = 32, M = 4096.
   const uint64_t scratch = wgs * (256u * (1 + p.G) + (p.S > 1 ? 512u * p.G : 0u));   // 64 slots a workgroup
-  const uint64_t cycle = (uint64_t)p.S * p.Hkv, xcd_keys = (uint64_t)p.Hkv * p.M * 256u /
-                                                           (cycle % 8 == 0 ? 8 : cycle % 4 == 0 ? 4 : cycle % 2 == 0 ? 2 : 1);
-  p.rescore = gqa && p.d == 128 && scratch >= (192u << 20) && xcd_keys <= (5u << 19) ? 1u : 0u;
+  auto keys_in_reach = [&](uint32_t splits) {
+    const uint64_t cycle = (uint64_t)splits * p.Hkv;
+    return (uint64_t)p.Hkv * p.M * 256u / (cycle % 8 == 0 ? 8 : cycle % 4 == 0 ? 4 : cycle % 2 == 0 ? 2 : 1) <= (5u << 19);
+  };
+  p.rescore = gqa && p.d == 128 && scratch >= (192u << 20) && keys_in_reach(p.S) ? 1u : 0u;
+  // Re-scored, a workgroup takes two tiles of 64 slots, which halves the partial outputs.  us, one | two: G = 3, n = 1536 memories of
+  // 80 tiles 736 | 721, 2400 of 40 581 | 564; G = 4, 512 of 128 409 | 392, 1200 of 60 456 | 436, 32000 of 2 (no merge left) 458 |
+  // 402, 12000 of 4 330 | 329; G = 8, 512 of 128 467 | 422, 1024 of 32 244 | 229.  An odd number of tiles leaves the last workgroup
+  // one: G = 4, 768 of 97 469 | 476, 480 of 159 473 | 476; G = 5, 512 of 127 426 | 424; G = 6, 2048 of 19 268 | 268; G = 7, 800 of 49
+  // 280 | 270; G = 8, 4000 of 17 512 | 478, 480 of 159 576 | 503, 16000 of 3 402 | 459.  Three and four tiles: 426 and 424 where one
+  // takes 406 and two 395.  With stored scores two tiles lose as often as they win (G = 3 and 4, M = 6080 162 | 178).
+  const uint32_t two = (p.S + 1) / 2;
+  if (p.rescore && (p.S % 2 == 0 || (p.G > 6 && p.S > 16)) && keys_in_reach(two)) p.S = two;
 }
 
 template <typename DT, int D, int GT, int BS, int U, bool NORM>
@@ -298,7 +308,11 @@ static bool launch_shape(const DecodeParams& p, hipStream_t s) {
       return true;
     }
   } else if (p.mv_bs == kGqa.bs && p.mv_u == kGqa.u && G > 2 && !p.has_read) {
-    launch_mode<DT, D, 1, 128, 8>(p, s);   // write-only step of a cache whose reads take the MFMA pass
+    // write-only step of a cache whose reads take the MFMA pass, where a workgroup may have two tiles: here it has one
+    DecodeParams q = p;
+    const uint32_t slots = kGqa.bs * kGqa.u * 8u / p.d;
+    q.S = (p.M + slots - 1) / slots;
+    launch_mode<DT, D, 1, 128, 8>(q, s);
     return true;
   }
   return false;

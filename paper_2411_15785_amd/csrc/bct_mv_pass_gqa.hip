@@ -18,7 +18,10 @@
 // key row 4 a + c of group n = slot 8 a + 4 n + c, column g = query head g, column 15 = the write row.  Lane
 // (sub, sl) then holds, in the two groups, exactly the scores of head g = sub for its 8 slots, the A
 // operand above; the write weights reach the 16 lanes of a slot row by a row broadcast from column 15.
-// For large grids only (plan_mv_pass has the measurements); those take their normalisers from the launch.
+// For large grids only (plan_mv_pass has the measurements); those take their normalisers from the launch.  What is left beside
+// MV are the partial outputs, 512 G bytes a workgroup that the merge reads again (B = 64, Hkv = 8, G = 4, M = 8192: 134 MB both
+// ways), so a workgroup takes two tiles of slots, one after the other.  180 registers, two wavefronts a SIMD; held to three:
+// 395 us of that step against 391.
 #include "bct_device.h"
 #include "bct_internal.h"
 
@@ -43,13 +46,7 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
   const int col = lane % 16, kg = lane / 16;     // query head (row of A), group of eight entries of the contraction
   const uint32_t R = p.R, G = p.G, M = p.M;
 
-  // M is a multiple of 64: the SPI * U (32 or 64) slots of a wavefront are all inside the memory or all outside
-  const uint32_t slot0 = split * SPB + wave * (SPI * U) + sl * U;
-  const bool active = slot0 < M;
-  uint16_t* mv = (uint16_t*)p.mv + ((size_t)unit * M + slot0) * D + sub * 8;
-
-  // RESCORE: the keys and this lane's query row (column sub), requested before MV
-  u32x4 kf[RESCORE ? 2 : 1][4], xq[4];
+  u32x4 xq[4];   // RESCORE: this lane's query row (column sub)
   const bool wcol = WRITE && col == 15;
   if (RESCORE) {
 #pragma unroll
@@ -60,124 +57,139 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) xq[ks] = *(const u32x4*)(x + ks * 32 + sl * 8);
     }
-    if (active) {
-      const uint16_t* mk = (const uint16_t*)p.mk + ((size_t)h * M + split * SPB + wave * (4 * U)) * D + sl * 8;
-#pragma unroll
-      for (int n = 0; n < 2; ++n)
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-          kf[RESCORE ? n : 0][ks] = *(const u32x4*)(mk + (size_t)(8 * (sub / 4) + 4 * n + sub % 4) * D + ks * 32);
-    }
   }
-  u32x4 raw[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) raw[u] = (u32x4){0u, 0u, 0u, 0u};
-  if (active) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) raw[u] = __builtin_nontemporal_load((const u32x4*)(mv + (size_t)u * D));
-  }
-
-  // (max, 1/sum) of the write row and of this lane's read row (query head g = col)
-  float2 nw = make_float2(0.f, 0.f), nr = make_float2(0.f, 0.f);
-  if (NORM) {
-    // all rows' pairs are requested before the first is reduced (rows past R repeat row 0 and are dropped)
-    TileStats ts[kMaxRows];
-#pragma unroll
-    for (uint32_t r = 0; r < kMaxRows; ++r)
-      ts[r] = load_tile_stats(p.stats + ((size_t)unit * R + (r < R ? r : 0u)) * p.n_tiles, p.n_tiles, lane);
-#pragma unroll
-    for (uint32_t r = 0; r < kMaxRows; ++r) {
-      if (r < R) {
-        const float2 ms = merge_tile_stats(ts[r]);
-        const float mx = ms.x;
-        float inv = 1.0f / ms.y;
-        if (WRITE && r == 0) {
-          if (p.gate) inv *= p.gate[(size_t)b * p.gate_bstride + h];
-          nw = make_float2(mx, inv);
-        }
-        if (r == W + (uint32_t)col && r >= W) nr = make_float2(mx, inv);
-      }
-    }
-  } else {
-    if (WRITE) nw = p.norm[(size_t)unit * R];
-    if ((uint32_t)col < G) nr = p.norm[(size_t)unit * R + W + col];
-  }
-
-  // rw: the lane's weights as an A operand (zero in lanes without a query head); ww: the write weights of its slots, with
-  // stored scores only where they are used (here as well, the pass takes 1-2 % longer)
-  const float* sc = p.scores + (size_t)unit * R * M + slot0;  // row r at sc + r * M
-  float rw[PARTS][U], ww[U];
-#pragma unroll
-  for (int j = 0; j < PARTS; ++j)
-#pragma unroll
-    for (int u = 0; u < U; ++u) rw[j][u] = 0.f;
-  if (RESCORE) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) ww[u] = 0.f;
-    if (active) {
-      const float scale = wcol ? p.wscale_l2e : p.rscale_l2e;
-      const float2 n2 = wcol ? nw : nr;
-#pragma unroll
-      for (int n = 0; n < 2; ++n) {
-        const f32x4 c = score16<D>(kf[RESCORE ? n : 0], xq);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const float e = fast_exp2(c[v] * scale - n2.x) * n2.y;
-          if (WRITE) ww[4 * n + v] = row_lane<15>(e);
-          rw[0][4 * n + v] = (uint32_t)col < G ? e : 0.f;
-        }
-      }
-    }
-  } else {
-    if (active && (uint32_t)col < G) {
-      // this lane's entries of the contraction: its own slots with one part, with two those of both groups
-      const float* from = PARTS == 1 ? sc : p.scores + (size_t)unit * R * M + split * SPB + wave * (SPI * U) + kg * (PARTS * U);
-#pragma unroll
-      for (int j = 0; j < PARTS; ++j)
-#pragma unroll
-        for (int k = 0; k < U / 4; ++k) {
-          const f32x4 a = *(const f32x4*)(from + (size_t)(W + col) * M + j * U + 4 * k);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) rw[j][4 * k + i] = fast_exp2(a[i] - nr.x) * nr.y;
-        }
-    }
-  }
-  // hi + lo bf16 parts of the lane's weights, 8 slots per block: the A operands
-  u32x4 ahi[NB][PARTS], alo[NB][PARTS];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-    for (int j = 0; j < PARTS; ++j) split_hi_lo(&rw[j][8 * nb], ahi[nb][j], alo[nb][j]);
-
-  if (WRITE && active) {
-    if (!RESCORE) {
-#pragma unroll
-      for (int k = 0; k < U / 4; ++k) {
-        const f32x4 a = *(const f32x4*)(sc + 4 * k);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) ww[4 * k + i] = fast_exp2(a[i] - nw.x) * nw.y;
-      }
-    }
-    float wvf[8];
-    const uint16_t* wv = (const uint16_t*)p.wv + (size_t)b * p.kv_bstride + (size_t)h * D;
-    unpack16<BF16>(*(const u32x4*)(wv + sub * 8), wvf);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float x[8];
-      unpack16<BF16>(raw[u], x);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = __builtin_fmaf(ww[u], wvf[e], x[e]);
-      raw[u] = pack16_round<BF16>(x);
-      __builtin_nontemporal_store(raw[u], (u32x4*)(mv + (size_t)u * D));
-    }
-  }
-
   constexpr int NP = ReadShape<LPS>::kProducts;
   f32x4 acc[NP];
 #pragma unroll
   for (int e = 0; e < NP; ++e) acc[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  // RESCORE: as many tiles of SPB slots as the plan's splits leave a workgroup, otherwise one
+  const uint32_t n_tiles = (M + SPB - 1) / SPB, per = RESCORE ? (n_tiles + p.S - 1) / p.S : 1u, first = split * per;
+  const uint32_t end = RESCORE ? min(first + per, n_tiles) : first + 1;
+  float2 nw = make_float2(0.f, 0.f), nr = make_float2(0.f, 0.f);
+  for (uint32_t tile = first; tile < end; ++tile) {
+    // M is a multiple of 64: the SPI * U (32 or 64) slots of a wavefront are all inside the memory or all outside
+    const uint32_t slot0 = tile * SPB + wave * (SPI * U) + sl * U;
+    const bool active = slot0 < M;
+    uint16_t* mv = (uint16_t*)p.mv + ((size_t)unit * M + slot0) * D + sub * 8;
+
+    // RESCORE: the keys, requested before MV
+    u32x4 kf[RESCORE ? 2 : 1][4];
+    if (RESCORE) {
+      if (active) {
+        const uint16_t* mk = (const uint16_t*)p.mk + ((size_t)h * M + tile * SPB + wave * (4 * U)) * D + sl * 8;
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) mfma_read<LPS>(raw + 8 * nb, ahi[nb], alo[nb], acc);
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks)
+            kf[RESCORE ? n : 0][ks] = *(const u32x4*)(mk + (size_t)(8 * (sub / 4) + 4 * n + sub % 4) * D + ks * 32);
+      }
+    }
+    u32x4 raw[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) raw[u] = (u32x4){0u, 0u, 0u, 0u};
+    if (active) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) raw[u] = __builtin_nontemporal_load((const u32x4*)(mv + (size_t)u * D));
+    }
+
+    if (tile == first) {
+      // (max, 1/sum) of the write row and of this lane's read row (query head g = col)
+      if (NORM) {
+        // all rows' pairs are requested before the first is reduced (rows past R repeat row 0 and are dropped)
+        TileStats ts[kMaxRows];
+#pragma unroll
+        for (uint32_t r = 0; r < kMaxRows; ++r)
+          ts[r] = load_tile_stats(p.stats + ((size_t)unit * R + (r < R ? r : 0u)) * p.n_tiles, p.n_tiles, lane);
+#pragma unroll
+        for (uint32_t r = 0; r < kMaxRows; ++r) {
+          if (r < R) {
+            const float2 ms = merge_tile_stats(ts[r]);
+            const float mx = ms.x;
+            float inv = 1.0f / ms.y;
+            if (WRITE && r == 0) {
+              if (p.gate) inv *= p.gate[(size_t)b * p.gate_bstride + h];
+              nw = make_float2(mx, inv);
+            }
+            if (r == W + (uint32_t)col && r >= W) nr = make_float2(mx, inv);
+          }
+        }
+      } else {
+        if (WRITE) nw = p.norm[(size_t)unit * R];
+        if ((uint32_t)col < G) nr = p.norm[(size_t)unit * R + W + col];
+      }
+    }
+    // rw: the lane's weights as an A operand (zero in lanes without a query head); ww: the write weights of its slots, with
+    // stored scores only where they are used (here as well, the pass takes 1-2 % longer)
+    const float* sc = p.scores + (size_t)unit * R * M + slot0;  // row r at sc + r * M
+    float rw[PARTS][U], ww[U];
+#pragma unroll
+    for (int j = 0; j < PARTS; ++j)
+#pragma unroll
+      for (int u = 0; u < U; ++u) rw[j][u] = 0.f;
+    if (RESCORE) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) ww[u] = 0.f;
+      if (active) {
+        const float scale = wcol ? p.wscale_l2e : p.rscale_l2e;
+        const float2 n2 = wcol ? nw : nr;
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          const f32x4 c = score16<D>(kf[RESCORE ? n : 0], xq);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float e = fast_exp2(c[v] * scale - n2.x) * n2.y;
+            if (WRITE) ww[4 * n + v] = row_lane<15>(e);
+            rw[0][4 * n + v] = (uint32_t)col < G ? e : 0.f;
+          }
+        }
+      }
+    } else {
+      if (active && (uint32_t)col < G) {
+        // this lane's entries of the contraction: its own slots with one part, with two those of both groups
+        const float* from = PARTS == 1 ? sc : p.scores + (size_t)unit * R * M + tile * SPB + wave * (SPI * U) + kg * (PARTS * U);
+#pragma unroll
+        for (int j = 0; j < PARTS; ++j)
+#pragma unroll
+          for (int k = 0; k < U / 4; ++k) {
+            const f32x4 a = *(const f32x4*)(from + (size_t)(W + col) * M + j * U + 4 * k);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) rw[j][4 * k + i] = fast_exp2(a[i] - nr.x) * nr.y;
+          }
+      }
+    }
+    // hi + lo bf16 parts of the lane's weights, 8 slots per block: the A operands
+    u32x4 ahi[NB][PARTS], alo[NB][PARTS];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int j = 0; j < PARTS; ++j) split_hi_lo(&rw[j][8 * nb], ahi[nb][j], alo[nb][j]);
+
+    if (WRITE && active) {
+      if (!RESCORE) {
+#pragma unroll
+        for (int k = 0; k < U / 4; ++k) {
+          const f32x4 a = *(const f32x4*)(sc + 4 * k);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) ww[4 * k + i] = fast_exp2(a[i] - nw.x) * nw.y;
+        }
+      }
+      float wvf[8];
+      const uint16_t* wv = (const uint16_t*)p.wv + (size_t)b * p.kv_bstride + (size_t)h * D;
+      unpack16<BF16>(*(const u32x4*)(wv + sub * 8), wvf);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        float x[8];
+        unpack16<BF16>(raw[u], x);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = __builtin_fmaf(ww[u], wvf[e], x[e]);
+        raw[u] = pack16_round<BF16>(x);
+        __builtin_nontemporal_store(raw[u], (u32x4*)(mv + (size_t)u * D));
+      }
+    }
+
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) mfma_read<LPS>(raw + 8 * nb, ahi[nb], alo[nb], acc);
+  }
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const uint32_t g = 4 * kg + v;
