@@ -1,6 +1,7 @@
 // Decode-step kernels of libbct (gfx950).
 //
-// One decode step of one layer is four launches on the caller's stream:
+// One decode step of one layer is up to four launches on the caller's stream (small and mid-size caches: one, bct_whole.hip
+// and bct_fused.hip):
 //   1. scores : for every memory (b, h) and every row (the write query wq and
 //               the G read queries q), the scaled dot products with all M keys
 //               of MK, kept in the log2 domain, plus one (max, sum) pair per
