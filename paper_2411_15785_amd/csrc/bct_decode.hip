@@ -390,7 +390,6 @@ void plan_decode(DecodeParams& p, int dtype) {
   }
   p.n_tiles = p.M / p.stat_tile;
   plan_mv_pass(p, dtype);
-  if (!use_mfma_scores(p, dtype)) p.rescore = 0u;
   p.fused = (dtype == 0 && p.G == 1 && p.M <= kFusedMaxM && (uint64_t)p.B * p.Hkv <= kFusedMaxUnits) ? 1u : 0u;
 }
 

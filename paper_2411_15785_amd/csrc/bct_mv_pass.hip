@@ -250,6 +250,7 @@ void plan_mv_pass(DecodeParams& p, int dtype) {
   //                               scratch 100 to 192 MB  1.00 to 1.07 | 0.98 to 1.01, below 0.98 to 1.06 | 0.98 to 1.00
   //   3 MB 0.98 to 1.02 | 0.88 to 0.99, more 0.82 to 0.99 | 0.80 to 0.99 (B = 62, Hkv = 15, G = 3, M = 4032, all keys
   //   on every XCD: 360 -> 445 us in one workspace)
+  // Keys of each sequence come from memory, not from an XCD's cache, and their statistics are not made by the matrix cores.
   // With one query head per KV head (2 scores per slot) it loses at every size: 345 -> 378 us for the pass at
   // B = 32, H = 32, M = 4096.
   const uint64_t scratch = wgs * (256u * (1 + p.G) + (p.S > 1 ? 512u * p.G : 0u));   // 64 slots a workgroup
@@ -257,7 +258,7 @@ void plan_mv_pass(DecodeParams& p, int dtype) {
     const uint64_t cycle = (uint64_t)splits * p.Hkv;
     return (uint64_t)p.Hkv * p.M * 256u / (cycle % 8 == 0 ? 8 : cycle % 4 == 0 ? 4 : cycle % 2 == 0 ? 2 : 1) <= (5u << 19);
   };
-  p.rescore = gqa && p.d == 128 && scratch >= (192u << 20) && keys_in_reach(p.S) ? 1u : 0u;
+  p.rescore = gqa && p.d == 128 && !p.mk_per_seq && scratch >= (192u << 20) && keys_in_reach(p.S) ? 1u : 0u;
   // Re-scored, a workgroup takes two tiles of 64 slots, which halves the partial outputs.  us, one | two: G = 3, n = 1536 memories of
   // 80 tiles 736 | 721, 2400 of 40 581 | 564; G = 4, 512 of 128 409 | 392, 1200 of 60 456 | 436, 32000 of 2 (no merge left) 458 |
   // 402, 12000 of 4 330 | 329; G = 8, 512 of 128 467 | 422, 1024 of 32 244 | 229.  An odd number of tiles leaves the last workgroup

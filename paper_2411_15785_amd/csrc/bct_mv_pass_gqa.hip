@@ -239,7 +239,9 @@ static void launch_gqa_bs(const DecodeParams& p, hipStream_t s) {
 hipError_t launch_stream_gqa(const DecodeParams& p, hipStream_t s) {
   if (p.G <= 2 || p.G > kMaxG || !p.has_read) return hipErrorInvalidConfiguration;
   if (p.mv_bs != 128 || p.mv_u != 8) return hipErrorInvalidConfiguration;
-  if (p.rescore && (p.fuse_norm || p.d != 128)) return hipErrorInvalidConfiguration;
+  if (p.rescore && (p.fuse_norm || p.d != 128 || p.mk_per_seq)) return hipErrorInvalidConfiguration;
+  // with stored scores a workgroup has one tile of slots: the splits have to cover the memory
+  if (!p.rescore && (uint64_t)p.S * (128 * 8 * 8 / p.d) < p.M) return hipErrorInvalidConfiguration;
   if (p.d == 128) launch_gqa_bs<128, 8, 128>(p, s);
   else launch_gqa_bs<128, 8, 64>(p, s);
   return hipGetLastError();

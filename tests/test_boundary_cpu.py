@@ -351,3 +351,25 @@ def test_projection_of_ragged_feature_counts():
     assert plan(256, 11008, 544, swiglu=True) == T128 and plan(256, 11008, 480, swiglu=True) == S
     assert plan(4096, 4096, 112) == S and plan(4096, 4096, 144) == T128             # at least one tile of features
     assert plan(4096, 4096, 16384) == Mo.BCTM_KERNEL_TILE256 and plan(4096, 4096, 16400) == S
+
+
+def test_workgroups_of_the_mv_pass_cover_every_memory(L):
+    """Plans of streaming steps: splits of a memory x slots of a workgroup are M slots and no workgroup more; where the scores
+    are made again a workgroup has one tile of slots or two, and only keys that the batch shares are scored again."""
+    import itertools
+    rescored = 0
+    heads = [(8192, 64, 8), (8192, 32, 8), (4096, 64, 16), (2048, 64, 16), (1280, 1020, 3), (1344, 1000, 3), (128, 2000, 8),
+             (192, 2001, 8), (64, 10923, 8), (15360, 24, 1), (16384, 64, 16), (640, 3, 2)]
+    for (M, B, H), G, d, dt, keys in itertools.product(heads, range(1, 9), (64, 128), (P.BCT_F32, P.BCT_BF16),
+                                                       (0, P.BCT_MK_PER_SEQUENCE)):
+        dsc = P.make_desc(M, B, H * G, H, d, dt, 0.1, 0.1, keys | P.BCT_STEP_STREAMING)
+        (st, plan), (st2, again) = P.bct_plan_query(dsc), P.bct_plan_rescores(dsc)
+        assert st == st2 == P.BCT_OK
+        row = d * (4 if dt == P.BCT_F32 else 2)
+        tile = plan["mv_workgroup"] * plan["mv_loads_per_lane"] * 16 // row
+        tiles = -(-M // tile)
+        what = (M, B, H, G, d, dt, keys, plan, again)
+        assert plan["mv_splits"] in ((tiles, -(-tiles // 2)) if again else (tiles,)), what
+        assert not again or not keys, what
+        rescored += again
+    assert rescored > 0

@@ -39,3 +39,39 @@ def test_steps(B, Hkv, G, M, splits):
         else:
             assert torch.equal(got.view(torch.int16), whole.view(torch.int16))
     assert np.array_equal(to_np(gpu.keys_view(), "bf16"), mk)
+
+
+@pytest.mark.parametrize("B,Hkv,G,M", [(1020, 3, 4, 1280), (1000, 3, 8, 1344)])
+def test_steps_with_keys_of_each_sequence(B, Hkv, G, M):
+    """Grids as large, of keys that cannot be scored again from a shared table: one tile a workgroup, all slots are taken."""
+    import paper_2411_15785_amd as P
+    from oracle import bct_ref as R
+    import torch
+    w = syn.Workload("tiles_own_keys", 1, B, Hkv * G, Hkv, 128, M, "bf16", 5)
+    bs = [0, B - 1]
+    gpu = P.BctCache(M, B, Hkv * G, Hkv, 128, torch.bfloat16, w.scale, w.scale, P.BCT_MK_PER_SEQUENCE)
+    ref = R.RefCache(M, len(bs), Hkv * G, Hkv, 128, "bf16", w.scale, w.scale, P.BCT_MK_PER_SEQUENCE)
+    gpu.set_keys(torch.randn((B, Hkv, M, 128), generator=torch.Generator("cuda:0").manual_seed(3), device="cuda:0",
+                             dtype=torch.bfloat16))
+    gpu.randomize_values(7, 1.0)
+    assert P.bct_plan_rescores(gpu.desc) == (P.BCT_OK, 0) and P.bct_plan_query(gpu.desc)[1]["mv_splits"] == M // 64
+    for t, (read, keyed) in enumerate(((True, False), (False, False), (True, True))):
+        q, wq, wv = syn.make_step(w, t)
+        wk = np.roll(wq, 1, axis=-1) if keyed else None
+        q = q if read else None
+        before = to_np(gpu.values_view()[bs], "bf16")
+        keys = to_np(gpu.keys_view()[bs], "bf16")
+        ref.set_keys(keys)
+        ref.set_values(before)
+        what = f"M={M} G={G} read={read} keyed={keyed}"
+        dev = [to_dev(a, "bf16") for a in (q, wq, wv, wk)]
+        if keyed:
+            o = gpu.decode_step_keyed(*dev)
+            o_ref = ref.decode_step_keyed(sub(q, bs), sub(wq, bs), sub(wv, bs), sub(wk, bs))
+            check_state_one_step(to_np(gpu.keys_view()[bs], "bf16"), ref.keys(), "bf16", what + " keys", before=keys)
+        else:
+            o = gpu.decode_step(*dev[:3])
+            o_ref = ref.decode_step(sub(q, bs), sub(wq, bs), sub(wv, bs))
+        if read:
+            check_out(to_np(o[bs], "bf16"), o_ref, "bf16", what)
+        check_state_one_step(to_np(gpu.values_view()[bs], "bf16"), ref.values(), "bf16", what, before=before)
