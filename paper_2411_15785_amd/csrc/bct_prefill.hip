@@ -1429,7 +1429,8 @@ __global__ __launch_bounds__(256, D == 64 && NR == 1 ? 3 : D == 64 || NR == 1 ? 
 #pragma unroll
       for (int v = 1; v < 16; ++v) tm = fmaxf(tm, s[g][v]);
       tm = max_of_halves(tm);
-      if (half == 0) sMax[g][wave][col] = live ? tm * cs : kNegBig;
+      // a tile whose scores all overflowed to -inf still has a finite shift: its weights are zero
+      if (half == 0) sMax[g][wave][col] = live ? fmaxf(tm * cs, kNegBig) : kNegBig;
     }
 #pragma unroll
     for (int g = 0; g < NT; ++g) {

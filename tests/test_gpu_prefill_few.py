@@ -96,3 +96,26 @@ def test_repeats_itself_and_replays(P):
         assert torch.equal(c[0].values_view().view(torch.int16), c[1].values_view().view(torch.int16))
         for x in c:
             x.prefill(*long, 64)
+
+
+@pytest.mark.parametrize("d,G,T,first", [(64, 1, 5, 128), (128, 1, 5, 0), (128, 4, 12, 128), (64, 2, 24, 192)])
+def test_slots_masked_by_their_keys(P, R, d, G, T, first):
+    """Keys whose scores overflow to -inf take no weight, also where they are all of a 128-slot tile."""
+    B, Hkv, M = 2, 2, 320
+    w = syn.Workload("few_masked", 1, B, Hkv * G, Hkv, d, M, "bf16", 0)
+    ref, gpu, mk, mv, _ = make_pair(w, R.RefCache, P.BctCache, mv0=True, max_prefill_T=T)
+    keys = f64(mk, "bf16")
+    keys[:, first:first + 128] = 0.0
+    keys[:, first:first + 128, 0] = -3e38
+    mk = syn.pack(keys, "bf16")
+    gpu.set_keys(to_dev(mk, "bf16"))
+    ref.set_keys(mk)
+    q, wq, wv = (f64(a, "bf16") for a in syn.make_step(w, 0, T=T))
+    q[..., 0] = wq[..., 0] = 2.0
+    q, wq, wv = (syn.pack(a, "bf16") for a in (q, wq, wv))
+    o_ref = ref.prefill(q, wq, wv, T)
+    o = gpu.prefill(to_dev(q, "bf16"), to_dev(wq, "bf16"), to_dev(wv, "bf16"), T)
+    check_prefill_out(to_np(o, "bf16"), o_ref, "bf16", "masked")
+    got = to_np(gpu.values_view(), "bf16")
+    check_prefill_state(R, ref, mk, wq, wv, got, T, "masked")
+    assert np.array_equal(got[:, :, first:first + 128], mv[:, :, first:first + 128])
