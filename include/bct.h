@@ -108,6 +108,8 @@ bct_status bct_cache_randomize_values(bct_cache* c, uint64_t seed, float amplitu
  *   k_new == v_new == NULL : read-only step, MV untouched.
  *   q == out == NULL       : write-only step = one iteration of Algorithm 1.
  *   any other NULL mix     : BCT_ERR_INVALID_ARG.
+ * out may be q itself, or share memory with q and k_new in any other way: where one launch would store rows that another
+ * workgroup still has to read, the step takes other launches (bct_plan_step).
  * steps += 1.  Errors: INVALID_ARG, MISALIGNED, STATE, HIP. */
 bct_status bct_decode_step(bct_cache* c, const void* q, const void* k_new, const void* v_new,
                            void* out, void* hip_stream);
@@ -214,6 +216,14 @@ bct_status bct_plan_rescores(const bct_cache_desc* desc, uint32_t* rescores);
 /* *workgroups = how many workgroups of *threads threads take one memory through the whole step (sections 3.2 and 3.4, and
  * the read) in one launch, or 0 where several launches or the smallest caches' own one do.  Host logic only, as above. */
 bct_status bct_plan_whole(const bct_cache_desc* desc, uint32_t* workgroups, uint32_t* threads);
+
+/* The same for a step with these buffers, whose addresses are compared and never read: *workgroups per memory of a one-launch
+ * step of either kind, 0 where the step takes several launches, and *mv_splits of the pass over MV in that case.  What counts is how
+ * out lies to the inputs (section 3.2 steps 2-4 read q and k_new before the output exists); NULL and bytes of their own are alike.
+ * Host logic only, as above. */
+bct_status bct_plan_step(const bct_cache_desc* desc, const void* q, const void* k_new, const void* v_new,
+                         const void* key_new, const float* gate, const float* key_gate, const void* out,
+                         uint32_t* workgroups, uint32_t* mv_splits);
 
 /* Device addresses of the two regions inside cache_mem, MK first, then MV (section 3.1's two
  * sequences), for zero-copy views of the state: the bounded-cache layout in HBM as the caller sees it. */

@@ -28,7 +28,7 @@ struct bct_cache {
   uint64_t steps;
   bool keys_set;
   bct::DecodeParams plan;  // shape, strides and launch plan; pointers filled per call
-  bct::WholePlan whole;
+  bct::WholePlan whole, whole_one;   // the step as one launch: of any shape, of one workgroup per memory
   // optional per-launch timing: 4 events per recorded step
   std::vector<hipEvent_t> prof_ev;
   uint32_t prof_cap = 0, prof_n = 0;
@@ -90,7 +90,8 @@ struct Sizes {
   size_t ws_decode_bytes;
 };
 
-bct::WholePlan fill_plan(const bct_cache_desc* d, bct::DecodeParams& p) {
+// -> the step as one launch; `one`: with one workgroup per memory
+bct::WholePlan fill_plan(const bct_cache_desc* d, bct::DecodeParams& p, bct::WholePlan* one = nullptr) {
   memset(&p, 0, sizeof(p));
   p.B = d->batch;
   p.Hq = d->n_q_heads;
@@ -107,10 +108,48 @@ bct::WholePlan fill_plan(const bct_cache_desc* d, bct::DecodeParams& p) {
   p.R = 1 + p.G;
   p.has_write = p.has_read = 1;
   bct::plan_decode(p, d->dtype);
-  bct::WholePlan w = bct::plan_whole(p, d->dtype);
-  if (d->flags & BCT_STEP_STREAMING) w = bct::WholePlan{0u, 0u};
-  if (w.workgroups || (d->flags & BCT_STEP_STREAMING)) p.fused = 0u;
+  const bool streaming = (d->flags & BCT_STEP_STREAMING) != 0;
+  const bct::WholePlan none = {0u, 0u}, w = streaming ? none : bct::plan_whole(p, d->dtype, true);
+  if (one) *one = streaming ? none : bct::plan_whole(p, d->dtype, false);
+  if (w.workgroups || streaming) p.fused = 0u;
   return w;
+}
+
+// The path of a step with these buffers.  A one-launch step reads a memory's inputs in the launch that stores its output
+// row, so `out` may share memory with an input only where the two have the same rows, and then with one workgroup per memory;
+// otherwise the streaming launches take the step: they have read q and k_new before any launch stores to out, and with more
+// than one split v_new and the step sizes too.  (A pass that scores its slots again reads q and k_new itself: two
+// splits there, or stored scores.)  -> the one-launch plan; p.fused and p.S follow.
+bct::WholePlan route_step(bct::DecodeParams& p, const bct::WholePlan& any, const bct::WholePlan& one, size_t elem,
+                          const void* key_new, const float* key_gate) {
+  if (key_new) p.fused = 0u;   // that one-launch step has no key update
+  if (!p.out) return any;
+  const uintptr_t o0 = (uintptr_t)p.out;
+  auto span = [&](uint64_t bstride, uint64_t row, size_t size) { return ((p.B - 1) * bstride + row) * size; };
+  const uint64_t o_row = (uint64_t)p.Hq * p.d, kv_row = (uint64_t)p.Hkv * p.d;
+  const uintptr_t o1 = o0 + span(p.q_bstride, o_row, elem);
+  bool own = false, other = false;
+  auto look = [&](const void* x, uint64_t bstride, uint64_t row, size_t size) {
+    const uintptr_t x0 = (uintptr_t)x;
+    if (!x || x0 >= o1 || x0 + span(bstride, row, size) <= o0) return;
+    if (x0 == o0 && row == o_row && bstride == p.q_bstride) own = true;
+    else other = true;
+  };
+  look(p.q, p.q_bstride, o_row, elem);
+  look(p.wq, p.kv_bstride, kv_row, elem);
+  look(p.wv, p.kv_bstride, kv_row, elem);
+  look(key_new, p.kv_bstride, kv_row, elem);
+  look(p.gate, p.gate_bstride, p.Hkv, sizeof(float));
+  look(key_gate, p.gate_bstride, p.Hkv, sizeof(float));
+  if (other) {
+    p.fused = 0u;
+    if (p.rescore && p.S == 1) {
+      if (p.M > 64) p.S = 2;
+      else p.rescore = 0u;
+    }
+    return bct::WholePlan{0u, 0u};
+  }
+  return own ? one : any;
 }
 
 Sizes compute_sizes(const bct_cache_desc* d, uint32_t max_T) {
@@ -132,7 +171,9 @@ Sizes compute_sizes(const bct_cache_desc* d, uint32_t max_T) {
   z.off_norm = off;
   off += align_up(units * rows * sizeof(float2), 256);
   z.off_partial = off;
-  off += align_up((size_t)p.S * d->batch * d->n_q_heads * d->head_dim * sizeof(float), 256);
+  // (two splits where route_step may make two of one)
+  const uint32_t splits = p.rescore && p.S == 1 && p.M > 64 ? 2u : p.S;
+  off += align_up((size_t)splits * d->batch * d->n_q_heads * d->head_dim * sizeof(float), 256);
   z.ws_decode_bytes = off;
   // prefill of a bf16 cache: row normalisers and the MV snapshots at sub-chunk starts
   z.off_pf_norm_w = z.off_pf_norm_r = z.off_pf_wvt = z.off_pf_snap = off;
@@ -192,12 +233,12 @@ bct_status run_decode(bct_cache* c, char* ws, const void* q, const void* k_new, 
   hipError_t e;
   hipEvent_t* ev = (c->prof_n < c->prof_cap) ? &c->prof_ev[(size_t)c->prof_n * 4] : nullptr;
   if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return hip_fail(e, "event record");
-  if (key_new) p.fused = 0u;   // that one-launch step has no key update
-  if (p.fused || c->whole.workgroups) {
+  const bct::WholePlan whole = route_step(p, c->whole, c->whole_one, esize(c->desc.dtype), key_new, key_gate);
+  if (p.fused || whole.workgroups) {
     // a small cache: the whole step in one launch (timed as the MV pass)
     if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return hip_fail(e, "event record");
     e = p.fused ? bct::launch_fused(p, s)
-                : bct::launch_whole(p, c->whole, bct::KeyWrite{c->mk, key_new, key_gate}, c->desc.dtype, s);
+                : bct::launch_whole(p, whole, bct::KeyWrite{c->mk, key_new, key_gate}, c->desc.dtype, s);
     if (e != hipSuccess) return hip_fail(e, "one-launch step");
     if (ev && (e = hipEventRecord(ev[2], s)) != hipSuccess) return hip_fail(e, "event record");
   } else {
@@ -300,7 +341,7 @@ bct_status bct_cache_init(const bct_cache_desc* desc, uint32_t max_prefill_T, vo
   c->ws_decode_bytes = z.ws_decode_bytes;
   c->steps = 0;
   c->keys_set = false;
-  c->whole = fill_plan(desc, c->plan);
+  c->whole = fill_plan(desc, c->plan, &c->whole_one);
   {
     // set-up time is where the static scratch's address is looked up on this device (a caller of
     // bct_decode_step_static may be unable to make such a call later, e.g. under graph capture)
@@ -555,6 +596,27 @@ bct_status bct_plan_rescores(const bct_cache_desc* desc, uint32_t* rescores) {
   bct::DecodeParams p;
   const bool one = fill_plan(desc, p).workgroups || p.fused;
   *rescores = one ? 0u : p.rescore;
+  return BCT_OK;
+}
+
+bct_status bct_plan_step(const bct_cache_desc* desc, const void* q, const void* k_new, const void* v_new,
+                         const void* key_new, const float* gate, const float* key_gate, const void* out,
+                         uint32_t* workgroups, uint32_t* mv_splits) {
+  const bct_status st = check_desc(desc);
+  if (st != BCT_OK) return st;
+  if (!workgroups || !mv_splits) return fail(BCT_ERR_INVALID_ARG, "workgroups or mv_splits is NULL");
+  bct::DecodeParams p;
+  bct::WholePlan one;
+  const bct::WholePlan any = fill_plan(desc, p, &one);
+  p.q = q;
+  p.wq = k_new;
+  p.wv = v_new;
+  p.gate = gate;
+  p.gate_bstride = p.Hkv;
+  p.out = const_cast<void*>(out);
+  const bct::WholePlan w = route_step(p, any, one, esize(desc->dtype), key_new, key_gate);
+  *workgroups = p.fused ? 1u : w.workgroups;
+  *mv_splits = p.S;
   return BCT_OK;
 }
 

@@ -109,7 +109,8 @@ struct KeyWrite {
   const void* wk;
   const float* gate;
 };
-WholePlan plan_whole(const DecodeParams& p, int dtype);
+// two_allowed: a memory may be two workgroups', which read its inputs while the other one stores
+WholePlan plan_whole(const DecodeParams& p, int dtype, bool two_allowed);
 hipError_t launch_whole(const DecodeParams& p, const WholePlan& w, const KeyWrite& kw, int dtype, hipStream_t s);
 hipError_t launch_fill_zero(void* dst, size_t n_bytes, hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t n_bytes, hipStream_t s);

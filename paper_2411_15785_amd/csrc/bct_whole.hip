@@ -425,10 +425,10 @@ hipError_t launch_g(const DecodeParams& p, const WholePlan& w, const KeyWrite& k
 //   G = 1: streaming runs at the rate of memory once the chip is full;
 //   G = 2: at most the rounds that were measured; G > 2: streaming writes 1 + G scores a slot and its partial outputs, this
 //     kernel neither, so it stays ahead at every n that was measured; M <= 128 fills lanes only partly.
-WholePlan plan_whole(const DecodeParams& p, int dtype) {
+WholePlan plan_whole(const DecodeParams& p, int dtype, bool two_allowed) {
   const uint32_t row = p.d * (dtype == 0 ? 4u : 2u), G = p.G, M = p.M;
   const uint64_t n = (uint64_t)p.B * p.Hkv, mem = (uint64_t)M * row, KB = 1024;
-  const bool f32 = dtype == 0, mf = !f32 && G > 2, two = p.d == 128 && !p.mk_per_seq;
+  const bool f32 = dtype == 0, mf = !f32 && G > 2, two = two_allowed && p.d == 128 && !p.mk_per_seq;
   const WholePlan none = {0u, 0u};
   WholePlan w = none;
   auto fits = [&](uint32_t threads, uint32_t workgroups) {

@@ -373,3 +373,44 @@ def test_workgroups_of_the_mv_pass_cover_every_memory(L):
         assert not again or not keys, what
         rescored += again
     assert rescored > 0
+
+
+def test_route_of_a_step_whose_output_overlaps_its_inputs(L):
+    """A one-launch step stores its output rows while other workgroups may still read theirs: where `out` shares memory with
+    an input it is taken only for the same rows, by one workgroup per memory."""
+    def route(M, B, G, d, dt, flags=0, H=4, **at):
+        st, wgs, splits = P.bct_plan_step(P.make_desc(M, B, H * G, H, d, dt, 0.1, 0.1, flags), **at)
+        assert st == P.BCT_OK
+        return wgs, splits
+    a, far = 1 << 32, dict(k_new=1 << 33, v_new=3 << 32)
+    for dt, d, G, two in ((P.BCT_BF16, 128, 1, 2), (P.BCT_BF16, 128, 4, 2), (P.BCT_F32, 128, 1, 2), (P.BCT_BF16, 64, 4, 1),
+                          (P.BCT_F32, 64, 1, 1)):
+        row = d * (4 if dt == P.BCT_F32 else 2)
+        out_bytes, kv_bytes = 2 * 4 * G * row, 2 * 4 * row
+        go = lambda **at: route(128, 2, G, d, dt, out=a, **at)[0]
+        assert go(q=2 * a, **far) == two and go(q=None, **far) == two
+        assert go(q=a, **far) == 1                                            # out is q
+        assert go(q=a + 16, **far) == 0 and go(q=a - 16, **far) == 0          # other rows of it
+        assert go(q=a + out_bytes, **far) == two and go(q=a - out_bytes, **far) == two
+        for name in ("k_new", "v_new"):
+            at = dict(far, q=2 * a)
+            assert go(**dict(at, **{name: a})) == (1 if G == 1 else 0)
+            assert go(**dict(at, **{name: a + out_bytes - 16})) == 0 and go(**dict(at, **{name: a + 16 - kv_bytes})) == 0
+            assert go(**dict(at, **{name: a + out_bytes})) == two and go(**dict(at, **{name: a - kv_bytes})) == two
+        assert go(q=2 * a, gate=a + out_bytes - 4, **far) == 0 and go(q=2 * a, gate=a + out_bytes, **far) == two
+    own = P.BCT_MK_PER_SEQUENCE
+    keyed = dict(far, q=a, out=a, key_new=5 << 32)
+    assert route(256, 2, 1, 64, P.BCT_BF16, own, **keyed)[0] == 1
+    assert route(256, 2, 1, 64, P.BCT_BF16, own, **dict(keyed, key_new=a + 16))[0] == 0
+    assert route(256, 2, 1, 64, P.BCT_BF16, own, **dict(keyed, key_gate=a))[0] == 0
+    # the smallest caches' own launch: 300 memories, fp32, one query head
+    assert route(64, 75, 1, 64, P.BCT_F32, q=a, out=a, **far)[0] == 1 and route(64, 75, 1, 64, P.BCT_F32, q=a + 16, out=a, **far)[0] == 0
+    # one workgroup per memory would be a longer chain than the streaming launches: those
+    assert route(640, 2, 1, 128, P.BCT_BF16, q=2 * a, out=a, **far)[0] == 2 and route(640, 2, 1, 128, P.BCT_BF16, q=a, out=a, **far)[0] == 0
+    # no merge after the pass: it reads q and k_new itself where it scores again, so two splits for rows of others
+    big = dict(out=a, **far)
+    assert route(128, 2000, 8, 128, P.BCT_BF16, H=8, q=a, **big) == (0, 1) and route(128, 2000, 8, 128, P.BCT_BF16, H=8, q=a + 16, **big) == (0, 2)
+    dsc = P.make_desc(128, 2000, 64, 8, 128, P.BCT_BF16, 0.1, 0.1, 0)
+    one = P.make_desc(128, 2000, 64, 8, 128, P.BCT_BF16, 0.1, 0.1, P.BCT_MK_PER_SEQUENCE)   # two splits always
+    assert P.bct_cache_query(dsc, 0)[2] == P.bct_cache_query(one, 0)[2]   # the scratch for two is there
+    assert P.bct_plan_step(None, 0)[0] == P.BCT_ERR_INVALID_ARG

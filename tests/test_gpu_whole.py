@@ -124,3 +124,35 @@ def test_repeats_itself_and_graphs(P):
             torch.cuda.synchronize()
             assert torch.equal(o[0].view(torch.uint8), o[1].view(torch.uint8))
             assert torch.equal(cs[0].values_view().view(torch.uint8), cs[1].values_view().view(torch.uint8))
+
+
+# two workgroups per memory; one already; too long for one (streaming launches); the smallest caches' own launch; re-scored
+# with no merge after the pass
+@pytest.mark.parametrize("B,Hq,Hkv,d,M,dtype", [(3, 5, 5, 128, 128, "bf16"), (4, 32, 8, 128, 192, "bf16"), (2, 4, 4, 128, 64, "f32"),
+                                                (2, 8, 2, 64, 256, "bf16"), (2, 4, 4, 128, 640, "bf16"), (20, 15, 15, 64, 128, "f32"),
+                                                (2000, 64, 8, 128, 128, "bf16")])
+def test_output_in_the_memory_of_the_inputs(P, R, B, Hq, Hkv, d, M, dtype):
+    """out = q, out = the first write query of one head per memory, and rows of others: the results of buffers of their own
+    within the criteria of a step."""
+    import torch
+    w = syn.Workload("whole_alias", 1, B, Hq, Hkv, d, M, dtype, 4)
+    few = None if B < 100 else [0, B // 2, B - 1]
+    ref, gpu, _, mv, bs = make_pair(w, R.RefCache, P.BctCache, mv0=True, batch_subset=few)
+    q, wq, wv = syn.make_step(w, 0)
+    dev = lambda a: to_dev(a, dtype)
+    sub = lambda a: np.ascontiguousarray(a[bs])
+    row = Hq // Hkv * d
+    buf = torch.empty(q.size + row, dtype=dev(q).dtype, device="cuda:0")
+    cases = [("q", buf[:q.size], buf[:q.size], None), ("shifted", buf[row:], buf[:q.size], None)]
+    if Hq == Hkv:
+        cases.append(("k_new", None, buf[:q.size], buf[:q.size]))
+    for what, qbuf, obuf, kbuf in cases:
+        view = lambda b, a: None if b is None else b.view(a.shape).copy_(dev(a))
+        before = sub(mv)
+        ref.set_values(before)
+        gpu.set_values(dev(mv))
+        o_ref = ref.decode_step(sub(q), sub(wq), sub(wv))
+        dq, dk = view(qbuf, q), view(kbuf, wq)
+        o = gpu.decode_step(dev(q) if dq is None else dq, dev(wq) if dk is None else dk, dev(wv), obuf.view(q.shape))
+        check_out(to_np(o[bs], dtype), o_ref, dtype, what)
+        check_state_one_step(to_np(gpu.values_view()[bs], dtype), ref.values(), dtype, what, before=before)
