@@ -37,8 +37,7 @@ struct bct_cache {
 // Scratch of bct_decode_step_static: the scores, the per-tile statistics, the row normalisers and
 // the split-M partial outputs of one decode step live here instead of in a caller's workspace.
 // Every GPU the library runs on holds its own copy of this array until the process ends.
-#define BCT_STATIC_SCRATCH_BYTES (8u << 20)
-static __device__ __align__(256) unsigned char scratch[BCT_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[bct::kStaticScratchBytes];
 
 namespace {
 
@@ -162,18 +161,12 @@ Sizes compute_sizes(const bct_cache_desc* d, uint32_t max_T) {
   z.cache_bytes = align_up(z.mk_bytes, 256) + z.mv_bytes;
   bct::DecodeParams p;
   fill_plan(d, p);
-  const size_t rows = 1 + p.G;
-  size_t off = 0;
-  z.off_scores = off;
-  off += align_up(units * rows * p.M * sizeof(float), 256);
-  z.off_stats = off;
-  off += align_up(units * rows * (p.M / bct::kMinStatTile) * sizeof(float2), 256);
-  z.off_norm = off;
-  off += align_up(units * rows * sizeof(float2), 256);
-  z.off_partial = off;
-  // (two splits where route_step may make two of one)
-  const uint32_t splits = p.rescore && p.S == 1 && p.M > 64 ? 2u : p.S;
-  off += align_up((size_t)splits * d->batch * d->n_q_heads * d->head_dim * sizeof(float), 256);
+  const bct::DecodeScratch ds = bct::decode_scratch(p);
+  z.off_scores = ds.scores;
+  z.off_stats = ds.stats;
+  z.off_norm = ds.norm;
+  z.off_partial = ds.partial;
+  size_t off = ds.bytes;
   z.ws_decode_bytes = off;
   // prefill of a bf16 cache: row normalisers and the MV snapshots at sub-chunk starts
   z.off_pf_norm_w = z.off_pf_norm_r = z.off_pf_wvt = z.off_pf_snap = off;
@@ -456,17 +449,17 @@ bct_status bct_decode_step_keyed(bct_cache* c, const void* q, const void* k_new,
   return BCT_OK;
 }
 
-size_t bct_static_scratch_bytes(void) { return BCT_STATIC_SCRATCH_BYTES; }
+size_t bct_static_scratch_bytes(void) { return bct::kStaticScratchBytes; }
 
 bct_status bct_decode_step_static(bct_cache* c, const void* q, const void* k_new, const void* v_new, void* out,
                                   void* hip_stream) {
   bct_status st = check_io(c, q, k_new, v_new, out);
   if (st != BCT_OK) return st;
-  if (c->ws_decode_bytes > BCT_STATIC_SCRATCH_BYTES)
+  if (c->ws_decode_bytes > bct::kStaticScratchBytes)
     return fail(BCT_ERR_BUFFER_TOO_SMALL,
                 "a decode step of this cache needs %zu bytes of scratch, the static scratch holds %zu: "
                 "use bct_decode_step with a workspace",
-                c->ws_decode_bytes, (size_t)BCT_STATIC_SCRATCH_BYTES);
+                c->ws_decode_bytes, bct::kStaticScratchBytes);
   char* ws = nullptr;
   if ((st = static_scratch(&ws)) != BCT_OK) return st;
   // Nothing in the scratch has to start at zero: the scores pass writes every score and every

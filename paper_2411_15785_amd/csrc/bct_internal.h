@@ -64,6 +64,25 @@ struct DecodeParams {
   uint32_t rescore;    // 1: the MV pass of a step that reads scores its slots again; no scores in memory
 };
 
+// The scratch of a decode step: byte offsets of its parts, and their end.
+struct DecodeScratch {
+  size_t scores, stats, norm, partial, bytes;
+};
+inline DecodeScratch decode_scratch(const DecodeParams& p) {
+  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+  const size_t rows = (size_t)p.B * p.Hkv * (1 + p.G);
+  DecodeScratch z;
+  z.scores = 0;
+  z.stats = z.scores + up(rows * p.M * sizeof(float));
+  z.norm = z.stats + up(rows * (p.M / kMinStatTile) * sizeof(float2));
+  z.partial = z.norm + up(rows * sizeof(float2));
+  // (two splits where a step whose output lies in its inputs may need two of one)
+  const size_t splits = p.rescore && p.S == 1 && p.M > 64 ? 2 : p.S;
+  z.bytes = z.partial + up(splits * p.B * p.Hq * p.d * sizeof(float));
+  return z;
+}
+constexpr size_t kStaticScratchBytes = 8u << 20;   // of bct_decode_step_static
+
 // One prefill chunk of a bf16 cache: everything its launches need.
 struct PrefillParams {
   const uint16_t* mk;  // [Hkv][M][d] or [B][Hkv][M][d]

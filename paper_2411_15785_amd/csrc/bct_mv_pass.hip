@@ -232,6 +232,16 @@ void plan_mv_pass(DecodeParams& p, int dtype) {
   const uint32_t row_bytes = p.d * (dtype == 0 ? 4u : 2u);
   const uint32_t spb = s.bs * s.u * 16u / row_bytes;  // slots per workgroup
   p.S = (p.M + spb - 1) / spb;
+  // With 64 columns these workgroups have 128 slots, and their partial outputs can take a decode step's scratch past the
+  // static array, where larger workgroups would stay inside it (G = 3, 24 memories of 15360 slots: 9.6 MB with 128, 7.9 with 256).
+  // There a workgroup takes two, three or four tiles, the first that fits, and requests one ahead.  us a step, 512 x 8 on the
+  // vector ALU (which fits) | this: G = 3, n = 24, M = 15808 44.8 | 42.2; 17600 50.2 | 49.2; 18496 (four tiles) 52.7 | 52.7; n = 7,
+  // M = 62848 54.5 | 53.3; G = 4, n = 16, M = 19840 40.2 | 36.9; G = 8, n = 64, M = 3008 48.3 | 30.5.
+  if (gqa && p.d == 64 && decode_scratch(p).bytes > kStaticScratchBytes) {
+    const uint32_t tiles = p.S;
+    for (uint32_t per = 2; per <= 4 && decode_scratch(p).bytes > kStaticScratchBytes; ++per) p.S = (tiles + per - 1) / per;
+    if (decode_scratch(p).bytes > kStaticScratchBytes) p.S = tiles;
+  }
   // With at most two (max, sum) pairs per lane the workgroups of the MV pass merge them themselves.  In the
   // pass for several query heads that costs every workgroup a little (1 + G rows; 13 us over the 65536
   // workgroups of B = 64, Hkv = 8, M = 8192, where the normaliser launch takes 5), so a large grid leaves it

@@ -29,7 +29,7 @@ namespace bct {
 
 namespace {
 
-template <bool WRITE, int BS, bool NORM, int U, bool RESCORE, int D>
+template <bool WRITE, int BS, bool NORM, int U, bool RESCORE, int D, bool TILES = RESCORE>
 __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
   constexpr int LPS = D / 8, SPI = 64 / LPS, PARTS = ReadShape<LPS>::kParts;   // lanes per slot row, slots per load instruction
   constexpr int NB = U / 8, NW = BS / 64, SPB = NW * SPI * U;
@@ -62,10 +62,23 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
   f32x4 acc[NP];
 #pragma unroll
   for (int e = 0; e < NP; ++e) acc[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  // RESCORE: as many tiles of SPB slots as the plan's splits leave a workgroup, otherwise one
-  const uint32_t n_tiles = (M + SPB - 1) / SPB, per = RESCORE ? (n_tiles + p.S - 1) / p.S : 1u, first = split * per;
-  const uint32_t end = RESCORE ? min(first + per, n_tiles) : first + 1;
+  // TILES: as many tiles of SPB slots as the plan's splits leave a workgroup (perhaps none the last), otherwise one
+  const uint32_t n_tiles = (M + SPB - 1) / SPB, per = TILES ? (n_tiles + p.S - 1) / p.S : 1u, first = split * per;
+  const uint32_t end = TILES ? min(first + per, n_tiles) : first + 1;
   float2 nw = make_float2(0.f, 0.f), nr = make_float2(0.f, 0.f);
+  // stored scores: a tile's MV is requested while the one before is worked on
+  constexpr bool AHEAD = TILES && !RESCORE;
+  u32x4 next[AHEAD ? U : 1];
+  auto request = [&](uint32_t tile) __attribute__((always_inline)) {
+    const uint32_t slot = tile * SPB + wave * (SPI * U) + sl * U;
+    const uint16_t* from = (const uint16_t*)p.mv + ((size_t)unit * M + slot) * D + sub * 8;
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        next[u] = slot < M ? __builtin_nontemporal_load((const u32x4*)(from + (size_t)u * D)) : (u32x4){0u, 0u, 0u, 0u};
+    }
+  };
+  if (AHEAD && first < end) request(first);
   for (uint32_t tile = first; tile < end; ++tile) {
     // M is a multiple of 64: the SPI * U (32 or 64) slots of a wavefront are all inside the memory or all outside
     const uint32_t slot0 = tile * SPB + wave * (SPI * U) + sl * U;
@@ -86,8 +99,10 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
     }
     u32x4 raw[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) raw[u] = (u32x4){0u, 0u, 0u, 0u};
-    if (active) {
+    for (int u = 0; u < U; ++u) raw[u] = AHEAD ? next[AHEAD ? u : 0] : (u32x4){0u, 0u, 0u, 0u};
+    if (AHEAD) {
+      if (tile + 1 < end) request(tile + 1);
+    } else if (active) {
 #pragma unroll
       for (int u = 0; u < U; ++u) raw[u] = __builtin_nontemporal_load((const u32x4*)(mv + (size_t)u * D));
     }
@@ -225,6 +240,15 @@ static void launch_gqa_bs(const DecodeParams& p, hipStream_t s) {
       return;
     }
   }
+  if constexpr (D == 64) {
+    if ((uint64_t)p.S * 128 < p.M) {
+      if (p.has_write && p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, true, U, false, D, true>), grid, block, 0, s, p);
+      else if (p.has_write) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U, false, D, true>), grid, block, 0, s, p);
+      else if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, true, U, false, D, true>), grid, block, 0, s, p);
+      else hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, false, U, false, D, true>), grid, block, 0, s, p);
+      return;
+    }
+  }
   if (p.has_write) {
     if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, true, U, false, D>), grid, block, 0, s, p);
     else hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U, false, D>), grid, block, 0, s, p);
@@ -240,8 +264,8 @@ hipError_t launch_stream_gqa(const DecodeParams& p, hipStream_t s) {
   if (p.G <= 2 || p.G > kMaxG || !p.has_read) return hipErrorInvalidConfiguration;
   if (p.mv_bs != 128 || p.mv_u != 8) return hipErrorInvalidConfiguration;
   if (p.rescore && (p.fuse_norm || p.d != 128 || p.mk_per_seq)) return hipErrorInvalidConfiguration;
-  // with stored scores a workgroup has one tile of slots: the splits have to cover the memory
-  if (!p.rescore && (uint64_t)p.S * (128 * 8 * 8 / p.d) < p.M) return hipErrorInvalidConfiguration;
+  // with stored scores and d = 128 a workgroup has one tile of slots: the splits have to cover the memory
+  if (!p.rescore && p.d == 128 && (uint64_t)p.S * 64 < p.M) return hipErrorInvalidConfiguration;
   if (p.d == 128) launch_gqa_bs<128, 8, 128>(p, s);
   else launch_gqa_bs<128, 8, 64>(p, s);
   return hipGetLastError();

@@ -355,7 +355,8 @@ def test_projection_of_ragged_feature_counts():
 
 def test_workgroups_of_the_mv_pass_cover_every_memory(L):
     """Plans of streaming steps: splits of a memory x slots of a workgroup are M slots and no workgroup more; where the scores
-    are made again a workgroup has one tile of slots or two, and only keys that the batch shares are scored again."""
+    are made again a workgroup has one tile of slots or two, and only keys that the batch shares are scored again.  Several heads
+    with 64 columns: up to four."""
     import itertools
     rescored = 0
     heads = [(8192, 64, 8), (8192, 32, 8), (4096, 64, 16), (2048, 64, 16), (1280, 1020, 3), (1344, 1000, 3), (128, 2000, 8),
@@ -369,7 +370,8 @@ def test_workgroups_of_the_mv_pass_cover_every_memory(L):
         tile = plan["mv_workgroup"] * plan["mv_loads_per_lane"] * 16 // row
         tiles = -(-M // tile)
         what = (M, B, H, G, d, dt, keys, plan, again)
-        assert plan["mv_splits"] in ((tiles, -(-tiles // 2)) if again else (tiles,)), what
+        per = (1, 2) if again else (1, 2, 3, 4) if d == 64 and dt == P.BCT_BF16 and G > 2 else (1,)
+        assert plan["mv_splits"] in [-(-tiles // n) for n in per], what
         assert not again or not keys, what
         rescored += again
     assert rescored > 0
@@ -414,3 +416,24 @@ def test_route_of_a_step_whose_output_overlaps_its_inputs(L):
     one = P.make_desc(128, 2000, 64, 8, 128, P.BCT_BF16, 0.1, 0.1, P.BCT_MK_PER_SEQUENCE)   # two splits always
     assert P.bct_cache_query(dsc, 0)[2] == P.bct_cache_query(one, 0)[2]   # the scratch for two is there
     assert P.bct_plan_step(None, 0)[0] == P.BCT_ERR_INVALID_ARG
+
+
+def test_scratch_of_several_heads_with_64_columns(L):
+    """128 slots a workgroup, unless a step's scratch then passes the static array where 512 slots a workgroup stay inside it:
+    as many as fit.  Every cache that fits with 512 does."""
+    import itertools
+    up = lambda n: -(-n // 256) * 256
+    wider = 0
+    for G, units, M in itertools.product(range(3, 9), (1, 2, 5, 7, 16, 24, 31, 64, 100, 435), [64 * m for m in range(1, 1025)]):
+        rows = units * (1 + G)
+        rest = up(rows * M * 4) + up(rows * (M // 32) * 8) + up(rows * 8)
+        need = lambda per: rest + up(-(-(-(-M // 128)) // per) * units * G * 64 * 4)
+        limit = 8 << 20
+        if need(1) > limit + (1 << 21):
+            break
+        dsc = P.make_desc(M, 1, units * G, units, 64, P.BCT_BF16, 0.1, 0.1, P.BCT_STEP_STREAMING)
+        per = next((n for n in (1, 2, 3, 4) if need(n) <= limit), 1)
+        wider += per > 1
+        assert P.bct_cache_query(dsc, 0)[2] == need(per), (G, units, M)
+        assert P.bct_plan_query(dsc)[1]["mv_splits"] == -(-(-(-M // 128)) // per), (G, units, M)
+    assert wider > 100

@@ -34,3 +34,35 @@ def test_steps_from_a_common_state(B, Hkv, G, M, seq):
         if read:
             check_out(to_np(o, "bf16")[bs], o_ref, "bf16", what)
         check_state_one_step(to_np(gpu.values_view(), "bf16")[bs], ref.values(), "bf16", what, before=before)
+
+
+# two, three and four tiles a workgroup, the last workgroup with one, with half a tile; statistics merged in the pass and by their
+# own launch
+@pytest.mark.parametrize("G,Hkv,M,seq,splits", [(3, 24, 15808, 0, 62), (4, 31, 10880, 1, 29), (8, 64, 3008, 0, 6),
+                                               (8, 100, 1920, 0, 5)])
+def test_more_slots_a_workgroup_where_the_static_scratch_ends(G, Hkv, M, seq, splits):
+    import numpy as np
+    import paper_2411_15785_amd as P
+    from oracle import bct_ref as R
+    import torch
+    w = syn.Workload("heads_static", 1, 1, Hkv * G, Hkv, 64, M, "bf16", 3)
+    ref, gpu, mk, mv, _ = make_pair(w, R.RefCache, P.BctCache, flags=seq | P.BCT_STEP_STREAMING, mv0=True)
+    assert P.bct_plan_query(gpu.desc)[1]["mv_splits"] == splits
+    for t, (read, write) in enumerate(((True, True), (False, True), (True, False))):
+        q, wq, wv = syn.make_step(w, t)
+        q, wq, wv = q if read else None, wq if write else None, wv if write else None
+        before = ref.values()
+        gpu.set_values(to_dev(before, "bf16"))
+        o_ref = ref.decode_step(q, wq, wv)
+        o = torch.empty((1, w.Hq, 64), dtype=torch.bfloat16, device="cuda:0") if read else None
+        gpu.decode_step_static(to_dev(q, "bf16"), to_dev(wq, "bf16"), to_dev(wv, "bf16"), o)
+        what = f"M={M} G={G} read={read} write={write}"
+        if read:
+            check_out(to_np(o, "bf16"), o_ref, "bf16", what)
+        check_state_one_step(to_np(gpu.values_view(), "bf16"), ref.values(), "bf16", what, before=before)
+        if read and write:
+            state = gpu.values_view().clone()
+            gpu.set_values(to_dev(before, "bf16"))
+            again = gpu.decode_step(to_dev(q, "bf16"), to_dev(wq, "bf16"), to_dev(wv, "bf16"))
+            assert torch.equal(o.view(torch.int16), again.view(torch.int16)) and torch.equal(state.view(torch.int16), gpu.values_view().view(torch.int16))
+    assert np.array_equal(to_np(gpu.keys_view(), "bf16"), mk)
