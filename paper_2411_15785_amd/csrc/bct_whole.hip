@@ -5,12 +5,16 @@
 // memory (b, h) through the whole step.  It scores ALL M slots itself, so that the normaliser of section 3.2 step 2 is a
 // workgroup barrier and no output has to be summed over workgroups:
 //   A. scores of the write query and the G read queries against the M keys on the matrix cores (16 slots by 16 query rows,
-//      1 + G of them used), scaled, to LDS as fp32.  Keys come to LDS in whole rows (lds_request), two tiles
+//      1 + G of them used), to LDS as fp32.  Keys come to LDS in whole rows (lds_request), two tiles
 //      ahead per wavefront, the 16-byte chunks of a row exchanged so that operand reads have no bank conflicts;
-//   B. per row max, then exp2(score - max) in place and its sum;
+//   B. per row max of the scaled scores, then exp2(score * scale - max) in place, one rounding before the exponential, and its sum;
 //   C. the columns of MV: load, fma(ww[m], wv, MV[m,:]), round, store, rw[g][m] times the value just stored;
 //   D. the G output rows summed over lanes and wavefronts in a fixed order;
 //   E. a step that writes keys: the same update of the memory's own keys, with the weights they gave.
+// Sums over wavefronts are taken in halves and a score is rounded once on its way into the exponential, so the step is no further
+// from 64 bits than the launches it takes the place of (fp32, root mean square of the output: 1.27e-7 at 4 memories of 64 slots with 64
+// columns, where the one-workgroup launch has 1.33e-7; 1.55e-7 | 1.58e-7 streaming at 128 of 512; in a chain over the wavefronts and with
+// scaled scores 1.38e-7 and 1.66e-7, and 0.05 us less a step).
 // What bounds it: at few memories the chain of a workgroup (keys at about 64 bytes a cycle, one compute unit's share of L2),
 // at many the bytes.  A quarter of a lane's MV loads are requested before the first score and the others as soon as the
 // last keys are, so that MV streams while the keys come from the XCD's L2: workgroups are numbered so that those of one
@@ -32,6 +36,19 @@ __device__ __forceinline__ float half_sums(float a, float b) {
 __device__ __forceinline__ float row_sums(float a, float b) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// The sum of term(0) .. term(N - 1), N a power of two, in halves: log2(N) roundings deep.
+template <int N, typename F>
+__device__ __forceinline__ float sum_of(F term) {
+  float t[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) t[i] = term(i);
+#pragma unroll
+  for (int n = N / 2; n > 0; n /= 2)
+#pragma unroll
+    for (int i = 0; i < n; ++i) t[i] += t[i + n];
+  return t[0];
 }
 
 // 16 key rows by up to 16 query rows; chunk ks of a lane: 16 bytes of its row (row l % 16) at 16 * (4 ks + l / 16).
@@ -141,10 +158,7 @@ __global__ __launch_bounds__(BS) void decode_whole_kernel(const DecodeParams p, 
     const uint32_t t = i * NW + wave;
     if (t < tiles) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        c[v] *= scale;
-        mx = fmaxf(mx, c[v]);
-      }
+      for (int v = 0; v < 4; ++v) mx = fmaxf(mx, c[v] * scale);
       if ((uint32_t)col < R) *(f32x4*)(s_w + (size_t)col * M + t * 16 + kg * 4) = c;
     }
   };
@@ -199,19 +213,15 @@ __global__ __launch_bounds__(BS) void decode_whole_kernel(const DecodeParams p, 
       f32x4* at = (f32x4*)(s_w + row0 + t * 16 + kg * 4);
       f32x4 e = *at;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        e[v] = fast_exp2(e[v] - mx);
-        sm += e[v];
-      }
+      for (int v = 0; v < 4; ++v) e[v] = fast_exp2(__builtin_fmaf(e[v], scale, -mx));
+      sm += (e[0] + e[1]) + (e[2] + e[3]);
       *at = e;
     }
   }
   sm = xor_sum<16, 32>(sm);
   if (kg == 0) s_stat[NW * 16 + wave * 16 + col] = sm;
   lds_barrier();
-  sm = 0.f;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) sm += s_stat[NW * 16 + w * 16 + col];
+  sm = sum_of<NW>([&](int w) { return s_stat[NW * 16 + w * 16 + col]; });
   // lane r of the wavefront has row r's normaliser; a step size scales the write row's
   const float inv = 1.0f / sm;
   const float inv0 = __shfl(inv, 0, 64), invw = W && p.gate ? inv0 * p.gate[(size_t)b * p.gate_bstride + h] : inv0;
@@ -361,9 +371,7 @@ __global__ __launch_bounds__(BS) void decode_whole_kernel(const DecodeParams p, 
     lds_barrier();
     for (uint32_t k = tid; k < G * CW; k += BS) {
       const uint32_t g = k / CW, j = k % CW;
-      float v = 0.f;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) v += s_red[(w * GT + g) * CW + j];
+      const float v = sum_of<NW>([&](int w) { return s_red[(w * GT + g) * CW + j]; });
       store_elem((elem*)p.out, (size_t)b * p.q_bstride + (size_t)(h * G + g) * D + cs * CW + j, v);
     }
   }

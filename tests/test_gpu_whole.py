@@ -156,3 +156,31 @@ def test_output_in_the_memory_of_the_inputs(P, R, B, Hq, Hkv, d, M, dtype):
         o = gpu.decode_step(dev(q) if dq is None else dq, dev(wq) if dk is None else dk, dev(wv), obuf.view(q.shape))
         check_out(to_np(o[bs], dtype), o_ref, dtype, what)
         check_state_one_step(to_np(gpu.values_view()[bs], dtype), ref.values(), dtype, what, before=before)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,M", [(8, 8, 8, 64, 128), (8, 16, 16, 64, 512), (16, 32, 8, 64, 512), (8, 64, 16, 128, 256)])
+def test_fp32_error_is_no_larger_than_the_streaming_launches(P, B, Hq, Hkv, d, M):
+    """Root mean square error of the output and the state against 64 bits, over the same 8 steps from the same state."""
+    import torch
+    w = syn.Workload("whole_error", 1, B, Hq, Hkv, d, M, "f32", 8)
+    mk, mv = syn.make_keys(w), syn.make_values0(w)
+    k, m0 = mk.astype(np.float64), mv.astype(np.float64)
+    soft = lambda s: (lambda e: e / e.sum(-1, keepdims=True))(np.exp(s - s.max(-1, keepdims=True)))
+    err = {}
+    for name, flags in (("one launch", 0), ("streaming", P.BCT_STEP_STREAMING)):
+        c = P.BctCache(M, B, Hq, Hkv, d, torch.float32, w.scale, w.scale, flags)
+        assert (P.bct_plan_whole(c.desc)[1] > 0) == (flags == 0)
+        c.set_keys(to_dev(mk, "f32"))
+        total = np.zeros(2)
+        for t in range(8):
+            q, wq, wv = syn.make_step(w, t)
+            c.set_values(to_dev(mv, "f32"))
+            o = to_np(c.decode_step(*(to_dev(a, "f32") for a in (q, wq, wv))), "f32")
+            ww = soft(np.einsum("bhd,hmd->bhm", wq.astype(np.float64), k) * w.scale)
+            new = m0 + ww[..., None] * wv.astype(np.float64)[:, :, None, :]
+            rw = soft(np.einsum("bhgd,hmd->bhgm", q.astype(np.float64).reshape(B, Hkv, -1, d), k) * w.scale)
+            out = np.einsum("bhgm,bhmd->bhgd", rw, new).reshape(B, Hq, d)
+            total += [np.mean((o - out) ** 2) / np.mean(out ** 2), np.mean((to_np(c.values_view(), "f32") - new) ** 2) / np.mean(new ** 2)]
+        err[name] = np.sqrt(total / 8)
+    print("rms error out, state", err)
+    assert np.all(err["one launch"] <= err["streaming"]), err
