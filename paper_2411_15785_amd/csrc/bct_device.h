@@ -222,34 +222,36 @@ __device__ __forceinline__ f32x4 score16(const u32x4* key, const u32x4* query) {
 // LPS = 8: lanes l and l ^ 8 hold the same chunk of different slots.  They exchange halves, so that lanes c < 8 have
 // elements 0 to 3 and lanes c >= 8 elements 4 to 7 of both groups of slots: two contractions over 32 slots, part j the
 // slots of lanes with l / 8 % 2 = j.  acc[e]: column 8 (c % 8) + 4 (c / 8) + e.
-// hi, lo: per part the weights of head c for the slots 8 * (l / 16) .. of the part, as bf16 parts whose sum has fp32 grade.
+// w: per part the weights of head c for the slots 8 * (l / 16) .. of the part, as N bf16 addends (split_weights).
 template <int LPS>
 struct ReadShape {
   static constexpr int kParts = 16 / LPS, kProducts = LPS / 2;
   static __device__ __forceinline__ uint32_t column(uint32_t c) { return LPS == 16 ? 8 * c : 8 * (c % 8) + 4 * (c / 8); }
 };
-__device__ __forceinline__ f32x4 mfma_hi_lo(u32x4 hi, u32x4 lo, u32x4 b, f32x4 c) {
-  const bf16x8 bv = __builtin_bit_cast(bf16x8, b);
-  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, hi), bv, c, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, lo), bv, c, 0, 0, 0);
+template <int N>
+__device__ __forceinline__ f32x4 mfma_addends(const u32x4* w, u32x4 b, f32x4 c) {
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[n]), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  return c;
 }
-template <int LPS>
-__device__ __forceinline__ void mfma_read(const u32x4* raw, const u32x4* hi, const u32x4* lo, f32x4* acc) {
+template <int LPS, int N>
+__device__ __forceinline__ void mfma_read(const u32x4* raw, const u32x4 (*w)[N], f32x4* acc) {
   // element e % 2 of word w of the eight slots
-  auto operand = [](const uint32_t* w, int odd) -> u32x4 {
+  auto operand = [](const uint32_t* x, int odd) -> u32x4 {
     u32x4 t;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      t[i] = odd ? ((w[2 * i] >> 16) | (w[2 * i + 1] & 0xFFFF0000u)) : ((w[2 * i] & 0xFFFFu) | (w[2 * i + 1] << 16));
+      t[i] = odd ? ((x[2 * i] >> 16) | (x[2 * i + 1] & 0xFFFF0000u)) : ((x[2 * i] & 0xFFFFu) | (x[2 * i + 1] << 16));
     return t;
   };
   if constexpr (LPS == 16) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      uint32_t w[8];
+      uint32_t x[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) w[u] = raw[u][e / 2];
-      acc[e] = mfma_hi_lo(hi[0], lo[0], operand(w, e % 2), acc[e]);
+      for (int u = 0; u < 8; ++u) x[u] = raw[u][e / 2];
+      acc[e] = mfma_addends<N>(w[0], operand(x, e % 2), acc[e]);
     }
   } else {
 #pragma unroll
@@ -263,19 +265,34 @@ __device__ __forceinline__ void mfma_read(const u32x4* raw, const u32x4* hi, con
       }
 #pragma unroll
       for (int o = 0; o < 2; ++o) {
-        acc[2 * k + o] = mfma_hi_lo(hi[0], lo[0], operand(a, o), acc[2 * k + o]);
-        acc[2 * k + o] = mfma_hi_lo(hi[1], lo[1], operand(b, o), acc[2 * k + o]);
+        acc[2 * k + o] = mfma_addends<N>(w[0], operand(a, o), acc[2 * k + o]);
+        acc[2 * k + o] = mfma_addends<N>(w[1], operand(b, o), acc[2 * k + o]);
       }
     }
   }
 }
-// Eight fp32 weights as bf16 operands: their roundings, and what the roundings left.
-__device__ __forceinline__ void split_hi_lo(const float* w, u32x4& hi, u32x4& lo) {
+// Eight fp32 weights as N bf16 operands that add up to them.  N = 2: the weights' roundings and what those left, rounded: 16 to
+// 17 bits.  N = 3: the upper, middle and lower eight bits, cut off, so nothing is lost: a product of them is the fp32 product before
+// its rounding.  There no addend of a weight is zero (2^-30 of it at least), so that an infinity in MV is read as one, not as 0 * inf.
+template <int N>
+__device__ __forceinline__ void split_weights(const float* w, u32x4* out) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const uint32_t h = pack_bf16x2(w[2 * i], w[2 * i + 1]);
-    hi[i] = h;
-    lo[i] = pack_bf16x2(w[2 * i] - __uint_as_float(h << 16), w[2 * i + 1] - __uint_as_float(h & 0xFFFF0000u));
+    const float a = w[2 * i], b = w[2 * i + 1];
+    if constexpr (N == 2) {
+      const uint32_t h = pack_bf16x2(a, b);
+      out[0][i] = h;
+      out[1][i] = pack_bf16x2(a - __uint_as_float(h << 16), b - __uint_as_float(h & 0xFFFF0000u));
+    } else {
+      auto top = [](float x) -> float { return __uint_as_float(__float_as_uint(x) & 0xFFFF0000u); };
+      auto pack = [](float x, float y) -> uint32_t { return (__float_as_uint(x) >> 16) | (__float_as_uint(y) & 0xFFFF0000u); };
+      constexpr float kLeast = 1.0f / (1 << 30);
+      const float la = a * kLeast, lb = b * kLeast, ra = a - top(a), rb = b - top(b);
+      const float ma = top(fmaxf(ra, la)), mb = top(fmaxf(rb, lb));
+      out[0][i] = pack(a, b);
+      out[1][i] = pack(ma, mb);
+      out[2][i] = pack(fmaxf(ra - ma, la), fmaxf(rb - mb, lb));
+    }
   }
 }
 

@@ -232,15 +232,27 @@ void plan_mv_pass(DecodeParams& p, int dtype) {
   const uint32_t row_bytes = p.d * (dtype == 0 ? 4u : 2u);
   const uint32_t spb = s.bs * s.u * 16u / row_bytes;  // slots per workgroup
   p.S = (p.M + spb - 1) / spb;
-  // With 64 columns these workgroups have 128 slots, and their partial outputs can take a decode step's scratch past the
-  // static array, where larger workgroups would stay inside it (G = 3, 24 memories of 15360 slots: 9.6 MB with 128, 7.9 with 256).
-  // There a workgroup takes two, three or four tiles, the first that fits, and requests one ahead.  us a step, 512 x 8 on the
-  // vector ALU (which fits) | this: G = 3, n = 24, M = 15808 44.8 | 42.2; 17600 50.2 | 49.2; 18496 (four tiles) 52.7 | 52.7; n = 7,
-  // M = 62848 54.5 | 53.3; G = 4, n = 16, M = 19840 40.2 | 36.9; G = 8, n = 64, M = 3008 48.3 | 30.5.
-  if (gqa && p.d == 64 && decode_scratch(p).bytes > kStaticScratchBytes) {
+  // With 64 columns these workgroups have 128 slots each.  2560 of them are on the chip at once, so somewhat more are a second round
+  // that is mostly empty; of those that take several tiles, one requested ahead, 1536 are one round.  us a step, 512 x 8 on the vector
+  // ALU | one tile | this, n memories: two tiles, up to 3456: G = 3, n = 33, M = 10880 44.0 | 41.7 | 39.8; n = 256,
+  // M = 1536 36.0 | 35.1 | 29.8; G = 4, n = 24, M = 16384 38.8 | 39.3 | 33.6; G = 8, n = 64, M = 6144 59.3 | 40.6 | 37.1.  Three, up to 4096:
+  // G = 3, n = 32, M = 16384 43.4 | 45.9 | 42.8; n = 64, M = 8192 42.5 | 43.5 | 41.6; n = 256, M = 1792 40.6 | 39.8 | 37.2; M = 2048 42.3 |
+  // 42.1 | 40.6; n = 64, M = 7232 41.5 | 39.9 | 40.7; G = 4, n = 32, M = 16384 45.6 | 46.9 | 43.8; G = 5, n = 128, M = 4096 72.9 | 46.0 | 43.8.
+  // Outside, with three: 4608 (G = 4) 66.4 | 61.2 | 63.4 and 54.6 | 49.3 | 45.8, 2048 18.4 with one, 20.0 with two (G = 3, n = 32, M = 4096).
+  // Their partial outputs can also take a decode step's scratch past the static array, where larger workgroups would stay inside it
+  // (G = 3, 24 memories of 15360 slots: 9.6 MB with 128 slots, 7.9 with 256).  There a workgroup takes up to four tiles, the first that
+  // fits: G = 3, n = 24, M = 15808 44.8 | refused | 42.2; 18496 (four) 52.7 | refused | 52.7; G = 8, n = 64, M = 3008 48.3 | refused | 30.5.
+  if (gqa && p.d == 64) {
     const uint32_t tiles = p.S;
-    for (uint32_t per = 2; per <= 4 && decode_scratch(p).bytes > kStaticScratchBytes; ++per) p.S = (tiles + per - 1) / per;
-    if (decode_scratch(p).bytes > kStaticScratchBytes) p.S = tiles;
+    const uint64_t w = units * tiles;
+    const uint32_t few = w > 2560 && w <= 3456 ? 2 : w > 3456 && w <= 4096 ? 3 : 1;
+    auto take = [&](uint32_t per) {
+      p.S = (tiles + per - 1) / per;
+      return decode_scratch(p).bytes <= kStaticScratchBytes;
+    };
+    uint32_t per = few;
+    while (!take(per) && per < 4) ++per;
+    if (!take(per)) take(few);
   }
   // With at most two (max, sum) pairs per lane the workgroups of the MV pass merge them themselves.  In the
   // pass for several query heads that costs every workgroup a little (1 + G rows; 13 us over the 65536

@@ -8,10 +8,12 @@
 // all G softmax weights again), not by memory.  Here the contraction over the
 // wavefront's 32 slots runs on v_mfma_f32_16x16x32_bf16:
 //   B operand = MV_new (exactly the bf16 values just stored), A operand = the softmax weights: mfma_read.  A lane computes
-//     the weights of ONE query head (row l % 16; rows >= G hold zeros), split into hi + lo bf16 parts (two products) so that
-//     they keep fp32 grade.
+//     the weights of ONE query head (row l % 16; rows >= G hold zeros), as bf16 addends, a product each: d = 128 two (16 to 17
+//     bits), d = 64 three (all 24), as this pass took the place of fp32 products there.  Share of bf16 outputs that are not the rounding
+//     of the exact read: two 2.0e-3 to 2.9e-3, three and fp32 products 1e-4 to 3e-4; three cost 0 to 3 % of a step (G = 4, 32 memories of
+//     2048 slots 14.75 -> 15.1 us, G = 8, 256 of 8192 the same).
 // The products also sum over the lane groups, so no lane exchange of sums is needed.  d = 64, G = 8, 256 memories of 8192
-// slots: 155 us the step against 300 with the read on the vector ALU.
+// slots: 146 us the step against 305 with the read on the vector ALU.
 //
 // RESCORE (d = 128, keys shared by the batch): the scores are not read from memory but computed again from the
 // workgroup's 16 KB of keys (from L2: every sequence's workgroups read the same table): two v_mfma_f32_16x16x32_bf16 per 32 inputs,
@@ -34,6 +36,7 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
   constexpr int LPS = D / 8, SPI = 64 / LPS, PARTS = ReadShape<LPS>::kParts;   // lanes per slot row, slots per load instruction
   constexpr int NB = U / 8, NW = BS / 64, SPB = NW * SPI * U;
   constexpr uint32_t W = WRITE ? 1u : 0u;
+  constexpr int ADD = D == 64 ? 3 : 2;   // bf16 addends of a weight
   __shared__ float s_red[NW * kMaxG * D];
 
   static_assert(!RESCORE || (U == 8 && PARTS == 1), "a lane's slots are two MFMA groups of four");
@@ -172,12 +175,12 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
           }
       }
     }
-    // hi + lo bf16 parts of the lane's weights, 8 slots per block: the A operands
-    u32x4 ahi[NB][PARTS], alo[NB][PARTS];
+    // the lane's weights as bf16 addends, 8 slots per block: the A operands
+    u32x4 aw[NB][PARTS][ADD];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int j = 0; j < PARTS; ++j) split_hi_lo(&rw[j][8 * nb], ahi[nb][j], alo[nb][j]);
+      for (int j = 0; j < PARTS; ++j) split_weights<ADD>(&rw[j][8 * nb], aw[nb][j]);
 
     if (WRITE && active) {
       if (!RESCORE) {
@@ -203,7 +206,7 @@ __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
     }
 
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) mfma_read<LPS>(raw + 8 * nb, ahi[nb], alo[nb], acc);
+    for (int nb = 0; nb < NB; ++nb) mfma_read<LPS, ADD>(raw + 8 * nb, aw[nb], acc);
   }
 #pragma unroll
   for (int v = 0; v < 4; ++v) {

@@ -289,7 +289,9 @@ __global__ __launch_bounds__(BS) void decode_whole_kernel(const DecodeParams p, 
       }
     }
   } else {
-    // as the MV pass for several query heads: weights of 32 slots times the values just stored
+    // as the MV pass for several query heads: weights of 32 slots times the values just stored.  Three bf16 addends a weight (see
+    // split_weights): with two, 20 of every 10000 outputs were not the rounding of the exact read, in M <= 128 and d = 64 where fp32
+    // products were used before; the third costs 0.1 to 0.3 us of a step (G = 4, 32 memories of 64 slots 4.85 -> 5.15).
     constexpr int PARTS = ReadShape<LPS>::kParts, NP = ReadShape<LPS>::kProducts;
     const float invr = __shfl(inv, (int)min(W + (uint32_t)col, R - 1), 64);
     const size_t rrow = (size_t)min(W + (uint32_t)col, R - 1) * M;
@@ -316,7 +318,7 @@ __global__ __launch_bounds__(BS) void decode_whole_kernel(const DecodeParams p, 
           }
         }
         if (p.has_read) {
-          u32x4 hi[PARTS], lo[PARTS];
+          u32x4 aw[PARTS][3];
 #pragma unroll
           for (int j = 0; j < PARTS; ++j) {
             float rw[8];
@@ -325,9 +327,9 @@ __global__ __launch_bounds__(BS) void decode_whole_kernel(const DecodeParams p, 
             *(f32x4*)&rw[4] = *(const f32x4*)(from + 4);
 #pragma unroll
             for (int u = 0; u < 8; ++u) rw[u] = (uint32_t)col < G ? rw[u] * invr : 0.f;
-            split_hi_lo(rw, hi[j], lo[j]);
+            split_weights<3>(rw, aw[j]);
           }
-          mfma_read<LPS>(raw + ub * 8, hi, lo, acc);
+          mfma_read<LPS, 3>(raw + ub * 8, aw, acc);
         }
       }
     }
