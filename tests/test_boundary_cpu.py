@@ -440,3 +440,30 @@ def test_scratch_of_several_heads_with_64_columns(L):
         assert P.bct_cache_query(dsc, 0)[2] == need(per), (G, units, M)
         assert P.bct_plan_query(dsc)[1]["mv_splits"] == -(-(-(-M // 128)) // per), (G, units, M)
     assert wider > 50
+
+
+def test_where_the_one_launch_steps_begin_and_end(L):
+    """fp32, one query head, 257 to 512 memories of at most 128 slots: the smallest caches' own launch; below and beside it the
+    whole-step launch (workgroups per memory, threads), beyond both the streaming launches."""
+    def form(M, n, G, d, dt, keys=0):
+        dsc = P.make_desc(M, 1, n * G, n, d, dt, 0.1, 0.1, keys)
+        (st, wgs, threads), (st2, plan) = P.bct_plan_whole(dsc), P.bct_plan_query(dsc)
+        assert st == st2 == P.BCT_OK and (plan["launches"] == 1) == (plan["one_launch"] == 1)
+        if wgs:
+            assert plan["one_launch"] == 1 and threads in (512, 1024)
+            return wgs, threads
+        return "own" if plan["one_launch"] else "streaming"
+    F, B = P.BCT_F32, P.BCT_BF16
+    for d in (64, 128):
+        for M in (64, 128):
+            for keys in (0, P.BCT_MK_PER_SEQUENCE):
+                assert form(M, 256, 1, d, F, keys) == (1, 512) and form(M, 257, 1, d, F, keys) == "own"
+                assert form(M, 512, 1, d, F, keys) == "own" and form(M, 513, 1, d, F, keys) == "streaming"
+                assert form(M, 512, 2, d, F, keys) == (1, 512) and form(M, 513, 2, d, F, keys) == "streaming"
+                assert form(M, 1024, 4, d, F, keys) == (1, 512) and form(M, 1025, 4, d, F, keys) == "streaming"
+                assert form(M, 640, 1, d, B, keys) == (1, 512) and form(M, 641, 1, d, B, keys) == "streaming"
+        assert form(192, 300, 1, d, F) == ("streaming" if d == 128 else (1, 512))   # 96 and 48 KB of values a memory
+    assert form(64, 128, 1, 128, B) == (2, 512) and form(64, 129, 1, 128, B) == (1, 512)   # one round of workgroups
+    assert form(640, 63, 1, 128, B) == (2, 512) and form(704, 63, 1, 128, B) == "streaming"
+    assert form(512, 4096, 8, 128, B) == (1, 512) and form(512, 4097, 8, 128, B) == "streaming"
+    assert form(1024, 128, 1, 128, B) == (2, 512) and form(1024, 256, 1, 128, B) == "streaming"

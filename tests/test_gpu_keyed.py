@@ -47,7 +47,7 @@ def gdev(g):
 
 CASES = [
     # name, B, Hq, Hkv, d, M, dtype
-    ("f32_small", 2, 4, 4, 64, 128, "f32"),            # small enough for the one-launch step: the keyed step streams
+    ("f32_small", 2, 4, 4, 64, 128, "f32"),            # small: the whole step, the key update with it, in one launch
     ("f32_gqa2", 2, 4, 2, 128, 320, "f32"),
     ("bf16_m512", 3, 4, 4, 128, 512, "bf16"),
     ("bf16_gqa4", 2, 8, 2, 128, 2112, "bf16"),         # MFMA read for the values, vector write-only pass for the keys

@@ -117,22 +117,21 @@ SMALL = [
     ("bf16_d64_whole_m2048", 8, 32, 32, 64, 2048, "bf16"),    # 256 KB: 1024 threads, the largest
     ("f32_d128_whole_m128", 7, 28, 28, 128, 128, "f32"),      # 64 KB: 256 threads; 196 memories
     ("bf16_m1024_units128", 4, 32, 32, 128, 1024, "bf16"),    # too few memories: 16 KB workgroups, 16 partials
-    # Caches of at most 128 slots and 512 memories take the one-launch step, all others the four-launch
-    # step (flags = 2 forces the latter): these are cases on both sides of the two limits
+    # Small caches of few and of many memories, most of them one launch a step (flags = 2: several).  Where the one-launch
+    # forms begin and end is in test_boundary_cpu.py, their edges in test_gpu_whole.py
     ("f32_d64_units640", 40, 16, 16, 64, 128, "f32"),
     ("bf16_d128_gqa2_units576", 36, 32, 16, 128, 192, "bf16"),
     ("bf16_d64_units1024", 64, 16, 16, 64, 64, "bf16"),
     ("f32_d128_gqa4_units520", 130, 16, 4, 128, 64, "f32"),
     ("bf16_units4096", 512, 8, 8, 64, 64, "bf16"),            # many small memories
     ("bf16_gqa4_units2048", 256, 32, 8, 128, 64, "bf16"),     # the MFMA read with a single 64-slot tile per memory
-    ("bf16_m128_units512", 16, 32, 32, 128, 128, "bf16"),     # the largest cache of the one-launch step
+    ("bf16_m128_units512", 16, 32, 32, 128, 128, "bf16"),     # 512 memories of 32 KB
     ("f32_gqa8_m128", 1, 8, 1, 128, 128, "f32"),
     ("bf16_gqa4_m128_d64", 3, 8, 2, 64, 128, "bf16"),
 ]
 
 
-# flags: 0 shared keys, 1 per-sequence keys, 2 always the four-launch step (a different path only for
-# caches small enough for the one-launch step)
+# flags: 0 shared keys, 1 per-sequence keys, 2 always the step of several launches (a different path for these smallest caches)
 SMALL_FLAGS = [c + (f,) for c in SMALL for f in (0, 1, 2) if f < 2 or (c[5] <= 128 and c[1] * c[3] <= 512)]
 
 

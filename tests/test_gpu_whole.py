@@ -99,6 +99,49 @@ def _keyed(ref, mk, mv, q, wq, wv, wk, eta, kappa):
     return ref.decode_step_keyed(q, wq, wv, wk, gate=eta, kgate=np.full(eta.shape, kappa, np.float32))
 
 
+# fp32, one query head, 257 to 512 memories of at most 128 slots: one workgroup of 256 threads each (decode_fused_kernel).  Fewest and
+# most memories, both widths and both numbers of slots, keys shared and of each sequence
+@pytest.mark.parametrize("B,Hkv,d,M,seq", [(257, 1, 64, 64, 0), (32, 16, 64, 128, 0), (20, 15, 128, 64, 1), (64, 8, 128, 128, 0),
+                                           (43, 6, 64, 128, 1)])
+def test_smallest_caches_own_launch(P, R, B, Hkv, d, M, seq):
+    import torch
+    w = syn.Workload("fused", 1, B, Hkv, Hkv, d, M, "f32", 4)
+    ref, gpu, mk, mv, bs = make_pair(w, R.RefCache, P.BctCache, flags=seq, mv0=True)
+    assert P.bct_plan_whole(gpu.desc)[1] == 0 and P.bct_plan_query(gpu.desc)[1]["one_launch"] == 1
+    twin = make_pair(w, R.RefCache, P.BctCache, flags=seq, mv0=True)[1]
+    eta = syn.make_step(w, 7)[0][:, :, 0].astype(np.float32).copy()   # either sign
+    eta[0] = 0.0
+    dev = lambda a: to_dev(a, "f32")
+    steps = [("both", True, True, None), ("write", False, True, None), ("read", True, False, None), ("gated", True, True, eta)]
+    for t, (what, read, write, g) in enumerate(steps):
+        q, wq, wv = syn.make_step(w, t)
+        q, wq, wv = q if read else None, wq if write else None, wv if write else None
+        before = ref.values()
+        o_ref = ref.decode_step(q, wq, wv, **({} if g is None else {"gate": g}))
+        outs = []
+        for c in (gpu, twin):
+            c.set_values(dev(before))
+            o = c.decode_step(dev(q), dev(wq), dev(wv), **({} if g is None else {"gate": torch.from_numpy(g).cuda()}))
+            check_state_one_step(to_np(c.values_view(), "f32"), ref.values(), "f32", what, before=before)
+            outs.append(to_np(o, "f32") if read else None)
+        if read:
+            check_out(outs[0], o_ref, "f32", what)
+            assert np.array_equal(outs[0], outs[1])   # repeats itself
+        assert np.array_equal(to_np(gpu.values_view(), "f32"), to_np(twin.values_view(), "f32"))
+        if not write:
+            assert np.array_equal(to_np(gpu.values_view(), "f32"), before)
+    assert np.array_equal(to_np(gpu.keys_view(), "f32"), mk)
+    if seq:   # a step that writes keys takes the streaming launches
+        q, wq, wv = syn.make_step(w, 9)
+        wk = syn.make_step(w, 10)[2]
+        gpu.set_values(dev(mv))
+        o = gpu.decode_step_keyed(dev(q), dev(wq), dev(wv), dev(wk), gate=torch.from_numpy(eta).cuda(),
+                                  key_gate=torch.full((B, Hkv), 0.25, device="cuda:0"))
+        check_out(to_np(o, "f32"), _keyed(ref, mk, mv, q, wq, wv, wk, eta, 0.25), "f32", "keyed")
+        check_state_one_step(to_np(gpu.values_view(), "f32"), ref.values(), "f32", "keyed MV", before=mv)
+        check_state_one_step(to_np(gpu.keys_view(), "f32"), ref.keys(), "f32", "keyed MK", before=mk)
+
+
 def test_repeats_itself_and_graphs(P):
     """Equal inputs give equal bits, launched or replayed."""
     import torch
