@@ -59,10 +59,12 @@ bct_status bctm_pack_weight(const void* w, void* packed, uint32_t N, uint32_t K,
  * out/residual [rows][N] row-major;
  * K a multiple of 32, N a multiple of 16; fp32 accumulation (MFMA), one rounding to bf16 at the end.
  * out may alias residual; x must not alias out.  Two kernels: up to 127 rows (a decode batch) the weights
- * are streamed once per 32 rows against activations read from cache; from 128 rows on (a prompt chunk), when
- * N is a multiple of 128 (bctm_swiglu: 64) or N * rows is large (bctm_linear_plan), a tiled matrix-core kernel runs instead, with workgroup tiles from
- * 64 x 64 to 256 x 256 and 128 x 512 chosen to fill the chip - fastest with a tiled x.  Both sum in fp32, K in one or more parts added in
- * order.  The tile depends on rows, N, K and x's order, the number of parts on rows and N alone (bctm_linear_tile): equal calls give equal
+ * are streamed once per 32 rows against activations read from cache; from 128 rows on (a prompt chunk), a tiled matrix-core
+ * kernel runs instead where N is a multiple of 128 (bctm_swiglu: 64), or N is 128 to 16384 and the streaming kernel would have
+ * more than 256 workgroups of 32 rows x 16 features (bctm_linear with K beyond 8192: 512), with workgroup tiles of
+ * 64 x 64, 128 x 64, 128 x 128, 128 x 256, 256 x 256 and 128 x 512 chosen to fill the chip - fastest with a tiled x.  Both sum in fp32,
+ * K in one or more parts added in order.  The tile depends on rows, N, K and x's order, the number of parts on rows, N and K
+ * (bctm_linear_plan, bctm_linear_tile): equal calls give equal
  * bits, a tiled and a row-major x give the same bits, and so do calls of other rows or N with as many parts; calls with
  * other parts may differ in the last bits, a chunk's rows from the same rows alone or the parts of a bctm_linear_split
  * from separate projections. */

@@ -351,6 +351,8 @@ def test_projection_of_ragged_feature_counts():
     assert plan(256, 11008, 544, swiglu=True) == T128 and plan(256, 11008, 480, swiglu=True) == S
     assert plan(4096, 4096, 112) == S and plan(4096, 4096, 144) == T128             # at least one tile of features
     assert plan(4096, 4096, 16384) == Mo.BCTM_KERNEL_TILE256 and plan(4096, 4096, 16400) == S
+    tile = Mo.bctm_linear_tile   # so the parts that K is summed in follow from rows, N and K
+    assert tile(256, 8192, 736)[2] == 2 and tile(256, 8224, 736)[2] == 16 and tile(256, 8224, 736, swiglu=True)[2] == 2
 
 
 def test_workgroups_of_the_mv_pass_cover_every_memory(L):
