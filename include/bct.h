@@ -225,6 +225,10 @@ bct_status bct_plan_step(const bct_cache_desc* desc, const void* q, const void* 
                          const void* key_new, const float* gate, const float* key_gate, const void* out,
                          uint32_t* workgroups, uint32_t* mv_splits);
 
+/* *one_pass = 1 if a chunk of T tokens that reads and writes (section 3.5) takes one pass over keys and values, as chunks of
+ * few tokens of a bf16 cache do.  Host logic only, as above. */
+bct_status bct_plan_prefill(const bct_cache_desc* desc, uint32_t T, uint32_t* one_pass);
+
 /* Device addresses of the two regions inside cache_mem, MK first, then MV (section 3.1's two
  * sequences), for zero-copy views of the state: the bounded-cache layout in HBM as the caller sees it. */
 bct_status bct_cache_regions(const bct_cache* c, void** mk_dev, size_t* mk_bytes,

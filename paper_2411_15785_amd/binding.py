@@ -33,7 +33,7 @@ EXPORTS = [
     "bct_cache_regions", "bct_cache_destroy", "bct_strerror", "bct_last_error", "bct_stream_copy",
     "bct_profile_enable", "bct_profile_read", "bct_decode_step_static", "bct_static_scratch_bytes",
     "bct_decode_step_keyed", "bct_plan_rescores", "bct_plan_whole",
-    "bct_plan_step",
+    "bct_plan_step", "bct_plan_prefill",
 ]
 
 
@@ -90,6 +90,7 @@ def lib() -> ctypes.CDLL:
     L.bct_plan_rescores.argtypes = [dp, ctypes.POINTER(u32)]
     L.bct_plan_whole.argtypes = [dp, ctypes.POINTER(u32), ctypes.POINTER(u32)]
     L.bct_plan_step.argtypes = [dp] + [vp] * 7 + [ctypes.POINTER(u32)] * 2
+    L.bct_plan_prefill.argtypes = [dp, u32, ctypes.POINTER(u32)]
     L.bct_cache_randomize_values.argtypes = [vp, u64, ctypes.c_float, vp]
     L.bct_cache_export_sequence.argtypes = [vp, u32, vp, vp, vp]
     L.bct_cache_import_sequence.argtypes = [vp, u32, vp, vp, vp]
@@ -167,6 +168,13 @@ def bct_plan_step(desc, out, q=None, k_new=None, v_new=None, key_new=None, gate=
     st = lib().bct_plan_step(ctypes.byref(desc) if desc is not None else None, q, k_new, v_new, key_new, gate, key_gate, out,
                              ctypes.byref(n), ctypes.byref(s))
     return st, n.value, s.value
+
+
+def bct_plan_prefill(desc, T):
+    """-> (status, 1 if a chunk of T tokens that reads and writes takes one pass over keys and values)"""
+    n = ctypes.c_uint32()
+    st = lib().bct_plan_prefill(ctypes.byref(desc) if desc is not None else None, T, ctypes.byref(n))
+    return st, n.value
 
 
 def bct_last_error() -> str:

@@ -261,6 +261,25 @@ bct_status run_decode(bct_cache* c, char* ws, const void* q, const void* k_new, 
   return BCT_OK;
 }
 
+// A chunk without its buffers.
+bct::PrefillParams prefill_shape(const bct::DecodeParams& p, uint32_t T, bool write, bool read) {
+  bct::PrefillParams pp;
+  memset(&pp, 0, sizeof(pp));
+  pp.B = p.B;
+  pp.Hq = p.Hq;
+  pp.Hkv = p.Hkv;
+  pp.G = p.G;
+  pp.M = p.M;
+  pp.d = p.d;
+  pp.T = T;
+  pp.has_write = write ? 1u : 0u;
+  pp.has_read = read ? 1u : 0u;
+  pp.mk_per_seq = p.mk_per_seq;
+  pp.rscale_l2e = p.rscale_l2e;
+  pp.wscale_l2e = p.wscale_l2e;
+  return pp;
+}
+
 // Device address of `scratch` on each GPU.  In host code the array's name is only a handle for
 // hipGetSymbolAddress, not an address a kernel can use: the address is looked up once per device,
 // with that device current, and everything below uses the pointer.
@@ -496,8 +515,7 @@ bct_status bct_prefill_gated(bct_cache* c, const void* q, const void* k_new, con
     c->steps += T;
     return BCT_OK;
   }
-  bct::PrefillParams pp;
-  memset(&pp, 0, sizeof(pp));
+  bct::PrefillParams pp = prefill_shape(c->plan, T, k_new != nullptr, q != nullptr);
   pp.mk = (const uint16_t*)c->mk;
   pp.mv = (uint16_t*)c->mv;
   pp.q = (const uint16_t*)q;
@@ -509,18 +527,6 @@ bct_status bct_prefill_gated(bct_cache* c, const void* q, const void* k_new, con
   pp.norm_r = (float*)(c->ws + c->off_pf_norm_r);
   pp.snap = (uint16_t*)(c->ws + c->off_pf_snap);
   pp.wvt = (uint16_t*)(c->ws + c->off_pf_wvt);
-  pp.B = c->plan.B;
-  pp.Hq = c->plan.Hq;
-  pp.Hkv = c->plan.Hkv;
-  pp.G = c->plan.G;
-  pp.M = c->plan.M;
-  pp.d = c->plan.d;
-  pp.T = T;
-  pp.has_write = k_new ? 1u : 0u;
-  pp.has_read = q ? 1u : 0u;
-  pp.mk_per_seq = c->plan.mk_per_seq;
-  pp.rscale_l2e = c->plan.rscale_l2e;
-  pp.wscale_l2e = c->plan.wscale_l2e;
   const hipError_t e = bct::launch_prefill_bf16(pp, (hipStream_t)hip_stream);
   if (e != hipSuccess) return hip_fail(e, "prefill launch");
   c->steps += T;
@@ -610,6 +616,16 @@ bct_status bct_plan_step(const bct_cache_desc* desc, const void* q, const void* 
   const bct::WholePlan w = route_step(p, any, one, esize(desc->dtype), key_new, key_gate);
   *workgroups = p.fused ? 1u : w.workgroups;
   *mv_splits = p.S;
+  return BCT_OK;
+}
+
+bct_status bct_plan_prefill(const bct_cache_desc* desc, uint32_t T, uint32_t* one_pass) {
+  const bct_status st = check_desc(desc);
+  if (st != BCT_OK) return st;
+  if (T == 0 || !one_pass) return fail(BCT_ERR_INVALID_ARG, "T is 0 or one_pass is NULL");
+  bct::DecodeParams p;
+  fill_plan(desc, p);
+  *one_pass = desc->dtype == BCT_BF16 && bct::prefill_one_pass(prefill_shape(p, T, true, true)) ? 1u : 0u;
   return BCT_OK;
 }
 

@@ -108,7 +108,7 @@ struct PrefillParams {
 };
 constexpr uint32_t kPrefillSubChunk = 128;
 hipError_t launch_prefill_bf16(const PrefillParams& p, hipStream_t s);
-
+bool prefill_one_pass(const PrefillParams& p);   // a chunk of few tokens that is one pass over keys and values
 
 // dtype: 0 = fp32, 1 = bf16 (the ABI's bct_dtype values).
 hipError_t launch_scores(const DecodeParams& p, int dtype, hipStream_t s);

@@ -1320,7 +1320,9 @@ __global__ __launch_bounds__(256) void prefill_begin_kernel(const PassParams q) 
 //      moves its shift; weights of the write tokens (lane = token);
 //   2. weights, sums and MV of all wavefronts meet in LDS as operand tiles;
 //   3. a wavefront makes 32 columns of 32 read rows: += RW . MV + mask(RW . WW^T) . WV;
-//   4. the state, as in prefill_state_kernel: the same products in the same order, so MV has the same bits.
+//   4. the state, as in prefill_state_kernel: the same products in the same order, so from equal shifts MV has the same bits.  (The
+//      shifts come from other sums: prefill_begin_kernel's, of every fourth 32 slots and up to eight shares, not prefill_stats_kernel's;
+//      so a chunk that only writes, which takes that one, may leave MV an ulp from this one's here and there.)
 // A workgroup is one chain of these steps, 6 us alone and 10 beside another one, and two fit a compute unit (d = 64: three, 10 %
 // faster than two): 3456 of them (B = 3, H = 36, M = 4096, T = 10) take 74 us, 4.6 TB/s.  Keys in operand order from memory instead of
 // in whole rows: 78; the operands of the rows from memory where they are used, not staged: 92; walking several tiles in a
@@ -1690,13 +1692,15 @@ static hipError_t launch_pass(const PassParams& q, hipStream_t s) {
 
 // A chunk of few tokens in one pass: up to 32 read rows of a memory always; up to 64 rows (and tokens), whose workgroups are
 // alone on a compute unit with d = 128, where a memory is one workgroup or the memories are few, so that the others' chains over
-// a whole memory leave the chip idle.  us a chunk, transpose, statistics, state and read launches | begin, pass and merge (430
+// a whole memory leave the chip idle, and the scratch holds them (below).  us a chunk, transpose, statistics, state and read launches | begin, pass and merge (430
 // shapes): d = 128, G = 1: 3 memories of 192 slots, T = 5 24.6 | 13.6; 44 of 12864, T = 6 343 | 122; 108 of 4096, T = 10 176 | 98; 512
 // of 4096, T = 32 564 | 426; d = 64: 234 of 3904, G = 4, T = 4 161 | 100, 1024 of 192, T = 32 68.7 | 64.5 (the smallest gain up to 32 rows).
 // Up to 64 rows: d = 128, 6 of 12800, T = 55 255 | 60; 28 of 1088, T = 38 49 | 27; 1024 of 128, G = 4, T = 16 93 | 67; but 208 of 1152,
 // T = 41 104 | 141; 128 of 6976, G = 3, T = 19 323 | 387; 66 of 576, T = 47 41.6 | 40.2; d = 64, 232 of 1088, T = 45 64.5 | 68.2.
 // Its scratch lies where the other launches keep WV and the copies of MV, which are one after another: of a chunk of up to
-// 128 tokens 2 d (128 + M) bytes per memory.
+// 128 tokens 2 d (128 + M) bytes per memory.  32 rows always fit, and 64 in one tile of
+// slots, but none of 33 to 64 tokens at M = 64.  In several tiles: up to 32 tokens 60 rows, where 128 does not divide M 45 (M = 192), 51 (320)
+// to 60; 33 tokens or more none at M = 192, 40 (320), 45 (256), 52 (512) to 61 (from 4096 on).
 static bool pass_params(const PrefillParams& p, PassParams& q, int& nt, int& nr) {
   if (!p.has_write || !p.has_read || p.T > 64 || p.T * p.G > 64) return false;
   const uint64_t units = (uint64_t)p.B * p.Hkv, D = p.d;
@@ -1719,6 +1723,12 @@ static bool pass_params(const PrefillParams& p, PassParams& q, int& nt, int& nr)
   q.mz = (float2*)(q.part + part * D);
   q.pairs = q.mz + part;
   return true;
+}
+
+bool prefill_one_pass(const PrefillParams& p) {
+  PassParams q;
+  int nt, nr;
+  return pass_params(p, q, nt, nr);
 }
 
 hipError_t launch_prefill_bf16(const PrefillParams& p0, hipStream_t s) {

@@ -469,3 +469,23 @@ def test_where_the_one_launch_steps_begin_and_end(L):
     assert form(640, 63, 1, 128, B) == (2, 512) and form(704, 63, 1, 128, B) == "streaming"
     assert form(512, 4096, 8, 128, B) == (1, 512) and form(512, 4097, 8, 128, B) == "streaming"
     assert form(1024, 128, 1, 128, B) == (2, 512) and form(1024, 256, 1, 128, B) == "streaming"
+
+
+def test_chunks_of_few_tokens(L):
+    """One pass over keys and values: 32 rows (tokens x heads of a memory) always; 33 to 64 where a memory is one tile of 128 slots
+    or there are 64 memories at most, if their operands and partial outputs fit where a chunk of 128 tokens keeps its values."""
+    import itertools
+    def one(B, H, G, d, M, T, dt=P.BCT_BF16):
+        st, v = P.bct_plan_prefill(P.make_desc(M, B, H * G, H, d, dt, 0.1, 0.1, 0), T)
+        assert st == P.BCT_OK
+        return v
+    for d, M, G, T in itertools.product((64, 128), (64, 128, 192, 256, 448, 1088, 4096, 65536), range(1, 9), (1, 7, 12, 15, 16, 31, 32, 33, 40, 45, 58, 64, 65)):
+        rows, tiles = T * G, -(-M // 128)
+        shares = -(-tiles // -(-tiles // 8))
+        need = (2 * (2 if T > 32 else 1) + (2 if rows > 32 else 1)) * 64 * d + 8 * T * shares + (tiles > 1) * tiles * rows * (4 * d + 8)
+        fits = need <= (128 + M) * 2 * d
+        assert fits or rows > 32
+        assert one(64, 1, G, d, M, T) == (rows <= 64 and fits), (d, M, G, T)
+        assert one(65, 1, G, d, M, T) == (rows <= 64 and fits and (rows <= 32 or tiles == 1)), (d, M, G, T)
+        assert one(1, 1, G, d, M, T, P.BCT_F32) == 0
+    assert P.bct_plan_prefill(desc(), 0)[0] == P.BCT_ERR_INVALID_ARG

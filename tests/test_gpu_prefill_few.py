@@ -28,7 +28,8 @@ def R():
 # one tile of slots (the output is finished in the pass), two, several; 1, 31, 32, 33 tokens; rows up to 32, 33 to 64 and beyond
 CASES = [(1, 1, 1, 64, 1, 0), (2, 3, 1, 64, 31, 0), (1, 2, 1, 128, 32, 1), (3, 2, 1, 192, 33, 0), (1, 3, 2, 192, 16, 1),
          (2, 1, 3, 320, 11, 0), (1, 2, 8, 1088, 4, 0), (1, 1, 8, 128, 5, 1), (2, 2, 4, 64, 16, 0), (1, 1, 1, 2112, 55, 0),
-         (1, 2, 1, 128, 64, 0), (1, 1, 1, 1088, 64, 0), (3, 1, 5, 448, 13, 1), (17, 4, 1, 192, 40, 0), (16, 4, 1, 192, 40, 0)]
+         (1, 2, 1, 128, 64, 0), (1, 1, 1, 1088, 64, 0), (1, 1, 1, 1088, 54, 0), (1, 2, 5, 256, 12, 0), (3, 1, 5, 448, 13, 1), (17, 4, 1, 192, 40, 0), (16, 4, 1, 192, 40, 0),
+         (16, 4, 1, 320, 40, 0), (17, 4, 1, 320, 40, 0)]
 
 
 @pytest.mark.parametrize("d", [64, 128])
@@ -37,6 +38,9 @@ def test_chunk(P, R, d, B, Hkv, G, M, T, seq):
     w = syn.Workload("few", 1, B, Hkv * G, Hkv, d, M, "bf16", 0)
     # a cache sized for longer chunks as well: the scratch is where that one's is
     ref, gpu, mk, mv, _ = make_pair(w, R.RefCache, P.BctCache, flags=seq, mv0=True, max_prefill_T=T + 130 * (M == 192))
+    # beyond the border: too many rows, too many for the scratch, too many memories of several tiles
+    several = (B, M, T) in ((3, 448, 13), (3, 192, 33), (1, 1088, 64), (17, 192, 40), (16, 192, 40), (17, 320, 40))
+    assert P.bct_plan_prefill(gpu.desc, T) == (P.BCT_OK, 0 if several else 1)
     for chunk in range(2):
         q, wq, wv = syn.make_step(w, chunk * T, T=T)
         before = ref.values()
@@ -55,6 +59,7 @@ def test_step_sizes_and_scales(P, R, rs, ws):
     B, Hkv, G, d, M, T = 2, 2, 2, 128, 320, 15
     w = syn.Workload("few_gate", 1, B, Hkv * G, Hkv, d, M, "bf16", 0)
     ref, gpu, mk, mv, _ = make_pair(w, R.RefCache, P.BctCache, read_scale=rs, write_scale=ws, mv0=True, max_prefill_T=T)
+    assert P.bct_plan_prefill(gpu.desc, T) == (P.BCT_OK, 1)
     q, wq, wv = syn.make_step(w, 0, T=T)
     g = gates(5, (B, T, Hkv))
     g[:, ::3] *= -1.0
@@ -104,6 +109,7 @@ def test_slots_masked_by_their_keys(P, R, d, G, T, first):
     B, Hkv, M = 2, 2, 320
     w = syn.Workload("few_masked", 1, B, Hkv * G, Hkv, d, M, "bf16", 0)
     ref, gpu, mk, mv, _ = make_pair(w, R.RefCache, P.BctCache, mv0=True, max_prefill_T=T)
+    assert P.bct_plan_prefill(gpu.desc, T) == (P.BCT_OK, 1)
     keys = f64(mk, "bf16")
     keys[:, first:first + 128] = 0.0
     keys[:, first:first + 128, 0] = -3e38
