@@ -60,8 +60,11 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
   if (vid >= total) return;   // the grid is 8 * per workgroups: every id below total comes up once
   // The last band takes the remainder as well (HB to 2 * HB - 1 row tiles): a band of one row tile of its own would read
   // every weight for that row tile alone.  us, own band | this: 320 rows, 11008 -> 4096 89.5 | 82.5, 4096 -> 12288 73 | 67,
-  // SwiGLU 4096 -> 11008 120 | 111, 640 rows 107 | 102.
-  const uint32_t nfull = RT < 2 * HB ? 0u : RT / HB - 1;
+  // 640 rows 107 | 102; 180 shapes 0.965 to 1.09, in the mean 1.004 to 1.017 for each tile.  Not where two workgroups share a compute
+  // unit (no turns): the two are 32 ids of their XCD apart, so in bands of HB they have the same row tile and its activations
+  // from L1, in others not.  1060 rows, 928 -> 4480 21.0 | 24.3, 1598, 4000 -> 3456 56.2 | 62.6, 515, 10464 -> 7296 132 | 151 (but
+  // 616, 8704 -> 6784 131 | 110).
+  const uint32_t nfull = !PING ? RT / HB : RT < 2 * HB ? 0u : RT / HB - 1;
   uint32_t rt, nt;
   if (vid < nfull * HB * NT) {
     const uint32_t band = vid / (HB * NT), rem = vid % (HB * NT);
