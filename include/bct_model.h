@@ -61,7 +61,7 @@ bct_status bctm_pack_weight(const void* w, void* packed, uint32_t N, uint32_t K,
  * out may alias residual; x must not alias out.  Two kernels: up to 127 rows (a decode batch) the weights
  * are streamed once per 32 rows against activations read from cache; from 128 rows on (a prompt chunk), a tiled matrix-core
  * kernel runs instead where N is a multiple of 128 (bctm_swiglu: 64), or N is 128 to 16384 and the streaming kernel would have
- * more than 256 workgroups of 32 rows x 16 features (bctm_linear with K beyond 8192: 512), with workgroup tiles of
+ * more than 256 workgroups of 32 rows x 16 features (bctm_linear with K beyond 3072: 512), with workgroup tiles of
  * 64 x 64, 128 x 64, 128 x 128, 128 x 256, 256 x 256 and 128 x 512 chosen to fill the chip - fastest with a tiled x.  Both sum in fp32,
  * K in one or more parts added in order.  The tile depends on rows, N, K and x's order, the number of parts on rows, N and K
  * (bctm_linear_plan, bctm_linear_tile): equal calls give equal

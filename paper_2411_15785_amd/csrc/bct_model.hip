@@ -389,16 +389,19 @@ static void launch_linear_w(const void* x, const void* w, const void* residual, 
 // The kernel of a projection shape.  Many rows (from 128 on): the matrix-core kernel (bct_linear_rows.hip); its two values
 // name ranges of shapes, the tile inside it is linear_rows_tile's choice.  Feature counts that no tile divides take it as
 // well, with a last tile that is partly used, once the streaming kernel, which reads the weights again for every 32 rows, has
-// more than one round of workgroups (of inputs beyond 8192: two).  us, streaming | matrix-core, weights from memory:
+// more than one round of workgroups (of inputs beyond 3072: two; SwiGLU, whose weights are twice as many, one).  us, streaming | matrix-core, weights from memory:
 //   709 rows, 11264 -> 2912 332 | 94; 2381, 1664 -> 1344 142 | 20; 4096, 4096 -> 4128 959 | 157; 8192, 5088 -> 5088 3679 | 361;
-//   SwiGLU 1500, 4000 -> 1504 188 | 54; 640, 1024 -> 2848 42 | 14; 256, 1024 -> 736 (368 workgroups) 11.8 | 6.9, 256, 5120 -> 736
-//   23.6 | 19.3, SwiGLU 27 | 24; 200, 5120 -> 480 (210) 12.9 | 19.0, SwiGLU 15.8 | 20.8; 256, 11008 -> 736 39 | 47, -> 1504 (752) 67 | 45
+//   SwiGLU 1500, 4000 -> 1504 188 | 54; 640, 1024 -> 2848 42 | 14; 256, 1024 -> 736 (368 workgroups) 11.8 | 6.9; 700, 3072
+//   -> 320 (440) 13.3 | 12.6; 516, 10976 -> 576 (612) 50.4 | 44.6; 256, 11008 -> 1504 (752) 67 | 45; SwiGLU 256, 5120 -> 736 27 | 24, 167,
+//   8992 -> 720 (270) 45.7 | 43.6.  One to two rounds of more than 3072 inputs, where few tiles are one long chain each, either way:
+//   145, 4032 -> 1200 (375) 15.9 | 19.3; 360, 7072 -> 448 (336) 23.4 | 27.9; 700, 4096 -> 320 14.5 | 15.7; but 700, 4096 -> 272 17.4 | 15.7.
+//   Up to one round: 200, 5120 -> 480 (210) 12.9 | 19.0, SwiGLU 15.8 | 20.8
 // Not below 128 features, where no tile is half used, and not beyond 16384.
 // Few rows: the streaming kernel; measured at 32 rows (weights in TB/s): K = 4096, N = 4096 / 12288: 16
 // wavefronts, one feature tile 3.6 / 4.0 against 2.8 / 3.8 for two tiles (too few workgroups); N = 32000:
 // two tiles 5.0 against 4.3.
 static uint32_t linear_kernel_of(uint32_t rows, uint32_t K, uint32_t N, bool swiglu) {
-  const bool ragged = N >= 128 && N <= 16384 && (uint64_t)(N / 16) * ((rows + 31) / 32) > (!swiglu && K > 8192 ? 512u : 256u);
+  const bool ragged = N >= 128 && N <= 16384 && (uint64_t)(N / 16) * ((rows + 31) / 32) > (!swiglu && K > 3072 ? 512u : 256u);
   if (rows >= 128 && (N % (swiglu ? 64u : 128u) == 0 || ragged))
     return (rows >= 1024 && N % (swiglu ? 128u : 256u) == 0) ? BCTM_KERNEL_TILE256 : BCTM_KERNEL_TILE128;
   if (!swiglu && N >= 16384 && N % 32 == 0) return BCTM_KERNEL_STREAMING_WIDE;

@@ -346,13 +346,15 @@ def test_projection_of_ragged_feature_counts():
     from paper_2411_15785_amd import model as Mo
     S, T128, plan = Mo.BCTM_KERNEL_STREAMING, Mo.BCTM_KERNEL_TILE128, Mo.bctm_linear_plan
     assert plan(709, 11264, 2912) == T128 and plan(1500, 4000, 1504, swiglu=True) == T128 and plan(127, 4096, 12336) == S + 4
-    assert plan(256, 4096, 512 + 16) == T128 and plan(256, 4096, 496) == S          # 264 and 248 workgroups
+    assert plan(256, 3072, 512 + 16) == T128 and plan(256, 3072, 496) == S          # 264 and 248 workgroups
+    assert plan(256, 3104, 1024 + 16) == T128 and plan(256, 3104, 1008) == S        # 520 and 504: streaming is the faster up to there
+    assert plan(145, 4032, 1200) == S and plan(360, 7072, 448) == S
     assert plan(256, 11008, 1024 + 16) == T128 and plan(256, 11008, 1008) == S      # 520 and 504
     assert plan(256, 11008, 544, swiglu=True) == T128 and plan(256, 11008, 480, swiglu=True) == S
     assert plan(4096, 4096, 112) == S and plan(4096, 4096, 144) == T128             # at least one tile of features
     assert plan(4096, 4096, 16384) == Mo.BCTM_KERNEL_TILE256 and plan(4096, 4096, 16400) == S
     tile = Mo.bctm_linear_tile   # so the parts that K is summed in follow from rows, N and K
-    assert tile(256, 8192, 736)[2] == 2 and tile(256, 8224, 736)[2] == 16 and tile(256, 8224, 736, swiglu=True)[2] == 2
+    assert tile(256, 3072, 736)[2] == 2 and tile(256, 3104, 736)[2] == 16 and tile(256, 3104, 736, swiglu=True)[2] == 2
 
 
 def test_workgroups_of_the_mv_pass_cover_every_memory(L):
