@@ -85,7 +85,7 @@ def dominant_kernel(plan, rescores, whole, w):
     if w.dtype == "bf16" and w.G > 2:
         again = "true" if rescores else "false"
         slots = plan["mv_workgroup"] * plan["mv_loads_per_lane"] * 8 // w.d
-        tiles = "true" if rescores or plan["mv_splits"] * slots < w.M else "false"
+        tiles = "true" if plan["mv_splits"] * slots < w.M else "false"
         return f"mv_pass_gqa_kernel<true,{plan['mv_workgroup']},{norm},{plan['mv_loads_per_lane']},{again},{w.d},{tiles}>"
     return f"mv_pass_kernel<{dt},{w.d},{gt},true,true,{plan['mv_workgroup']},{plan['mv_loads_per_lane']},{norm}>"
 

@@ -31,7 +31,7 @@ namespace bct {
 
 namespace {
 
-template <bool WRITE, int BS, bool NORM, int U, bool RESCORE, int D, bool TILES = RESCORE>
+template <bool WRITE, int BS, bool NORM, int U, bool RESCORE, int D, bool TILES>
 __global__ __launch_bounds__(BS) void mv_pass_gqa_kernel(const DecodeParams p) {
   constexpr int LPS = D / 8, SPI = 64 / LPS, PARTS = ReadShape<LPS>::kParts;   // lanes per slot row, slots per load instruction
   constexpr int NB = U / 8, NW = BS / 64, SPB = NW * SPI * U;
@@ -238,8 +238,13 @@ static void launch_gqa_bs(const DecodeParams& p, hipStream_t s) {
   const dim3 grid = unit_grid(p.S, (uint64_t)p.B * p.Hkv), block(BS);
   if constexpr (D == 128) {
     if (p.rescore) {
-      if (p.has_write) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U, true, D>), grid, block, 0, s, p);
-      else hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, false, U, true, D>), grid, block, 0, s, p);
+      // one tile a workgroup (an odd number of them, or keys out of reach) without the loop over tiles, which leaves a SIMD two
+      // wavefronts where this has three: us a step, loop | this: G = 6, 1295 memories of 54 tiles 494 | 482, G = 3, 1950 of 45 548 | 535
+      const bool one = (uint64_t)p.S * (BS * U * 16 / 256) >= p.M;
+      if (p.has_write && one) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U, true, D, false>), grid, block, 0, s, p);
+      else if (p.has_write) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U, true, D, true>), grid, block, 0, s, p);
+      else if (one) hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, false, U, true, D, false>), grid, block, 0, s, p);
+      else hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, false, U, true, D, true>), grid, block, 0, s, p);
       return;
     }
   }
@@ -253,11 +258,11 @@ static void launch_gqa_bs(const DecodeParams& p, hipStream_t s) {
     }
   }
   if (p.has_write) {
-    if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, true, U, false, D>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U, false, D>), grid, block, 0, s, p);
+    if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, true, U, false, D, false>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((mv_pass_gqa_kernel<true, BS, false, U, false, D, false>), grid, block, 0, s, p);
   } else {
-    if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, true, U, false, D>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, false, U, false, D>), grid, block, 0, s, p);
+    if (p.fuse_norm) hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, true, U, false, D, false>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((mv_pass_gqa_kernel<false, BS, false, U, false, D, false>), grid, block, 0, s, p);
   }
 }
 
