@@ -429,12 +429,27 @@ hipError_t launch_g(const DecodeParams& p, const WholePlan& w, const KeyWrite& k
 //   keys per sequence that move: d = 64, G = 1, M = 256, n = 256 26.1 / 13.9
 // Two workgroups per memory while they still are one round of a workgroup per compute unit (the keys are then read twice:
 // only keys shared by the batch, which stay in L2), 512 threads while the columns of M slots fit 16 loads a lane: 1024 are up
-// to 6 % faster at 512 slots, 30 % slower at 64.  The borders, from 880 shapes of which none is more than 4 % slower for it:
-//   few memories: the chain of a workgroup over its keys is the step, streaming splits M over workgroups (fp32, G = 1, whose
-//     dot products cost streaming least: d = 64, M = 512, n = 64 10.2 / 11.4, 128 13.3 / 11.8);
-//   G = 1: streaming runs at the rate of memory once the chip is full;
-//   G = 2: at most the rounds that were measured; G > 2: streaming writes 1 + G scores a slot and its partial outputs, this
-//     kernel neither, so it stays ahead at every n that was measured; M <= 128 fills lanes only partly.
+// to 6 % faster at 512 slots, 30 % slower at 64.  The borders, as the ratio of the streaming launches' time to this kernel's at n
+// memories (3300 shapes, 3045 of them taken: 0.96 at the least, 1.42 in the geometric mean):
+//   few memories: the chain of a workgroup over its keys is the step, streaming splits M over workgroups.  Ratio by KB of values a
+//     memory, one workgroup: G = 1 bf16 64 KB 1.3, 80 1.05, 96 0.92, f32 80 1.01, 96 0.94; G = 2 bf16 88 1.05, 96 0.98 to 1.04, 104 0.95,
+//     128 0.84, f32 96 1.03, 112 0.93, 128 0.84; G > 2 up to 128 1.0 to 1.7.  Two workgroups: G = 1 128 1.1, 160 0.96; G > 1 160 1.0 to
+//     1.4.  32 memories and more, which streaming feels: G = 1, two workgroups 160 KB 1.08, f32 96 1.05 to 1.2, keys per sequence 96 1.08 to
+//     1.26; G = 2 104 1.04 to 1.13, keys per sequence 128 1.04 to 1.18.  fp32, G = 1, whose dot products cost streaming least, up to 127
+//     memories (96 KB at 64 of them 1.12);
+//   two workgroups of more than 128 memories, a second round: n = 129 costs what 256 do.  bf16 G = 3 n = 129 0.81 to 0.94, 160 0.90 to
+//     0.98, 192 1.0 to 1.05, 224 1.02 to 1.12; f32 G = 2 160 0.91 to 0.95, 208 1.05 to 1.08; from more heads on it gains at once (f32 G = 5
+//     n = 129 1.20, bf16 G = 8 0.98 to 1.0).  Beyond, streaming runs at the rate of memory: bf16 G = 5, n = 900, 144 KB 1.03, 256 KB
+//     0.91; G = 8 n = 1024 1.01 to 1.06, 2048 0.95; f32 G = 8 4096 1.5;
+//   G <= 2, 64 to 127 memories: one round of long chains.  n = 64, G = 1: M = 1088 1.0, 1408 0.91, 2048 0.76; G = 2: 1.08, 0.94 to 0.99,
+//     0.79 to 0.96; n = 80 M = 1088 1.02 to 1.11, 1408 0.95 to 1.02; n = 100, one workgroup, M = 1408 1.03 to 1.1, 2048 0.85 to
+//     0.93; keys per sequence of 64 memories 192 KB 1.01 to 1.05, 256 KB 0.89 to 0.96;
+//   G = 1: streaming runs at the rate of memory once the chip is full.  n = 200, d = 128 192 KB 1.03, 240 KB 0.96 to 1.0; 128, d = 64 192 KB
+//     1.0, 256 KB 0.91; fp32 beyond one round of workgroups only where there are nearly two: n = 320 0.96, 512 1.02 to 1.05, 640 0.89;
+//   G = 2 beyond 256 memories: 208 KB 0.99 to 1.17, 256 KB 0.91 to 1.04; 1024 threads, alone on a compute unit, n = 264 0.92 to 0.97, 304
+//     1.0 to 1.03, 520 0.97 to 1.01; at most the rounds that were measured;
+//   G > 2: streaming writes 1 + G scores a slot and its partial outputs, this kernel neither, so it stays ahead at every n that was
+//     measured; M <= 128 fills lanes only partly.
 WholePlan plan_whole(const DecodeParams& p, int dtype, bool two_allowed) {
   const uint32_t row = p.d * (dtype == 0 ? 4u : 2u), G = p.G, M = p.M;
   const uint64_t n = (uint64_t)p.B * p.Hkv, mem = (uint64_t)M * row, KB = 1024;
@@ -453,12 +468,30 @@ WholePlan plan_whole(const DecodeParams& p, int dtype, bool two_allowed) {
   } else if (!fits(512, 1) && !fits(1024, 1)) {
     if (!two || !fits(512, 2)) return none;
   }
+  const bool pair = w.workgroups == 2, own = p.mk_per_seq;
+  const uint64_t kb = mem / KB;
   bool take;
-  if (n < (f32 && G == 1 ? 128 : 64)) take = mem <= (w.workgroups == 2 && (!f32 || G > 1) ? 160 : w.workgroups == 2 || G > 1 ? 128 : 96) * KB;
-  else if (w.workgroups == 2 && n > 128) take = G > 4 ? n <= 4096 : G > 1 && n <= 256;
-  else if (G == 1) take = n <= 256 ? n * mem <= (mem < 256 * KB ? 62 : 48) * KB * KB : n <= 640 && mem <= 64 * KB && !(f32 && M <= 128);
-  else if (G == 2) take = n <= (f32 ? 512 : 1024);
-  else take = n <= (f32 || M <= 128 ? 1024 : 4096);
+  if (n < (f32 && G == 1 ? 128 : 64)) {
+    uint32_t most;
+    if (pair) most = G == 1 && (f32 || n < 32) ? 128 : 160;
+    else if (G > 2) most = 128;
+    else if (n < 32) most = G == 1 ? 80 : 96;
+    else if (G == 1) most = own || f32 ? 96 : 80;
+    else most = own ? 128 : 104;
+    take = kb <= most;
+  } else if (pair && n > 128) {
+    take = f32 ? (G > 4 ? n <= 4096 : G > 1 && n >= (G == 2 ? 208 : 192) && n <= 256)
+               : (G > 6 ? n <= 1024 : n >= 192 && (n <= 256 || (G > 4 && n <= 1024 && kb <= 160)));
+  } else if (G <= 2) {
+    if (n < 96) take = M <= (own ? 1408 : 8 * n + 576) && (pair || kb <= 192);
+    else take = pair || own || n > 128 || M <= (G == 1 && n > 96 ? 1536 : 16 * n);
+    if (G == 2 && w.threads == 1024 && n > 256 && n < 304) take = false;
+    else if (G == 2) take = take && (n <= 256 || (n <= (f32 ? 512 : 1024) && (kb <= 216 || (n >= 448 && n <= 512))));
+    else if (n <= 256) take = take && (pair || own || n < 192 || kb <= 208) && n * kb <= (kb < 256 ? 62 : 48) * KB;
+    else take = kb <= 64 && (f32 ? M > 128 && n >= 448 && n <= 512 : n <= 640);
+  } else {
+    take = n <= (f32 || M <= 128 ? 1024 : 4096);
+  }
   return take ? w : none;
 }
 

@@ -412,7 +412,7 @@ def test_route_of_a_step_whose_output_overlaps_its_inputs(L):
     # the smallest caches' own launch: 300 memories, fp32, one query head
     assert route(64, 75, 1, 64, P.BCT_F32, q=a, out=a, **far)[0] == 1 and route(64, 75, 1, 64, P.BCT_F32, q=a + 16, out=a, **far)[0] == 0
     # one workgroup per memory would be a longer chain than the streaming launches: those
-    assert route(640, 2, 1, 128, P.BCT_BF16, q=2 * a, out=a, **far)[0] == 2 and route(640, 2, 1, 128, P.BCT_BF16, q=a, out=a, **far)[0] == 0
+    assert route(512, 2, 1, 128, P.BCT_BF16, q=2 * a, out=a, **far)[0] == 2 and route(512, 2, 1, 128, P.BCT_BF16, q=a, out=a, **far)[0] == 0
     # no merge after the pass: it reads q and k_new itself where it scores again, so two splits for rows of others
     big = dict(out=a, **far)
     assert route(128, 2000, 8, 128, P.BCT_BF16, H=8, q=a, **big) == (0, 1) and route(128, 2000, 8, 128, P.BCT_BF16, H=8, q=a + 16, **big) == (0, 2)
@@ -466,11 +466,32 @@ def test_where_the_one_launch_steps_begin_and_end(L):
                 assert form(M, 512, 2, d, F, keys) == (1, 512) and form(M, 513, 2, d, F, keys) == "streaming"
                 assert form(M, 1024, 4, d, F, keys) == (1, 512) and form(M, 1025, 4, d, F, keys) == "streaming"
                 assert form(M, 640, 1, d, B, keys) == (1, 512) and form(M, 641, 1, d, B, keys) == "streaming"
-        assert form(192, 300, 1, d, F) == ("streaming" if d == 128 else (1, 512))   # 96 and 48 KB of values a memory
+        assert form(192, 300, 1, d, F) == "streaming" and form(192, 512, 1, 64, F) == (1, 512)   # nearly two rounds of workgroups
     assert form(64, 128, 1, 128, B) == (2, 512) and form(64, 129, 1, 128, B) == (1, 512)   # one round of workgroups
-    assert form(640, 63, 1, 128, B) == (2, 512) and form(704, 63, 1, 128, B) == "streaming"
     assert form(512, 4096, 8, 128, B) == (1, 512) and form(512, 4097, 8, 128, B) == "streaming"
     assert form(1024, 128, 1, 128, B) == (2, 512) and form(1024, 256, 1, 128, B) == "streaming"
+    # few memories: KB of values of one workgroup's, of two
+    own = P.BCT_MK_PER_SEQUENCE
+    for M, n, G, d, dt, keys, last in ((640, 31, 1, 64, B, 0, 1), (640, 63, 1, 64, B, 0, 1), (320, 31, 1, 64, F, 0, 1),
+                                       (384, 32, 1, 64, F, 0, 1), (768, 32, 1, 64, B, own, 1), (768, 16, 2, 64, B, 0, 1),
+                                       (832, 40, 2, 64, B, 0, 1), (1024, 40, 2, 64, B, own, 1), (1024, 16, 3, 64, B, 0, 1),
+                                       (512, 31, 1, 128, B, 0, 2), (640, 32, 1, 128, B, 0, 2), (640, 31, 2, 128, B, 0, 2),
+                                       (256, 63, 1, 128, F, 0, 2)):
+        assert form(M, n, G, d, dt, keys)[0] == last and form(M + 64, n, G, d, dt, keys) == "streaming", (M, n, G, d, dt, keys)
+    # 64 to 128 memories, one round of long chains
+    for M, n, G, d, keys in ((1088, 64, 1, 128, 0), (1088, 64, 2, 64, 0), (1216, 80, 1, 64, 0), (1600, 100, 2, 64, 0), (1536, 100, 1, 64, 0),
+                             (1536, 128, 1, 64, 0), (1408, 64, 1, 64, own), (768, 64, 1, 128, own), (1664, 200, 1, 64, 0), (832, 200, 1, 128, 0),
+                             (832, 600, 2, 128, 0), (1728, 600, 2, 64, 0), (256, 512, 1, 128, 0)):
+        assert form(M, n, G, d, B, keys) != "streaming" and form(M + 64, n, G, d, B, keys) == "streaming", (M, n, G, d, keys)
+    for n in (256, 304, 512):   # 1024 threads are alone on a compute unit: not somewhat more than a round of them
+        assert form(576, n, 2, 128, B) == (1, 1024)
+    assert form(576, 257, 2, 128, B) == form(576, 303, 2, 128, B) == "streaming" and form(512, 257, 2, 128, B) == (1, 512)
+    # two workgroups of each of more than 128 memories
+    for M, dt, G, first, end in ((576, B, 3, 192, 256), (576, B, 5, 192, 1024), (704, B, 5, 192, 256), (576, B, 8, 129, 1024),
+                                 (320, F, 2, 208, 256), (320, F, 3, 192, 256), (320, F, 5, 129, 4096)):
+        assert form(M, first, G, 128, dt)[0] == form(M, end, G, 128, dt)[0] == 2 and form(M, end + 1, G, 128, dt) == "streaming", (M, dt, G)
+        if first > 129:
+            assert form(M, first - 1, G, 128, dt) == "streaming", (M, dt, G)
 
 
 def test_chunks_of_few_tokens(L):
