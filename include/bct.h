@@ -159,7 +159,8 @@ bct_status bct_prefill_gated(bct_cache* c, const void* q, const void* k_new, con
  * so the moved keys address the NEXT token.  key_new: [B][n_kv_heads][head_dim], storage dtype;
  * key_gate: float32 [B][n_kv_heads] step sizes kappa, NULL = 1; gate as in bct_decode_step_gated.
  * Needs per-sequence keys (BCT_MK_PER_SEQUENCE, else BCT_ERR_STATE) and a write (k_new, v_new); the
- * read (q, out) may be absent.  key_gate = 0 is bct_decode_step_gated bit for bit and leaves MK alone.
+ * read (q, out) may be absent.  key_gate = 0 leaves MK alone and is bct_decode_step_gated, bit for bit but where only the
+ * latter is one launch (float32, one query head per KV head, 257 to 512 memories of at most 128 slots: to the tolerances).
  * This is the only call besides bct_cache_set_keys / import that writes MK.  There is no chunk form:
  * unrolling a chunk (section 3.5) needs keys that do not move.  Moves 2 MK more bytes than the plain
  * step (the keys of every sequence are read and written once more). */

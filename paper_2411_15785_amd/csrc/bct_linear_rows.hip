@@ -60,7 +60,8 @@ __global__ __launch_bounds__(64 * WR * WC * KS, 2) void linear_rows_kernel(
   if (vid >= total) return;   // the grid is 8 * per workgroups: every id below total comes up once
   // The last band takes the remainder as well (HB to 2 * HB - 1 row tiles): a band of one row tile of its own would read
   // every weight for that row tile alone.  us, own band | this: 320 rows, 11008 -> 4096 89.5 | 82.5, 4096 -> 12288 73 | 67,
-  // 640 rows 107 | 102; 180 shapes 0.965 to 1.09, in the mean 1.004 to 1.017 for each tile.  Not where two workgroups share a compute
+  // 640 rows 107 | 102; 330 shapes 0.95 to 1.2, in the mean 1.004 to 1.02 for each tile (64 x 64: 434, 6464 -> 2176 35.6 |
+  // 37.6, 283, 10752 -> 6016 125 | 106).  Not where two workgroups share a compute
   // unit (no turns): the two are 32 ids of their XCD apart, so in bands of HB they have the same row tile and its activations
   // from L1, in others not.  1060 rows, 928 -> 4480 21.0 | 24.3, 1598, 4000 -> 3456 56.2 | 62.6, 515, 10464 -> 7296 132 | 151 (but
   // 616, 8704 -> 6784 131 | 110).

@@ -27,8 +27,8 @@
 //
 // Precision: scores in fp32 from exact bf16 products; softmax weights are
 // rounded to bf16 as MFMA operands for the reads; for the state they are split
-// into hi + lo bf16 parts (two MFMAs) so that the stored MV carries fp32-grade
-// weights like the decode step does.
+// into hi + lo bf16 parts (two MFMAs), 16 to 17 bits, so that the stored MV is within one rounding of the
+// decode step's.
 #include "bct_device.h"
 #include "bct_internal.h"
 
