@@ -82,7 +82,7 @@ def dominant_kernel(plan, rescores, whole, w):
         return f"decode_whole_kernel<{dt},{w.d},{gt},{loads},{wgs},{threads}>"
     if plan["one_launch"]:
         return f"decode_fused_kernel<{dt},{w.d}>"
-    if w.dtype == "bf16" and w.G > 2:
+    if w.dtype == "bf16" and w.G > 2 and plan["mv_workgroup"] == 128:
         again = "true" if rescores else "false"
         slots = plan["mv_workgroup"] * plan["mv_loads_per_lane"] * 8 // w.d
         tiles = "true" if plan["mv_splits"] * slots < w.M else "false"

@@ -221,8 +221,21 @@ static constexpr uint64_t kWholeMinUnits = 192, kWholeMaxTotal = 64ull << 20;
 // 2048 44.9 -> 42.5, 1024 of 16384 1077 -> 948; G = 3, 512 of 8192 247 -> 213; G = 8, 256 of 8192 300 -> 144.
 static constexpr MvShape kGqa = {128, 8};
 
+// Three or four heads with 64 columns, where 128 does not divide M, of long memories and much of them stay on the vector ALU.  Those
+// workgroups of 128 slots begin half a tile off in every other memory and the pass loses what it gains (820 memories of
+// 10240 slots 374 us, of 10304 404; the vector ALU's 415 and 392; the same bytes).  us a step, vector ALU | matrix cores, G = 3: n = 1759,
+// M = 8256 772 | 837; 1064, 13760 759 | 819; 820, 10304 437 | 455 to 473; 344, 24000 432 | 459; 2304, 7744 963 | 1002; 1467, 9408 729 |
+// 747 to 764; 464, 14784 385 | 383.  Not fewer slots (n = 1184, M = 6336 430 | 396; 1260, 5824 396 | 393; 1636, 5312 447 | 462) nor fewer bytes
+// (296, 11712 291 | 287; 284, 8000 136 | 126).  G = 4: n = 700, M = 17344 703 | 765; 540, 17984 534 | 560; 1188, 14784 1024 | 1051; but
+// 396, 22976 504 | 490; 800, 12224 541 | 530.
+static bool vector_read(const DecodeParams& p) {
+  const uint64_t mv = (uint64_t)p.B * p.Hkv * p.M * p.d * 2u;
+  if (p.d != 64 || p.M % 128 == 0) return false;
+  return (p.G == 3 && p.M >= 7040 && mv >= 800000000u) || (p.G == 4 && p.M >= 14016 && mv >= 1200000000u);
+}
+
 void plan_mv_pass(DecodeParams& p, int dtype) {
-  const bool gqa = p.G > 2 && dtype == 1;
+  const bool gqa = p.G > 2 && dtype == 1 && !vector_read(p);
   MvShape s = (p.G <= 2) ? kSmall : gqa ? kGqa : kWide;
   const uint64_t mem = (uint64_t)p.M * p.d * (dtype == 0 ? 4u : 2u), units = (uint64_t)p.B * p.Hkv;
   if (p.G <= 1 && mem > kWholeMinBytes && mem <= kWholeMaxBytes && units >= kWholeMinUnits && units * mem <= kWholeMaxTotal)
@@ -323,26 +336,30 @@ static bool launch_shape(const DecodeParams& p, hipStream_t s) {
     else launch_mode<DT, D, 2, 256, 4>(p, s);
     return true;
   }
-  if constexpr (DT::kElemsPerVec == 4) {
+  if constexpr (DT::kElemsPerVec == 4 || D == 64) {
     if (p.mv_bs == kWide.bs && p.mv_u == kWide.u && G > 2) {
       if (!p.has_read) launch_mode<DT, D, 1, 512, 8>(p, s);
       else if (G <= 4) launch_mode<DT, D, 4, 512, 8>(p, s);
-      else launch_mode<DT, D, 8, 512, 8>(p, s);
+      else if constexpr (DT::kElemsPerVec == 4) launch_mode<DT, D, 8, 512, 8>(p, s);
+      else return false;
       return true;
     }
-  } else if (p.mv_bs == kGqa.bs && p.mv_u == kGqa.u && G > 2 && !p.has_read) {
-    // write-only step of a cache whose reads take the MFMA pass, where a workgroup may have two tiles: here it has one
-    DecodeParams q = p;
-    const uint32_t slots = kGqa.bs * kGqa.u * 8u / p.d;
-    q.S = (p.M + slots - 1) / slots;
-    launch_mode<DT, D, 1, 128, 8>(q, s);
-    return true;
+  }
+  if constexpr (DT::kElemsPerVec == 8) {
+    if (p.mv_bs == kGqa.bs && p.mv_u == kGqa.u && G > 2 && !p.has_read) {
+      // write-only step of a cache whose reads take the MFMA pass, where a workgroup may have two tiles: here it has one
+      DecodeParams q = p;
+      const uint32_t slots = kGqa.bs * kGqa.u * 8u / p.d;
+      q.S = (p.M + slots - 1) / slots;
+      launch_mode<DT, D, 1, 128, 8>(q, s);
+      return true;
+    }
   }
   return false;
 }
 
 hipError_t launch_stream(const DecodeParams& p, int dtype, hipStream_t s) {
-  if (dtype == 1 && p.G > 2 && p.has_read) return launch_stream_gqa(p, s);
+  if (dtype == 1 && p.G > 2 && p.has_read && p.mv_bs == kGqa.bs) return launch_stream_gqa(p, s);
   bool ok;
   if (dtype == 0) ok = (p.d == 128) ? launch_shape<F32, 128>(p, s) : launch_shape<F32, 64>(p, s);
   else ok = (p.d == 128) ? launch_shape<BF16, 128>(p, s) : launch_shape<BF16, 64>(p, s);

@@ -446,6 +446,19 @@ def test_scratch_of_several_heads_with_64_columns(L):
     assert wider > 50
 
 
+def test_odd_memories_of_64_columns_read_on_the_vector_alu(L):
+    """Three or four heads, bf16, 64 columns, M an odd multiple of 64, long memories and much of them: workgroups of 512 slots."""
+    def threads(M, n, G, d=64, dt=P.BCT_BF16, keys=0):
+        st, plan = P.bct_plan_query(P.make_desc(M, 1, n * G, n, d, dt, 0.1, 0.1, keys))
+        assert st == P.BCT_OK and plan["mv_splits"] * plan["mv_workgroup"] * plan["mv_loads_per_lane"] * 16 >= M * d * (2 if dt == P.BCT_BF16 else 4)
+        return plan["mv_workgroup"]
+    for keys in (0, P.BCT_MK_PER_SEQUENCE):
+        assert threads(10304, 820, 3, keys=keys) == 512 and threads(10240, 820, 3, keys=keys) == 128
+    assert threads(7104, 880, 3) == 512 and threads(7104, 879, 3) == 128 and threads(6976, 2000, 3) == 128
+    assert threads(14144, 663, 4) == 512 and threads(14144, 662, 4) == 128 and threads(13888, 900, 4) == 128
+    assert threads(14144, 900, 5) == 128 and threads(14144, 900, 3, d=128) == 128
+
+
 def test_where_the_one_launch_steps_begin_and_end(L):
     """fp32, one query head, 257 to 512 memories of at most 128 slots: the smallest caches' own launch; below and beside it the
     whole-step launch (workgroups per memory, threads), beyond both the streaming launches."""
